@@ -312,14 +312,14 @@ void profile_mark(int idx, hipStream_t stream)
     if (idx & 1) ++g_ev_count[role];
 }
 
-// Shortest tile handed to the prefix-sum evaluator by the fast search: its
-// cost per candidate grows with the number of levels (2L+1 look-ups) and does
-// not depend on the tile length, the plain evaluation costs one pass over the
-// tile.
+// Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
+// candidate grows with the number of half-way points (2L look-ups) and hardly depends on
+// the tile length, the plain evaluation costs one pass over the tile.  16384 tiles, 1000
+// candidates, b = 4, look-ups against pass: 96 elements 188 / 179 us, 160 elements 193 / 249.
 int fast_min_len(int bits)
 {
     const int L = (1 << (bits - 1)) - 1;
-    return 16 * (2 * L + 1) + 64;
+    return 8 * (2 * L) + 8;
 }
 
 // Largest number of groups a search call may have and still run as one fused launch
@@ -400,63 +400,49 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     }
     g_last_search_kernel = fast ? "k_fast" : "k_search";
     if (pl.n_mgroups > 0) k_tile_absmax<<<NT, kWG, 0, stream>>>(tb, tile_max);
-    int longest = 0, longest_fast = 0, fast_tiles = 0;
+    int longest = 0, fast_tiles = 0;
     for (const TensorRec &r : pl.recs) {
-        if (r.fast) { longest_fast = std::max(longest_fast, r.tile_len); fast_tiles += r.ntiles; }
+        if (r.fast) fast_tiles += r.ntiles;
         else longest = std::max(longest, r.tile_len);
     }
     if (fast_tiles > 0) {
+        static_assert(sizeof(unsigned long long) * kFastWords + sizeof(unsigned) * (kTileMax + kFastWalk) <= 63 * 1024,
+                      "k_fast must fit the LDS a launch gets without asking for more");
         // tensors are ordered longest tile first, so the fast tiles are 0 .. fast_tiles-1
-        static_assert(sizeof(double) * (kFastTMax + 1 + (kFastTMax >> kFastP2ShiftMax) + 1) +
-                          sizeof(unsigned short) * (kFastTMax + 2) + sizeof(float) * (kTileMax + kFastWalkSq) <=
-                      64 * 1024, "k_fast must fit the LDS a launch gets without asking for more");
-        auto tcap_of = [](int longest_len) {
-            int tcap = 64;
-            while (tcap < kFastTMax && tcap <= 2 * longest_len) tcap <<= 1;
-            return tcap;
+        auto lds_bytes = [](int len) {
+            return sizeof(unsigned long long) * ((size_t)kFastOct << fast_octave_bits(len)) +
+                   sizeof(unsigned) * (size_t)(len + kFastWalk);
         };
-        auto lds_bytes = [&](int longest_len, int p2_shift) {
-            const int tcap = tcap_of(longest_len);
-            return sizeof(double) * (size_t)(tcap + 1 + (tcap >> p2_shift) + 1) +
-                   sizeof(unsigned short) * (size_t)(tcap + 2) +
-                   sizeof(float) * (size_t)(longest_len + kFastWalkSq);
-        };
-        // workgroups of a launch per CU: 160 KB of LDS (256 bytes of it static per workgroup),
-        // 32 wavefront slots
-        auto per_cu = [](size_t bytes) {
-            return std::min((size_t)(32 / kFastWaves), (size_t)(160 * 1024) / (bytes + 256));
-        };
-        // A launch's LDS is sized for its longest tile.  When the longest tiles keep the others
-        // from a fourth workgroup per CU, they get a launch of their own.
-        int split = 0;          // tiles of the first launch; 0: one launch
-        {
-            int seen = 0, first_full = -1;
-            for (const TensorRec &r : pl.recs) {
-                if (!r.fast) break;
-                if (first_full < 0 && per_cu(lds_bytes(r.tile_len, kFastP2ShiftMax)) >
-                                          per_cu(lds_bytes(longest_fast, kFastP2ShiftMax)))
-                    first_full = seen;
-                seen += r.ntiles;
-            }
-            if (first_full >= 1024 && fast_tiles - first_full >= 1024) split = first_full;
-        }
+        // magnitudes in units of 1 / (2 L q) of a candidate
+        const int q = (int)kFastTop / (n_cand * 2 * ((1 << (bits - 1)) - 1));
+        // A launch's workgroups and LDS are sized for its longest tile; shorter tiles get
+        // launches of their own where both sides have enough of them.
+        auto size_class = [](int len) { return len > kFastLong ? 0 : len > kFastMid ? 1 : len > kSmallTile ? 2 : 3; };
         profile_mark(4, stream);
-        for (int part = 0; part < (split ? 2 : 1); ++part) {
-            const int begin = part ? split : 0;
-            const int count = split ? (part ? fast_tiles - split : split) : fast_tiles;
-            int part_longest = 0, seen = 0;
-            for (const TensorRec &r : pl.recs) {
-                if (!r.fast) break;
-                if (seen >= begin && seen < begin + count) part_longest = std::max(part_longest, r.tile_len);
-                seen += r.ntiles;
+        int begin = 0, seen = 0, part_longest = 0;
+        for (size_t i = 0; i < pl.recs.size() && pl.recs[i].fast; ++i) {
+            const TensorRec &r = pl.recs[i];
+            part_longest = std::max(part_longest, r.tile_len);
+            seen += r.ntiles;
+            const bool last = seen == fast_tiles;
+            if (!last && (size_class(pl.recs[i + 1].tile_len) == size_class(part_longest) ||
+                          seen - begin < kFastLaunchTiles || fast_tiles - seen < kFastLaunchTiles))
+                continue;
+            const int count = seen - begin;
+            const size_t lds = lds_bytes(part_longest);
+            switch (size_class(part_longest)) {
+                case 0:
+                    k_fast<1024, kTileMax / 1024><<<count, 1024, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
+                    break;
+                case 1:
+                case 2:
+                    k_fast<512, kFastLong / 512><<<count, 512, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
+                    break;
+                default:
+                    k_fast<256, kSmallTile / 256><<<count, 256, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
             }
-            // the finer prefix of squares shortens a walk; taken unless it costs a workgroup per CU
-            int p2_shift = kFastP2ShiftMax;
-            while (p2_shift > kFastP2ShiftMin && lds_bytes(part_longest, p2_shift - 1) <= 64 * 1024 &&
-                   per_cu(lds_bytes(part_longest, p2_shift - 1)) == per_cu(lds_bytes(part_longest, kFastP2ShiftMax)))
-                --p2_shift;
-            k_fast<<<count, kFastWG, lds_bytes(part_longest, p2_shift), stream>>>(
-                tb, begin, n_cand, bits, tcap_of(part_longest), p2_shift, tile_max, gm, sse32);
+            begin = seen;
+            part_longest = 0;
         }
         profile_mark(5, stream);
     }

@@ -4,19 +4,29 @@
 // re-evaluation and the argmin that follow are shared.
 //
 // With u = |w|/m * n, candidate k quantizes the centre elements (u <= k) to the
-// grid j*k/L and the tail elements to k + j*(n-k)/L, j = 0..L.  The elements
-// that round to level j form a run of the sorted order whose ends are the
-// half-way points (j +- 1/2) steps.  With cumulative counts N(b) and sums
-// C(b) = sum of u over {u <= b}, summation by parts gives for a piece with
-// step s, levels from offset z, and values v = u - z
-//   sum (v - j s)^2 = S2 - 2 s (L C_L - sum_{j<L} C_j) + s^2 (L^2 N_L - sum_{j<L} (2j+1) N_j)
-// where C_j, N_j are taken at the upper end of level j's run and S2 = sum v^2.
-// So a candidate costs 2L+1 cumulative look-ups instead of a pass over the tile.
+// grid j*k/L and the tail elements to k + j*(n-k)/L, j = 0..L.  An element of a
+// piece with step s and offset z rounds to level j when it lies above j of the
+// half-way points b_i = z + (2i+1) s/2, so
+//   (u - z - j s)^2 = (u - z)^2 - 2 s sum_{i<L} max(u - b_i, 0).
+// Summed over both pieces, with H(b) = sum_u max(b - u, 0), everything that
+// depends on the region of an element cancels:
+//   SSE(k) = sum_u (n - u)^2 - 2 (k/L) sum_i H((2i+1) k/(2L))
+//                            - 2 ((n-k)/L) sum_i H(k + (2i+1) (n-k)/(2L)).
+// A candidate costs 2L look-ups of H, whatever the tile's length.
 //
-// A look-up needs no full sort: elements are grouped into T buckets that are
-// monotone in u (one counting pass in LDS), bucket-level prefix sums of the
-// count, of u and of u^2 are kept in binary64, and the look-up adds the part of
-// the boundary's own bucket that lies at or below the boundary.
+// Whole numbers.  Every half-way point is a multiple of 1/(2L), so magnitudes are
+// held as integers in units of 1/(2L q), q the largest that keeps n below 2^24:
+// half-way points are exact, an element moves by at most 2^-24 n (an eighth of
+// the rounding that the filter's slack allows an element), and every sum below
+// is exact; binary64 enters once per candidate, where the three terms meet.
+//
+// A look-up needs no full sort: elements are grouped into buckets that are
+// monotone in the magnitude (one counting pass in LDS), and a bucket's 64-bit word
+// holds the sum (38 bits) and count (14 bits) of the elements before it and its
+// own count (12 bits).  H(b) is b * count - sum of the bucket of b, plus
+// max(b - u, 0) over the bucket's own elements: elements past its end are above b
+// and add nothing, so the first four are read without looking at the count.
+// Elements that are exactly zero (pruned weights) are counted, never walked.
 #pragma once
 
 #include "pwlq_prep.h"
@@ -25,155 +35,140 @@
 
 namespace pwlq {
 
-constexpr int kFastWG = 512;                       // threads per workgroup
-constexpr int kFastWaves = kFastWG / 64;
-constexpr int kFastPer = kTileMax / kFastWG;       // elements of a tile held by one thread
-constexpr int kFastTMax = 2048;                    // most buckets per tile
+constexpr int kFastOctBits = 9;                    // most buckets per octave: 2^9
+constexpr int kFastOct = 7;                        // octaves, or twice as many of half as many buckets each
+constexpr int kFastWords = kFastOct << kFastOctBits;   // most buckets per tile
+constexpr unsigned kFastTop = (1u << 24) - 1 - (1u << (24 - kFastOct));   // largest magnitude
+static_assert(kFastTop >= 65535u * 254u, "every grid fits");
 constexpr int kFastCrowd = 64;                     // fullest bucket the look-ups may walk: this or 1/16 of the tile
+constexpr int kFastWalk = 4;                       // elements read per step of a walk
+constexpr int kFastLong = 5120, kFastMid = 2816;   // longest tiles of a launch of 512 threads: three, then four workgroups' LDS per CU
+constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones
 
-// Error of a tile's filter value from the binary64 prefix arithmetic: every
-// cumulative sum is within (tile length + 64) * 2^-53 of its magnitude (at most
-// n^2 K for the squares, n K for the sums), and about 32 such terms are
-// combined with coefficients of at most n; kFastRelErr * n^2 * K bounds it and
-// is added to the slack of the filter (keep_threshold).
+// Error of a tile's filter value beyond the rounding of its elements: the three
+// binary64 terms, each at most n^2 K, a few roundings each; kFastRelErr * n^2 * K
+// bounds it with room and is added to the slack of the filter (keep_threshold).
 
-// Bucket of a magnitude 0 <= u <= n: the top bits of its binary32 pattern
-// (monotone in u), i.e. 2^(23-shift) buckets per octave over the 16 octaves
-// below n; everything smaller shares bucket 0.  Weight distributions are dense
-// near zero, so equal-width buckets would pile most elements into a few.
-__device__ inline int fast_bucket(float u, int shift, int base)
+// log2 of a tile's buckets per octave, about two buckets per element.
+__host__ __device__ inline int fast_octave_bits(int len)
 {
-    const int c = (__float_as_int(u) >> shift) - base;
-    return c > 0 ? c : 0;
+    int bits = 1;
+    while (bits < kFastOctBits && (8 << bits) <= len) ++bits;
+    return bits;
 }
 
-__device__ inline double wave_scan_incl_f64(double v)
+// inclusive prefix sum of 64-bit words over the wavefront
+template <int kCtrl, int kRows>
+__device__ inline unsigned long long dpp_u64(unsigned long long v)
 {
-    v += dpp_f64<0x111, 0xf>(0.0, v);
-    v += dpp_f64<0x112, 0xf>(0.0, v);
-    v += dpp_f64<0x114, 0xf>(0.0, v);
-    v += dpp_f64<0x118, 0xf>(0.0, v);
-    v += dpp_f64<0x142, 0xa>(0.0, v);
-    v += dpp_f64<0x143, 0xc>(0.0, v);
+    const unsigned lo = (unsigned)dpp_i32<kCtrl, kRows>(0, (int)(unsigned)v);
+    const unsigned hi = (unsigned)dpp_i32<kCtrl, kRows>(0, (int)(unsigned)(v >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+__device__ inline unsigned long long wave_scan_incl_u64(unsigned long long v)
+{
+    v += dpp_u64<0x111, 0xf>(v);
+    v += dpp_u64<0x112, 0xf>(v);
+    v += dpp_u64<0x114, 0xf>(v);
+    v += dpp_u64<0x118, 0xf>(v);
+    v += dpp_u64<0x142, 0xa>(v);
+    v += dpp_u64<0x143, 0xc>(v);
     return v;
 }
 
-constexpr int kFastP2ShiftMin = 1, kFastP2ShiftMax = 3;   // 2, 4 or 8 buckets per entry of the prefix of squares:
-                                                          // as fine as costs no workgroup per CU
+constexpr int kFastSumBits = 38, kFastCountBits = 14;   // then 12 bits: the bucket's own count
+
+typedef __attribute__((address_space(3))) const unsigned long long FastWordLds;
+typedef __attribute__((address_space(3))) const unsigned FastElemLds;
 
 struct FastLds {
-    const unsigned short *start;   // [T+1] first element of each bucket
-    const double *P1;              // [T+1] sum of u over the buckets before
-    const double *P2;              // [(T >> p2_shift) + 1] sum of u^2 before every (1 << p2_shift)-th bucket
-    const float *elems;            // grouped by bucket
-    int shift, base;
-    int p2_shift;
+    unsigned words;                // LDS address of the word of bucket 0, less 8 times its number
+    FastElemLds *elems;            // grouped by bucket; index 0 is the first of the zero elements
+    int shift;                     // bits of the binary32 pattern below a bucket number
 };
 
-// Elements with u <= b: count and sum of u.  Every element of an earlier
-// bucket is below b, every element of a later bucket above.  The boundary's own
-// bucket is walked four elements at a time (the reads of a step are in flight
-// together; the array has four spare words behind the tile, and what is read
-// past the bucket's end is masked by position).
-constexpr int kFastWalk = 2;          // elements per step of a bucket walk
-constexpr int kFastWalkSq = 4;        // ... of the walk for the sum of squares, which spans several buckets
+// Bucket number of value v (magnitude plus `low`): the top bits of its binary32
+// pattern, i.e. 2^m buckets per octave.  Below `low` the added offset makes them
+// equally wide.
+__device__ inline unsigned fast_bucket(unsigned v, int shift) { return __float_as_uint((float)v) >> shift; }
 
-__device__ inline void fast_query(const FastLds &L, float b, int &count, double &s1)
+struct FastSums {
+    unsigned long long c;          // sums of the elements below
+    unsigned n, m, d;              // counts; counts times 2i+1; parts inside buckets
+};
+
+struct FastWord {
+    unsigned before, own;
+    unsigned long long c;
+};
+__device__ inline FastWord fast_word(const FastLds &L, unsigned b)
 {
-    const int c = fast_bucket(b, L.shift, L.base);
-    const int st = L.start[c], en = L.start[c + 1];
-    int nn = st;
-    double a1 = L.P1[c];
-    for (int i = st; i < en; i += kFastWalk) {
-        float u[kFastWalk];
-#pragma unroll
-        for (int x = 0; x < kFastWalk; ++x) u[x] = L.elems[i + x];
-#pragma unroll
-        for (int x = 0; x < kFastWalk; ++x) {
-            const bool le = (i + x < en) && (u[x] <= b);
-            nn += le ? 1 : 0;
-            a1 += (double)(le ? u[x] : 0.0f);
-        }
-    }
-    count = nn;
-    s1 = a1;
+    const unsigned long long w = *(FastWordLds *)(uintptr_t)((fast_bucket(b, L.shift) << 3) + L.words);
+    const unsigned hi = (unsigned)(w >> 32);
+    FastWord f;
+    f.before = (hi >> (kFastSumBits - 32)) & ((1u << kFastCountBits) - 1u);
+    f.own = hi >> (kFastSumBits - 32 + kFastCountBits);
+    f.c = w & ((1ull << kFastSumBits) - 1ull);
+    return f;
 }
 
-// The same with the sum of squares, which is kept per 2, 4 or 8 buckets (it
-// is needed once per candidate): the walk starts at that coarser boundary.
-__device__ inline void fast_query_squares(const FastLds &L, float b, int &count, double &s1,
-                                          double &s2)
+// H at one half-way point of each piece: the two chains of reads run side by side.
+__device__ inline void fast_query2(const FastLds &L, unsigned b0, unsigned b1, unsigned odd, FastSums &s0,
+                                   FastSums &s1)
 {
-    const int c = fast_bucket(b, L.shift, L.base);
-    const int c0 = (c >> L.p2_shift) << L.p2_shift;
-    const int st = L.start[c0], en = L.start[c + 1];
-    int nn = st;
-    double a1 = L.P1[c0];
-    double a2 = L.P2[c0 >> L.p2_shift];
-    for (int i = st; i < en; i += kFastWalkSq) {
-        float u[kFastWalkSq];
+    const FastWord w0 = fast_word(L, b0), w1 = fast_word(L, b1);
+    FastElemLds *e0 = L.elems + w0.before, *e1 = L.elems + w1.before;
+    unsigned x0[kFastWalk], x1[kFastWalk];
 #pragma unroll
-        for (int x = 0; x < kFastWalkSq; ++x) u[x] = L.elems[i + x];
+    for (int x = 0; x < kFastWalk; ++x) { x0[x] = e0[x]; x1[x] = e1[x]; }
 #pragma unroll
-        for (int x = 0; x < kFastWalkSq; ++x) {
-            const bool le = (i + x < en) && (u[x] <= b);
-            const double d = (double)(le ? u[x] : 0.0f);
-            nn += le ? 1 : 0;
-            a1 += d;
-            a2 += d * d;
-        }
+    for (int x = 0; x < kFastWalk; ++x) {
+        s0.d += __builtin_elementwise_sub_sat(b0, x0[x]);
+        s1.d += __builtin_elementwise_sub_sat(b1, x1[x]);
     }
-    count = nn;
-    s1 = a1;
-    s2 = a2;
+    for (unsigned i = kFastWalk; i < w0.own; i += kFastWalk) {
+#pragma unroll
+        for (int x = 0; x < kFastWalk; ++x) s0.d += __builtin_elementwise_sub_sat(b0, e0[i + x]);
+    }
+    for (unsigned i = kFastWalk; i < w1.own; i += kFastWalk) {
+#pragma unroll
+        for (int x = 0; x < kFastWalk; ++x) s1.d += __builtin_elementwise_sub_sat(b1, e1[i + x]);
+    }
+    s0.c += w0.c;
+    s1.c += w1.c;
+    s0.n += w0.before;
+    s1.n += w1.before;
+    s0.m += __umul24(odd, w0.before);
+    s1.m += __umul24(odd, w1.before);
 }
 
-// Filter value of every candidate of the tile.
-__device__ inline void fast_candidates(const FastLds &Q, int n, int len, int Li, double S1tot,
-                                       double S2tot, float *__restrict__ row)
+// Filter value of every candidate of the tile.  `low` is the offset of the stored
+// values, A = sum (n - u)^2.
+template <int kT>
+__device__ inline void fast_candidates(const FastLds &Q, int n, int Li, int q, unsigned low, double A,
+                                       float *__restrict__ row)
 {
-    const double Ld = (double)Li;
-    for (int k = threadIdx.x + 1; k <= n; k += kFastWG) {
-        const double kd = (double)k;
-        // centre piece: offset 0, step k/L
-        double sumC = 0.0;
-        int sumN = 0;          // at most L^2 K < 2^31
-        int cn;
-        double c1;
-        // half-way points in binary32: an element within a rounding of one is as far from
-        // the level below as from the level above
-        const float half_c = (float)(kd / (2.0 * Ld));
-        for (int j = 0; j < Li; ++j) {
-            fast_query(Q, (float)(2 * j + 1) * half_c, cn, c1);
-            sumC += c1;
-            sumN += __mul24(2 * j + 1, cn);
-        }
-        int nL;
-        double cL, s2L;
-        fast_query_squares(Q, (float)k, nL, cL, s2L);
-        const double sc = kd / Ld;
-        double sse = s2L - 2.0 * sc * (Ld * cL - sumC) +
-                     sc * sc * (Ld * Ld * (double)nL - (double)sumN);
-        if (k < n) {
-            // tail piece: offset k, step (n-k)/L, values v = u - k
-            const double wd = (double)(n - k);
-            const float half_t = (float)(wd / (2.0 * Ld));
-            const float kf = (float)k;
-            double sumCt = 0.0;
-            int sumNt = 0;
-            for (int j = 0; j < Li; ++j) {
-                fast_query(Q, __builtin_fmaf((float)(2 * j + 1), half_t, kf), cn, c1);
-                const int nt = cn - nL;
-                sumCt += (c1 - cL) - kd * (double)nt;
-                sumNt += __mul24(2 * j + 1, nt);
+    const double inv = 1.0 / ((double)Li * (double)Li * (double)q);            // 2 / (L * 2L q)
+    for (int k = threadIdx.x + 1; k <= n; k += kT) {
+        const unsigned kk = (unsigned)(k * q), ww = (unsigned)((n - k) * q);   // half steps of the two pieces
+        const unsigned zt = 2u * (unsigned)Li * kk + low;
+        FastSums fc = {0, 0, 0, 0}, ft = {0, 0, 0, 0};
+        unsigned bc = kk + low, bt = zt + ww;
+        for (int i = 0; i < Li;) {
+            // the parts inside buckets stay below 2^28 each: eight of them fit a word
+            const int stop = i + 8 < Li ? i + 8 : Li;
+            fc.d = ft.d = 0;
+            for (; i < stop; ++i) {
+                fast_query2(Q, bc, bt, 2 * i + 1, fc, ft);
+                bc += 2 * kk;
+                bt += 2 * ww;
             }
-            const int ntL = len - nL;
-            const double ctL = (S1tot - cL) - kd * (double)ntL;
-            const double s2t = (S2tot - s2L) - 2.0 * kd * (S1tot - cL) + kd * kd * (double)ntL;
-            const double st = wd / Ld;
-            sse += s2t - 2.0 * st * (Ld * ctL - sumCt) +
-                   st * st * (Ld * Ld * (double)ntL - (double)sumNt);
+            fc.c -= fc.d;
+            ft.c -= ft.d;
         }
+        const double hc = (double)kk * (double)fc.m + (double)low * (double)fc.n - (double)(long long)fc.c;
+        const double ht = (double)ww * (double)ft.m + (double)zt * (double)ft.n - (double)(long long)ft.c;
+        const double sse = A - inv * ((double)k * hc + (double)(n - k) * ht);
         row[k - 1] = (float)(sse > 0.0 ? sse : 0.0);
     }
 }
@@ -182,11 +177,12 @@ __device__ inline void fast_candidates(const FastLds &Q, int n, int len, int Li,
 // holding more than 1/16 of the tile) would make every look-up walk a long bucket; it is evaluated element by element
 // instead, in binary32 with the chunked sums of the plain search kernel (all
 // lanes read the same LDS word, which is a broadcast).
-__device__ inline void fast_plain(const float *__restrict__ elems, int len, int n, int Li,
-                                  float *__restrict__ row)
+template <int kT>
+__device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, int n, int Li, unsigned low,
+                                  float per_unit, float *__restrict__ row)
 {
     const float Lf = (float)Li;
-    for (int k = threadIdx.x + 1; k <= n; k += kFastWG) {
+    for (int k = threadIdx.x + 1; k <= n; k += kT) {
         const float kf = (float)k;
         const float nk = (float)(n - k);
         const float rc = Lf / kf;
@@ -198,7 +194,7 @@ __device__ inline void fast_plain(const float *__restrict__ elems, int len, int 
             const int ce = (cb + kChunk < len) ? cb + kChunk : len;
             float acc = 0.0f;
             for (int i = cb; i < ce; ++i) {
-                const float u = elems[i];
+                const float u = (float)(elems[i] - low) * per_unit;
                 const bool tail = u > kf;
                 const float t = tail ? __builtin_fmaf(u, rt, ct) : u * rc;
                 const float err = (t - __builtin_rintf(t)) * (tail ? stept : stepc);
@@ -210,185 +206,169 @@ __device__ inline void fast_plain(const float *__restrict__ elems, int len, int 
     }
 }
 
-__global__ __launch_bounds__(kFastWG) void k_fast(Tables tb, int tile_begin, int n, int bits, int tcap, int p2_shift,
-                                                  const float *__restrict__ tile_max,
-                                                  float *__restrict__ gm,
-                                                  float *__restrict__ sse32)
+template <int kT, int kPer>
+__global__ __launch_bounds__(kT, kT == 512 ? 6 : 8) void k_fast(Tables tb, int tile_begin, int n, int bits, int q,
+                                             const float *__restrict__ tile_max,
+                                             float *__restrict__ gm,
+                                             float *__restrict__ sse32)
 {
-    // dynamic LDS: P1[tcap+1] (binary64; its space first serves as the histogram
-    // and scatter cursor), P2[(tcap >> p2_shift) + 1], start[tcap+2] (16-bit), then
-    // the grouped elements
-    extern __shared__ double fast_lds[];
-    __shared__ float redm[kFastWaves];
-    __shared__ int redbad[kFastWaves];
-    __shared__ int wsum[kFastWaves];
-    __shared__ int wcrowd[kFastWaves];
-    __shared__ double wsum1[kFastWaves], wsum2[kFastWaves];
+    // dynamic LDS: the buckets' words (first the counts and sums of the buckets
+    // themselves, then of everything before them), then the grouped elements
+    extern __shared__ unsigned long long fast_lds[];
+    constexpr int kW = kT / 64;
+    constexpr int kScan = (kFastWords + kT - 1) / kT;   // words a thread holds at most
+    __shared__ float redm[kW], redsum[kW];
+    __shared__ int redbad[kW], redzero[kW], wcrowd[kW];
+    __shared__ unsigned long long wsum[kW];
+    __shared__ double redA[kW];
 
     int t;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = uni(tid >> 6);
     TensorRec r;
     TileInfo ti = tile_of(tb, tile_begin + blockIdx.x, r, t);
     if (!r.fast) return;
     const int len = ti.len;
+    const int Li = (1 << (bits - 1)) - 1;
 
-    double *P1 = fast_lds;
-    double *P2 = fast_lds + (tcap + 1);
-    int *cnt = reinterpret_cast<int *>(P1);
-    unsigned short *start =
-        reinterpret_cast<unsigned short *>(fast_lds + (tcap + 1) + ((tcap >> p2_shift) + 1));
-    float *elems = reinterpret_cast<float *>(start + (tcap + 2));
-
-    int T = 64;
-    while (T < tcap && T <= 2 * len) T <<= 1;
-
-    float a[kFastPer];
+    float a[kPer];
 #pragma unroll
-    for (int e = 0; e < kFastPer; ++e) {
-        const int i = tid + e * kFastWG;
+    for (int e = 0; e < kPer; ++e) {
+        const int i = tid + e * kT;
         a[e] = (i < len) ? fabsf(ti.src[i]) : 0.0f;
     }
 
-    // group absmax: from the registers (single-tile group) or the tile maxima
-    float m = 0.0f;
+    // group absmax: from the registers (single-tile group) or the tile maxima; the
+    // tile's mean magnitude places the buckets
+    float m = 0.0f, sum = 0.0f;
     int bad = 0;
-    if (r.tpg == 1) {
 #pragma unroll
-        for (int e = 0; e < kFastPer; ++e) { bad |= (a[e] != a[e]); m = fmaxf(m, a[e]); }
-    } else {
+    for (int e = 0; e < kPer; ++e) { bad |= (a[e] != a[e]); m = fmaxf(m, a[e]); sum += a[e]; }
+    if (r.tpg > 1) {
         const int tile0 = r.tile_base + ti.group_local * r.tpg;
-        for (int j = tid; j < r.tpg; j += kFastWG) {
+        for (int j = tid; j < r.tpg; j += kT) {
             const float v = tile_max[tile0 + j];
             bad |= (v != v);
             m = fmaxf(m, v);
         }
     }
     m = wave_max(m);
+    sum = (float)wave_sum((double)sum);
     bad = wave_or(bad);
-    if (lane == 0) { redm[wave] = m; redbad[wave] = bad; }
-    for (int i = tid; i < T; i += kFastWG) cnt[i] = 0;
+    if (lane == 0) { redm[wave] = m; redsum[wave] = sum; redbad[wave] = bad; }
+    int obits = fast_octave_bits(len);
+    const int T = kFastOct << obits;
+    for (int i = tid; i < T; i += kT) fast_lds[i] = 0ull;
     __syncthreads();
     m = redm[0];
+    sum = redsum[0];
     bad = redbad[0];
-    for (int i = 1; i < kFastWaves; ++i) { m = fmaxf(m, redm[i]); bad |= redbad[i]; }
+    for (int i = 1; i < kW; ++i) { m = fmaxf(m, redm[i]); sum += redsum[i]; bad |= redbad[i]; }
     if (bad) m = __builtin_nanf("");
     if (ti.tile_in_group == 0 && tid == 0) gm[ti.group] = m;
 
     const bool usable = (m > 0.0f) && (m < __builtin_inff());
     const float nf = (float)n;
     const float scale = usable ? nf / m : 0.0f;
-    int shift = 16;                        // T = 2048: 128 buckets per octave
-    for (int x = T; x < 2048; x <<= 1) ++shift;
-    const int base = (__float_as_int(nf) >> shift) - (T - 1);
+    const unsigned top = (unsigned)(n * 2 * Li * q);                      // the magnitude m: 2^23 to kFastTop
+    const float unit = (float)(2 * Li * q);                               // per candidate unit; exact, like top
 
-    // units and histogram
+    // Values run from `low` to top + low, whose exponents are 24 - octaves and 23.  Seven
+    // octaves, and 14 of half as many buckets where the mean lies in the lowest: near zero
+    // these are 64 times as fine, elsewhere half as fine.
+    const float mean = sum / (float)len * scale * unit;
+    const bool deep = uni(mean < (float)(1u << (23 - kFastOct)) ? 1 : 0) != 0;
+    obits -= deep ? 1 : 0;
+    const unsigned low = 1u << (24 - (deep ? 2 * kFastOct : kFastOct));
+    FastLds Q;
+    Q.shift = 23 - obits;
+    const unsigned bucket0 = fast_bucket(low, Q.shift);
+    Q.words = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)fast_lds - (bucket0 << 3);
+
+    // values, counts and sums per bucket; the count an add returns is the element's
+    // rank inside its bucket
+    unsigned v[kPer];
+    unsigned short rank[kPer];
+    int zeros = 0;
+    double A = 0.0;
 #pragma unroll
-    for (int e = 0; e < kFastPer; ++e) {
-        const int i = tid + e * kFastWG;
+    for (int e = 0; e < kPer; ++e) {
+        const int i = tid + e * kT;
+        unsigned u = 0;
         if (i < len) {
-            const float u = usable ? to_units(a[e], scale, nf) : 0.0f;
-            a[e] = u;
-            atomicAdd(&cnt[fast_bucket(u, shift, base)], 1);
+            u = (unsigned)__builtin_rintf(to_units(a[e], scale, nf) * unit);     // at most top; 0 if not usable
+            const double d = (double)(top - u);
+            A += d * d;
+            zeros += u == 0;
+        }
+        v[e] = u + low;
+        rank[e] = 0;
+        if (u > 0) {
+            rank[e] = (unsigned short)(atomicAdd(&fast_lds[fast_bucket(v[e], Q.shift) - bucket0],
+                                                 (1ull << kFastSumBits) | v[e]) >> kFastSumBits);
         }
     }
+    zeros = wave_scan_incl(zeros);
+    A = wave_sum(A);
+    if (lane == 63) { redzero[wave] = zeros; redA[wave] = A; }
     __syncthreads();
+    zeros = 0;
+    A = 0.0;
+#pragma unroll 4
+    for (int i = 0; i < kW; ++i) { zeros += redzero[i]; A += redA[i]; }
+    A *= 1.0 / ((double)unit * (double)unit);
 
-    // bucket starts (exclusive scan); the histogram becomes the scatter cursor
-    const int per = (T + kFastWG - 1) / kFastWG;
+    // exclusive prefix of counts and sums, both fields in one word
+    const int per = (T + kT - 1) / kT;
     const int lo = tid * per < T ? tid * per : T;
     const int hi = lo + per < T ? lo + per : T;
     {
-        // bucket 0 (zeros and near-zeros, e.g. pruned weights) only counts as
-        // crowded if the lowest boundary, half a centre step of k = 1, can fall in it
-        const float lowest = 0.5f / (float)((1 << (bits - 1)) - 1);
-        const int first = (fast_bucket(lowest, shift, base) == 0) ? 0 : 1;
-        int sum = 0, fullest = 0;
-        for (int i = lo; i < hi; ++i) {
-            sum += cnt[i];
-            if (i >= first && cnt[i] > fullest) fullest = cnt[i];
+        unsigned long long w[kScan], tot = 0;
+        unsigned fullest = 0;
+#pragma unroll
+        for (int x = 0; x < kScan; ++x) {
+            w[x] = (lo + x < hi) ? fast_lds[lo + x] : 0ull;
+            tot += w[x];
+            const unsigned c = (unsigned)(w[x] >> kFastSumBits);
+            fullest = c > fullest ? c : fullest;
         }
-        const int incl = wave_scan_incl(sum);
-        const int crowd = (len >> 4) > kFastCrowd ? (len >> 4) : kFastCrowd;
-        fullest = (__ballot(fullest > crowd) != 0ull) ? 1 : 0;
-        if (lane == 63) { wsum[wave] = incl; wcrowd[wave] = fullest; }
+        const unsigned long long incl = wave_scan_incl_u64(tot);
+        const unsigned crowd = (len >> 4) > kFastCrowd ? (unsigned)(len >> 4) : (unsigned)kFastCrowd;
+        const int over = __ballot(fullest > crowd) != 0ull;
+        if (lane == 63) { wsum[wave] = incl; wcrowd[wave] = over; }
         __syncthreads();
-        int run = incl - sum;
+        // the zero elements come before everything
+        unsigned long long run = incl - tot + ((unsigned long long)zeros << kFastSumBits) +
+                                 (unsigned long long)zeros * low;
+#pragma unroll 2
         for (int i = 0; i < wave; ++i) run += wsum[i];
-        for (int i = lo; i < hi; ++i) {
-            const int v = cnt[i];
-            start[i] = (unsigned short)run;
-            cnt[i] = 0;
-            run += v;
+#pragma unroll
+        for (int x = 0; x < kScan; ++x) {
+            if (lo + x < hi) {
+                // a count of 4096 or more would not fit, but such a tile is crowded
+                fast_lds[lo + x] = run | ((w[x] >> kFastSumBits) << (kFastSumBits + kFastCountBits));
+                run += w[x];
+            }
         }
-        if (tid == 0) start[T] = (unsigned short)len;
     }
     __syncthreads();
+    unsigned *elems = reinterpret_cast<unsigned *>(fast_lds + T);
+    Q.elems = (FastElemLds *)elems - zeros;
 #pragma unroll
-    for (int e = 0; e < kFastPer; ++e) {
-        const int i = tid + e * kFastWG;
-        if (i < len) {
-            const float u = a[e];
-            const int c = fast_bucket(u, shift, base);
-            elems[start[c] + atomicAdd(&cnt[c], 1)] = u;
+    for (int e = 0; e < kPer; ++e) {
+        if (v[e] > low) {
+            elems[fast_word(Q, v[e]).before - zeros + rank[e]] = v[e];
         }
     }
+    // what a walk reads past the last element adds nothing
+    if (tid < kFastWalk) elems[len - zeros + tid] = ~0u;
     int crowded = 0;
-    for (int i = 0; i < kFastWaves; ++i) crowded |= wcrowd[i];
+    for (int i = 0; i < kW; ++i) crowded |= wcrowd[i];
     __syncthreads();
-    if (crowded) {
-        fast_plain(elems, len, n, (1 << (bits - 1)) - 1, sse32 + (long long)t * n);
-        return;
-    }
-
-    // per-bucket sums and their exclusive prefix (binary64)
-    {
-        double b1[(kFastTMax + kFastWG - 1) / kFastWG], b2[(kFastTMax + kFastWG - 1) / kFastWG];
-        double t1 = 0.0, t2 = 0.0;
-#pragma unroll
-        for (int x = 0; x < (kFastTMax + kFastWG - 1) / kFastWG; ++x) {
-            const int c = lo + x;
-            double s1 = 0.0, s2 = 0.0;
-            if (c < hi) {
-                for (int i = start[c]; i < start[c + 1]; ++i) {
-                    const double d = (double)elems[i];
-                    s1 += d;
-                    s2 += d * d;
-                }
-            }
-            b1[x] = t1;
-            b2[x] = t2;
-            t1 += s1;
-            t2 += s2;
-        }
-        const double i1 = wave_scan_incl_f64(t1), i2 = wave_scan_incl_f64(t2);
-        if (lane == 63) { wsum1[wave] = i1; wsum2[wave] = i2; }
-        __syncthreads();           // also: every use of the cursor (aliases P1) is done
-        double o1 = i1 - t1, o2 = i2 - t2;
-        for (int i = 0; i < wave; ++i) { o1 += wsum1[i]; o2 += wsum2[i]; }
-#pragma unroll
-        for (int x = 0; x < (kFastTMax + kFastWG - 1) / kFastWG; ++x) {
-            const int c = lo + x;
-            if (c < hi) {
-                P1[c] = o1 + b1[x];
-                if ((c & ((1 << p2_shift) - 1)) == 0) P2[c >> p2_shift] = o2 + b2[x];
-            }
-        }
-        if (tid == kFastWG - 1) { P1[T] = o1 + t1; P2[T >> p2_shift] = o2 + t2; }
-    }
-    __syncthreads();
-
-    FastLds Q;
-    Q.start = start;
-    Q.P1 = P1;
-    Q.P2 = P2;
-    Q.elems = elems;
-    Q.shift = shift;
-    Q.base = base;
-    Q.p2_shift = p2_shift;
-    fast_candidates(Q, n, len, (1 << (bits - 1)) - 1, P1[T], P2[T >> p2_shift],
-                    sse32 + (long long)t * n);
+    float *row = sse32 + (long long)t * n;
+    if (crowded) fast_plain<kT>(elems, len - zeros, n, Li, low, 1.0f / unit, row);
+    else fast_candidates<kT>(Q, n, Li, q, low, A, row);
 }
 
 } // namespace pwlq

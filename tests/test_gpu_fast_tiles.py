@@ -1,0 +1,44 @@
+"""Fast search at the edges of its tile sizes, against the oracle: the shortest tiles it
+takes, the lengths where a launch changes its workgroup, tiles cut from a longer group, values
+in the few octaves of a bell and in the many of a heavy tail, pruned and equal weights."""
+import numpy as np
+import pytest
+
+from oracle import pwlq_ref as R
+from parity import assert_search_matches
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2002_00104_amd import pwlq
+    return pwlq
+
+
+def rows(K, rng):
+    w = np.stack([rng.standard_normal(K), rng.standard_t(1.2, K), rng.laplace(0, 1, K),
+                  rng.standard_normal(K) * (rng.random(K) < 0.1), np.full(K, 0.37) * np.sign(rng.standard_normal(K)),
+                  np.exp(rng.uniform(-30, 0, K))])
+    return w.astype(np.float32)
+
+
+@pytest.mark.parametrize("bits,n,lengths", [(4, 100, (119, 120, 121, 255, 256, 257, 1023, 1024, 1025)),
+                                            (4, 1000, (64, 120, 2816, 2817, 5120, 5121)),
+                                            (2, 60, (23, 24, 25, 8191, 8192, 8193)),
+                                            (3, 2000, (56, 57, 1500, 16385)), (8, 130, (2039, 2040, 2041, 8200))])
+def test_fast_search_at_the_edges_of_its_tiles(P, bits, n, lengths):
+    import torch
+    rng = np.random.default_rng(bits * 1000 + n)
+    before = P.set_small_call_tiles(0)
+    try:
+        for K in lengths:
+            w = rows(K, rng)
+            print(f"[case] bits={bits} n={n} K={K}", flush=True)
+            got = P.search(torch.from_numpy(w).cuda(), bits, n, fast=True)
+            got = {k: v.cpu().numpy() for k, v in got.items()}
+            assert_search_matches(got, R.search(w, bits, n, want_curve=True), f"bits={bits} n={n} K={K}")
+    finally:
+        P.set_small_call_tiles(before)
