@@ -701,8 +701,36 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     hipStream_t stream = (hipStream_t)stream_v;
     float *wconst = (float *)workspace;
     const unsigned wsum_wgs = (unsigned)((N + kLinWG / 64 - 1) / (kLinWG / 64));
+    // Few rows, or so few tiles that k_linear would leave CUs idle and walk the reduction in
+    // one long chain: k_linear_rows, every call that one of its row tiles covers and larger
+    // ones up to about 900 of its workgroups (K = 4096, b = 4, M x N, us, k_linear against
+    // k_linear_rows: 8x11008 58.7/12.0, 63x11008 59.5/27.8, 126x11008 60.5/46, 250x11008
+    // 61/78, 512x1000 49/25, 1024x1000 49/39, 512x11008 83/150).
+    const int row_cap = M <= 15 ? 15 : M <= 31 ? 31 : 63;          // and one row of ones
+    const int row_tile = row_cap <= 31 ? 16 : 32;
+    const long long row_tiles = (M + row_cap - 1) / row_cap, row_cols = (N + row_tile - 1) / row_tile;
+    const int rows_per_tile = (int)((M + row_tiles - 1) / row_tiles);
+    const bool by_rows = row_tiles == 1 || row_tiles * row_cols <= kRowsMaxWgs;
+    const dim3 row_grid((unsigned)row_cols, (unsigned)row_tiles);
+#define PWLQ_LINEAR_ROWS(B, P, T, MT)                                                              \
+    k_linear_rows<B, P, T, MT><<<row_grid, 64 * kRowWaves, 0, stream>>>(                           \
+        xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, y, acc, rows_per_tile)
 #define PWLQ_LINEAR_CASE(B)                                                                       \
     case B:                                                                                        \
+        if (by_rows) {                                                                             \
+            profile_mark(6, stream);                                                               \
+            if (planes == 3) {                                                                     \
+                if (row_cap == 15) PWLQ_LINEAR_ROWS(B, 3, 16, 1);                                  \
+                else if (row_cap == 31) PWLQ_LINEAR_ROWS(B, 3, 16, 2);                             \
+                else PWLQ_LINEAR_ROWS(B, 3, 32, 2);                                                \
+            } else {                                                                               \
+                if (row_cap == 15) PWLQ_LINEAR_ROWS(B, 2, 16, 1);                                  \
+                else if (row_cap == 31) PWLQ_LINEAR_ROWS(B, 2, 16, 2);                             \
+                else PWLQ_LINEAR_ROWS(B, 2, 32, 2);                                                \
+            }                                                                                      \
+            profile_mark(7, stream);                                                               \
+            break;                                                                                 \
+        }                                                                                          \
         k_linear_wsum<B><<<wsum_wgs, kLinWG, 0, stream>>>(packed_codes, packed_flags, N, K, p, m,  \
                                                           wconst);                                 \
         profile_mark(6, stream);                                                                   \

@@ -172,10 +172,9 @@ __device__ inline void planes4_folded(uint32_t codes, uint32_t f, int bits, uint
 // wconst[n] = s1 * sum_R1 w_q + s2 * sum_R2 w_q + p * sum_R2 sigma (binary64,
 // rounded to binary32): multiplied by z_x it is C3 + C6 of Section 4.  One
 // wavefront per channel.
-__device__ inline int sum_bytes(uint32_t w)
+__device__ inline int add_bytes(uint32_t w, int sum)
 {
-    return (int)(int8_t)(w & 0xff) + (int)(int8_t)((w >> 8) & 0xff) +
-           (int)(int8_t)((w >> 16) & 0xff) + (int)(int8_t)(w >> 24);
+    return __builtin_amdgcn_sdot4((int)w, 0x01010101, sum, false);
 }
 
 template <int kBits>
@@ -201,9 +200,9 @@ __global__ __launch_bounds__(kLinWG) void k_linear_wsum(const uint8_t *__restric
         for (int x = 0; x < 4; ++x) {
             uint32_t w1, w2, w3;
             planes4(c[x], f >> (4 * x), kBits, w1, w2, w3);
-            b1 += sum_bytes(w1);
-            b2 += sum_bytes(w2);
-            b3 += sum_bytes(w3);
+            b1 = add_bytes(w1, b1);
+            b2 = add_bytes(w2, b2);
+            b3 = add_bytes(w3, b3);
         }
     }
     for (int off = 32; off > 0; off >>= 1) {
@@ -498,6 +497,259 @@ __global__ __launch_bounds__(kLinWG, 2) void k_linear(const int8_t *__restrict__
                     y[row * N + n] = __builtin_fmaf(s_x, t, cst);
                 }
             }
+        }
+    }
+}
+
+// -------------------------------------------------------------- few rows
+// k_linear_rows: the same sums where the tiles of k_linear would leave the chip
+// idle (few rows of activations, or few channels).  Nothing goes through LDS on
+// the way in: in the B fragment of a matrix instruction a lane holds 16
+// consecutive weights of one channel, i.e. a run of its packed codes, which it
+// loads and decodes itself.  The eight wavefronts of a workgroup share 16 or 32
+// channels and take every eighth piece of their rows, so that together they read
+// whole lines of every row; their integer sums meet in LDS and are added there
+// (exact, whatever the split).  One row of the activation tile is all ones: its
+// sums are those of the weights themselves, which the offset z_x multiplies, so
+// no other pass reads the weights.  Bound by the packed weights' bytes for a few
+// rows, then by the decoding (about 80 vector instructions per 16 weights of a
+// lane, paid again by every tile of rows).
+constexpr int kRowWaves = 8;
+constexpr int kRowLane = 64;           // weights of a lane per step
+constexpr int kRowsMaxWgs = 900;       // workgroups up to which several row tiles beat k_linear
+
+// kTile x kTile outputs of one matrix instruction: 16 (64 deep) or 32 (32 deep).
+template <int kTile>
+struct RowTile {
+    static constexpr int kGroups = 64 / kTile;             // groups of lanes along the reduction
+    static constexpr int kRun = kRowLane * kGroups;        // weights of a channel per step
+    static constexpr int kRegs = kTile * kTile / 64;       // accumulators of a lane
+    typedef int Acc __attribute__((ext_vector_type(kRegs)));
+    __device__ static inline Acc mfma(const v4i &a, const v4i &b, const Acc &c)
+    {
+        if constexpr (kTile == 16) return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+    }
+    // row of the tile that register r of a lane in group g holds
+    __device__ static inline int row(int r, int g) { return kTile == 16 ? g * 4 + r : (r >> 2) * 8 + g * 4 + (r & 3); }
+};
+
+template <int kBits>
+struct RowStage {
+    uint32_t codes[2 * kBits];         // 64 packed codes
+    uint32_t flags[2];
+};
+
+// Unaligned loads: a run of 16 codes starts 2-byte aligned.
+template <int kWords>
+__device__ inline void load_words2(uint32_t (&out)[kWords], const uint8_t *__restrict__ src)
+{
+    struct __attribute__((packed, aligned(2))) Words { uint32_t w[kWords]; };
+    const Words v = *reinterpret_cast<const Words *>(src);
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) out[i] = v.w[i];
+}
+
+// Codes and region bits of elements e0 .. e0+63 of the streams.
+template <int kBits>
+__device__ inline void row_load(RowStage<kBits> &st, const uint8_t *__restrict__ pcodes,
+                                const uint8_t *__restrict__ pflags, long long e0)
+{
+    load_words2<2 * kBits>(st.codes, pcodes + (e0 >> 4) * (2 * kBits));
+    load_words2<2>(st.flags, pflags + (e0 >> 3));
+}
+
+// The same where only `pieces` runs of 16 exist; the others read as code 0 in the
+// centre, which adds nothing.
+template <int kBits>
+__device__ inline void row_load_part(RowStage<kBits> &st, const uint8_t *__restrict__ pcodes,
+                                     const uint8_t *__restrict__ pflags, long long e0, int pieces)
+{
+    const uint16_t *c = reinterpret_cast<const uint16_t *>(pcodes + (e0 >> 4) * (2 * kBits));
+    const uint16_t *f = reinterpret_cast<const uint16_t *>(pflags + (e0 >> 3));
+#pragma unroll
+    for (int i = 0; i < 2 * kBits; ++i) st.codes[i] = 0;
+    st.flags[0] = st.flags[1] = 0;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        if (p < pieces) {
+#pragma unroll
+            for (int i = 0; i < kBits; ++i) {          // half-words
+                const int at = p * kBits + i;
+                st.codes[at >> 1] |= (uint32_t)c[at] << (16 * (at & 1));
+            }
+            st.flags[p >> 1] |= (uint32_t)f[p] << (16 * (p & 1));
+        }
+    }
+}
+
+// The operand planes of run p (0..3, 16 weights) of a stage.
+template <int kBits, int kPlanes>
+__device__ inline void row_planes(const RowStage<kBits> &st, int p, v4i (&b)[kPlanes])
+{
+    RawCodes<kBits> raw;
+#pragma unroll
+    for (int i = 0; i < (2 * kBits + 3) / 4; ++i) {
+        const int at = p * kBits + 2 * i;              // in half-words
+        uint32_t v = st.codes[at >> 1];
+        if (at & 1) {
+            v >>= 16;
+            if ((at >> 1) + 1 < 2 * kBits) v |= st.codes[(at >> 1) + 1] << 16;
+        }
+        raw.w[i] = v;
+    }
+    uint32_t c[4];
+    unpack16<kBits>(raw, c);
+    const uint32_t f = st.flags[p >> 1] >> (16 * (p & 1));
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        uint32_t w1, w2, w3 = 0;
+        if (kPlanes == 3)
+            planes4(c[x], f >> (4 * x), kBits, w1, w2, w3);
+        else
+            planes4_folded(c[x], f >> (4 * x), kBits, w1, w2);
+        b[0][x] = (int)w1;
+        b[1][x] = (int)w2;
+        if (kPlanes == 3) b[kPlanes - 1][x] = (int)w3;
+    }
+}
+
+// A workgroup's rows: [row0, row0 + rows), rows < kTile kMT; row `rows` of its tile is
+// the row of ones.
+template <int kBits, int kPlanes, int kTile, int kMT>
+__global__ __launch_bounds__(64 * kRowWaves) void k_linear_rows(
+    const int8_t *__restrict__ xq, long long M, long long K, float s_x, float z_x,
+    const uint8_t *__restrict__ pcodes, const uint8_t *__restrict__ pflags, long long N,
+    const float *__restrict__ p, const float *__restrict__ m, float *__restrict__ y,
+    int *__restrict__ acc_out, int rows_per_tile)
+{
+    typedef RowTile<kTile> T;
+    typedef typename T::Acc Acc;
+    __shared__ int row_sums[kPlanes][kTile * kMT][kTile];        // [plane][row][channel]
+    constexpr int kSums = kPlanes * kTile * kMT * kTile;
+    for (int i = threadIdx.x; i < kSums; i += 64 * kRowWaves) (&row_sums[0][0][0])[i] = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = lane / kTile, col = lane % kTile;
+    const long long col0 = (long long)blockIdx.x * kTile;
+    const long long row0 = (long long)blockIdx.y * rows_per_tile;
+    const int rows = (int)(M - row0 < rows_per_tile ? M - row0 : rows_per_tile);
+
+    long long n = col0 + col;
+    n = n < N ? n : N - 1;
+    const long long e_lane = n * K + group * kRowLane;
+    const int8_t *a_lane[kMT];
+    bool ones[kMT];
+#pragma unroll
+    for (int mt = 0; mt < kMT; ++mt) {
+        const int r = mt * kTile + col;
+        ones[mt] = r == rows;
+        a_lane[mt] = xq + (row0 + (r < rows ? r : rows - 1)) * K + group * kRowLane;
+    }
+
+    Acc acc[kMT][kPlanes];
+#pragma unroll
+    for (int a = 0; a < kMT; ++a)
+#pragma unroll
+        for (int b = 0; b < kPlanes; ++b)
+#pragma unroll
+            for (int c = 0; c < T::kRegs; ++c) acc[a][b][c] = 0;
+
+    v4i a[kMT][4];
+    auto products = [&](const RowStage<kBits> &st, int s) {
+        v4i b[kPlanes];
+        row_planes<kBits, kPlanes>(st, s, b);
+#pragma unroll
+        for (int mt = 0; mt < kMT; ++mt) {
+            v4i x = a[mt][s];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = ones[mt] ? 0x01010101 : x[i];
+#pragma unroll
+            for (int pl = 0; pl < kPlanes; ++pl) acc[mt][pl] = T::mfma(x, b[pl], acc[mt][pl]);
+        }
+    };
+    auto load_a = [&](long long k0, int s) {
+#pragma unroll
+        for (int mt = 0; mt < kMT; ++mt) a[mt][s] = *reinterpret_cast<const v4i *>(a_lane[mt] + k0 + s * 16);
+    };
+
+    // whole runs; the next run's codes are in flight while this one is decoded, and a
+    // fragment of activations is loaded again as soon as it has been used
+    const int runs = (int)(K / T::kRun);
+    RowStage<kBits> cur, next;
+    if (wave < runs) {
+        row_load<kBits>(cur, pcodes, pflags, e_lane + (long long)wave * T::kRun);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) load_a((long long)wave * T::kRun, s);
+        for (int run = wave; run < runs; run += kRowWaves) {
+            // after the wavefront's last run: that run again, unused
+            const long long k1 = (long long)(run + kRowWaves < runs ? run + kRowWaves : run) * T::kRun;
+            row_load<kBits>(next, pcodes, pflags, e_lane + k1);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                products(cur, s);
+                load_a(k1, s);
+            }
+            cur = next;
+        }
+    }
+    // what is left of the rows, in runs of 16: the first groups of lanes have four of them
+    if (K % T::kRun && wave == runs % kRowWaves) {
+        const long long k0 = (long long)runs * T::kRun;
+        const int left = (int)((K - k0) / 16) - 4 * group;
+        const int pieces = left > 4 ? 4 : left < 0 ? 0 : left;
+        row_load_part<kBits>(cur, pcodes, pflags, e_lane + k0, pieces);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            // weights that do not exist are 0: their activations are the row's first
+            load_a(s < pieces ? k0 : -(long long)(group * kRowLane + s * 16), s);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) products(cur, s);
+    }
+
+    // the wavefronts' sums, rows 0 .. rows (ones) only; whole numbers, so the order is free
+#pragma unroll
+    for (int mt = 0; mt < kMT; ++mt)
+#pragma unroll
+        for (int r = 0; r < T::kRegs; ++r) {
+            const int row = mt * kTile + T::row(r, group);
+            if (row <= rows) {
+#pragma unroll
+                for (int pl = 0; pl < kPlanes; ++pl) atomicAdd(&row_sums[pl][row][col], acc[mt][pl][r]);
+            }
+        }
+    __syncthreads();
+
+    // C2 A1 + C4 A2 + C5 A3 + (C3 + C6), per output channel
+    const float Lf = (float)((1 << (kBits - 1)) - 1);
+    for (int i = threadIdx.x; i < rows * kTile; i += 64 * kRowWaves) {
+        const int row = i / kTile, c = i % kTile;
+        const long long nn = col0 + c;
+        if (nn >= N) continue;
+        const float pn = p[nn], mn = m[nn];
+        const float s1 = pn / Lf;
+        const float width = mn - pn;
+        const float s2 = width / Lf;
+        int sum[kPlanes], wsum[kPlanes];
+#pragma unroll
+        for (int pl = 0; pl < kPlanes; ++pl) {
+            sum[pl] = row_sums[pl][row][c];
+            wsum[pl] = row_sums[pl][rows][c];
+        }
+        // the sums of the weights: with two planes wsum[0] holds b1 + L b3, and s1 L is p
+        const double w = kPlanes == 3 ? (double)s1 * (double)wsum[0] + (double)s2 * (double)wsum[1] +
+                                            (double)pn * (double)wsum[kPlanes - 1]
+                                      : (double)pn / (double)Lf * (double)wsum[0] + (double)s2 * (double)wsum[1];
+        float t = s1 * (float)sum[0];
+        t = __builtin_fmaf(s2, (float)sum[1], t);
+        if (kPlanes == 3) t = __builtin_fmaf(pn, (float)sum[kPlanes - 1], t);
+        const long long at = (row0 + row) * N + nn;
+        y[at] = __builtin_fmaf(s_x, t, z_x * (float)w);
+        if (kPlanes == 3 && acc_out) {
+#pragma unroll
+            for (int pl = 0; pl < kPlanes; ++pl) acc_out[pl * M * N + at] = sum[pl];
         }
     }
 }
