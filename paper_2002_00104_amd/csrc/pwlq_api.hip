@@ -287,6 +287,33 @@ bool fill_emit_args(const Plan &pl, EmitArgs &ea)
     return true;
 }
 
+// The same for the selectors and the error.
+bool fill_stat_args(const Plan &pl, StatArgs &sa)
+{
+    memset(&sa, 0, sizeof(sa));
+    if (pl.nt > kStatArgTensors) return false;
+    for (int i = 0; i < pl.nt; ++i) {
+        const TensorRec &r = pl.recs[i];
+        sa.w[i] = (long long)reinterpret_cast<uintptr_t>(r.w);
+        sa.gcount[i] = r.gcount;
+        sa.out_group[i] = r.out_group;
+        sa.tile_prefix[i] = pl.tile_prefix[i];
+        sa.group_prefix[i] = pl.group_prefix[i];
+    }
+    sa.tile_prefix[pl.nt] = pl.tile_prefix[pl.nt];
+    sa.group_prefix[pl.nt] = pl.group_prefix[pl.nt];
+    sa.nt = pl.nt;
+    return true;
+}
+
+// Whether some group's tiles are too many for one thread.
+bool wide_groups(const Plan &pl)
+{
+    for (const TensorRec &r : pl.recs)
+        if (r.tpg >= kWideTiles) return true;
+    return false;
+}
+
 int launch_status(const char *what)
 {
     hipError_t e = hipGetLastError();
@@ -634,15 +661,27 @@ int run_select(const pwlq_tensor_desc *desc, int n_tensors, int mode, int select
     hipStream_t stream = (hipStream_t)stream_v;
     char *ws = (char *)workspace;
     Tables tb;
-    rc = upload_tables(pl, ws, stream, tb);
-    if (rc) return rc;
+    StatArgs sa;
+    static_assert(sizeof(Tables) + sizeof(StatArgs) + 128 <= 4096, "a launch passes at most 4 KB");
+    if (fill_stat_args(pl, sa)) {
+        memset(&tb, 0, sizeof(tb));
+        tb.nt = pl.nt;
+    } else {
+        rc = upload_tables(pl, ws, stream, tb);
+        if (rc) return rc;
+    }
     float *tile_max = (float *)(ws + pl.off_stat_max);
     double *tile_s2 = (double *)(ws + pl.off_stat_s2);
     double *tile_s1 = (double *)(ws + pl.off_stat_s1);
-    k_stats<<<(int)((pl.n_tiles + kWaves - 1) / kWaves), kWG, 0, stream>>>(tb, (int)pl.n_tiles, tile_max, tile_s2,
-                                                                      tile_s1);
-    k_select<<<(int)((pl.n_groups + kSelectWG - 1) / kSelectWG), kSelectWG, 0, stream>>>(
-        tb, (int)pl.n_groups, selector, tile_max, tile_s2, tile_s1, p_out, m_out);
+    const unsigned tile_wgs = (unsigned)((pl.n_tiles + kWaves - 1) / kWaves);
+    const unsigned group_wgs = (unsigned)((pl.n_groups + kSelectWG - 1) / kSelectWG);
+    k_stats<<<tile_wgs, kWG, 0, stream>>>(tb, sa, (int)pl.n_tiles, tile_max, tile_s2, tile_s1);
+    if (wide_groups(pl))
+        k_select<true><<<(unsigned)pl.n_groups, kSelectWG, 0, stream>>>(tb, sa, (int)pl.n_groups, selector, tile_max,
+                                                                        tile_s2, tile_s1, p_out, m_out);
+    else
+        k_select<false><<<group_wgs, kSelectWG, 0, stream>>>(tb, sa, (int)pl.n_groups, selector, tile_max, tile_s2,
+                                                             tile_s1, p_out, m_out);
     return launch_status("select launch");
 }
 
@@ -660,13 +699,23 @@ int run_mse(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode, con
     hipStream_t stream = (hipStream_t)stream_v;
     char *ws = (char *)workspace;
     Tables tb;
-    rc = upload_tables(pl, ws, stream, tb);
-    if (rc) return rc;
+    StatArgs sa;
+    if (fill_stat_args(pl, sa)) {
+        memset(&tb, 0, sizeof(tb));
+        tb.nt = pl.nt;
+    } else {
+        rc = upload_tables(pl, ws, stream, tb);
+        if (rc) return rc;
+    }
     double *tile_sse = (double *)(ws + pl.off_stat_s2);
-    k_mse_tile<<<(int)((pl.n_tiles + kWaves - 1) / kWaves), kWG, 0, stream>>>(tb, (int)pl.n_tiles, bits, p, m,
-                                                                         tile_sse);
-    k_mse_final<<<(int)((pl.n_groups + kWG - 1) / kWG), kWG, 0, stream>>>(tb, (int)pl.n_groups,
-                                                                        tile_sse, mse);
+    const unsigned tile_wgs = (unsigned)((pl.n_tiles + kWaves - 1) / kWaves);
+    const unsigned group_wgs = (unsigned)((pl.n_groups + kSelectWG - 1) / kSelectWG);
+    k_mse_tile<<<tile_wgs, kWG, 0, stream>>>(tb, sa, (int)pl.n_tiles, bits, p, m, tile_sse, mse);
+    if (pl.n_mgroups == 0) return launch_status("mse launch");
+    if (wide_groups(pl))
+        k_mse_final<true><<<(unsigned)pl.n_groups, kSelectWG, 0, stream>>>(tb, sa, (int)pl.n_groups, tile_sse, mse);
+    else
+        k_mse_final<false><<<group_wgs, kSelectWG, 0, stream>>>(tb, sa, (int)pl.n_groups, tile_sse, mse);
     return launch_status("mse launch");
 }
 

@@ -7,17 +7,86 @@
 
 namespace pwlq {
 
-// Tensor of a per-lane index (lanes may ask for different tensors): largest i
-// with prefix[i] <= x.
-__device__ inline int find_tensor_lane(const int *__restrict__ prefix, int nt, int x)
+// What the kernels of this file need to know of a tensor.  A call of up
+// to kStatArgTensors tensors carries these fields in its kernels' arguments and uploads
+// no table (two launches of about 4.5 us each per call on 54 tensors); a longer table
+// is read from the workspace.
+constexpr int kStatArgTensors = 56;
+struct StatArgs {
+    long long w[kStatArgTensors], gcount[kStatArgTensors], out_group[kStatArgTensors];
+    int tile_prefix[kStatArgTensors + 1], group_prefix[kStatArgTensors + 1];
+    int nt;                                     // 0: not used, the table is in the workspace
+};
+struct StatRec {
+    const float *w;
+    long long gcount, out_group;
+    int tpg, tile_base, group_base;
+};
+__device__ inline StatRec stat_rec(const Tables &tb, const StatArgs &sa, int i)
 {
-    int lo = 0, hi = nt;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (prefix[mid] <= x) lo = mid;
-        else hi = mid;
+    StatRec s;
+    if (sa.nt > 0) {
+        s.w = reinterpret_cast<const float *>(sa.w[i]);
+        s.gcount = sa.gcount[i];
+        s.out_group = sa.out_group[i];
+        s.tpg = (int)((s.gcount + kTileMax - 1) / kTileMax);
+        s.tile_base = sa.tile_prefix[i];
+        s.group_base = sa.group_prefix[i];
+    } else {
+        const TensorRec &r = tb.recs[i];
+        s.w = r.w;
+        s.gcount = r.gcount;
+        s.out_group = r.out_group;
+        s.tpg = r.tpg;
+        s.tile_base = r.tile_base;
+        s.group_base = r.group_base;
     }
-    return lo;
+    return s;
+}
+struct StatTile {
+    const float *src;
+    long long og;                // the group's index in the caller's arrays
+    int len, t;
+    bool whole;                  // the only tile of its group
+};
+// Tile of a wavefront; of a tensor whose groups are cut into several tiles the full
+// ones first (see slot_to_tile).
+__device__ inline StatTile stat_tile(const Tables &tb, const StatArgs &sa, int slot)
+{
+    const int i = sa.nt > 0 ? find_tensor(sa.tile_prefix, sa.nt, slot) : find_tensor(tb.tile_prefix, tb.nt, slot);
+    const StatRec r = stat_rec(tb, sa, i);
+    int g = slot - r.tile_base, tig = 0;
+    if (r.tpg > 1) {
+        const int end = sa.nt > 0 ? sa.tile_prefix[i + 1] : tb.tile_prefix[i + 1];
+        const int nfull = (end - r.tile_base) / r.tpg * (r.tpg - 1);
+        const int ls = g;
+        g = ls < nfull ? ls / (r.tpg - 1) : ls - nfull;
+        tig = ls < nfull ? ls - g * (r.tpg - 1) : r.tpg - 1;
+    }
+    const long long first = (long long)tig * kTileMax;
+    StatTile st;
+    st.src = reinterpret_cast<const float *>(uni((long long)reinterpret_cast<uintptr_t>(
+        r.w + (long long)g * r.gcount + first)));
+    const long long left = r.gcount - first;
+    st.len = uni((int)(left < kTileMax ? left : kTileMax));
+    st.og = uni(r.out_group + g);
+    st.t = uni(r.tile_base + g * r.tpg + tig);
+    st.whole = r.tpg == 1;
+    return st;
+}
+// Tensor of group g, where groups first_g (the wavefront's first; the same in every
+// lane) to first_g + 63 ask together.
+__device__ inline StatRec stat_group(const Tables &tb, const StatArgs &sa, int first_g, int g)
+{
+    int i;
+    if (sa.nt > 0) {
+        i = find_tensor(sa.group_prefix, sa.nt, first_g);
+        while (sa.group_prefix[i + 1] <= g) ++i;
+    } else {
+        i = find_tensor(tb.group_prefix, tb.nt, first_g);
+        while (tb.group_prefix[i + 1] <= g) ++i;
+    }
+    return stat_rec(tb, sa, i);
 }
 
 // ------------------------------------------------------------------- stats
@@ -28,15 +97,13 @@ __device__ inline int find_tensor_lane(const int *__restrict__ prefix, int nt, i
 // added in a fixed order.
 constexpr int kStatUnroll = 4;
 
-__global__ __launch_bounds__(kWG) void k_stats(Tables tb, int n_tiles, float *__restrict__ tile_max,
+__global__ __launch_bounds__(kWG) void k_stats(Tables tb, StatArgs sa, int n_tiles, float *__restrict__ tile_max,
                                                double *__restrict__ tile_s2,
                                                double *__restrict__ tile_s1)
 {
     const int slot = uni((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
     if (slot >= n_tiles) return;
-    int t;
-    TensorRec r;
-    TileInfo ti = tile_of(tb, slot, r, t);
+    const StatTile ti = stat_tile(tb, sa, slot);
     const int lane = threadIdx.x & 63;
     float mx = 0.0f;
     int bad = 0;
@@ -70,97 +137,119 @@ __global__ __launch_bounds__(kWG) void k_stats(Tables tb, int n_tiles, float *__
     mx = wave_max(mx);
     bad = wave_or(bad);
     if (lane == 0) {
-        tile_max[t] = bad ? __builtin_nanf("") : mx;
-        tile_s2[t] = t2;
-        tile_s1[t] = t1;
+        tile_max[ti.t] = bad ? __builtin_nanf("") : mx;
+        tile_s2[ti.t] = t2;
+        tile_s1[ti.t] = t1;
     }
 }
 
 // ------------------------------------------------------------------ select
-// Density and distribution function of the assumed zero-mean law truncated to
-// [-m, m] (F(-m) = 0, F(m) = 1), at 0 < p < m.
-struct Law {
-    double F, f, df;     // CDF, PDF, derivative of the PDF
-};
-__device__ inline double std_normal_cdf(double x)
-{
-    return 0.5 * erfc(-x * 0.70710678118654752440);
-}
-__device__ inline Law truncated_law(double p, double m, double scale, bool laplace)
-{
-    Law w;
-    if (laplace) {
-        const double z = 1.0 - exp(-m / scale);
-        const double e = exp(-p / scale);
-        w.F = 0.5 + 0.5 * (1.0 - e) / z;
-        w.f = e / (2.0 * scale) / z;
-        w.df = -w.f / scale;
-    } else {
-        const double z = 2.0 * std_normal_cdf(m / scale) - 1.0;
-        const double x = p / scale;
-        w.F = (std_normal_cdf(x) - std_normal_cdf(-m / scale)) / z;
-        w.f = exp(-0.5 * x * x) / (scale * 2.50662827463100050242) / z;
-        w.df = -x / scale * w.f;
-    }
-    return w;
-}
-
-// Minimiser of the expected error of Eq.6 over (0, m/2): root of its derivative
-// (Eq.8; Eq.11 is that root written out).  The derivative is increasing there
-// (Lemma 1: the second derivative, Eq.9, is positive), so Newton steps are kept
-// inside a shrinking bracket and replaced by its midpoint when they leave it.
+// Minimiser of the expected error of Eq.6 over (0, m/2) for a zero-mean law truncated to
+// [-m, m]: root of its derivative (Eq.8; Eq.11 is that root written out).  In units of
+// the law's scale, x = p / scale and t = m / scale, with the law's mass above x and above
+// t, both over the mass inside [-t, t]:
+//   g = x - 2 t (above(x) - above(t)) + t (2 x - t) f(x)
+// The derivative is increasing there (Lemma 1: the second derivative, Eq.9, is positive),
+// so Newton steps are kept inside a shrinking bracket and replaced by its midpoint when
+// they leave it; the end t/2 is looked at when a step would pass it.  A Newton step of
+// 1e-9 x is the last: the error after it is of the order of its square, below the
+// rounding of a binary64.
+//
+// One thread per group leaves most SIMDs with one wavefront, which runs at the latency of
+// its instructions and of fetching them: the loop body is the only copy of the law (its
+// first trip evaluates it at t).  27 560 groups, Gaussian: 44 us with three erfc per step
+// and steps that ended on the bracket answered by bisection (50 trips in one group of
+// 64 weights in a hundred), 5.4 us like this.
 __device__ inline double solve_breakpoint(double m, double scale, bool laplace, double start)
 {
-    double lo = 0.0, hi = 0.5 * m;
-    {
-        const Law w = truncated_law(hi, m, scale, laplace);
-        const double g = hi - 2.0 * m + 2.0 * m * w.F + m * (2.0 * hi - m) * w.f;
-        if (g <= 0.0) return hi;
-    }
-    double p = (start > lo && start < hi) ? start : 0.5 * (lo + hi);
+    const double t = m / scale;
+    double lo = 0.0, hi = 0.5 * t, above_t = 0.0, inv_z = 1.0;
+    double x = t;                                      // first trip: the mass outside [-t, t]
+    double next = start / scale;
+    if (!(next > lo && next < hi)) next = 0.5 * (lo + hi);
+    bool first = true, at_end = false, end_seen = false;
     for (int it = 0; it < 100; ++it) {
-        const Law w = truncated_law(p, m, scale, laplace);
-        const double g = p - 2.0 * m + 2.0 * m * w.F + m * (2.0 * p - m) * w.f;
-        const double dg = 1.0 + 4.0 * m * w.f + m * (2.0 * p - m) * w.df;
-        if (g > 0.0) hi = p;
-        else lo = p;
-        double next = p - g / dg;
-        if (!(next > lo && next < hi)) next = 0.5 * (lo + hi);
-        const double step = fabs(next - p);
-        p = next;
-        if (step <= 2.0e-16 * m || hi - lo <= 2.0e-16 * m) break;
+        const double ex = exp(laplace ? -x : -0.5 * x * x);
+        const double above = 0.5 * (laplace ? ex : erfc(x * 0.70710678118654752440));
+        if (first) {
+            above_t = above;
+            inv_z = 1.0 / (1.0 - 2.0 * above);
+            x = next;
+            first = false;
+            continue;
+        }
+        const double f = ex * (laplace ? 0.5 : 0.39894228040143267794) * inv_z;
+        const double df = laplace ? -f : -x * f;
+        const double lever = t * (2.0 * x - t);
+        const double g = x - 2.0 * t * (above - above_t) * inv_z + lever * f;
+        if (at_end) {                                  // x is t/2
+            if (g <= 0.0) break;
+            end_seen = true;
+            x = 0.5 * (lo + hi);
+            at_end = false;
+            continue;
+        }
+        const double dg = 1.0 + 4.0 * t * f + lever * df;
+        if (g > 0.0) hi = x;
+        else lo = x;
+        const double step = -g / dg;
+        next = x + step;
+        if (fabs(step) <= 1.0e-9 * x) {                // before the bracket is asked: the last steps may end on it
+            x = fmin(fmax(next, lo), hi);
+            break;
+        }
+        if (next >= hi && hi == 0.5 * t && !end_seen) {
+            x = hi;
+            at_end = true;
+            continue;
+        }
+        x = (next > lo && next < hi) ? next : 0.5 * (lo + hi);
+        if (hi - lo <= 2.0e-16 * t) break;
     }
-    return p;
+    return x * scale;
 }
 
-// One thread per group: add the tiles' statistics in tile order, estimate the
-// scale about zero (sigma^2 = mean w^2, beta = mean |w|) and select p.
+// Add the tiles' statistics, estimate the scale about zero (sigma^2 = mean w^2,
+// beta = mean |w|) and select p.
 // selector 0: Section 5.1's logarithmic fit, p = sigma ln(0.8614 m/sigma + 0.6079);
 // selector 1: Eq.11 for the truncated Gaussian; 2: for the truncated Laplacian.
+// One thread per group, tiles in order; where some group has kWideTiles tiles or more
+// (a tensor as one group) one wavefront per group, lanes over the tiles, the lanes' sums
+// added in a fixed order.
 constexpr int kSelectWG = 64;     // one wavefront per workgroup: a few ten thousand groups reach every CU
+constexpr int kWideTiles = 16;
 
-__global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, int n_groups, int selector,
+template <bool kWide>
+__global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, StatArgs sa, int n_groups, int selector,
                                                 const float *__restrict__ tile_max,
                                                 const double *__restrict__ tile_s2,
                                                 const double *__restrict__ tile_s1,
                                                 float *__restrict__ p_out,
                                                 float *__restrict__ m_out)
 {
-    const int g = blockIdx.x * kSelectWG + threadIdx.x;
-    if (g >= n_groups) return;
-    const int tensor = (tb.nt == 1) ? 0 : find_tensor_lane(tb.group_prefix, tb.nt, g);
-    const TensorRec &r = (tb.nt == 1) ? tb.one : tb.recs[tensor];
+    const int first = kWide ? blockIdx.x : blockIdx.x * kSelectWG;
+    const int g = kWide ? first : (first + (int)threadIdx.x < n_groups ? first + (int)threadIdx.x : n_groups - 1);
+    const StatRec r = stat_group(tb, sa, first, g);
     const int gl = g - r.group_base;
     const long long tile0 = r.tile_base + (long long)gl * r.tpg;
     float mf = 0.0f;
     int bad = 0;
     double s2 = 0.0, s1 = 0.0;
-    for (int j = 0; j < r.tpg; ++j) {
+    for (int j = kWide ? threadIdx.x : 0; j < r.tpg; j += kWide ? kSelectWG : 1) {
         const float v = tile_max[tile0 + j];
         bad |= (v != v);
         mf = fmaxf(mf, v);
         s2 += tile_s2[tile0 + j];
         s1 += tile_s1[tile0 + j];
+    }
+    if (kWide) {
+        mf = wave_max(mf);
+        bad = wave_or(bad);
+        s2 = wave_sum(s2);
+        s1 = wave_sum(s1);
+        if (threadIdx.x > 0) return;
+    } else if (first + (int)threadIdx.x >= n_groups) {
+        return;
     }
     if (bad) mf = __builtin_nanf("");
     const long long og = r.out_group + gl;
@@ -184,18 +273,16 @@ __global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, int n_groups, i
 // Squared error of Eq.3 over one tile with the group's (m, p): canonical
 // binary32 code, binary64 error, fixed summation order.  One wavefront per
 // tile, as in k_stats.
-__global__ __launch_bounds__(kWG) void k_mse_tile(Tables tb, int n_tiles, int bits,
+__global__ __launch_bounds__(kWG) void k_mse_tile(Tables tb, StatArgs sa, int n_tiles, int bits,
                                                   const float *__restrict__ p_in,
                                                   const float *__restrict__ m_in,
-                                                  double *__restrict__ tile_sse)
+                                                  double *__restrict__ tile_sse,
+                                                  double *__restrict__ mse)
 {
     const int slot = uni((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
     if (slot >= n_tiles) return;
-    int t;
-    TensorRec r;
-    TileInfo ti = tile_of(tb, slot, r, t);
-    const long long og = r.out_group + ti.group_local;
-    const Pieces q = make_pieces(m_in[og], p_in[og], bits);
+    const StatTile ti = stat_tile(tb, sa, slot);
+    const Pieces q = make_pieces(m_in[ti.og], p_in[ti.og], bits);
     const int lane = threadIdx.x & 63;
     double acc[kStatUnroll];
 #pragma unroll
@@ -210,21 +297,33 @@ __global__ __launch_bounds__(kWG) void k_mse_tile(Tables tb, int n_tiles, int bi
     }
     for (; i < ti.len; i += 64) acc[0] += exact_error_sq(q, fabsf(ti.src[i]));
     const double s = wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
-    if (lane == 0) tile_sse[t] = s;
+    if (lane == 0) {
+        if (ti.whole) mse[ti.og] = s / (double)ti.len;      // the group's only tile
+        else tile_sse[ti.t] = s;
+    }
 }
 
-__global__ __launch_bounds__(kWG) void k_mse_final(Tables tb, int n_groups,
+// Groups of several tiles: tiles added as in k_select.  (Those of one tile are done; a call
+// that has no others does not come here.)
+template <bool kWide>
+__global__ __launch_bounds__(kSelectWG) void k_mse_final(Tables tb, StatArgs sa, int n_groups,
                                                    const double *__restrict__ tile_sse,
                                                    double *__restrict__ mse)
 {
-    const int g = blockIdx.x * kWG + threadIdx.x;
-    if (g >= n_groups) return;
-    const int tensor = (tb.nt == 1) ? 0 : find_tensor_lane(tb.group_prefix, tb.nt, g);
-    const TensorRec &r = (tb.nt == 1) ? tb.one : tb.recs[tensor];
+    const int first = kWide ? blockIdx.x : blockIdx.x * kSelectWG;
+    const int g = kWide ? first : (first + (int)threadIdx.x < n_groups ? first + (int)threadIdx.x : n_groups - 1);
+    const StatRec r = stat_group(tb, sa, first, g);
     const int gl = g - r.group_base;
+    if (r.tpg == 1) return;
     const long long tile0 = r.tile_base + (long long)gl * r.tpg;
     double s = 0.0;
-    for (int j = 0; j < r.tpg; ++j) s += tile_sse[tile0 + j];
+    for (int j = kWide ? threadIdx.x : 0; j < r.tpg; j += kWide ? kSelectWG : 1) s += tile_sse[tile0 + j];
+    if (kWide) {
+        s = wave_sum(s);
+        if (threadIdx.x > 0) return;
+    } else if (first + (int)threadIdx.x >= n_groups) {
+        return;
+    }
     mse[r.out_group + gl] = s / (double)r.gcount;
 }
 
