@@ -384,6 +384,17 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     const long long unit_groups = (pl.n_units + upw - 1) / upw;
     const long long wgs = (unit_groups + 7) / 8 * 8 * ny;
     if (wgs > 0x7fffffffLL) return fail(PWLQ_EINVAL, "search grid too large");
+    // too few wavefronts to keep the SIMDs busy: the tiles' elements are cut into slices
+    int slices = 1;
+    {
+        int longest_plain = 0;
+        bool one_tile = true;
+        for (const TensorRec &r : pl.recs)
+            if (!r.fast) { longest_plain = std::max(longest_plain, r.tile_len); one_tile &= r.tpu == 1; }
+        while (one_tile && slices < 8 && 2 * slices * pl.n_units * pl.nblk <= kSlicedWaves &&
+               longest_plain >= 2 * slices * kSliceMin)
+            slices *= 2;
+    }
     const long long group_sum_wgs = pl.n_mgroups * (long long)((n_cand + kSumCand - 1) / kSumCand);
     if (group_sum_wgs > 0x7fffffffLL) return fail(PWLQ_EINVAL, "too many groups longer than one tile");
 
@@ -517,8 +528,14 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                     tb, nt_large, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
         }
         profile_mark(0, stream);
-        k_search<<<(unsigned)wgs, kSearchWaves * 64, 0, stream>>>(tb, n_cand, pl.nblk, bits, ny, upw, bpw_log2,
-                                                    offsets, sorted, fine, pl.fine ? nt_large : 0, sse32);
+        if (slices > 1) {
+            const int search_ny = (pl.nblk * slices + kSearchWaves - 1) / kSearchWaves;
+            const int bw = (pl.nblk + search_ny - 1) / search_ny;
+            k_search_sliced<<<(unsigned)(pl.n_units * search_ny), (unsigned)(bw * slices) * 64, 0, stream>>>(
+                tb, n_cand, pl.nblk, bits, search_ny, bw, slices, offsets, sorted, fine, pl.fine ? nt_large : 0, sse32);
+        } else
+            k_search<<<(unsigned)wgs, kSearchWaves * 64, 0, stream>>>(tb, n_cand, pl.nblk, bits, ny, upw, bpw_log2,
+                                                        offsets, sorted, fine, pl.fine ? nt_large : 0, sse32);
         profile_mark(1, stream);
     }
     if (pl.n_mgroups > 0) {

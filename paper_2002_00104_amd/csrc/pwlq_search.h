@@ -106,9 +106,11 @@ __device__ inline void mixed8(const float8 &cur, float kf, float rc, float rt, f
 // compare, no branch.  The one vector that holds the lane's switch contributes
 // nothing in that loop; every lane evaluates its own switch vector afterwards,
 // element by element (a per-lane load of 32 bytes, once per tile).
+// (own_begin, own_end: the vectors a slice of the tile holds; the switch vector is the
+// slice's that has it.)
 __device__ inline void zone_mixed_fine(const float *__restrict__ us, int begin, int end, int sw,
                                        float kf, float rc, float rt, float ct, float &sum_c,
-                                       float &sum_t)
+                                       float &sum_t, int own_begin = 0, int own_end = 0x7fffffff)
 {
     for (int cb = begin; cb < end; cb += kChunk) {
         const int ce = (cb + kChunk < end) ? cb + kChunk : end;
@@ -136,8 +138,9 @@ __device__ inline void zone_mixed_fine(const float *__restrict__ us, int begin, 
         sum_t += acc_t;
     }
     // the lane's own switch vector (none if the switch falls between two vectors)
-    const bool has = (sw & (kVec - 1)) != 0;
-    const int i0 = has ? (sw & ~(kVec - 1)) : begin;
+    const int sv = sw & ~(kVec - 1);
+    const bool has = (sw & (kVec - 1)) != 0 && sv >= own_begin && sv < own_end;
+    const int i0 = has ? sv : begin;
     const float4 v0 = *reinterpret_cast<const float4 *>(us + i0);
     const float4 v1 = *reinterpret_cast<const float4 *>(us + i0 + 4);
     const float own[kVec] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
@@ -248,6 +251,76 @@ __global__ __launch_bounds__(kSearchWaves * 64) void k_search(Tables tb, int n, 
         else sm = zone_mixed(us, lo, hi, kf, rc, rt, ct, stepc, stept);
         if (live)
             sse32[(long long)t * n + (k - 1)] = (stepc * stepc) * sc + (stept * stept) * st + sm;
+    }
+}
+
+// The same for a call with few tiles and candidate blocks.  A wavefront on its own
+// issues one vector instruction every eight or nine cycles, and a SIMD needs four or more
+// to be busy: where the call's wavefronts (tile, block) are few, the elements of a tile are
+// cut into 2, 4 or 8 slices, one wavefront each, whose sums meet in LDS and are added in
+// slice order.  A workgroup holds `bw` blocks of one tile, all their slices.  As many
+// slices as all fit the chip at once (kSlicedWaves, eight per SIMD); search + quantize, us,
+// without and with: [64, 4608] n = 1000 132 / 57, [1000, 2048] n = 200 136 / 69,
+// [2048, 512] n = 100 66 / 44, [64, 2304] as one group n = 300 242 / 63, [256, 2304]
+// n = 1000 78 / 71; one doubling more: [515, 1155] n = 300 49 -> 52, [256, 2304] 71 -> 81.
+constexpr int kSlicedWaves = 8192;
+constexpr int kSliceMin = 128;           // elements
+
+__global__ __launch_bounds__(kSearchWaves * 64) void k_search_sliced(Tables tb, int n, int nblk, int bits, int ny,
+                                                                     int bw, int slices,
+                                                                     const int *__restrict__ offsets,
+                                                                     const float *__restrict__ sorted,
+                                                                     const unsigned short *__restrict__ fine,
+                                                                     int fine_tiles, float *__restrict__ sse32)
+{
+    __shared__ float part[kSearchWaves][kBlk];
+    const int wave = uni((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    const int unit = blockIdx.x / ny;
+    const int slice = wave / bw, jb = wave - slice * bw;
+    const int j = (blockIdx.x - unit * ny) * bw + jb;
+    const int tensor = find_tensor(tb.unit_prefix, tb.nt, unit);
+    const TensorRec r = rec_of(tb, tensor);
+    if (r.fast) return;               // evaluated by k_fast
+    const int t = slot_to_tile(r, r.tile_base + unit - r.unit_base);      // one tile per unit
+    int k = j * kBlk + lane + 1;
+    const bool live = k <= n;
+    if (!live) k = n;
+    float sum = 0.0f;
+    if (j < nblk) {
+        const float Lf = (float)((1 << (bits - 1)) - 1);
+        const float kf = (float)k;
+        const float nk = (float)(n - k);
+        const float rc = Lf / kf;
+        const float rt = (k < n) ? Lf / nk : 0.0f;
+        const float ct = -kf * rt;
+        const float stepc = kf / Lf;
+        const float stept = nk / Lf;
+        const int local = t - r.tile_base;
+        const int len = (local % r.tpg == r.tpg - 1) ? r.last_len : r.tile_len;
+        const int vecs = (len + kVec - 1) / kVec;
+        const int s0 = vecs * slice / slices * kVec, s1 = vecs * (slice + 1) / slices * kVec;
+        const float *us = sorted + (r.sorted_base + (long long)local * r.stride);
+        const int *off = offsets + (long long)t * (nblk + 1);
+        const int lo = off[j] & ~(kVec - 1);
+        const int hi = (off[j + 1] + kVec - 1) & ~(kVec - 1);
+        const int mlo = lo > s0 ? lo : s0, mhi = hi < s1 ? hi : s1;
+        float sc = zone_one_region<false>(us, s0, lo < s1 ? lo : s1, rc, 0.0f);
+        float st = zone_one_region<true>(us, hi > s0 ? hi : s0, s1, rt, ct);
+        float sm = 0.0f;
+        if (t < fine_tiles && hi - lo >= kFineMin) {
+            if (mlo < mhi)
+                zone_mixed_fine(us, mlo, mhi, fine[(long long)t * (n + 1) + k], kf, rc, rt, ct, sc, st, s0, s1);
+        } else {
+            sm = zone_mixed(us, mlo, mhi, kf, rc, rt, ct, stepc, stept);
+        }
+        sum = (stepc * stepc) * sc + (stept * stept) * st + sm;
+    }
+    part[wave][lane] = sum;
+    __syncthreads();
+    if (slice == 0 && j < nblk && live) {
+        for (int x = 1; x < slices; ++x) sum += part[x * bw + jb][lane];
+        sse32[(long long)t * n + (k - 1)] = sum;
     }
 }
 
