@@ -598,7 +598,7 @@ int run_quantize(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode
     Tables tb;
     static_assert(sizeof(Tables) + sizeof(EmitArgs) + 64 <= 4096, "a launch passes at most 4 KB");
     EmitArgs ea;
-    if (fill_emit_args(pl, ea)) {          // the table travels with the launch
+    if (pl.nt > 1 && fill_emit_args(pl, ea)) {          // the table travels with the launch
         memset(&tb, 0, sizeof(tb));
         tb.nt = pl.nt;
     } else {
@@ -606,7 +606,8 @@ int run_quantize(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode
         if (rc) return rc;
     }
     profile_mark(2, stream);
-    k_emit<<<(int)pl.n_chunks, kWG, 0, stream>>>(tb, ea, bits, p_star, m, codes, flags, w_hat);
+    if (pl.nt == 1) k_emit<<<(int)pl.n_chunks, kWG, 0, stream>>>(tb, EmitOne{0}, bits, p_star, m, codes, flags, w_hat);
+    else k_emit<<<(int)pl.n_chunks, kWG, 0, stream>>>(tb, ea, bits, p_star, m, codes, flags, w_hat);
     profile_mark(3, stream);
     return launch_status("quantize launch");
 }
@@ -633,21 +634,25 @@ int run_quantize_packed(const pwlq_tensor_desc *desc, int n_tensors, int bits, i
     hipStream_t stream = (hipStream_t)stream_v;
     Tables tb;
     EmitArgs ea;
-    if (fill_emit_args(pl, ea)) {
+    if (pl.nt > 1 && fill_emit_args(pl, ea)) {
         memset(&tb, 0, sizeof(tb));
         tb.nt = pl.nt;
     } else {
         rc = upload_tables(pl, (char *)workspace, stream, tb);
         if (rc) return rc;
     }
+#define PWLQ_PACKED(B, PER, ARGS)                                                                  \
+    k_emit_packed<B, PER><<<(int)pl.n_chunks, kEmitChunk / PER, 0, stream>>>(                      \
+        tb, ARGS, p_star, m, packed_codes, packed_flags, w_hat)
 #define PWLQ_PACKED_CASE(B)                                                                        \
     case B:                                                                                        \
-        if (w_hat)                                                                                 \
-            k_emit_packed<B, 8><<<(int)pl.n_chunks, kEmitChunk / 8, 0, stream>>>(                  \
-                tb, ea, p_star, m, packed_codes, packed_flags, w_hat);                             \
-        else                                                                                       \
-            k_emit_packed<B, 16><<<(int)pl.n_chunks, kEmitChunk / 16, 0, stream>>>(                \
-                tb, ea, p_star, m, packed_codes, packed_flags, w_hat);                             \
+        if (w_hat) {                                                                               \
+            if (pl.nt == 1) PWLQ_PACKED(B, 8, EmitOne{0});                                         \
+            else PWLQ_PACKED(B, 8, ea);                                                            \
+        } else {                                                                                   \
+            if (pl.nt == 1) PWLQ_PACKED(B, 16, EmitOne{0});                                        \
+            else PWLQ_PACKED(B, 16, ea);                                                           \
+        }                                                                                          \
         break;
     switch (bits) {
         PWLQ_PACKED_CASE(2)
@@ -659,6 +664,7 @@ int run_quantize_packed(const pwlq_tensor_desc *desc, int n_tensors, int bits, i
         PWLQ_PACKED_CASE(8)
     }
 #undef PWLQ_PACKED_CASE
+#undef PWLQ_PACKED
     return launch_status("packed quantize launch");
 }
 

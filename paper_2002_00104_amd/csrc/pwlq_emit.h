@@ -66,11 +66,21 @@ struct EmitArgs {
     int emit_prefix[kEmitArgTensors + 1];       // first chunk of each tensor, then the total
     int nt;                                     // 0: not used, the table is in the workspace
 };
+// A call with one tensor passes its record in `Tables` and nothing here: 3.4 KB of
+// arguments less to hand to the launch.
+struct EmitOne {
+    int nt;                                     // 0
+};
 struct EmitRec {
     const float *w;
     long long gcount, out_elem, out_group, out_code_byte, out_flag_byte;
     int ngroups, emit_base;
 };
+__device__ inline EmitRec emit_rec(const Tables &tb, const EmitOne &, int)
+{
+    const TensorRec &r = tb.one;
+    return {r.w, r.gcount, r.out_elem, r.out_group, r.out_code_byte, r.out_flag_byte, r.ngroups, 0};
+}
 __device__ inline EmitRec emit_rec(const Tables &tb, const EmitArgs &ea, int chunk)
 {
     EmitRec e;
@@ -103,7 +113,8 @@ __device__ inline EmitRec emit_rec(const Tables &tb, const EmitArgs &ea, int chu
 // in flight per thread.  The group of an element is its row-major index
 // divided by the group length; a vector of four that stays inside one group
 // shares one set of parameters.
-__global__ __launch_bounds__(kWG) void k_emit(Tables tb, EmitArgs ea, int bits,
+template <typename Args>
+__global__ __launch_bounds__(kWG) void k_emit(Tables tb, Args ea, int bits,
                                               const float *__restrict__ p_star,
                                               const float *__restrict__ m_in,
                                               uint8_t *__restrict__ codes,
@@ -194,8 +205,8 @@ __global__ __launch_bounds__(kWG) void k_emit(Tables tb, EmitArgs ea, int bits,
 // nothing goes through LDS and nothing waits on another wavefront.  Other
 // widths (and streams that are not word-aligned) assemble the workgroup's code
 // and flag bytes in LDS and write them out as whole words.
-template <int kBits, int kPackPer>
-__global__ __launch_bounds__(kEmitChunk / kPackPer) void k_emit_packed(Tables tb, EmitArgs ea,
+template <int kBits, int kPackPer, typename Args>
+__global__ __launch_bounds__(kEmitChunk / kPackPer) void k_emit_packed(Tables tb, Args ea,
                                                         const float *__restrict__ p_star,
                                                         const float *__restrict__ m_in,
                                                         uint8_t *__restrict__ packed_codes,

@@ -132,8 +132,14 @@ def _check(status: int) -> None:
         raise PwlqError(status, lib.pwlq_last_error().decode())
 
 
+# The handle of the current stream of the current device, without the Python Stream object
+# that torch.cuda.current_stream() makes on every call (2.7 us against 0.1 us).
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _dev32(w: torch.Tensor) -> torch.Tensor:
