@@ -82,12 +82,13 @@ __device__ inline float zone_mixed(const float *__restrict__ us, int begin, int 
     return outer;
 }
 
-// One vector of 8 elements in the per-lane form (see zone_mixed).
+// One vector of 8 elements, from the kFirst-th on, in the per-lane form (see zone_mixed).
+template <int kFirst = 0>
 __device__ inline void mixed8(const float8 &cur, float kf, float rc, float rt, float ct,
                               float stepc, float stept, float &acc)
 {
 #pragma unroll
-    for (int e = 0; e < kVec; ++e) {
+    for (int e = kFirst; e < kVec; ++e) {
         const float u = cur[e];
         const bool tail = u > kf;
         const float tc = u * rc;
@@ -216,6 +217,7 @@ __global__ __launch_bounds__(kSearchWaves * 64) void k_search(Tables tb, int n, 
     // nothing), and the next tile's vectors are loaded while this one is evaluated.
     if (r.tile_len <= kTinyTile && r.tpg == 1) {
         const bool two = r.tile_len > kVec;                 // the second vector holds elements
+        const bool one_first = r.tile_len == kVec + 1;      // 3 x 3 filters: seven zeros, then the nine elements
         const float *us = sorted + (r.sorted_base + (long long)(first - r.tile_base) * r.stride);
         float8 c0 = load8(us), c1 = load8(us + kVec);       // the spare vector of a tile, if not its second
         for (int t = first; t < last; ++t) {
@@ -223,7 +225,8 @@ __global__ __launch_bounds__(kSearchWaves * 64) void k_search(Tables tb, int n, 
             const float *nx = (t + 1 < last) ? us + r.stride : us;
             const float8 n0 = load8(nx), n1 = load8(nx + kVec);
             float acc0 = 0.0f, acc1 = 0.0f;
-            mixed8(c0, kf, rc, rt, ct, stepc, stept, acc0);
+            if (one_first) mixed8<kVec - 1>(c0, kf, rc, rt, ct, stepc, stept, acc0);
+            else mixed8(c0, kf, rc, rt, ct, stepc, stept, acc0);
             if (two) mixed8(c1, kf, rc, rt, ct, stepc, stept, acc1);
             if (live) sse32[(long long)t * n + (k - 1)] = acc0 + acc1;
             c0 = n0;
