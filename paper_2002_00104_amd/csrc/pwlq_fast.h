@@ -42,6 +42,7 @@ constexpr unsigned kFastTop = (1u << 24) - 1 - (1u << (24 - kFastOct));   // lar
 static_assert(kFastTop >= 65535u * 254u, "every grid fits");
 constexpr int kFastCrowd = 64;                     // fullest bucket the look-ups may walk: this or 1/16 of the tile
 constexpr int kFastWalk = 4;                       // elements read per step of a walk
+constexpr int kFastShort = 256;                    // longest tile of a launch of 128 threads
 constexpr int kFastLong = 5120, kFastMid = 2816;   // longest tiles of a launch of 512 threads: three, then four workgroups' LDS per CU
 constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones
 
@@ -50,7 +51,7 @@ constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launc
 // bounds it with room and is added to the slack of the filter (keep_threshold).
 
 // log2 of a tile's buckets per octave, about two buckets per element.
-__host__ __device__ inline int fast_octave_bits(int len)
+__host__ __device__ constexpr int fast_octave_bits(int len)
 {
     int bits = 1;
     while (bits < kFastOctBits && (8 << bits) <= len) ++bits;
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kT, kT == 512 ? 6 : 8) void k_fast(Tables tb, int t
     // themselves, then of everything before them), then the grouped elements
     extern __shared__ unsigned long long fast_lds[];
     constexpr int kW = kT / 64;
-    constexpr int kScan = (kFastWords + kT - 1) / kT;   // words a thread holds at most
+    constexpr int kScan = ((kFastOct << fast_octave_bits(kT * kPer)) + kT - 1) / kT;   // words a thread holds at most
     __shared__ float redm[kW], redsum[kW];
     __shared__ int redbad[kW], redzero[kW], wcrowd[kW];
     __shared__ unsigned long long wsum[kW];
