@@ -455,7 +455,7 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
         const int q = (int)kFastTop / (n_cand * 2 * ((1 << (bits - 1)) - 1));
         // A launch's workgroups and LDS are sized for its longest tile; shorter tiles get
         // launches of their own where both sides have enough of them.
-        auto size_class = [](int len) { return len > kFastLong ? 0 : len > kFastMid ? 1 : len > kSmallTile ? 2 : len > kFastShort ? 3 : 4; };
+        auto size_class = [](int len) { return len > kFastLong ? 0 : len > kSmallTile ? 1 : len > kFastShort ? 2 : 3; };
         profile_mark(4, stream);
         int begin = 0, seen = 0, part_longest = 0;
         for (size_t i = 0; i < pl.recs.size() && pl.recs[i].fast; ++i) {
@@ -473,10 +473,9 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                     k_fast<1024, kTileMax / 1024><<<count, 1024, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
                     break;
                 case 1:
-                case 2:
                     k_fast<512, kFastLong / 512><<<count, 512, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
                     break;
-                case 4:
+                case 3:
                     k_fast<128, kFastShort / 128><<<count, 128, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
                     break;
                 default:

@@ -25,7 +25,7 @@
 // holds the sum (38 bits) and count (14 bits) of the elements before it and its
 // own count (12 bits).  H(b) is b * count - sum of the bucket of b, plus
 // max(b - u, 0) over the bucket's own elements: elements past its end are above b
-// and add nothing, so the first four are read without looking at the count.
+// and add nothing, so the first three are read without looking at the count.
 // Elements that are exactly zero (pruned weights) are counted, never walked.
 #pragma once
 
@@ -35,15 +35,17 @@
 
 namespace pwlq {
 
-constexpr int kFastOctBits = 9;                    // most buckets per octave: 2^9
+// Most buckets per octave, 2^8.  2^9 halves the walks and costs the fourth workgroup per
+// CU its LDS (38 400 tiles of 4096, search + quantize: 1228 us with 2^9, 1145 with 2^8).
+constexpr int kFastOctBits = 8;
 constexpr int kFastOct = 7;                        // octaves, or twice as many of half as many buckets each
 constexpr int kFastWords = kFastOct << kFastOctBits;   // most buckets per tile
 constexpr unsigned kFastTop = (1u << 24) - 1 - (1u << (24 - kFastOct));   // largest magnitude
 static_assert(kFastTop >= 65535u * 254u, "every grid fits");
 constexpr int kFastCrowd = 64;                     // fullest bucket the look-ups may walk: this or 1/16 of the tile
-constexpr int kFastWalk = 4;                       // elements read per step of a walk
+constexpr int kFastWalk = 3;                       // elements read per step of a walk (4: 0.5-2 % slower, 6: 3-7 %)
 constexpr int kFastShort = 256;                    // longest tile of a launch of 128 threads
-constexpr int kFastLong = 5120, kFastMid = 2816;   // longest tiles of a launch of 512 threads: three, then four workgroups' LDS per CU
+constexpr int kFastLong = 5120;                    // longest tile of a launch of 512 threads: four workgroups' LDS per CU
 constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones
 
 // Error of a tile's filter value beyond the rounding of its elements: the three
@@ -208,7 +210,7 @@ __device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, i
 }
 
 template <int kT, int kPer>
-__global__ __launch_bounds__(kT, kT == 512 ? 6 : 8) void k_fast(Tables tb, int tile_begin, int n, int bits, int q,
+__global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n, int bits, int q,
                                              const float *__restrict__ tile_max,
                                              float *__restrict__ gm,
                                              float *__restrict__ sse32)
