@@ -788,6 +788,13 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     const int rows_per_tile = (int)((M + row_tiles - 1) / row_tiles);
     const bool by_rows = row_tiles == 1 || row_tiles * row_cols <= kRowsMaxWgs;
     const dim3 row_grid((unsigned)row_cols, (unsigned)row_tiles);
+    // k_linear_split up to one and a half of its workgroups per CU (each XCD counted as full as its
+    // fullest: few channel tiles fill few XCDs); above that k_linear has as many
+    // wavefronts without the second half's LDS traffic (K = 4096, b = 4, workgroups: us, k_linear
+    // against k_linear_split: 256: 50.8/33.3, 320: 51.3/47.7, 352: 56.4/52.5, 384: 51.6/49.2,
+    // 512: 52.5/54.3, 704: 77.2/79.0, 1024: 83/99).
+    const long long split_m = (M + kSplitBM - 1) / kSplitBM, split_wgs = 8 * tn_per_xcd * split_m;
+    const bool by_split = planes == 2 && K % (2 * kLinBK) == 0 && K >= kSplitMinK && split_wgs <= kSplitMaxWgs;
 #define PWLQ_LINEAR_ROWS(B, P, T, MT)                                                              \
     k_linear_rows<B, P, T, MT><<<row_grid, 64 * kRowWaves, 0, stream>>>(                           \
         xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, y, acc, rows_per_tile)
@@ -810,7 +817,11 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
         k_linear_wsum<B><<<wsum_wgs, kLinWG, 0, stream>>>(packed_codes, packed_flags, N, K, p, m,  \
                                                           wconst);                                 \
         profile_mark(6, stream);                                                                   \
-        if (planes == 3)                                                                           \
+        if (by_split)                                                                              \
+            k_linear_split<B><<<(unsigned)split_wgs, 2 * kLinWG, 0, stream>>>(                     \
+                xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, wconst, y,                \
+                (int)split_m, (int)tiles_n, (int)tn_per_xcd);                                      \
+        else if (planes == 3)                                                                      \
             k_linear<B, 3><<<(unsigned)wgs, kLinWG, 0, stream>>>(                                  \
                 xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, wconst, y, acc,           \
                 (int)tiles_m, (int)tiles_n, (int)tn_per_xcd);                                      \

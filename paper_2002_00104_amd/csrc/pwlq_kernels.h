@@ -27,7 +27,8 @@
 // magnitudes) and k_select (one thread per group solves for p); the error at a
 // given (m, p) runs k_mse_tile and, for groups of several tiles, k_mse_final.
 //
-// The inner product runs k_linear_wsum and k_linear, or k_linear_rows for few rows.
+// The inner product runs k_linear_wsum and k_linear (k_linear_split
+// for tiles that do not fill the chip), or k_linear_rows for few rows.
 #pragma once
 
 #include "pwlq_prep.h"

@@ -43,6 +43,9 @@ constexpr int lin_mt(int planes) { return planes == 3 ? 3 : 4; }
 constexpr int lin_bm(int planes) { return kLinWM * 32 * lin_mt(planes); }   // activation rows per workgroup
 constexpr int lin_avec(int planes) { return lin_bm(planes) * kLinBK / 16 / kLinWG; }   // 16-byte activation loads per thread
 
+// Thread of a group of four wavefronts (k_linear_split has two groups).
+__device__ inline int lin_thread() { return threadIdx.x & (kLinWG - 1); }
+
 // LDS rows hold 64 reduction bytes as four 16-byte chunks; chunk c of row r is
 // stored at position c ^ swz(r), swz(r) = (r >> 3) & 3.  A 16-byte LDS read of a
 // wavefront is served 16 lanes per cycle over 64 banks, and the lanes of a cycle
@@ -242,7 +245,7 @@ __device__ inline void lin_load(LinStage<kBits, kAVec> &st, const int8_t *__rest
                                 long long col0, long long k0, int kvalid)
 {
     static_assert(kLinWG == 4 * kLinBN, "every thread carries 16 weights of the tile");
-    const int t = threadIdx.x;
+    const int t = lin_thread();
     const int c = ((t & 3) < kvalid) ? (t & 3) : 0;     // piece & 3 == t & 3: kLinWG is a multiple of 4
 #pragma unroll
     for (int v = 0; v < kAVec; ++v) {
@@ -273,7 +276,7 @@ __device__ inline LinOffsets<kBits, kAVec> lin_offsets(long long M, long long K,
                                                 long long row0, long long col0)
 {
     LinOffsets<kBits, kAVec> o;
-    const int t = threadIdx.x;
+    const int t = lin_thread();
 #pragma unroll
     for (int v = 0; v < kAVec; ++v) {
         const int piece = t + v * kLinWG;
@@ -304,14 +307,14 @@ __device__ inline void lin_load_whole(LinStage<kBits, kAVec> &st, const LinOffse
 
 // Writes one step into LDS: activations as they are, weights decoded into the
 // operand planes (three, or two in the folded form).
-template <int kBits, int kPlanes>
-__device__ inline void lin_store(const LinStage<kBits, lin_avec(kPlanes)> &st, int8_t *__restrict__ sA,
+template <int kBits, int kPlanes, int kAVec>
+__device__ inline void lin_store(const LinStage<kBits, kAVec> &st, int8_t *__restrict__ sA,
                                  int8_t *__restrict__ sB, int kvalid)
 {
-    const int t = threadIdx.x;
+    const int t = lin_thread();
     const int keep = ((t & 3) < kvalid) ? -1 : 0;       // all ones for a piece below K
 #pragma unroll
-    for (int v = 0; v < lin_avec(kPlanes); ++v) {
+    for (int v = 0; v < kAVec; ++v) {
         const int piece = t + v * kLinWG;
         v4i a = st.a[v];
         a[0] &= keep; a[1] &= keep; a[2] &= keep; a[3] &= keep;
@@ -341,14 +344,13 @@ __device__ inline void lin_store(const LinStage<kBits, lin_avec(kPlanes)> &st, i
 // One reduction step of a wavefront: fragments of LDS buffer `buf`, the next
 // step decoded into the other buffer (kStore), 2 * kMT * kPlanes matrix
 // instructions, one barrier.
-template <int kBits, int kPlanes, bool kStore>
-__device__ inline void lin_step(v16i (&acc)[lin_mt(kPlanes)][kPlanes],
-                                const LinStage<kBits, lin_avec(kPlanes)> &next, int kvalid_next,
+template <int kBits, int kPlanes, bool kStore, int kMT, int kAVec>
+__device__ inline void lin_step(v16i (&acc)[kMT][kPlanes],
+                                const LinStage<kBits, kAVec> &next, int kvalid_next,
                                 const int8_t *a_lane, const int8_t *b_lane, int swz, int half,
                                 int8_t *sA0, int8_t *sB0, int buf)
 {
-    constexpr int kMT = lin_mt(kPlanes);
-    constexpr int kABuf = lin_bm(kPlanes) * kLinStride, kBBuf = kPlanes * kLinBN * kLinStride;
+    constexpr int kABuf = kLinWM * 32 * kMT * kLinStride, kBBuf = kPlanes * kLinBN * kLinStride;
     const int8_t *a_base = a_lane + buf * kABuf;
     const int8_t *b_base = b_lane + buf * kBBuf;
     v4i bf[kLinBK / 32][kPlanes], af[kLinBK / 32][kMT];
@@ -363,7 +365,7 @@ __device__ inline void lin_step(v16i (&acc)[lin_mt(kPlanes)][kPlanes],
             af[ks][mt] = *reinterpret_cast<const v4i *>(a_base + mt * 32 * kLinStride + chunk);
     }
     if (kStore)
-        lin_store<kBits, kPlanes>(next, sA0 + (buf ^ 1) * kABuf, sB0 + (buf ^ 1) * kBBuf, kvalid_next);
+        lin_store<kBits, kPlanes, kAVec>(next, sA0 + (buf ^ 1) * kABuf, sB0 + (buf ^ 1) * kBBuf, kvalid_next);
 #pragma unroll
     for (int ks = 0; ks < kLinBK / 32; ++ks)
 #pragma unroll
@@ -428,7 +430,7 @@ __global__ __launch_bounds__(kLinWG, 2) void k_linear(const int8_t *__restrict__
     auto valid = [&](int step) { return step == steps - 1 ? last_valid : 4; };
     LinStage<kBits, kAVec> near, far;
     lin_load<kBits, kAVec>(near, xq, M, K, pcodes, pflags, N, row0, col0, 0, valid(0));
-    lin_store<kBits, kPlanes>(near, sA[0], sB[0], valid(0));
+    lin_store<kBits, kPlanes, kAVec>(near, sA[0], sB[0], valid(0));
     if (steps > 1) lin_load<kBits, kAVec>(near, xq, M, K, pcodes, pflags, N, row0, col0, kLinBK, valid(1));
     __syncthreads();
     // row of this lane's fragments (every 32-row tile of a wavefront has the same
@@ -497,6 +499,127 @@ __global__ __launch_bounds__(kLinWG, 2) void k_linear(const int8_t *__restrict__
                     y[row * N + n] = __builtin_fmaf(s_x, t, cst);
                 }
             }
+        }
+    }
+}
+
+// ------------------------------------------------------- half the reduction each
+// k_linear_split: the folded form for calls whose tiles do not fill the chip.  One
+// workgroup of k_linear per CU is one wavefront per SIMD, which issues an instruction
+// every eight or nine cycles and waits out every barrier and LDS read alone.  Here the
+// tile is 128 rows instead of 256 and a workgroup has two groups of four wavefronts,
+// each with LDS buffers of its own and half of the reduction; their whole-number sums are
+// exchanged through LDS, each group finishing half of the rows.  The sums are whole
+// numbers, so the split changes no result.  Bound by the latency of a step (LDS write,
+// barrier, fragment reads, matrix instructions): K = 4096, b = 4, k_linear against this
+// kernel, whole call in us: 512x4096 50.8/33.3, 128x11008 55.6/37.7; K = 8192 90.7/58.5;
+// K = 512, 1024x2048 15.7/12.6; K = 1024, 2048x1024 20.5/15.2.
+constexpr int kSplitMT = 2, kSplitBM = kLinWM * 32 * kSplitMT;
+constexpr int kSplitAVec = kSplitBM * kLinBK / 16 / kLinWG;
+constexpr int kSplitMaxWgs = 384;      // the rule stands where it is applied
+constexpr int kSplitMinK = 512;        // K is a multiple of 128: whole steps, as many in both halves
+
+template <int kBits>
+__global__ __launch_bounds__(2 * kLinWG, 4) void k_linear_split(const int8_t *__restrict__ xq, long long M, long long K,
+                                                         float s_x, float z_x, const uint8_t *__restrict__ pcodes,
+                                                         const uint8_t *__restrict__ pflags, long long N,
+                                                         const float *__restrict__ p, const float *__restrict__ m,
+                                                         const float *__restrict__ wconst, float *__restrict__ y,
+                                                         int tiles_m, int tiles_n, int tn_per_xcd)
+{
+    constexpr int kMT = kSplitMT, kAVec = kSplitAVec;
+    __shared__ __attribute__((aligned(16))) int8_t sA[2][2 * kSplitBM * kLinStride];         // [group][two buffers]
+    __shared__ __attribute__((aligned(16))) int8_t sB[2][2 * 2 * kLinBN * kLinStride];
+
+    const int xcd = blockIdx.x & 7;
+    const int slot = blockIdx.x >> 3;
+    const int bn = xcd * tn_per_xcd + slot % tn_per_xcd;
+    const int bm = slot / tn_per_xcd;
+    if (bm >= tiles_m || bn >= tiles_n) return;
+    const long long row0 = (long long)bm * kSplitBM, col0 = (long long)bn * kLinBN;
+    const int lane = threadIdx.x & 63;
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    v16i acc[kMT][2];
+#pragma unroll
+    for (int a = 0; a < kMT; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int c = 0; c < 16; ++c) acc[a][b][c] = 0;
+
+    const int steps = (int)(K / (2 * kLinBK));                      // of this group; at least four
+    const long long kb = (long long)group * steps * kLinBK;         // where its half begins
+    LinStage<kBits, kAVec> near, far;
+    const LinOffsets<kBits, kAVec> offs = lin_offsets<kBits, kAVec>(M, K, N, row0, col0);
+    const int8_t *a_base = xq + row0 * K + kb;
+    const uint8_t *code_base = pcodes + ((col0 * K + kb) >> 4) * (2 * kBits);
+    const uint8_t *flag_base = pflags + ((col0 * K + kb) >> 3);
+    auto load = [&](LinStage<kBits, kAVec> &st, int step) {
+        const long long k0 = (long long)step * kLinBK;
+        lin_load_whole<kBits, kAVec>(st, offs, a_base + k0, code_base + (k0 >> 4) * (2 * kBits), flag_base + (k0 >> 3));
+    };
+    load(near, 0);
+    lin_store<kBits, 2, kAVec>(near, sA[group], sB[group], 4);
+    load(near, 1);
+    __syncthreads();
+    const int8_t *a_lane = sA[group] + (wm * 32 * kMT + (lane & 31)) * kLinStride;
+    const int8_t *b_lane = sB[group] + (wn * 32 + (lane & 31)) * kLinStride;
+    const int swz = lin_swz(lane & 31), half = lane >> 5;
+    int kt = 0;
+    for (; kt + 3 < steps; kt += 2) {
+        load(far, kt + 2);
+        lin_step<kBits, 2, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 0);
+        load(near, kt + 3);
+        lin_step<kBits, 2, true>(acc, far, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 1);
+    }
+    if (kt + 2 < steps) {
+        load(far, kt + 2);
+        lin_step<kBits, 2, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 0);
+        near = far;
+        ++kt;
+    }
+    lin_step<kBits, 2, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], kt & 1);
+    lin_step<kBits, 2, false>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], (kt + 1) & 1);
+
+    // the last step's barrier has ended every fragment read, so the buffers are free:
+    // group g finishes the rows of its g-th 32-row tile: the other's sums of them come through LDS
+    static_assert(kMT == 2 && sizeof(sA) >= 2 * 16 * kLinWG * sizeof(int) && sizeof(sB) >= 2 * 16 * kLinWG * sizeof(int),
+                  "one array per group");
+    int *mine = reinterpret_cast<int *>(group ? &sB[0][0] : &sA[0][0]);
+    const int *theirs = reinterpret_cast<const int *>(group ? &sA[0][0] : &sB[0][0]);
+    const int t = lin_thread();
+    v16i sum[2];
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            mine[(pl * 16 + r) * kLinWG + t] = group ? acc[0][pl][r] : acc[1][pl][r];
+            sum[pl][r] = group ? acc[1][pl][r] : acc[0][pl][r];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[pl][r] += theirs[(pl * 16 + r) * kLinWG + t];
+
+    const long long n = col0 + wn * 32 + (lane & 31);
+    if (n >= N) return;
+    const float Lf = (float)((1 << (kBits - 1)) - 1);
+    const float pn = p[n], mn = m[n];
+    const float s1 = pn / Lf;
+    const float width = mn - pn;
+    const float s2 = width / Lf;
+    const float cst = z_x * wconst[n];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const long long row = row0 + wm * 32 * kMT + group * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+        if (row < M) {
+            float t1 = s1 * (float)sum[0][r];
+            t1 = __builtin_fmaf(s2, (float)sum[1][r], t1);
+            y[row * N + n] = __builtin_fmaf(s_x, t1, cst);
         }
     }
 }
