@@ -15,17 +15,24 @@
 // A candidate costs 2L look-ups of H, whatever the tile's length.
 //
 // Whole numbers.  Every half-way point is a multiple of 1/(2L), so magnitudes are
-// held as integers in units of 1/(2L q), q the largest that keeps n below 2^24:
-// half-way points are exact, an element moves by at most 2^-24 n (an eighth of
-// the rounding that the filter's slack allows an element), and every sum below
-// is exact; binary64 enters once per candidate, where the three terms meet.
+// held as integers in units of 1/(2L q), q the largest that keeps n below 2^30:
+// half-way points are exact, every sum below is exact, and binary64 enters once
+// per candidate, where the three terms meet.  An element is one binary64 product
+// rounded to a whole number: it moves by at most 0.52 * 2^-30 n (q is 63 or more,
+// so n is at least 0.97 * 2^30 units).  Weights far below the absmax keep that
+// many bits too, so a candidate's value is closer to the exact error than prefix
+// sums of binary32 magnitudes (two roundings of up to 2^-24 u each) come: rms error
+// 0.024 against 0.032 squared candidate units for 1024 Gaussian weights, b = 4,
+// n = 1000 (units of 2^-24 n: 0.061), 3.0e-5 against 5.3e-5 for 2048 of a heavy
+// tail, b = 8, n = 500 (5.1e-4).
 //
 // A look-up needs no full sort: elements are grouped into buckets that are
 // monotone in the magnitude (one counting pass in LDS), and a bucket's 64-bit word
-// holds the sum (38 bits) and count (14 bits) of the elements before it and its
-// own count (12 bits).  H(b) is b * count - sum of the bucket of b, plus
-// max(b - u, 0) over the bucket's own elements: elements past its end are above b
-// and add nothing, so the first three are read without looking at the count.
+// holds the sum (43 bits) and count (14 bits) of the elements before it and its
+// own count in whole fours (7 bits).  H(b) is b * count - sum of the bucket of b, plus
+// max(b - u, 0) over the bucket's own elements: elements past its end are above b and
+// add nothing, so the first three are read without looking at the count, the others
+// four at a time.
 // Elements that are exactly zero (pruned weights) are counted, never walked.
 //
 // Bound by vector issue and LDS together: 57 vector instructions and six LDS accesses per
@@ -45,22 +52,33 @@ namespace pwlq {
 constexpr int kFastOctBits = 8;
 constexpr int kFastOct = 7;                        // octaves, or twice as many of half as many buckets each
 constexpr int kFastWords = kFastOct << kFastOctBits;   // most buckets per tile
-constexpr unsigned kFastTop = (1u << 24) - 1 - (1u << (24 - kFastOct));   // largest magnitude
-static_assert(kFastTop >= 65535u * 254u, "every grid fits");
-constexpr int kFastCrowd = 64;                     // fullest bucket the look-ups may walk: this or 1/16 of the tile
-constexpr int kFastWalk = 3;                       // elements read per step of a walk (4: 0.5-2 % slower, 6: 3-7 %)
+constexpr int kFastBits = 30;
+// Largest magnitude: with the offset `low` it is at most 2^30 - 64, the largest
+// binary32 below 2^30, so that no bucket number passes the last octave's.
+constexpr unsigned kFastTop = (1u << kFastBits) - 64u - (1u << (kFastBits - kFastOct));
+static_assert(kFastTop / (65535u * 254u) >= 63u, "every grid fits, with 63 units or more to half its finest step");
+constexpr int kFastCrowd = 64;                     // fullest bucket the look-ups may walk: this or 1/16 of the tile,
+constexpr int kFastCrowdMax = 511;                 // ... and never more
+constexpr int kFastWalk = 3;                       // elements read unasked (4: 0.5-2 % slower, 6: 3-7 %)
+constexpr int kFastWalkOn = 4;                     // ... and then per step
 constexpr int kFastShort = 256;                    // longest tile of a launch of 128 threads
 constexpr int kFastLong = 5120;                    // longest tile of a launch of 512 threads: four workgroups' LDS per CU
 constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones
 
-// Error of a tile's filter value beyond the rounding of its elements: the three
-// binary64 terms, each at most n^2 K, a few roundings each; kFastRelErr * n^2 * K
-// bounds it with room and is added to the slack of the filter (keep_threshold).
+// Error of a tile's filter value beyond the rounding of its elements: A is a sum of
+// squares added in at most 33 steps (10 per thread, 6 over the wavefront, 16 over the
+// workgroup) and scaled in three roundings, the rest is exact up to seven roundings
+// of a value of at most A, and A is at most n^2 K: below 48 * 2^-53 n^2 K = 5.4e-15
+// n^2 K.  kFastRelErr * n^2 * K is added to the slack of the filter (keep_threshold).
 
-// log2 of a tile's buckets per octave, about two buckets per element.
+// log2 of a tile's buckets per octave, about two buckets per element, 32 at least: the
+// parts of H inside one bucket then fit 32 bits.  With 2^m buckets in an octave
+// (2^(m-1) where there are 14 octaves) the widest, in the last octave, has 2^(30-m) units,
+// and a tile is crowded when a bucket has more than max(kFastCrowd, len / 16) elements:
+// 64 * 2^25 for m = 5 (up to 255 elements), 511 * 2^22 at most for m = 8 (from 1024 on).
 __host__ __device__ constexpr int fast_octave_bits(int len)
 {
-    int bits = 1;
+    int bits = 5;
     while (bits < kFastOctBits && (8 << bits) <= len) ++bits;
     return bits;
 }
@@ -84,7 +102,9 @@ __device__ inline unsigned long long wave_scan_incl_u64(unsigned long long v)
     return v;
 }
 
-constexpr int kFastSumBits = 38, kFastCountBits = 14;   // then 12 bits: the bucket's own count
+constexpr int kFastSumBits = kFastBits + 13, kFastCountBits = 14;   // then 7 bits: the bucket's own count / 4
+static_assert(kFastSumBits + kFastCountBits == 57 && kFastCrowdMax / kFastWalkOn < 128 && kFastWalkOn == kFastWalk + 1,
+              "a bucket of c elements is walked in kFastWalk and c / kFastWalkOn steps of kFastWalkOn");
 
 typedef __attribute__((address_space(3))) const unsigned long long FastWordLds;
 typedef __attribute__((address_space(3))) const unsigned FastElemLds;
@@ -96,7 +116,8 @@ struct FastLds {
 };
 
 // Bucket number of value v (magnitude plus `low`): the top bits of its binary32
-// pattern, i.e. 2^m buckets per octave.  Below `low` the added offset makes them
+// pattern, i.e. 2^m buckets per octave (values above 2^24 are rounded to binary32 on
+// the way, which keeps their order).  Below `low` the added offset makes them
 // equally wide.
 __device__ inline unsigned fast_bucket(unsigned v, int shift) { return __float_as_uint((float)v) >> shift; }
 
@@ -106,7 +127,7 @@ struct FastSums {
 };
 
 struct FastWord {
-    unsigned before, own;
+    unsigned before, steps;        // elements before the bucket; steps of a walk past the first elements
     unsigned long long c;
 };
 __device__ inline FastWord fast_word(const FastLds &L, unsigned b)
@@ -115,9 +136,21 @@ __device__ inline FastWord fast_word(const FastLds &L, unsigned b)
     const unsigned hi = (unsigned)(w >> 32);
     FastWord f;
     f.before = (hi >> (kFastSumBits - 32)) & ((1u << kFastCountBits) - 1u);
-    f.own = hi >> (kFastSumBits - 32 + kFastCountBits);
+    f.steps = hi >> (kFastSumBits - 32 + kFastCountBits);
     f.c = w & ((1ull << kFastSumBits) - 1ull);
     return f;
+}
+
+// max(b - u, 0) over kCount elements.
+template <int kCount>
+__device__ inline unsigned fast_walk(FastElemLds *e, unsigned b)
+{
+    unsigned x[kCount], d = 0;
+#pragma unroll
+    for (int i = 0; i < kCount; ++i) x[i] = e[i];
+#pragma unroll
+    for (int i = 0; i < kCount; ++i) d += __builtin_elementwise_sub_sat(b, x[i]);
+    return d;
 }
 
 // H at one half-way point of each piece: the two chains of reads run side by side.
@@ -126,22 +159,10 @@ __device__ inline void fast_query2(const FastLds &L, unsigned b0, unsigned b1, u
 {
     const FastWord w0 = fast_word(L, b0), w1 = fast_word(L, b1);
     FastElemLds *e0 = L.elems + w0.before, *e1 = L.elems + w1.before;
-    unsigned x0[kFastWalk], x1[kFastWalk];
-#pragma unroll
-    for (int x = 0; x < kFastWalk; ++x) { x0[x] = e0[x]; x1[x] = e1[x]; }
-#pragma unroll
-    for (int x = 0; x < kFastWalk; ++x) {
-        s0.d += __builtin_elementwise_sub_sat(b0, x0[x]);
-        s1.d += __builtin_elementwise_sub_sat(b1, x1[x]);
-    }
-    for (unsigned i = kFastWalk; i < w0.own; i += kFastWalk) {
-#pragma unroll
-        for (int x = 0; x < kFastWalk; ++x) s0.d += __builtin_elementwise_sub_sat(b0, e0[i + x]);
-    }
-    for (unsigned i = kFastWalk; i < w1.own; i += kFastWalk) {
-#pragma unroll
-        for (int x = 0; x < kFastWalk; ++x) s1.d += __builtin_elementwise_sub_sat(b1, e1[i + x]);
-    }
+    s0.d += fast_walk<kFastWalk>(e0, b0);
+    s1.d += fast_walk<kFastWalk>(e1, b1);
+    for (unsigned i = 0; i < w0.steps; ++i) s0.d += fast_walk<kFastWalkOn>(e0 + kFastWalk + kFastWalkOn * i, b0);
+    for (unsigned i = 0; i < w1.steps; ++i) s1.d += fast_walk<kFastWalkOn>(e1 + kFastWalk + kFastWalkOn * i, b1);
     s0.c += w0.c;
     s1.c += w1.c;
     s0.n += w0.before;
@@ -152,9 +173,11 @@ __device__ inline void fast_query2(const FastLds &L, unsigned b0, unsigned b1, u
 
 // Filter value of every candidate of the tile.  `low` is the offset of the stored
 // values, A = sum (n - u)^2.
+// The parts inside a bucket, summed in 32 bits over `run` look-ups: those of its own
+// elements are below its width, those past it are zero.
 template <int kT>
 __device__ inline void fast_candidates(const FastLds &Q, int n, int Li, int q, unsigned low, double A,
-                                       float *__restrict__ row)
+                                       int run, float *__restrict__ row)
 {
     const double inv = 1.0 / ((double)Li * (double)Li * (double)q);            // 2 / (L * 2L q)
     for (int k = threadIdx.x + 1; k <= n; k += kT) {
@@ -163,8 +186,7 @@ __device__ inline void fast_candidates(const FastLds &Q, int n, int Li, int q, u
         FastSums fc = {0, 0, 0, 0}, ft = {0, 0, 0, 0};
         unsigned bc = kk + low, bt = zt + ww;
         for (int i = 0; i < Li;) {
-            // the parts inside buckets stay below 2^28 each: eight of them fit a word
-            const int stop = i + 8 < Li ? i + 8 : Li;
+            const int stop = i + run < Li ? i + run : Li;
             fc.d = ft.d = 0;
             for (; i < stop; ++i) {
                 fast_query2(Q, bc, bt, 2 * i + 1, fc, ft);
@@ -174,6 +196,7 @@ __device__ inline void fast_candidates(const FastLds &Q, int n, int Li, int q, u
             fc.c -= fc.d;
             ft.c -= ft.d;
         }
+        // whole numbers below 2^52, so exact in binary64
         const double hc = (double)kk * (double)fc.m + (double)low * (double)fc.n - (double)(long long)fc.c;
         const double ht = (double)ww * (double)ft.m + (double)zt * (double)ft.n - (double)(long long)ft.c;
         const double sse = A - inv * ((double)k * hc + (double)(n - k) * ht);
@@ -183,11 +206,11 @@ __device__ inline void fast_candidates(const FastLds &Q, int n, int Li, int q, u
 
 // A tile whose values crowd into a few buckets (many equal magnitudes: a bucket
 // holding more than 1/16 of the tile) would make every look-up walk a long bucket; it is evaluated element by element
-// instead, in binary32 with the chunked sums of the plain search kernel (all
-// lanes read the same LDS word, which is a broadcast).
+// instead, from binary32 magnitudes in candidate units, with the chunked sums of the
+// plain search kernel (all lanes read the same LDS word, which is a broadcast).
 template <int kT>
-__device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, int n, int Li, unsigned low,
-                                  float per_unit, float *__restrict__ row)
+__device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, int n, int Li,
+                                  float *__restrict__ row)
 {
     const float Lf = (float)Li;
     for (int k = threadIdx.x + 1; k <= n; k += kT) {
@@ -202,7 +225,7 @@ __device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, i
             const int ce = (cb + kChunk < len) ? cb + kChunk : len;
             float acc = 0.0f;
             for (int i = cb; i < ce; ++i) {
-                const float u = (float)(elems[i] - low) * per_unit;
+                const float u = __uint_as_float(elems[i]);
                 const bool tail = u > kf;
                 const float t = tail ? __builtin_fmaf(u, rt, ct) : u * rc;
                 const float err = (t - __builtin_rintf(t)) * (tail ? stept : stepc);
@@ -226,7 +249,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     constexpr int kW = kT / 64;
     constexpr int kScan = ((kFastOct << fast_octave_bits(kT * kPer)) + kT - 1) / kT;   // words a thread holds at most
     __shared__ float redm[kW], redsum[kW];
-    __shared__ int redbad[kW], redzero[kW], wcrowd[kW];
+    __shared__ int redbad[kW], redzero[kW], wfull[kW];
     __shared__ unsigned long long wsum[kW];
     __shared__ double redA[kW];
 
@@ -277,18 +300,21 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     if (ti.tile_in_group == 0 && tid == 0) gm[ti.group] = m;
 
     const bool usable = (m > 0.0f) && (m < __builtin_inff());
-    const float nf = (float)n;
-    const float scale = usable ? nf / m : 0.0f;
-    const unsigned top = (unsigned)(n * 2 * Li * q);                      // the magnitude m: 2^23 to kFastTop
-    const float unit = (float)(2 * Li * q);                               // per candidate unit; exact, like top
+    const unsigned top = (unsigned)(n * 2 * Li * q);                      // the magnitude m: 0.97 * 2^30 or more
+    const double unit = (double)(2 * Li * q);                             // per candidate unit
+    const double scale = usable ? (double)top / (double)m : 0.0;
+    // A group so small that n / m overflows binary32: the weights' own steps are too coarse
+    // there for the filter's slack.  Every element counts as m then, which gives all
+    // candidates the value 0 and keeps them.
+    const bool keep_all = usable && !((float)n / m < __builtin_inff());
 
-    // Values run from `low` to top + low, whose exponents are 24 - octaves and 23.  Seven
+    // Values run from `low` to top + low, whose exponents are 30 - octaves and 29.  Seven
     // octaves, and 14 of half as many buckets where the mean lies in the lowest: near zero
     // these are 64 times as fine, elsewhere half as fine.
-    const float mean = sum / (float)len * scale * unit;
-    const bool deep = uni(mean < (float)(1u << (23 - kFastOct)) ? 1 : 0) != 0;
+    const double mean = (double)sum / (double)len * scale;
+    const bool deep = uni(mean < (double)(1u << (kFastBits - 1 - kFastOct)) ? 1 : 0) != 0;
     obits -= deep ? 1 : 0;
-    const unsigned low = 1u << (24 - (deep ? 2 * kFastOct : kFastOct));
+    const unsigned low = 1u << (kFastBits - (deep ? 2 * kFastOct : kFastOct));
     FastLds Q;
     Q.shift = 23 - obits;
     const unsigned bucket0 = fast_bucket(low, Q.shift);
@@ -305,7 +331,8 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
         const int i = tid + e * kT;
         unsigned u = 0;
         if (i < len) {
-            u = (unsigned)__builtin_rintf(to_units(a[e], scale, nf) * unit);     // at most top; 0 if not usable
+            // at most top: a <= m, and the product is within 2^-22 of the exact one
+            if (usable) u = keep_all ? (a[e] > 0.0f ? top : 0u) : (unsigned)__builtin_rint((double)a[e] * scale);
             const double d = (double)(top - u);
             A += d * d;
             zeros += u == 0;
@@ -325,7 +352,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     A = 0.0;
 #pragma unroll 4
     for (int i = 0; i < kW; ++i) { zeros += redzero[i]; A += redA[i]; }
-    A *= 1.0 / ((double)unit * (double)unit);
+    A *= 1.0 / (unit * unit);
 
     // exclusive prefix of counts and sums, both fields in one word
     const int per = (T + kT - 1) / kT;
@@ -342,9 +369,8 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
             fullest = c > fullest ? c : fullest;
         }
         const unsigned long long incl = wave_scan_incl_u64(tot);
-        const unsigned crowd = (len >> 4) > kFastCrowd ? (unsigned)(len >> 4) : (unsigned)kFastCrowd;
-        const int over = __ballot(fullest > crowd) != 0ull;
-        if (lane == 63) { wsum[wave] = incl; wcrowd[wave] = over; }
+        const int full = (int)wave_max((float)fullest);
+        if (lane == 63) { wsum[wave] = incl; wfull[wave] = full; }
         __syncthreads();
         // the zero elements come before everything
         unsigned long long run = incl - tot + ((unsigned long long)zeros << kFastSumBits) +
@@ -354,8 +380,9 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
 #pragma unroll
         for (int x = 0; x < kScan; ++x) {
             if (lo + x < hi) {
-                // a count of 4096 or more would not fit, but such a tile is crowded
-                fast_lds[lo + x] = run | ((w[x] >> kFastSumBits) << (kFastSumBits + kFastCountBits));
+                // (a count that does not fit is a crowded tile's)
+                const unsigned long long own = w[x] >> kFastSumBits;
+                fast_lds[lo + x] = run | ((own / kFastWalkOn) << (kFastSumBits + kFastCountBits));
                 run += w[x];
             }
         }
@@ -371,12 +398,24 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     }
     // what a walk reads past the last element adds nothing
     if (tid < kFastWalk) elems[len - zeros + tid] = ~0u;
-    int crowded = 0;
-    for (int i = 0; i < kW; ++i) crowded |= wcrowd[i];
+    int full = 1;
+    for (int i = 0; i < kW; ++i) full = wfull[i] > full ? wfull[i] : full;
+    full = uni(full);
+    int crowd = (len >> 4) > kFastCrowd ? len >> 4 : kFastCrowd;
+    crowd = crowd < kFastCrowdMax ? crowd : kFastCrowdMax;
+    const bool crowded = full > crowd;
+    // look-ups whose parts inside buckets fit 32 bits together: one at least (see
+    // fast_octave_bits), eight or more as a rule
+    const int run = (int)(0xffffffffu >> (kFastBits - 1 - obits)) / full;
     __syncthreads();
     float *row = sse32 + (long long)t * n;
-    if (crowded) fast_plain<kT>(elems, len - zeros, n, Li, low, 1.0f / unit, row);
-    else fast_candidates<kT>(Q, n, Li, q, low, A, row);
+    if (crowded) {
+        const double per_unit = 1.0 / unit;
+        for (int i = tid; i < len - zeros; i += kT)
+            elems[i] = __float_as_uint((float)((double)(elems[i] - low) * per_unit));
+        __syncthreads();
+        fast_plain<kT>(elems, len - zeros, n, Li, row);
+    } else fast_candidates<kT>(Q, n, Li, q, low, A, run, row);
 }
 
 } // namespace pwlq

@@ -13,7 +13,7 @@ namespace pwlq {
 // element error (candidate units) and 3e-5 relative for the binary32 sums.
 // Tiles evaluated by prefix sums add the bound of that arithmetic
 // (kFastRelErr n^2 per element).
-constexpr double kFastRelErr = 3.0e-11;
+constexpr double kFastRelErr = 1.0e-14;
 __device__ inline double keep_threshold(double mn, double count, int n, bool fast)
 {
     const double eps = (double)n * 4.76837158203125e-07;   // 2^-21 n

@@ -42,3 +42,30 @@ def test_fast_search_at_the_edges_of_its_tiles(P, bits, n, lengths):
             assert_search_matches(got, R.search(w, bits, n, want_curve=True), f"bits={bits} n={n} K={K}")
     finally:
         P.set_small_call_tiles(before)
+
+
+@pytest.mark.parametrize("bits,n,K", [(4, 300, 8192), (3, 1000, 2000), (8, 130, 4300)])
+def test_full_buckets_and_tiny_scales(P, bits, n, K):
+    """Runs of 62 to K/16 weights within one bucket (walked three and then four at a time; from
+    K/16 on a tile is evaluated element by element), also in the last bucket, and scales down
+    to where n / max|w| overflows binary32 (below about 3e-36 for n = 1000)."""
+    import torch
+    rng = np.random.default_rng(bits * 1000 + K)
+    base = rng.standard_normal(K)
+    out = []
+    for run in (62, 63, 64, 65, K // 16 - 1, K // 16, K // 16 + 1):
+        w = base.copy()
+        top = np.abs(w).max()
+        for at in (0.31, 0.77, 0.99999):
+            i = rng.choice(K, run, replace=False)
+            w[i] = top * at * (1 - rng.random(run) * 2.0 ** -14)
+        out.append(w)
+    out += [base * s for s in (1e-30, 4e-36, 1e-36, 1e-37, 1e-38)]
+    w = np.stack(out).astype(np.float32)
+    before = P.set_small_call_tiles(0)
+    try:
+        print(f"[case] bits={bits} n={n} K={K}", flush=True)
+        got = {k: v.cpu().numpy() for k, v in P.search(torch.from_numpy(w).cuda(), bits, n, fast=True).items()}
+        assert_search_matches(got, R.search(w, bits, n, want_curve=True), f"bits={bits} n={n} K={K}")
+    finally:
+        P.set_small_call_tiles(before)
