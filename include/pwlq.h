@@ -267,7 +267,8 @@ int pwlq_mse_list(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mod
  * With acc NULL the library may form A1 + L A3 as one integer sum (p = s1 L, so
  * s1 A1 + p A3 = s1 (A1 + L A3); L sigma is an int8 like any code) and issue two
  * matrix products per weight instead of three; y then differs from the
- * three-sum form by binary32 rounding only.
+ * three-sum form by binary32 rounding only.  In either form a row of y depends
+ * on its own activations alone, to the last bit, not on M.
  * Requirements: K a multiple of 16; xq and packed_codes 16-byte aligned,
  * packed_flags 2-byte aligned; K * 128 * L below 2^31.  Workspace: device,
  * 256-byte aligned, pwlq_linear_workspace_bytes(N) bytes.

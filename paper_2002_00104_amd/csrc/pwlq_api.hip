@@ -814,8 +814,12 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
             profile_mark(7, stream);                                                               \
             break;                                                                                 \
         }                                                                                          \
-        k_linear_wsum<B><<<wsum_wgs, kLinWG, 0, stream>>>(packed_codes, packed_flags, N, K, p, m,  \
-                                                          wconst);                                 \
+        if (planes == 3)                                                                           \
+            k_linear_wsum<B, 3><<<wsum_wgs, kLinWG, 0, stream>>>(packed_codes, packed_flags, N, K, \
+                                                                 p, m, wconst);                    \
+        else                                                                                       \
+            k_linear_wsum<B, 2><<<wsum_wgs, kLinWG, 0, stream>>>(packed_codes, packed_flags, N, K, \
+                                                                 p, m, wconst);                    \
         profile_mark(6, stream);                                                                   \
         if (by_split)                                                                              \
             k_linear_split<B><<<(unsigned)split_wgs, 2 * kLinWG, 0, stream>>>(                     \

@@ -172,15 +172,27 @@ __device__ inline void planes4_folded(uint32_t codes, uint32_t f, int bits, uint
 }
 
 // ---------------------------------------------------------------- constants
-// wconst[n] = s1 * sum_R1 w_q + s2 * sum_R2 w_q + p * sum_R2 sigma (binary64,
-// rounded to binary32): multiplied by z_x it is C3 + C6 of Section 4.  One
-// wavefront per channel.
+// s1 * sum_R1 w_q + s2 * sum_R2 w_q + p * sum_R2 sigma (binary64, rounded to
+// binary32): multiplied by z_x it is C3 + C6 of Section 4.  `sums` are those of the
+// weights in each plane.  The folded form has the first and third as one sum and p / L
+// for both.  Every kernel forms a channel's constant here, so that a row of y is the
+// same whichever kernel the number of rows chooses.
+template <int kPlanes>
+__device__ inline float lin_constant(const int (&sums)[kPlanes], float pn, float s1, float s2, float Lf)
+{
+    if (kPlanes == 3)
+        return (float)((double)s1 * (double)sums[0] + (double)s2 * (double)sums[1] +
+                       (double)pn * (double)sums[kPlanes - 1]);
+    return (float)((double)pn / (double)Lf * (double)sums[0] + (double)s2 * (double)sums[1]);
+}
+
+// wconst[n]: the constant of channel n.  One wavefront per channel.
 __device__ inline int add_bytes(uint32_t w, int sum)
 {
     return __builtin_amdgcn_sdot4((int)w, 0x01010101, sum, false);
 }
 
-template <int kBits>
+template <int kBits, int kPlanes>
 __global__ __launch_bounds__(kLinWG) void k_linear_wsum(const uint8_t *__restrict__ pcodes,
                                                         const uint8_t *__restrict__ pflags,
                                                         long long N, long long K,
@@ -191,7 +203,7 @@ __global__ __launch_bounds__(kLinWG) void k_linear_wsum(const uint8_t *__restric
     const long long n = (long long)blockIdx.x * (kLinWG / 64) + (threadIdx.x >> 6);
     if (n >= N) return;
     const int lane = threadIdx.x & 63;
-    int b1 = 0, b2 = 0, b3 = 0;
+    int sums[kPlanes] = {};
     for (long long k0 = 16LL * lane; k0 < K; k0 += 16 * 64) {
         const long long e0 = n * K + k0;
         RawCodes<kBits> raw;
@@ -201,17 +213,16 @@ __global__ __launch_bounds__(kLinWG) void k_linear_wsum(const uint8_t *__restric
         const uint32_t f = *reinterpret_cast<const uint16_t *>(pflags + (e0 >> 3));
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-            uint32_t w1, w2, w3;
-            planes4(c[x], f >> (4 * x), kBits, w1, w2, w3);
-            b1 = add_bytes(w1, b1);
-            b2 = add_bytes(w2, b2);
-            b3 = add_bytes(w3, b3);
+            uint32_t w[3];
+            if (kPlanes == 3) planes4(c[x], f >> (4 * x), kBits, w[0], w[1], w[2]);
+            else planes4_folded(c[x], f >> (4 * x), kBits, w[0], w[1]);
+#pragma unroll
+            for (int pl = 0; pl < kPlanes; ++pl) sums[pl] = add_bytes(w[pl], sums[pl]);
         }
     }
     for (int off = 32; off > 0; off >>= 1) {
-        b1 += __shfl_xor(b1, off, 64);
-        b2 += __shfl_xor(b2, off, 64);
-        b3 += __shfl_xor(b3, off, 64);
+#pragma unroll
+        for (int pl = 0; pl < kPlanes; ++pl) sums[pl] += __shfl_xor(sums[pl], off, 64);
     }
     if (lane == 0) {
         const float Lf = (float)((1 << (kBits - 1)) - 1);
@@ -219,7 +230,7 @@ __global__ __launch_bounds__(kLinWG) void k_linear_wsum(const uint8_t *__restric
         const float s1 = pn / Lf;
         const float width = mn - pn;
         const float s2 = width / Lf;
-        wconst[n] = (float)((double)s1 * (double)b1 + (double)s2 * (double)b2 + (double)pn * (double)b3);
+        wconst[n] = lin_constant<kPlanes>(sums, pn, s1, s2, Lf);
     }
 }
 
@@ -861,15 +872,12 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_linear_rows(
             sum[pl] = row_sums[pl][row][c];
             wsum[pl] = row_sums[pl][rows][c];
         }
-        // the sums of the weights: with two planes wsum[0] holds b1 + L b3, and s1 L is p
-        const double w = kPlanes == 3 ? (double)s1 * (double)wsum[0] + (double)s2 * (double)wsum[1] +
-                                            (double)pn * (double)wsum[kPlanes - 1]
-                                      : (double)pn / (double)Lf * (double)wsum[0] + (double)s2 * (double)wsum[1];
+        const float w = lin_constant<kPlanes>(wsum, pn, s1, s2, Lf);
         float t = s1 * (float)sum[0];
         t = __builtin_fmaf(s2, (float)sum[1], t);
         if (kPlanes == 3) t = __builtin_fmaf(pn, (float)sum[kPlanes - 1], t);
         const long long at = (row0 + row) * N + nn;
-        y[at] = __builtin_fmaf(s_x, t, z_x * (float)w);
+        y[at] = __builtin_fmaf(s_x, t, z_x * w);
         if (kPlanes == 3 && acc_out) {
 #pragma unroll
             for (int pl = 0; pl < kPlanes; ++pl) acc_out[pl * M * N + at] = sum[pl];
