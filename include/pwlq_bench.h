@@ -32,10 +32,19 @@ double pwlq_profile_last_ms(int role);
  * back = 1 the one before, up to the last 64 recorded launches; -1 beyond. */
 double pwlq_profile_ms(int role, int back);
 
-/* Name of the candidate-evaluation kernel that the calling thread's last search launched
- * (role 0 of the event timing): "k_search", or "k_small" for a call small enough to be one
- * fused launch, or "k_fast" for a fast search. */
+/* Route that the calling thread's last search took: "k_small" for a call small enough to
+ * be one fused launch, else "k_fast" for a fast search, else "k_search".  In a trace the
+ * candidate-evaluation kernel's name begins so (k_search_sliced where wavefronts are few);
+ * the tiles of a fast search that are too short, or too few, for k_fast run k_search. */
 const char *pwlq_last_search_kernel(void);
+
+/* The kernels themselves that the calling thread's last search or inner product launched
+ * to evaluate candidates or to multiply, in order, with a space between: "k_small";
+ * "k_fast<T>" per launch of T threads to a tile, and "k_search" or "k_search_sliced(S)",
+ * a tile in S slices; "k_linear_rows<bits, planes, tile, row tiles>",
+ * "k_linear_split<bits>" or "k_linear<bits, planes>".  The text is the thread's own and
+ * valid until its next such call. */
+const char *pwlq_last_kernels(void);
 
 /* Test and measurement aid.  A search call of at most this many groups (all of at
  * most 1024 elements, at most 1024 candidates) runs as one fused launch, one
@@ -45,9 +54,10 @@ const char *pwlq_last_search_kernel(void);
  * can be put through both, and returns the limit it replaces.  Process-wide. */
 int pwlq_set_small_call_tiles(int tiles);
 
-/* Name of the library's kernels as they appear in a kernel trace, by role:
- * 0 search (dominant), 1 quantize, 2 prefix-sum evaluation, 3 integer inner
- * product.  Returns NULL for other roles. */
+/* What the names of the library's kernels begin with in a kernel trace, by role:
+ * 0 search (dominant; also k_search_sliced), 1 quantize, 2 prefix-sum evaluation,
+ * 3 integer inner product (also k_linear_rows and k_linear_split).  Returns NULL for
+ * other roles. */
 const char *pwlq_kernel_name(int role);
 
 #ifdef __cplusplus

@@ -28,6 +28,16 @@ using namespace pwlq;
 thread_local char g_error[512] = "";
 thread_local long long g_last_tiles = 0, g_last_groups = 0, g_last_units = 0;
 thread_local const char *g_last_search_kernel = "k_search";
+// What the thread's last search or inner product launched, for pwlq_last_kernels.
+struct Launched {
+    enum { kNone, kSmall, kSearch, kLinearRows, kLinearSplit, kLinear } what = kNone;
+    int fast_threads[4] = {};      // workgroup sizes of the k_fast launches, in order
+    int n_fast = 0;
+    int slices = 0;                // of k_search_sliced; 1: k_search; 0: neither
+    int bits = 0, planes = 0, row_tile = 0, row_mt = 0;
+};
+thread_local Launched g_launched;
+thread_local char g_launched_text[160] = "";
 
 int fail(int status, const char *fmt, ...)
 {
@@ -435,10 +445,14 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
             g_last_groups = pl.n_groups;
             g_last_units = pl.n_tiles;
             g_last_search_kernel = "k_small";
+            g_launched = Launched();
+            g_launched.what = Launched::kSmall;
             return launch_status("search launch");
         }
     }
     g_last_search_kernel = fast ? "k_fast" : "k_search";
+    Launched launched;
+    launched.what = Launched::kSearch;
     if (pl.n_mgroups > 0) k_tile_absmax<<<NT, kWG, 0, stream>>>(tb, tile_max);
     int longest = 0, fast_tiles = 0;
     for (const TensorRec &r : pl.recs) {
@@ -470,6 +484,8 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                 continue;
             const int count = seen - begin;
             const size_t lds = lds_bytes(part_longest);
+            constexpr int kThreads[4] = {1024, 512, 256, 128};
+            launched.fast_threads[launched.n_fast++] = kThreads[size_class(part_longest)];
             switch (size_class(part_longest)) {
                 case 0:
                     k_fast<1024, kTileMax / 1024><<<count, 1024, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
@@ -532,6 +548,7 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                     tb, nt_large, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
         }
         profile_mark(0, stream);
+        launched.slices = slices;
         if (slices > 1) {
             const int search_ny = (pl.nblk * slices + kSearchWaves - 1) / kSearchWaves;
             const int bw = (pl.nblk + search_ny - 1) / search_ny;
@@ -580,6 +597,7 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     g_last_tiles = pl.n_tiles;
     g_last_groups = pl.n_groups;
     g_last_units = pl.n_units;
+    g_launched = launched;
     return launch_status("search launch");
 }
 
@@ -795,6 +813,12 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     // 512: 52.5/54.3, 704: 77.2/79.0, 1024: 83/99).
     const long long split_m = (M + kSplitBM - 1) / kSplitBM, split_wgs = 8 * tn_per_xcd * split_m;
     const bool by_split = planes == 2 && K % (2 * kLinBK) == 0 && K >= kSplitMinK && split_wgs <= kSplitMaxWgs;
+    g_launched = Launched();
+    g_launched.what = by_rows ? Launched::kLinearRows : by_split ? Launched::kLinearSplit : Launched::kLinear;
+    g_launched.bits = bits;
+    g_launched.planes = planes;
+    g_launched.row_tile = row_tile;
+    g_launched.row_mt = row_cap == 15 ? 1 : 2;
 #define PWLQ_LINEAR_ROWS(B, P, T, MT)                                                              \
     k_linear_rows<B, P, T, MT><<<row_grid, 64 * kRowWaves, 0, stream>>>(                           \
         xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, y, acc, rows_per_tile)
@@ -1120,6 +1144,31 @@ int pwlq_set_small_call_tiles(int tiles)
 }
 
 const char *pwlq_last_search_kernel(void) { return g_last_search_kernel; }
+
+const char *pwlq_last_kernels(void)
+{
+    const Launched &l = g_launched;
+    char *const text = g_launched_text;
+    const size_t room = sizeof(g_launched_text);
+    text[0] = 0;
+    size_t at = 0;
+    switch (l.what) {
+        case Launched::kNone: break;
+        case Launched::kSmall: snprintf(text, room, "k_small"); break;
+        case Launched::kSearch:
+            for (int i = 0; i < l.n_fast; ++i)
+                at += (size_t)snprintf(text + at, room - at, "%sk_fast<%d>", at ? " " : "", l.fast_threads[i]);
+            if (l.slices > 1) snprintf(text + at, room - at, "%sk_search_sliced(%d)", at ? " " : "", l.slices);
+            else if (l.slices == 1) snprintf(text + at, room - at, "%sk_search", at ? " " : "");
+            break;
+        case Launched::kLinearRows:
+            snprintf(text, room, "k_linear_rows<%d, %d, %d, %d>", l.bits, l.planes, l.row_tile, l.row_mt);
+            break;
+        case Launched::kLinearSplit: snprintf(text, room, "k_linear_split<%d>", l.bits); break;
+        case Launched::kLinear: snprintf(text, room, "k_linear<%d, %d>", l.bits, l.planes); break;
+    }
+    return text;
+}
 
 const char *pwlq_kernel_name(int role)
 {

@@ -32,6 +32,7 @@ EXPORTS = (
     "pwlq_linear_workspace_bytes", "pwlq_linear_i8",
     "pwlq_last_error", "pwlq_last_search_shape", "pwlq_profile_enable",
     "pwlq_profile_last_ms", "pwlq_profile_ms", "pwlq_kernel_name", "pwlq_last_search_kernel",
+    "pwlq_last_kernels",
     "pwlq_set_small_call_tiles",
 )
 
@@ -119,6 +120,8 @@ def _load() -> ctypes.CDLL:
     lib.pwlq_kernel_name.argtypes = [ci]
     lib.pwlq_last_search_kernel.restype = ctypes.c_char_p
     lib.pwlq_last_search_kernel.argtypes = []
+    lib.pwlq_last_kernels.restype = ctypes.c_char_p
+    lib.pwlq_last_kernels.argtypes = []
     lib.pwlq_set_small_call_tiles.restype = ctypes.c_int
     lib.pwlq_set_small_call_tiles.argtypes = [ctypes.c_int]
     return lib
@@ -477,6 +480,11 @@ def last_search_shape():
 
 def last_search_kernel() -> str:
     return lib.pwlq_last_search_kernel().decode()
+
+
+def last_kernels() -> str:
+    """Kernels that the calling thread's last search or inner product launched (pwlq_bench.h)."""
+    return lib.pwlq_last_kernels().decode()
 
 
 def set_small_call_tiles(tiles: int) -> int:

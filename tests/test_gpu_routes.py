@@ -1,0 +1,59 @@
+"""Which kernels a call launches (pwlq_last_kernels), either side of the limits that choose
+between them: the tests of a kernel's edges count only while their calls reach it."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2002_00104_amd import pwlq
+    return pwlq
+
+
+def searched(P, shapes, bits, n, mode=0, fast=False, small=False):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(1)
+    before = P.set_small_call_tiles(-1 if small else 0)
+    try:
+        tl = P.TensorList([torch.randn(s, generator=g, device="cuda") for s in shapes], mode)
+        P.search_list(tl, bits, n, fast=fast)
+        return P.last_kernels()
+    finally:
+        P.set_small_call_tiles(before)
+
+
+@pytest.mark.parametrize("shapes,n,want", [
+    ([(3, 255)], 64, "k_search"), ([(3, 256)], 64, "k_search_sliced(2)"),        # 128 elements to a slice
+    ([(5, 2047)], 333, "k_search_sliced(8)"), ([(40, 1030)], 100, "k_search_sliced(8)"),
+    ([(4096, 300)], 64, "k_search_sliced(2)"), ([(4097, 300)], 64, "k_search"),   # 8192 wavefronts in all
+    ([(2, 9000), (7, 1500), (20, 300), (30, 65), (16, 17), (8, 9)], 200, "k_search_sliced(8)")])
+def test_search(P, shapes, n, want):
+    assert searched(P, shapes, 4, n) == want
+
+
+def test_small_call_and_fast_search(P):
+    assert searched(P, [(64, 576)], 4, 100, small=True) == "k_small"
+    assert searched(P, [(2048, 119)], 4, 100, fast=True) == "k_search"
+    assert searched(P, [(2048, 120)], 4, 100, fast=True) == "k_fast<128>"
+    assert searched(P, [(2048, 257), (2048, 1025), (2048, 256)], 4, 100, fast=True) == "k_fast<512> k_fast<256> k_fast<128>"
+    assert searched(P, [(1024, 5121), (1024, 100)], 4, 100, fast=True) == "k_fast<1024> k_search"
+    assert P.last_search_kernel() == "k_fast"
+
+
+@pytest.mark.parametrize("M,K,N,bits,acc,want", [
+    (15, 256, 16, 4, False, "k_linear_rows<4, 2, 16, 1>"), (16, 272, 17, 4, True, "k_linear_rows<4, 3, 16, 2>"),
+    (32, 512, 33, 4, False, "k_linear_rows<4, 2, 32, 2>"), (63, 2304, 64, 4, True, "k_linear_rows<4, 3, 32, 2>"),
+    (64, 64, 14400, 4, False, "k_linear_rows<4, 2, 32, 2>"), (64, 64, 14432, 4, False, "k_linear<4, 2>"),
+    (1025, 512, 1729, 4, False, "k_linear_split<4>"), (1025, 528, 1729, 4, False, "k_linear<4, 2>"),
+    (1025, 448, 1729, 4, False, "k_linear<4, 2>"), (1025, 512, 1729, 4, True, "k_linear<4, 3>"),
+    (768, 512, 4096, 4, False, "k_linear_split<4>"), (768, 512, 4097, 4, False, "k_linear<4, 2>")])
+def test_inner_product(P, M, K, N, bits, acc, want):
+    import torch
+    x = torch.zeros((M, K), dtype=torch.int8, device="cuda")
+    z = torch.zeros(N * K, dtype=torch.uint8, device="cuda")
+    p = torch.ones(N, device="cuda")
+    P.linear_i8(x, 1.0, 0.0, z, z, N, bits, p, p, want_acc=acc)
+    assert P.last_kernels() == want
