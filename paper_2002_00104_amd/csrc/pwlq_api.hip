@@ -764,6 +764,50 @@ int run_mse(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode, con
     return launch_status("mse launch");
 }
 
+// Whether an inner product goes to k_linear_rows, against k_linear_split where that is
+// possible and k_linear where not.  Its workgroups of eight wavefronts, two to a CU, decode
+// the weights once per row tile: one tile, or up to 512 workgroups in one pass over the chip,
+// beat both at every K, bit width and form (b = 4, us, rows / split / k_linear: K = 4096,
+// 250x4096 26.1/31.6/48.8, 441x1000 19.1/28.6/46.1, 8x11008 12/-/59, 63x50000 102/-/186;
+// K = 1024, 250x4096 10.3/13.4/18.9; sums apart, K = 4096, 250x4096 33.1/-/52.2).  Against
+// that:
+//  - b = 8 decodes a lane's weights in more registers and, on reductions beyond 2048, loses
+//    to k_linear_split past one workgroup per CU (K = 4096: 256 workgroups 21.7/30.8, 512
+//    36.5/31.0; K = 2048: 0.86-1.12 of it at 470 to 512).
+//  - One tile of 32 to 63 rows, sums apart, short reductions, many channels: the call is its
+//    output, which k_linear writes in longer runs (63x200000, K = 64 / 256: 122/102, 138/120,
+//    faster by rows from K = 1024; 63x50000 36/33 and 40/39, at odd widths 38/42).
+// Past 512 workgroups there is a second pass:
+//  - k_linear_split is the better one (K = 4096, 441x4096 48.9/33.8, 1024x1000 38.3/30.5), but
+//    for two row tiles up to K = 2048 (K = 1024, 126x11008 15.2/15.7; 2048: 0.87-0.97 of it),
+//    or of up to 38 rows, whose upper halves read one row (K = 4096, N = 11008: 64 rows
+//    32.8/36.8, 76 34.3/36.9, 88 38.3/37.0; b = 2, 112 rows 34.7/39.0, 126 42.3/39.1), at
+//    b = 8 for those up to K = 1024; and at K = 512, its shortest, up to 768 workgroups
+//    (0.90-1.05 of it; b = 8 1.10).
+//  - With the sums apart k_linear, but for two row tiles, a third of its 192 rows (K = 1024,
+//    126x11008 22.1/25.4, K = 4096 57.3/57.5; K = 64: 1.07 of it), and at up to 5 bits on
+//    reductions from 1024 (189 to 378 rows, 640 to 768 workgroups: 0.85-1.04 of it; 896:
+//    441x4096 29.0/23.9).
+//  - Else, against k_linear, up to 900 workgroups, 740 on long reductions (K = 4096, 378x4096
+//    0.96 of it at b = 4, 0.99 at 7; b = 8 1.08-1.3 past 512).
+bool linear_by_rows(int planes, int bits, long long K, int row_cap, long long row_tiles, long long row_cols,
+                    int rows_per_tile, bool can_split)
+{
+    const long long wgs = row_tiles * row_cols;
+    const bool wide = bits == 8 && K > 2048;
+    if (row_tiles == 1) {
+        if (planes == 3) return !(row_cap == 63 && K <= 256 && wgs > 2048);
+        return !(can_split && wide && wgs > 512);
+    }
+    if (wgs <= 512) return !(can_split && wide && wgs > 256);
+    const bool two = row_tiles == 2 && wgs <= 700, short_tiles = rows_per_tile <= (bits == 2 ? 56 : 38);
+    if (can_split && bits < 8) return (two && (K <= 2048 || short_tiles)) || (K <= 512 && wgs <= 770);
+    if (can_split) return two && K <= 1024 && short_tiles;
+    if (planes == 3)
+        return (two && K >= 256 && (!wide || (short_tiles && K <= 4096))) || (bits <= 5 && K >= 1024 && wgs <= 770);
+    return wgs <= (K <= 2048 ? 900 : bits == 8 ? 512 : 740);
+}
+
 int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
                const uint8_t *packed_codes, const uint8_t *packed_flags, int64_t N, int bits,
                const float *p, const float *m, float *y, int32_t *acc, void *workspace,
@@ -795,24 +839,20 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     hipStream_t stream = (hipStream_t)stream_v;
     float *wconst = (float *)workspace;
     const unsigned wsum_wgs = (unsigned)((N + kLinWG / 64 - 1) / (kLinWG / 64));
-    // Few rows, or so few tiles that k_linear would leave CUs idle and walk the reduction in
-    // one long chain: k_linear_rows, every call that one of its row tiles covers and larger
-    // ones up to about 900 of its workgroups (K = 4096, b = 4, M x N, us, k_linear against
-    // k_linear_rows: 8x11008 58.7/12.0, 63x11008 59.5/27.8, 126x11008 60.5/46, 250x11008
-    // 61/78, 512x1000 49/25, 1024x1000 49/39, 512x11008 83/150).
     const int row_cap = M <= 15 ? 15 : M <= 31 ? 31 : 63;          // and one row of ones
     const int row_tile = row_cap <= 31 ? 16 : 32;
     const long long row_tiles = (M + row_cap - 1) / row_cap, row_cols = (N + row_tile - 1) / row_tile;
     const int rows_per_tile = (int)((M + row_tiles - 1) / row_tiles);
-    const bool by_rows = row_tiles == 1 || row_tiles * row_cols <= kRowsMaxWgs;
     const dim3 row_grid((unsigned)row_cols, (unsigned)row_tiles);
-    // k_linear_split up to one and a half of its workgroups per CU (each XCD counted as full as its
+    // Where the rows leave it, k_linear_split up to one and a half of its workgroups per CU (each XCD counted as full as its
     // fullest: few channel tiles fill few XCDs); above that k_linear has as many
     // wavefronts without the second half's LDS traffic (K = 4096, b = 4, workgroups: us, k_linear
     // against k_linear_split: 256: 50.8/33.3, 320: 51.3/47.7, 352: 56.4/52.5, 384: 51.6/49.2,
     // 512: 52.5/54.3, 704: 77.2/79.0, 1024: 83/99).
     const long long split_m = (M + kSplitBM - 1) / kSplitBM, split_wgs = 8 * tn_per_xcd * split_m;
-    const bool by_split = planes == 2 && K % (2 * kLinBK) == 0 && K >= kSplitMinK && split_wgs <= kSplitMaxWgs;
+    const bool can_split = planes == 2 && K % (2 * kLinBK) == 0 && K >= kSplitMinK && split_wgs <= kSplitMaxWgs;
+    const bool by_rows = linear_by_rows(planes, bits, K, row_cap, row_tiles, row_cols, rows_per_tile, can_split);
+    const bool by_split = !by_rows && can_split;
     g_launched = Launched();
     g_launched.what = by_rows ? Launched::kLinearRows : by_split ? Launched::kLinearSplit : Launched::kLinear;
     g_launched.bits = bits;

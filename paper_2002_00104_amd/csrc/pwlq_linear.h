@@ -650,7 +650,6 @@ __global__ __launch_bounds__(2 * kLinWG, 4) void k_linear_split(const int8_t *__
 // lane, paid again by every tile of rows).
 constexpr int kRowWaves = 8;
 constexpr int kRowLane = 64;           // weights of a lane per step
-constexpr int kRowsMaxWgs = 900;       // workgroups up to which several row tiles beat k_linear
 
 // kTile x kTile outputs of one matrix instruction: 16 (64 deep) or 32 (32 deep).
 template <int kTile>

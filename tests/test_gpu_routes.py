@@ -49,7 +49,30 @@ def test_small_call_and_fast_search(P):
     (64, 64, 14400, 4, False, "k_linear_rows<4, 2, 32, 2>"), (64, 64, 14432, 4, False, "k_linear<4, 2>"),
     (1025, 512, 1729, 4, False, "k_linear_split<4>"), (1025, 528, 1729, 4, False, "k_linear<4, 2>"),
     (1025, 448, 1729, 4, False, "k_linear<4, 2>"), (1025, 512, 1729, 4, True, "k_linear<4, 3>"),
-    (768, 512, 4096, 4, False, "k_linear_split<4>"), (768, 512, 4097, 4, False, "k_linear<4, 2>")])
+    (768, 512, 4096, 4, False, "k_linear_split<4>"), (768, 512, 4097, 4, False, "k_linear<4, 2>"),
+    # up to 512 workgroups of 32 channels and up to 63 rows, at 8 bits and long reductions 256
+    (250, 4096, 4096, 4, False, "k_linear_rows<4, 2, 32, 2>"), (250, 4096, 4128, 4, False, "k_linear_split<4>"),
+    (250, 2176, 2048, 8, False, "k_linear_rows<8, 2, 32, 2>"), (250, 2176, 2080, 8, False, "k_linear_split<8>"),
+    (250, 2048, 4096, 8, False, "k_linear_rows<8, 2, 32, 2>"), (441, 4096, 4096, 4, False, "k_linear_split<4>"),
+    (1024, 4096, 1000, 4, False, "k_linear_split<4>"), (63, 2176, 16416, 8, False, "k_linear_split<8>"),
+    # two row tiles: up to 700, with k_linear_split possible to K = 2048 or 38 rows each
+    (126, 2048, 11008, 4, False, "k_linear_rows<4, 2, 32, 2>"), (126, 2176, 11008, 4, False, "k_linear_split<4>"),
+    (76, 4096, 11008, 7, False, "k_linear_rows<7, 2, 32, 2>"), (77, 4096, 11008, 7, False, "k_linear_split<7>"),
+    (64, 1024, 11008, 8, False, "k_linear_rows<8, 2, 32, 2>"), (64, 1152, 11008, 8, False, "k_linear_split<8>"),
+    (80, 1024, 11008, 8, False, "k_linear_split<8>"), (112, 4096, 11008, 2, False, "k_linear_rows<2, 2, 32, 2>"),
+    (378, 512, 4096, 4, False, "k_linear_rows<4, 2, 32, 2>"), (378, 512, 4128, 4, False, "k_linear_split<4>"), (126, 1024, 11232, 4, False, "k_linear_split<4>"),
+    # without it: 900, on long reductions 740, at 8 bits 512
+    (378, 4112, 3936, 4, False, "k_linear_rows<4, 2, 32, 2>"), (378, 4112, 3968, 4, False, "k_linear<4, 2>"),
+    (378, 4112, 2720, 8, False, "k_linear_rows<8, 2, 32, 2>"), (378, 4112, 2752, 8, False, "k_linear<8, 2>"),
+    (378, 528, 4800, 8, False, "k_linear_rows<8, 2, 32, 2>"), (378, 528, 4832, 8, False, "k_linear<8, 2>"),
+    # the sums apart
+    (250, 4096, 4096, 4, True, "k_linear_rows<4, 3, 32, 2>"), (441, 4096, 4096, 4, True, "k_linear<4, 3>"),
+    (126, 4096, 11008, 6, True, "k_linear_rows<6, 3, 32, 2>"), (126, 4096, 11008, 8, True, "k_linear<8, 3>"),
+    (64, 4096, 11008, 8, True, "k_linear_rows<8, 3, 32, 2>"), (126, 64, 11008, 4, True, "k_linear<4, 3>"),
+    (189, 4096, 6000, 4, True, "k_linear_rows<4, 3, 32, 2>"), (189, 4096, 6000, 6, True, "k_linear<6, 3>"),
+    (189, 4096, 8224, 4, True, "k_linear<4, 3>"), (189, 1008, 6000, 4, True, "k_linear<4, 3>"),
+    (63, 64, 65536, 4, True, "k_linear_rows<4, 3, 32, 2>"), (63, 64, 65568, 4, True, "k_linear<4, 3>"),
+    (63, 272, 65568, 4, True, "k_linear_rows<4, 3, 32, 2>"), (31, 64, 70000, 4, True, "k_linear_rows<4, 3, 16, 2>")])
 def test_inner_product(P, M, K, N, bits, acc, want):
     import torch
     x = torch.zeros((M, K), dtype=torch.int8, device="cuda")
