@@ -75,11 +75,62 @@ int check_common(int bits, int mode)
     return PWLQ_OK;
 }
 
+// Threads that k_fast gives a tile, by the longest of a launch's tiles.  A short tile is
+// served fastest by few threads where there are many tiles (see k_fast), but a thread then
+// walks many candidates one after the other: where the tiles are too few to hide that
+// (b = 4, n = 4000, us, 128 or 256 / 512 threads: 512x121 72/37, 512x300 46/39; n = 1000,
+// 1024x121 24.7/22.6, 2048x121 31.8/36.1; n = 300, 1024x121 14.9/17.2) they get 512.
+int fast_threads(int longest, long long tiles, int n, int L)
+{
+    if (longest > kFastLong) return 1024;
+    if (longest > kSmallTile) return 512;
+    const bool short_tiles = longest <= kFastShort;
+    if (tiles <= (short_tiles ? 1024 : 512) && (long long)n * L >= 3500) return 512;
+    return short_tiles ? 128 : 256;
+}
+
+// Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
+// candidate grows with the number of half-way points (2L look-ups) and hardly depends on
+// the tile length, the plain evaluation costs one pass over the tile.  16384 tiles, 1000
+// candidates, b = 4, us, look-ups / pass: 160 elements 168 / 249, 96 elements 162 / 178,
+// 64 elements 157 / 144; but a line at 6 * 2L cost MobileNetV2 shapes 216 -> 238, one more
+// launch beside the passes over the shorter tiles, which stay.  At b = 8 and many
+// candidates the line is a little longer (2048 and 1024 tiles of 2048, n = 1000: 299/289,
+// 170/160; n = 300: 149/195, 81/120).
+//
+// Below 2048 tiles the look-ups of a tile, L pairs for every candidate of a thread one after
+// the other at about 0.3 us, take as long for one tile as for all, and the passes are spread over
+// the chip: tiles not far above that length are handed over only where the look-ups'
+// time is less than the passes' at 1.6e13 evaluations a second on a full chip and 6 us for
+// their launch (16x121, n = 20000, us, look-ups / pass 273/55; 64x2048, b = 8, n = 2000 146/59; 512x121,
+// n = 1000 15.8/20.4).
+int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
+{
+    const int L = (1 << (bits - 1)) - 1;
+    const int shortest = (bits == 8 && n >= 800 ? 9 : 8) * (2 * L) + 8, always = 16 * (2 * L + 1) + 64;
+    long long tiles = 0, elements = 0;
+    int longest = 0;
+    for (const TensorRec &r : recs) {
+        if (r.tile_len < shortest || r.tile_len >= always) continue;
+        tiles += r.ntiles;
+        elements += (long long)r.ntiles * r.tile_len;
+        longest = std::max(longest, r.tile_len);
+    }
+    if (tiles >= 2048) return shortest;
+    const int threads = fast_threads(longest, tiles, n, L);
+    const long long look_ups_ns = (long long)((n + threads - 1) / threads) * L * 300;
+    const long long wavefronts = tiles * ((n + kBlk - 1) / kBlk);
+    const long long per_ns = 16000 * std::min(wavefronts + 1024, 8192LL) / 8192;
+    const long long passes_ns = 6000 + elements * n / per_ns;
+    return look_ups_ns <= passes_ns ? shortest : always;
+}
+
 // n_cand == 0 builds a plan without search scratch (quantizer, selectors, error).
+// fast_bits > 0: the bit width of a fast search.
 int build_plan(Plan &pl, const pwlq_tensor_desc *desc, int n_tensors, int n_cand, int mode,
                bool need_pointers, const int64_t *code_byte_offset = nullptr,
                const int64_t *flag_byte_offset = nullptr, Aux aux = kAuxNone,
-               int fast_min_len = 0)
+               int fast_bits = 0)
 {
     if (!desc) return fail(PWLQ_ENULL, "tensor descriptor table is NULL");
     if (n_tensors < 1) return fail(PWLQ_EINVAL, "n_tensors=%d must be >= 1", n_tensors);
@@ -118,9 +169,12 @@ int build_plan(Plan &pl, const pwlq_tensor_desc *desc, int n_tensors, int n_cand
         r.ntiles = (int)(groups * tpg);
         r.stride = (r.tile_len + kVec - 1) / kVec * kVec + kVec;   // one spare vector: loads may run one ahead
         r.tpu = std::max(1, kUnitElems / r.tile_len);
-        r.fast = (fast_min_len > 0 && r.tile_len >= fast_min_len) ? 1 : 0;
         tmp[i] = r;
         order[i] = {i, r.tile_len};
+    }
+    if (fast_bits > 0) {
+        const int min_len = fast_min_len(tmp, fast_bits, n_cand);
+        for (TensorRec &r : tmp) r.fast = r.tile_len >= min_len ? 1 : 0;
     }
     // a search workgroup walks tpu tiles one after the other; keep enough
     // workgroups to fill the chip when the call is small
@@ -349,18 +403,6 @@ void profile_mark(int idx, hipStream_t stream)
     if (idx & 1) ++g_ev_count[role];
 }
 
-// Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
-// candidate grows with the number of half-way points (2L look-ups) and hardly depends on
-// the tile length, the plain evaluation costs one pass over the tile.  16384 tiles, 1000
-// candidates, b = 4, us, look-ups / pass: 160 elements 168 / 249, 96 elements 162 / 178,
-// 64 elements 157 / 144; but a line at 6 * 2L cost MobileNetV2 shapes 216 -> 238, one more
-// launch beside the passes over the shorter tiles, which stay.
-int fast_min_len(int bits)
-{
-    const int L = (1 << (bits - 1)) - 1;
-    return 8 * (2 * L) + 8;
-}
-
 // Largest number of groups a search call may have and still run as one fused launch
 // (PWLQ_SMALL_CALL_TILES overrides the default once; pwlq_set_small_call_tiles at any time).
 std::atomic<int> &small_call_tiles()
@@ -382,7 +424,7 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     if (!p_star || !m_out || !k_star || !mse) return fail(PWLQ_ENULL, "an output pointer is NULL");
     Plan pl;
     rc = build_plan(pl, desc, n_tensors, n_cand, mode, true, nullptr, nullptr, kAuxNone,
-                    fast ? fast_min_len(bits) : 0);
+                    fast ? bits : 0);
     if (rc) return rc;
     rc = check_workspace(pl, workspace, workspace_bytes);
     if (rc) return rc;
@@ -484,16 +526,16 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                 continue;
             const int count = seen - begin;
             const size_t lds = lds_bytes(part_longest);
-            constexpr int kThreads[4] = {1024, 512, 256, 128};
-            launched.fast_threads[launched.n_fast++] = kThreads[size_class(part_longest)];
-            switch (size_class(part_longest)) {
-                case 0:
+            const int threads = fast_threads(part_longest, count, n_cand, (1 << (bits - 1)) - 1);
+            launched.fast_threads[launched.n_fast++] = threads;
+            switch (threads) {
+                case 1024:
                     k_fast<1024, kTileMax / 1024><<<count, 1024, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
                     break;
-                case 1:
+                case 512:
                     k_fast<512, kFastLong / 512><<<count, 512, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
                     break;
-                case 3:
+                case 128:
                     k_fast<128, kFastShort / 128><<<count, 128, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
                     break;
                 default:

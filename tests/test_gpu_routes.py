@@ -43,6 +43,19 @@ def test_small_call_and_fast_search(P):
     assert P.last_search_kernel() == "k_fast"
 
 
+@pytest.mark.parametrize("shape,bits,n,want", [
+    # few tiles: 512 threads each, or passes where the look-ups would take longer
+    ((300, 250), 4, 500, "k_fast<512>"), ((300, 250), 4, 499, "k_fast<128>"), ((1024, 250), 4, 500, "k_fast<512>"),
+    ((1025, 250), 4, 500, "k_fast<128>"), ((512, 500), 4, 500, "k_fast<512>"), ((513, 500), 4, 500, "k_fast<256>"),
+    ((16, 121), 4, 20000, "k_search"), ((2047, 121), 4, 20000, "k_search"), ((2048, 121), 4, 20000, "k_fast<128>"),
+    ((64, 303), 4, 4000, "k_search_sliced(2)"), ((64, 304), 4, 4000, "k_fast<512>"),
+    ((64, 2048), 8, 2000, "k_search_sliced(4)"), ((8, 3000), 8, 1000, "k_search_sliced(8)"),
+    ((2048, 2040), 8, 799, "k_fast<512>"), ((2048, 2039), 8, 799, "k_search"), ((2048, 2294), 8, 800, "k_fast<512>"),
+    ((2048, 2293), 8, 800, "k_search"), ((300, 2039), 8, 1000, "k_search"), ((8, 4144), 8, 1000, "k_fast<512>")])
+def test_fast_search_of_few_tiles(P, shape, bits, n, want):
+    assert searched(P, [shape], bits, n, fast=True) == want
+
+
 @pytest.mark.parametrize("M,K,N,bits,acc,want", [
     (15, 256, 16, 4, False, "k_linear_rows<4, 2, 16, 1>"), (16, 272, 17, 4, True, "k_linear_rows<4, 3, 16, 2>"),
     (32, 512, 33, 4, False, "k_linear_rows<4, 2, 32, 2>"), (63, 2304, 64, 4, True, "k_linear_rows<4, 3, 32, 2>"),
