@@ -438,14 +438,23 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     const long long unit_groups = (pl.n_units + upw - 1) / upw;
     const long long wgs = (unit_groups + 7) / 8 * 8 * ny;
     if (wgs > 0x7fffffffLL) return fail(PWLQ_EINVAL, "search grid too large");
-    // too few wavefronts to keep the SIMDs busy: the tiles' elements are cut into slices
+    // Too few wavefronts to keep the SIMDs busy: the tiles' elements are cut into slices.  With
+    // 16 candidate blocks or more k_search's workgroups are full without slices, and those
+    // past 2048 wavefronts gain only on long tiles (n = 4000, 4032 wavefronts, us, one / two
+    // slices: tiles of 300 27.0/29.2, 550 34.8/37.5, 2048 81.9/86.0; n = 1000, 2080: 400
+    // 21.7/23.0, 1150 39.4/39.2, 2048 59.9/55.6; n = 10000, 2512: 300 40.7/45.0, 2048 93.3/96.7,
+    // 4608 221/220); beyond kFineMax candidates tiles of less than 512 lose too (471: 256
+    // 33.5/35.1, 550 42.9/39.9).
     int slices = 1;
     {
         int longest_plain = 0;
         bool one_tile = true;
         for (const TensorRec &r : pl.recs)
             if (!r.fast) { longest_plain = std::max(longest_plain, r.tile_len); one_tile &= r.tpu == 1; }
-        while (one_tile && slices < 8 && 2 * slices * pl.n_units * pl.nblk <= kSlicedWaves &&
+        const long long wavefronts = pl.n_units * pl.nblk;
+        const bool pays = (pl.nblk < kSearchWaves || wavefronts <= 2048 || longest_plain >= (pl.fine ? 2048 : 4096)) &&
+                          (pl.fine || longest_plain >= 4 * kSliceMin);
+        while (one_tile && pays && slices < 8 && 2 * slices * wavefronts <= kSlicedWaves &&
                longest_plain >= 2 * slices * kSliceMin)
             slices *= 2;
     }

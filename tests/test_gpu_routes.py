@@ -29,6 +29,12 @@ def searched(P, shapes, bits, n, mode=0, fast=False, small=False):
     ([(3, 255)], 64, "k_search"), ([(3, 256)], 64, "k_search_sliced(2)"),        # 128 elements to a slice
     ([(5, 2047)], 333, "k_search_sliced(8)"), ([(40, 1030)], 100, "k_search_sliced(8)"),
     ([(4096, 300)], 64, "k_search_sliced(2)"), ([(4097, 300)], 64, "k_search"),   # 8192 wavefronts in all
+    # 16 candidate blocks fill a workgroup: to 2048 wavefronts, or tiles of 2048
+    ([(128, 1000)], 1000, "k_search_sliced(4)"), ([(129, 1000)], 1000, "k_search"),
+    ([(129, 2048)], 1000, "k_search_sliced(2)"), ([(136, 2047)], 960, "k_search_sliced(4)"),
+    # more than 2048 candidates: tiles of 512, and 4096 past 2048 wavefronts
+    ([(16, 512)], 4000, "k_search_sliced(4)"), ([(16, 511)], 4000, "k_search"), ([(64, 4095)], 4000, "k_search"),
+    ([(64, 4096)], 4000, "k_search_sliced(2)"),
     ([(2, 9000), (7, 1500), (20, 300), (30, 65), (16, 17), (8, 9)], 200, "k_search_sliced(8)")])
 def test_search(P, shapes, n, want):
     assert searched(P, shapes, 4, n) == want
@@ -48,8 +54,8 @@ def test_small_call_and_fast_search(P):
     ((300, 250), 4, 500, "k_fast<512>"), ((300, 250), 4, 499, "k_fast<128>"), ((1024, 250), 4, 500, "k_fast<512>"),
     ((1025, 250), 4, 500, "k_fast<128>"), ((512, 500), 4, 500, "k_fast<512>"), ((513, 500), 4, 500, "k_fast<256>"),
     ((16, 121), 4, 20000, "k_search"), ((2047, 121), 4, 20000, "k_search"), ((2048, 121), 4, 20000, "k_fast<128>"),
-    ((64, 303), 4, 4000, "k_search_sliced(2)"), ((64, 304), 4, 4000, "k_fast<512>"),
-    ((64, 2048), 8, 2000, "k_search_sliced(4)"), ((8, 3000), 8, 1000, "k_search_sliced(8)"),
+    ((64, 303), 4, 4000, "k_search"), ((64, 304), 4, 4000, "k_fast<512>"),
+    ((64, 2048), 8, 2000, "k_search_sliced(4)"), ((64, 550), 5, 4000, "k_search"), ((8, 3000), 8, 1000, "k_search_sliced(8)"),
     ((2048, 2040), 8, 799, "k_fast<512>"), ((2048, 2039), 8, 799, "k_search"), ((2048, 2294), 8, 800, "k_fast<512>"),
     ((2048, 2293), 8, 800, "k_search"), ((300, 2039), 8, 1000, "k_search"), ((8, 4144), 8, 1000, "k_fast<512>")])
 def test_fast_search_of_few_tiles(P, shape, bits, n, want):
