@@ -192,8 +192,11 @@ int build_plan(Plan &pl, const pwlq_tensor_desc *desc, int n_tensors, int n_cand
     }
     // longest tiles first: the search kernel's workgroups are dispatched in
     // index order, so the big items start early and the small ones fill gaps
-    std::stable_sort(order.begin(), order.end(),
-                     [](const Item &a, const Item &b) { return a.tile_len > b.tile_len; });
+    // (selectors and error: of these, the groups of most tiles in front)
+    std::stable_sort(order.begin(), order.end(), [&](const Item &a, const Item &b) {
+        if (a.tile_len != b.tile_len || aux == kAuxNone) return a.tile_len > b.tile_len;
+        return tmp[a.idx].tpg > tmp[b.idx].tpg;
+    });
     pl.recs.resize(n_tensors);
     pl.tile_prefix.assign(n_tensors + 1, 0);
     pl.group_prefix.assign(n_tensors + 1, 0);
@@ -370,12 +373,15 @@ bool fill_stat_args(const Plan &pl, StatArgs &sa)
     return true;
 }
 
-// Whether some group's tiles are too many for one thread.
-bool wide_groups(const Plan &pl)
+// Groups whose tiles are too many for one thread: in a plan for selectors or error the first.
+int wide_groups(const Plan &pl)
 {
-    for (const TensorRec &r : pl.recs)
-        if (r.tpg >= kWideTiles) return true;
-    return false;
+    int groups = 0;
+    for (const TensorRec &r : pl.recs) {
+        if (r.tpg < kWideTiles) break;
+        groups += r.ngroups;
+    }
+    return groups;
 }
 
 int launch_status(const char *what)
@@ -770,14 +776,14 @@ int run_select(const pwlq_tensor_desc *desc, int n_tensors, int mode, int select
     double *tile_s2 = (double *)(ws + pl.off_stat_s2);
     double *tile_s1 = (double *)(ws + pl.off_stat_s1);
     const unsigned tile_wgs = (unsigned)((pl.n_tiles + kWaves - 1) / kWaves);
-    const unsigned group_wgs = (unsigned)((pl.n_groups + kSelectWG - 1) / kSelectWG);
+    const int wide = wide_groups(pl), groups = (int)pl.n_groups;
     k_stats<<<tile_wgs, kWG, 0, stream>>>(tb, sa, (int)pl.n_tiles, tile_max, tile_s2, tile_s1);
-    if (wide_groups(pl))
-        k_select<true><<<(unsigned)pl.n_groups, kSelectWG, 0, stream>>>(tb, sa, (int)pl.n_groups, selector, tile_max,
-                                                                        tile_s2, tile_s1, p_out, m_out);
-    else
-        k_select<false><<<group_wgs, kSelectWG, 0, stream>>>(tb, sa, (int)pl.n_groups, selector, tile_max, tile_s2,
-                                                             tile_s1, p_out, m_out);
+    if (wide > 0)
+        k_select<true><<<(unsigned)wide, kSelectWG, 0, stream>>>(tb, sa, 0, wide, selector, tile_max, tile_s2, tile_s1,
+                                                                 p_out, m_out);
+    if (wide < groups)
+        k_select<false><<<(unsigned)((groups - wide + kSelectWG - 1) / kSelectWG), kSelectWG, 0, stream>>>(
+            tb, sa, wide, groups, selector, tile_max, tile_s2, tile_s1, p_out, m_out);
     return launch_status("select launch");
 }
 
@@ -805,13 +811,12 @@ int run_mse(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode, con
     }
     double *tile_sse = (double *)(ws + pl.off_stat_s2);
     const unsigned tile_wgs = (unsigned)((pl.n_tiles + kWaves - 1) / kWaves);
-    const unsigned group_wgs = (unsigned)((pl.n_groups + kSelectWG - 1) / kSelectWG);
+    const int wide = wide_groups(pl), groups = (int)pl.n_mgroups;       // of several tiles: the first ones
     k_mse_tile<<<tile_wgs, kWG, 0, stream>>>(tb, sa, (int)pl.n_tiles, bits, p, m, tile_sse, mse);
-    if (pl.n_mgroups == 0) return launch_status("mse launch");
-    if (wide_groups(pl))
-        k_mse_final<true><<<(unsigned)pl.n_groups, kSelectWG, 0, stream>>>(tb, sa, (int)pl.n_groups, tile_sse, mse);
-    else
-        k_mse_final<false><<<group_wgs, kSelectWG, 0, stream>>>(tb, sa, (int)pl.n_groups, tile_sse, mse);
+    if (wide > 0) k_mse_final<true><<<(unsigned)wide, kSelectWG, 0, stream>>>(tb, sa, 0, wide, tile_sse, mse);
+    if (wide < groups)
+        k_mse_final<false><<<(unsigned)((groups - wide + kSelectWG - 1) / kSelectWG), kSelectWG, 0, stream>>>(
+            tb, sa, wide, groups, tile_sse, mse);
     return launch_status("mse launch");
 }
 

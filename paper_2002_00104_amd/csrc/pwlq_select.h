@@ -75,17 +75,25 @@ __device__ inline StatTile stat_tile(const Tables &tb, const StatArgs &sa, int s
     return st;
 }
 // Tensor of group g, where groups first_g (the wavefront's first; the same in every
-// lane) to first_g + 63 ask together.
+// lane) to first_g + 63 ask together: as a rule one tensor's, else one of the 64 from
+// first_g's on.  (A walk from there took up to 63 dependent loads where tensors are single
+// groups.)
+__device__ inline int find_group(const int *__restrict__ prefix, int nt, int first_g, int g)
+{
+    int lo = find_tensor(prefix, nt, first_g);
+    if (prefix[lo + 1] > first_g + 63) return lo;
+    int hi = nt - lo > 64 ? lo + 64 : nt;              // prefix[lo] <= g < prefix[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (prefix[mid] <= g) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
 __device__ inline StatRec stat_group(const Tables &tb, const StatArgs &sa, int first_g, int g)
 {
-    int i;
-    if (sa.nt > 0) {
-        i = find_tensor(sa.group_prefix, sa.nt, first_g);
-        while (sa.group_prefix[i + 1] <= g) ++i;
-    } else {
-        i = find_tensor(tb.group_prefix, tb.nt, first_g);
-        while (tb.group_prefix[i + 1] <= g) ++i;
-    }
+    const int i = sa.nt > 0 ? find_group(sa.group_prefix, sa.nt, first_g, g)
+                            : find_group(tb.group_prefix, tb.nt, first_g, g);
     return stat_rec(tb, sa, i);
 }
 
@@ -213,22 +221,28 @@ __device__ inline double solve_breakpoint(double m, double scale, bool laplace, 
 // beta = mean |w|) and select p.
 // selector 0: Section 5.1's logarithmic fit, p = sigma ln(0.8614 m/sigma + 0.6079);
 // selector 1: Eq.11 for the truncated Gaussian; 2: for the truncated Laplacian.
-// One thread per group, tiles in order; where some group has kWideTiles tiles or more
-// (a tensor as one group) one wavefront per group, lanes over the tiles, the lanes' sums
-// added in a fixed order.
+// One thread per group, tiles in order; groups of kWideTiles tiles or more (a tensor as one
+// group) have one wavefront each, lanes over the tiles, the lanes' sums added in a fixed
+// order.  The groups of several tiles come first, the longest of them in front, so a launch
+// takes a range: kWide those in front, the other form the rest.  (One launch for all with one
+// live lane in the solver took 171 us for two such groups among 82 680 of 64 weights, the two
+// launches 45.)
 constexpr int kSelectWG = 64;     // one wavefront per workgroup: a few ten thousand groups reach every CU
+// One thread / one wavefront, k_select's whole call in us: 1, 64, 1024 and 4096 groups of 16
+// tiles 15.1/13.9, 20.8/19.5, 102/104, 362/370; of 8 14.3/13.7, 14.7/15.0, 47/51, 185/196; of
+// 32 16.9/14.0, 25.9/22.2, 189/188.
 constexpr int kWideTiles = 16;
 
 template <bool kWide>
-__global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, StatArgs sa, int n_groups, int selector,
+__global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, StatArgs sa, int begin, int end, int selector,
                                                 const float *__restrict__ tile_max,
                                                 const double *__restrict__ tile_s2,
                                                 const double *__restrict__ tile_s1,
                                                 float *__restrict__ p_out,
                                                 float *__restrict__ m_out)
 {
-    const int first = kWide ? blockIdx.x : blockIdx.x * kSelectWG;
-    const int g = kWide ? first : (first + (int)threadIdx.x < n_groups ? first + (int)threadIdx.x : n_groups - 1);
+    const int first = begin + (kWide ? blockIdx.x : blockIdx.x * kSelectWG);
+    const int g = kWide ? first : (first + (int)threadIdx.x < end ? first + (int)threadIdx.x : end - 1);
     const StatRec r = stat_group(tb, sa, first, g);
     const int gl = g - r.group_base;
     const long long tile0 = r.tile_base + (long long)gl * r.tpg;
@@ -248,7 +262,7 @@ __global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, StatArgs sa, in
         s2 = wave_sum(s2);
         s1 = wave_sum(s1);
         if (threadIdx.x > 0) return;
-    } else if (first + (int)threadIdx.x >= n_groups) {
+    } else if (first + (int)threadIdx.x >= end) {
         return;
     }
     if (bad) mf = __builtin_nanf("");
@@ -303,25 +317,24 @@ __global__ __launch_bounds__(kWG) void k_mse_tile(Tables tb, StatArgs sa, int n_
     }
 }
 
-// Groups of several tiles: tiles added as in k_select.  (Those of one tile are done; a call
-// that has no others does not come here.)
+// Groups of several tiles, which come first: tiles added as in k_select, ranges as there.
+// (Those of one tile are done.)
 template <bool kWide>
-__global__ __launch_bounds__(kSelectWG) void k_mse_final(Tables tb, StatArgs sa, int n_groups,
+__global__ __launch_bounds__(kSelectWG) void k_mse_final(Tables tb, StatArgs sa, int begin, int end,
                                                    const double *__restrict__ tile_sse,
                                                    double *__restrict__ mse)
 {
-    const int first = kWide ? blockIdx.x : blockIdx.x * kSelectWG;
-    const int g = kWide ? first : (first + (int)threadIdx.x < n_groups ? first + (int)threadIdx.x : n_groups - 1);
+    const int first = begin + (kWide ? blockIdx.x : blockIdx.x * kSelectWG);
+    const int g = kWide ? first : (first + (int)threadIdx.x < end ? first + (int)threadIdx.x : end - 1);
     const StatRec r = stat_group(tb, sa, first, g);
     const int gl = g - r.group_base;
-    if (r.tpg == 1) return;
     const long long tile0 = r.tile_base + (long long)gl * r.tpg;
     double s = 0.0;
     for (int j = kWide ? threadIdx.x : 0; j < r.tpg; j += kWide ? kSelectWG : 1) s += tile_sse[tile0 + j];
     if (kWide) {
         s = wave_sum(s);
         if (threadIdx.x > 0) return;
-    } else if (first + (int)threadIdx.x >= n_groups) {
+    } else if (first + (int)threadIdx.x >= end) {
         return;
     }
     mse[r.out_group + gl] = s / (double)r.gcount;
