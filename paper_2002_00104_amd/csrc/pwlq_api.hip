@@ -543,18 +543,22 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
             const size_t lds = lds_bytes(part_longest);
             const int threads = fast_threads(part_longest, count, n_cand, (1 << (bits - 1)) - 1);
             launched.fast_threads[launched.n_fast++] = threads;
-            switch (threads) {
-                case 1024:
-                    k_fast<1024, kTileMax / 1024><<<count, 1024, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
-                    break;
-                case 512:
-                    k_fast<512, kFastLong / 512><<<count, 512, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
-                    break;
-                case 128:
-                    k_fast<128, kFastShort / 128><<<count, 128, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
-                    break;
-                default:
-                    k_fast<256, kSmallTile / 256><<<count, 256, lds, stream>>>(tb, begin, n_cand, bits, q, tile_max, gm, sse32);
+            // a launch has less than 2^32 threads
+            for (int at = begin; at < seen; at += kFastGridMax) {
+                const unsigned wgs = (unsigned)std::min(seen - at, kFastGridMax);
+                switch (threads) {
+                    case 1024:
+                        k_fast<1024, kTileMax / 1024><<<wgs, 1024, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
+                        break;
+                    case 512:
+                        k_fast<512, kFastLong / 512><<<wgs, 512, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
+                        break;
+                    case 128:
+                        k_fast<128, kFastShort / 128><<<wgs, 128, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
+                        break;
+                    default:
+                        k_fast<256, kSmallTile / 256><<<wgs, 256, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
+                }
             }
             begin = seen;
             part_longest = 0;

@@ -63,6 +63,7 @@ constexpr int kFastWalk = 3;                       // elements read unasked (4: 
 constexpr int kFastWalkOn = 4;                     // ... and then per step
 constexpr int kFastShort = 256;                    // longest tile of a launch of 128 threads
 constexpr int kFastLong = 5120;                    // longest tile of a launch of 512 threads: four workgroups' LDS per CU
+constexpr int kFastGridMax = 1 << 21;              // workgroups of a launch
 constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones
 
 // Error of a tile's filter value beyond the rounding of its elements: A is a sum of
