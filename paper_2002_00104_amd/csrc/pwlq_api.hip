@@ -384,6 +384,13 @@ int wide_groups(const Plan &pl)
     return groups;
 }
 
+// Whether a launch holds so many workgroups of so many threads: from 2^32 threads on the
+// runtime starts what is left after the wrap and reports nothing.
+bool launch_fits(long long workgroups, int threads)
+{
+    return workgroups * threads <= 0xffffffffLL;
+}
+
 int launch_status(const char *what)
 {
     hipError_t e = hipGetLastError();
@@ -443,7 +450,6 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     const int upw = kSearchWaves >> bpw_log2;       // units per workgroup
     const long long unit_groups = (pl.n_units + upw - 1) / upw;
     const long long wgs = (unit_groups + 7) / 8 * 8 * ny;
-    if (wgs > 0x7fffffffLL) return fail(PWLQ_EINVAL, "search grid too large");
     // Too few wavefronts to keep the SIMDs busy: the tiles' elements are cut into slices.  With
     // 16 candidate blocks or more k_search's workgroups are full without slices, and those
     // past 2048 wavefronts gain only on long tiles (n = 4000, 4032 wavefronts, us, one / two
@@ -465,7 +471,31 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
             slices *= 2;
     }
     const long long group_sum_wgs = pl.n_mgroups * (long long)((n_cand + kSumCand - 1) / kSumCand);
-    if (group_sum_wgs > 0x7fffffffLL) return fail(PWLQ_EINVAL, "too many groups longer than one tile");
+    if (!launch_fits(group_sum_wgs, kWG) || !launch_fits(pl.n_mgroups ? pl.n_tiles : 0, kWG))
+        return fail(PWLQ_EINVAL, "too many groups longer than one tile");
+    const int NT = (int)pl.n_tiles;
+    int longest = 0, fast_tiles = 0;
+    // tiles of at most kSmallTile elements (a suffix of the tile order) get one wavefront each
+    int nt_large = 0, longest_small = 0;
+    for (const TensorRec &r : pl.recs) {
+        if (r.fast) fast_tiles += r.ntiles;
+        else longest = std::max(longest, r.tile_len);
+        if (r.tile_len > kSmallTile) nt_large += r.ntiles;
+        else if (!r.fast) longest_small = std::max(longest_small, r.tile_len);
+    }
+    if (NT - nt_large < 1024) nt_large = NT;     // too few short tiles to pay for launches of their own
+    const int nt_small = NT - nt_large;
+    // Single-tile groups only: the short tiles above 512 elements (next in the tile order) join
+    // the two-wavefront launch of k_exact, so that the one-wavefront launch holds 8 elements per
+    // thread instead of 16 and fits six wavefronts per SIMD like the other.
+    int nt_mid = 0;
+    if (pl.n_mgroups == 0 && nt_large > 0 && nt_small > 0)
+        for (const TensorRec &r : pl.recs)
+            if (r.tile_len <= kSmallTile && r.tile_len > 512) nt_mid += r.ntiles;
+    if ((fast_tiles < NT && slices == 1 && !launch_fits(wgs, kSearchWaves * 64)) || !launch_fits(nt_small, 64) ||
+        (longest > kSmallTile && !launch_fits(nt_large, pl.fine && longest > 256 * 16 ? 512 : kWG)) ||
+        !launch_fits(nt_large + nt_mid, 128))
+        return fail(PWLQ_EINVAL, "search grid too large");
 
     hipStream_t stream = (hipStream_t)stream_v;
     char *ws = (char *)workspace;
@@ -482,7 +512,6 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     double *part64 = (double *)(ws + pl.off_part);
     double *gsum = (double *)(ws + pl.off_gsum);
 
-    const int NT = (int)pl.n_tiles;
     // A call too small to fill the chip: everything for a group in one workgroup, one launch.
     {
         int longest_any = 0;
@@ -511,11 +540,6 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     Launched launched;
     launched.what = Launched::kSearch;
     if (pl.n_mgroups > 0) k_tile_absmax<<<NT, kWG, 0, stream>>>(tb, tile_max);
-    int longest = 0, fast_tiles = 0;
-    for (const TensorRec &r : pl.recs) {
-        if (r.fast) fast_tiles += r.ntiles;
-        else longest = std::max(longest, r.tile_len);
-    }
     if (fast_tiles > 0) {
         static_assert(sizeof(unsigned long long) * kFastWords + sizeof(unsigned) * (kTileMax + kFastWalk) <= 63 * 1024,
                       "k_fast must fit the LDS a launch gets without asking for more");
@@ -565,14 +589,6 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
         }
         profile_mark(5, stream);
     }
-    // tiles of at most kSmallTile elements (a suffix of the tile order) get one wavefront each
-    int nt_large = 0, longest_small = 0;
-    for (const TensorRec &r : pl.recs) {
-        if (r.tile_len > kSmallTile) nt_large += r.ntiles;
-        else if (!r.fast) longest_small = std::max(longest_small, r.tile_len);
-    }
-    if (NT - nt_large < 1024) nt_large = NT;     // too few short tiles to pay for launches of their own
-    const int nt_small = NT - nt_large;
     if (fast_tiles < NT) {
         auto stage_bytes = [](int len) { return sizeof(float) * (size_t)((len + kVec - 1) / kVec * kVec); };
         const int nb2 = (pl.nblk + 1) / 2;
@@ -624,13 +640,6 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
         k_group_sum<<<(unsigned)group_sum_wgs, kWG, 0, stream>>>(tb, n_cand, sse32, gsum);
         k_flag<<<(int)pl.n_mgroups, kWG, 0, stream>>>(tb, n_cand, gm, gsum, klist);
     }
-    // Single-tile groups only: the short tiles above 512 elements (next in the tile order) join
-    // the two-wavefront launch, so that the one-wavefront launch holds 8 elements per thread
-    // instead of 16 and fits six wavefronts per SIMD like the other.
-    int nt_mid = 0;
-    if (pl.n_mgroups == 0 && nt_large > 0 && nt_small > 0)
-        for (const TensorRec &r : pl.recs)
-            if (r.tile_len <= kSmallTile && r.tile_len > 512) nt_mid += r.ntiles;
     if (nt_large > 0) {
         // single-tile groups only: workgroups of two wavefronts, twice as many in flight (the
         // stage is bound by latency); with groups spread over tiles, where a tile's threads
@@ -677,6 +686,7 @@ int run_quantize(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode
         rc = check_workspace(pl, workspace, workspace_bytes);
         if (rc) return rc;
     }
+    if (!launch_fits(pl.n_chunks, kWG)) return fail(PWLQ_EINVAL, "call has too many elements");
     hipStream_t stream = (hipStream_t)stream_v;
     Tables tb;
     static_assert(sizeof(Tables) + sizeof(EmitArgs) + 64 <= 4096, "a launch passes at most 4 KB");
@@ -714,6 +724,8 @@ int run_quantize_packed(const pwlq_tensor_desc *desc, int n_tensors, int bits, i
         rc = check_workspace(pl, workspace, workspace_bytes);
         if (rc) return rc;
     }
+    if (!launch_fits(pl.n_chunks, kEmitChunk / (w_hat ? 8 : 16)))
+        return fail(PWLQ_EINVAL, "call has too many elements");
     hipStream_t stream = (hipStream_t)stream_v;
     Tables tb;
     EmitArgs ea;
@@ -764,6 +776,7 @@ int run_select(const pwlq_tensor_desc *desc, int n_tensors, int mode, int select
     if (rc) return rc;
     rc = check_workspace(pl, workspace, workspace_bytes);
     if (rc) return rc;
+    if (!launch_fits((pl.n_tiles + kWaves - 1) / kWaves, kWG)) return fail(PWLQ_EINVAL, "call has too many tiles");
     hipStream_t stream = (hipStream_t)stream_v;
     char *ws = (char *)workspace;
     Tables tb;
@@ -802,6 +815,7 @@ int run_mse(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode, con
     if (rc) return rc;
     rc = check_workspace(pl, workspace, workspace_bytes);
     if (rc) return rc;
+    if (!launch_fits((pl.n_tiles + kWaves - 1) / kWaves, kWG)) return fail(PWLQ_EINVAL, "call has too many tiles");
     hipStream_t stream = (hipStream_t)stream_v;
     char *ws = (char *)workspace;
     Tables tb;
@@ -895,8 +909,6 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     const long long tiles_m = (M + lin_bm(planes) - 1) / lin_bm(planes), tiles_n = (N + kLinBN - 1) / kLinBN;
     const long long tn_per_xcd = (tiles_n + 7) / 8;
     const long long wgs = 8 * tn_per_xcd * tiles_m;
-    if (wgs > 0x7fffffffLL) return fail(PWLQ_EINVAL, "grid too large");
-    hipStream_t stream = (hipStream_t)stream_v;
     float *wconst = (float *)workspace;
     const unsigned wsum_wgs = (unsigned)((N + kLinWG / 64 - 1) / (kLinWG / 64));
     const int row_cap = M <= 15 ? 15 : M <= 31 ? 31 : 63;          // and one row of ones
@@ -913,6 +925,10 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     const bool can_split = planes == 2 && K % (2 * kLinBK) == 0 && K >= kSplitMinK && split_wgs <= kSplitMaxWgs;
     const bool by_rows = linear_by_rows(planes, bits, K, row_cap, row_tiles, row_cols, rows_per_tile, can_split);
     const bool by_split = !by_rows && can_split;
+    if (by_rows ? !launch_fits(row_cols, 64 * kRowWaves)
+                : !launch_fits(wgs, kLinWG) || !launch_fits((N + kLinWG / 64 - 1) / (kLinWG / 64), kLinWG))
+        return fail(PWLQ_EINVAL, "grid too large");
+    hipStream_t stream = (hipStream_t)stream_v;
     g_launched = Launched();
     g_launched.what = by_rows ? Launched::kLinearRows : by_split ? Launched::kLinearSplit : Launched::kLinear;
     g_launched.bits = bits;
