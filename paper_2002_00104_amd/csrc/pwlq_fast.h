@@ -35,10 +35,11 @@
 // four at a time.
 // Elements that are exactly zero (pruned weights) are counted, never walked.
 //
-// Bound by vector issue and LDS together: 57 vector instructions and six LDS accesses per
-// wavefront and look-up (a third of the former for building the tables), the LDS index
-// unit busy 60 % of the time.  38 400 tiles of 4096, 1000 candidates, b = 4: 1498 us with
-// binary64 prefixes of counts, sums and squares and walks of nine elements, 700 us now.
+// Bound by vector issue and LDS together.  Per wavefront and look-up, building the tables
+// included: 52 vector instructions in tiles of 4096, 33 in tiles of 257 to 1024, 26 in
+// shorter ones, and six LDS instructions; the LDS index unit busy 66, 47 and 39 % of the
+// time.  38 400 tiles of 4096, 1000 candidates, b = 4: 1498 us with binary64 prefixes of
+// counts, sums and squares and walks of nine elements, 697 us now.
 #pragma once
 
 #include "pwlq_prep.h"
@@ -48,7 +49,7 @@
 namespace pwlq {
 
 // Most buckets per octave, 2^8.  2^9 halves the walks and costs the fourth workgroup per
-// CU its LDS (38 400 tiles of 4096, search + quantize: 1228 us with 2^9, 1145 with 2^8).
+// CU its LDS (38 400 tiles of 4096, search + quantize, with 24-bit units: 1228 us with 2^9, 1145 with 2^8).
 constexpr int kFastOctBits = 8;
 constexpr int kFastOct = 7;                        // octaves, or twice as many of half as many buckets each
 constexpr int kFastWords = kFastOct << kFastOctBits;   // most buckets per tile
