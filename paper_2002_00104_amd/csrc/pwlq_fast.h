@@ -36,10 +36,10 @@
 // Elements that are exactly zero (pruned weights) are counted, never walked.
 //
 // Bound by vector issue and LDS together.  Per wavefront and look-up, building the tables
-// included: 52 vector instructions in tiles of 4096, 33 in tiles of 257 to 1024, 26 in
-// shorter ones, and six LDS instructions; the LDS index unit busy 66, 47 and 39 % of the
+// included: 51 vector instructions in tiles of 4096, 32 in tiles of 257 to 1024, 25 in
+// shorter ones, and six LDS instructions; the LDS index unit busy 68, 48 and 39 % of the
 // time.  38 400 tiles of 4096, 1000 candidates, b = 4: 1498 us with binary64 prefixes of
-// counts, sums and squares and walks of nine elements, 697 us now.
+// counts, sums and squares and walks of nine elements, 682 us now.
 #pragma once
 
 #include "pwlq_prep.h"
@@ -60,6 +60,8 @@ constexpr unsigned kFastTop = (1u << kFastBits) - 64u - (1u << (kFastBits - kFas
 static_assert(kFastTop / (65535u * 254u) >= 63u, "every grid fits, with 63 units or more to half its finest step");
 constexpr int kFastCrowd = 64;                     // fullest bucket the look-ups may walk: this or 1/16 of the tile,
 constexpr int kFastCrowdMax = 511;                 // ... and never more
+constexpr int kFastCrowdLog = 6, kFastCrowdBits = 9;
+static_assert(kFastCrowd <= 1 << kFastCrowdLog && kFastCrowdMax < 1 << kFastCrowdBits, "as powers of two");
 constexpr int kFastWalk = 3;                       // elements read unasked (4: 0.5-2 % slower, 6: 3-7 %)
 constexpr int kFastWalkOn = 4;                     // ... and then per step
 constexpr int kFastShort = 256;                    // longest tile of a launch of 128 threads
@@ -251,7 +253,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     constexpr int kW = kT / 64;
     constexpr int kScan = ((kFastOct << fast_octave_bits(kT * kPer)) + kT - 1) / kT;   // words a thread holds at most
     __shared__ float redm[kW], redsum[kW];
-    __shared__ int redbad[kW], redzero[kW], wfull[kW];
+    __shared__ int redbad[kW], redzero[kW], wfull[kW];      // wfull: a bucket fuller than 16, than kFastCrowd, crowded
     __shared__ unsigned long long wsum[kW];
     __shared__ double redA[kW];
 
@@ -309,6 +311,10 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     // there for the filter's slack.  Every element counts as m then, which gives all
     // candidates the value 0 and keeps them.
     const bool keep_all = usable && !((float)n / m < __builtin_inff());
+    if (!usable || keep_all) {
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) a[e] = (usable && a[e] > 0.0f) ? m : 0.0f;
+    }
 
     // Values run from `low` to top + low, whose exponents are 30 - octaves and 29.  Seven
     // octaves, and 14 of half as many buckets where the mean lies in the lowest: near zero
@@ -328,15 +334,18 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     unsigned short rank[kPer];
     int zeros = 0;
     double A = 0.0;
+    // 2^52 + a scale, rounded once, holds the whole number in its low word: at most top, since
+    // a <= m and scale is within 2^-53 of top / m
+    const double one52 = 4503599627370496.0;
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
         const int i = tid + e * kT;
         unsigned u = 0;
         if (i < len) {
-            // at most top: a <= m, and the product is within 2^-22 of the exact one
-            if (usable) u = keep_all ? (a[e] > 0.0f ? top : 0u) : (unsigned)__builtin_rint((double)a[e] * scale);
-            const double d = (double)(top - u);
-            A += d * d;
+            const double whole = __builtin_fma((double)a[e], scale, one52);
+            u = (unsigned)__double2loint(whole);
+            const double d = one52 + (double)top - whole;             // exact
+            A = __builtin_fma(d, d, A);
             zeros += u == 0;
         }
         v[e] = u + low;
@@ -356,6 +365,8 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     for (int i = 0; i < kW; ++i) { zeros += redzero[i]; A += redA[i]; }
     A *= 1.0 / (unit * unit);
 
+    int crowd = (len >> 4) > kFastCrowd ? len >> 4 : kFastCrowd;
+    crowd = crowd < kFastCrowdMax ? crowd : kFastCrowdMax;
     // exclusive prefix of counts and sums, both fields in one word
     const int per = (T + kT - 1) / kT;
     const int lo = tid * per < T ? tid * per : T;
@@ -371,8 +382,10 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
             fullest = c > fullest ? c : fullest;
         }
         const unsigned long long incl = wave_scan_incl_u64(tot);
-        const int full = (int)wave_max((float)fullest);
-        if (lane == 63) { wsum[wave] = incl; wfull[wave] = full; }
+        const int over = (__ballot(fullest > 16u) != 0ull ? 1 : 0) |
+                         (__ballot(fullest > (unsigned)kFastCrowd) != 0ull ? 2 : 0) |
+                         (__ballot(fullest > (unsigned)crowd) != 0ull ? 4 : 0);
+        if (lane == 63) { wsum[wave] = incl; wfull[wave] = over; }
         __syncthreads();
         // the zero elements come before everything
         unsigned long long run = incl - tot + ((unsigned long long)zeros << kFastSumBits) +
@@ -400,18 +413,15 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     }
     // what a walk reads past the last element adds nothing
     if (tid < kFastWalk) elems[len - zeros + tid] = ~0u;
-    int full = 1;
-    for (int i = 0; i < kW; ++i) full = wfull[i] > full ? wfull[i] : full;
+    int full = 0;
+    for (int i = 0; i < kW; ++i) full |= wfull[i];
     full = uni(full);
-    int crowd = (len >> 4) > kFastCrowd ? len >> 4 : kFastCrowd;
-    crowd = crowd < kFastCrowdMax ? crowd : kFastCrowdMax;
-    const bool crowded = full > crowd;
-    // look-ups whose parts inside buckets fit 32 bits together: one at least (see
+    // look-ups whose parts inside buckets fit 32 bits together: one or two at least (see
     // fast_octave_bits), eight or more as a rule
-    const int run = (int)(0xffffffffu >> (kFastBits - 1 - obits)) / full;
+    const int run = (int)(0xffffffffu >> (kFastBits - 1 - obits)) >> (full & 2 ? kFastCrowdBits : full & 1 ? kFastCrowdLog : 4);
     __syncthreads();
     float *row = sse32 + (long long)t * n;
-    if (crowded) {
+    if (full & 4) {
         const double per_unit = 1.0 / unit;
         for (int i = tid; i < len - zeros; i += kT)
             elems[i] = __float_as_uint((float)((double)(elems[i] - low) * per_unit));
