@@ -373,15 +373,17 @@ bool fill_stat_args(const Plan &pl, StatArgs &sa)
     return true;
 }
 
-// Groups whose tiles are too many for one thread: in a plan for selectors or error the first.
+// How many groups of a plan for the selectors get a wavefront each: those whose tiles are too
+// many for one thread, which come first, and a few others with them.
 int wide_groups(const Plan &pl)
 {
-    int groups = 0;
+    const int groups = (int)pl.n_groups;
+    int wide = 0;
     for (const TensorRec &r : pl.recs) {
         if (r.tpg < kWideTiles) break;
-        groups += r.ngroups;
+        wide += r.ngroups;
     }
-    return groups;
+    return wide > 0 && groups - wide <= kWideRest ? groups : wide;
 }
 
 // Whether a launch holds so many workgroups of so many threads: from 2^32 threads on the
@@ -776,7 +778,8 @@ int run_select(const pwlq_tensor_desc *desc, int n_tensors, int mode, int select
     if (rc) return rc;
     rc = check_workspace(pl, workspace, workspace_bytes);
     if (rc) return rc;
-    if (!launch_fits((pl.n_tiles + kWaves - 1) / kWaves, kWG)) return fail(PWLQ_EINVAL, "call has too many tiles");
+    if (!launch_fits((pl.n_tiles + kWaves - 1) / kWaves, kWG) || !launch_fits(pl.n_mgroups, kSelectWG))
+        return fail(PWLQ_EINVAL, "call has too many tiles");
     hipStream_t stream = (hipStream_t)stream_v;
     char *ws = (char *)workspace;
     Tables tb;
@@ -793,7 +796,7 @@ int run_select(const pwlq_tensor_desc *desc, int n_tensors, int mode, int select
     double *tile_s2 = (double *)(ws + pl.off_stat_s2);
     double *tile_s1 = (double *)(ws + pl.off_stat_s1);
     const unsigned tile_wgs = (unsigned)((pl.n_tiles + kWaves - 1) / kWaves);
-    const int wide = wide_groups(pl), groups = (int)pl.n_groups;
+    const int groups = (int)pl.n_groups, wide = wide_groups(pl);
     k_stats<<<tile_wgs, kWG, 0, stream>>>(tb, sa, (int)pl.n_tiles, tile_max, tile_s2, tile_s1);
     if (wide > 0)
         k_select<true><<<(unsigned)wide, kSelectWG, 0, stream>>>(tb, sa, 0, wide, selector, tile_max, tile_s2, tile_s1,
@@ -815,7 +818,8 @@ int run_mse(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode, con
     if (rc) return rc;
     rc = check_workspace(pl, workspace, workspace_bytes);
     if (rc) return rc;
-    if (!launch_fits((pl.n_tiles + kWaves - 1) / kWaves, kWG)) return fail(PWLQ_EINVAL, "call has too many tiles");
+    if (!launch_fits((pl.n_tiles + kWaves - 1) / kWaves, kWG) || !launch_fits(pl.n_mgroups, kSelectWG))
+        return fail(PWLQ_EINVAL, "call has too many tiles");
     hipStream_t stream = (hipStream_t)stream_v;
     char *ws = (char *)workspace;
     Tables tb;
@@ -829,12 +833,15 @@ int run_mse(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode, con
     }
     double *tile_sse = (double *)(ws + pl.off_stat_s2);
     const unsigned tile_wgs = (unsigned)((pl.n_tiles + kWaves - 1) / kWaves);
-    const int wide = wide_groups(pl), groups = (int)pl.n_mgroups;       // of several tiles: the first ones
+    // groups of several tiles, which come first, a wavefront each where the first is a wide one:
+    // there is nothing to solve, so the others lose nothing by it
+    const int groups = (int)pl.n_mgroups;
     k_mse_tile<<<tile_wgs, kWG, 0, stream>>>(tb, sa, (int)pl.n_tiles, bits, p, m, tile_sse, mse);
-    if (wide > 0) k_mse_final<true><<<(unsigned)wide, kSelectWG, 0, stream>>>(tb, sa, 0, wide, tile_sse, mse);
-    if (wide < groups)
-        k_mse_final<false><<<(unsigned)((groups - wide + kSelectWG - 1) / kSelectWG), kSelectWG, 0, stream>>>(
-            tb, sa, wide, groups, tile_sse, mse);
+    if (groups > 0 && pl.recs[0].tpg >= kWideTiles)
+        k_mse_final<true><<<(unsigned)groups, kSelectWG, 0, stream>>>(tb, sa, groups, tile_sse, mse);
+    else if (groups > 0)
+        k_mse_final<false><<<(unsigned)((groups + kSelectWG - 1) / kSelectWG), kSelectWG, 0, stream>>>(
+            tb, sa, groups, tile_sse, mse);
     return launch_status("mse launch");
 }
 

@@ -232,6 +232,9 @@ constexpr int kSelectWG = 64;     // one wavefront per workgroup: a few ten thou
 // tiles 15.1/13.9, 20.8/19.5, 102/104, 362/370; of 8 14.3/13.7, 14.7/15.0, 47/51, 185/196; of
 // 32 16.9/14.0, 25.9/22.2, 189/188.
 constexpr int kWideTiles = 16;
+// Up to this many groups beside the wide ones join their launch, a wavefront each: 1024 of
+// them cost about 4 us more in it, a launch of their own 5 to 6.
+constexpr int kWideRest = 1024;
 
 template <bool kWide>
 __global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, StatArgs sa, int begin, int end, int selector,
@@ -249,18 +252,21 @@ __global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, StatArgs sa, in
     float mf = 0.0f;
     int bad = 0;
     double s2 = 0.0, s1 = 0.0;
-    for (int j = kWide ? threadIdx.x : 0; j < r.tpg; j += kWide ? kSelectWG : 1) {
+    const bool spread = kWide && r.tpg >= kWideTiles;      // else the lanes repeat the sums in tile order
+    for (int j = spread ? threadIdx.x : 0; j < r.tpg; j += spread ? kSelectWG : 1) {
         const float v = tile_max[tile0 + j];
         bad |= (v != v);
         mf = fmaxf(mf, v);
         s2 += tile_s2[tile0 + j];
         s1 += tile_s1[tile0 + j];
     }
-    if (kWide) {
+    if (spread) {
         mf = wave_max(mf);
         bad = wave_or(bad);
         s2 = wave_sum(s2);
         s1 = wave_sum(s1);
+    }
+    if (kWide) {
         if (threadIdx.x > 0) return;
     } else if (first + (int)threadIdx.x >= end) {
         return;
@@ -317,22 +323,23 @@ __global__ __launch_bounds__(kWG) void k_mse_tile(Tables tb, StatArgs sa, int n_
     }
 }
 
-// Groups of several tiles, which come first: tiles added as in k_select, ranges as there.
-// (Those of one tile are done.)
+// Groups of several tiles, which come first: tiles added as in k_select.  (Those of one tile
+// are done.)
 template <bool kWide>
-__global__ __launch_bounds__(kSelectWG) void k_mse_final(Tables tb, StatArgs sa, int begin, int end,
+__global__ __launch_bounds__(kSelectWG) void k_mse_final(Tables tb, StatArgs sa, int end,
                                                    const double *__restrict__ tile_sse,
                                                    double *__restrict__ mse)
 {
-    const int first = begin + (kWide ? blockIdx.x : blockIdx.x * kSelectWG);
+    const int first = kWide ? blockIdx.x : blockIdx.x * kSelectWG;
     const int g = kWide ? first : (first + (int)threadIdx.x < end ? first + (int)threadIdx.x : end - 1);
     const StatRec r = stat_group(tb, sa, first, g);
     const int gl = g - r.group_base;
     const long long tile0 = r.tile_base + (long long)gl * r.tpg;
     double s = 0.0;
-    for (int j = kWide ? threadIdx.x : 0; j < r.tpg; j += kWide ? kSelectWG : 1) s += tile_sse[tile0 + j];
+    const bool spread = kWide && r.tpg >= kWideTiles;
+    for (int j = spread ? threadIdx.x : 0; j < r.tpg; j += spread ? kSelectWG : 1) s += tile_sse[tile0 + j];
+    if (spread) s = wave_sum(s);
     if (kWide) {
-        s = wave_sum(s);
         if (threadIdx.x > 0) return;
     } else if (first + (int)threadIdx.x >= end) {
         return;

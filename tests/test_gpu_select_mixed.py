@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("shapes", [
     [(70, 8192), (2, 140000), (5, 64), (3, 30000), (130, 33), (1, 131072), (1, 131073), (2, 8193)],
     [(3, 17), (2, 150000), (64, 40), (1, 122880), (65, 41)],
+    [(2, 150000), (1020, 33), (3, 25000), (1, 8192)], [(2, 150000), (1020, 33), (3, 25000), (2, 8192)],
     [(1 + i % 3, 20 + i) for i in range(200)], [(1, 40)] * 130 + [(129, 50)] + [(1, 41)] * 70])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_lists(P, shapes, mode):  # noqa: F811
