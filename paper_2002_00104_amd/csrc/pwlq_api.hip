@@ -869,8 +869,9 @@ int run_mse(const pwlq_tensor_desc *desc, int n_tensors, int bits, int mode, con
 //    126x11008 22.1/25.4, K = 4096 57.3/57.5; K = 64: 1.07 of it), and at up to 5 bits on
 //    reductions from 1024 (189 to 378 rows, 640 to 768 workgroups: 0.85-1.04 of it; 896:
 //    441x4096 29.0/23.9).
-//  - Else, against k_linear, up to 900 workgroups, 740 on long reductions (K = 4096, 378x4096
-//    0.96 of it at b = 4, 0.99 at 7; b = 8 1.08-1.3 past 512).
+//  - Else, against k_linear, up to 900 workgroups, 740 on long reductions from 3 bits on (K =
+//    4112, 378x4096, 378x4800, us, b = 2 50.8/55.7, 55.8/57.5, b = 3 57.4/60.4, 65.4/62.8; K =
+//    4096, 378x4096 0.96 of it at b = 4, 0.99 at 7; b = 8 1.08-1.3 past 512).
 bool linear_by_rows(int planes, int bits, long long K, int row_cap, long long row_tiles, long long row_cols,
                     int rows_per_tile, bool can_split)
 {
@@ -886,7 +887,7 @@ bool linear_by_rows(int planes, int bits, long long K, int row_cap, long long ro
     if (can_split) return two && K <= 1024 && short_tiles;
     if (planes == 3)
         return (two && K >= 256 && (!wide || (short_tiles && K <= 4096))) || (bits <= 5 && K >= 1024 && wgs <= 770);
-    return wgs <= (K <= 2048 ? 900 : bits == 8 ? 512 : 740);
+    return wgs <= (K <= 2048 || bits == 2 ? 900 : bits == 8 ? 512 : 740);
 }
 
 int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,

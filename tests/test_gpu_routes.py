@@ -82,6 +82,8 @@ def test_fast_search_of_few_tiles(P, shape, bits, n, want):
     (378, 512, 4096, 4, False, "k_linear_rows<4, 2, 32, 2>"), (378, 512, 4128, 4, False, "k_linear_split<4>"), (126, 1024, 11232, 4, False, "k_linear_split<4>"),
     # without it: 900, on long reductions 740, at 8 bits 512
     (378, 4112, 3936, 4, False, "k_linear_rows<4, 2, 32, 2>"), (378, 4112, 3968, 4, False, "k_linear<4, 2>"),
+    (378, 4112, 4800, 2, False, "k_linear_rows<2, 2, 32, 2>"), (378, 4112, 4832, 2, False, "k_linear<2, 2>"),
+    (378, 4112, 4800, 3, False, "k_linear<3, 2>"),
     (378, 4112, 2720, 8, False, "k_linear_rows<8, 2, 32, 2>"), (378, 4112, 2752, 8, False, "k_linear<8, 2>"),
     (378, 528, 4800, 8, False, "k_linear_rows<8, 2, 32, 2>"), (378, 528, 4832, 8, False, "k_linear<8, 2>"),
     # the sums apart
