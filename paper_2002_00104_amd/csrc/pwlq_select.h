@@ -74,14 +74,13 @@ __device__ inline StatTile stat_tile(const Tables &tb, const StatArgs &sa, int s
     st.whole = r.tpg == 1;
     return st;
 }
-// Tensor of group g, where groups first_g (the wavefront's first; the same in every
-// lane) to first_g + 63 ask together: as a rule one tensor's, else one of the 64 from
-// first_g's on.  (A walk from there took up to 63 dependent loads where tensors are single
+// Tensor of group g, where groups first_g to last_g (the same in every lane, 64 at most) ask
+// together: as a rule one tensor's, else one of the 64 from first_g's on.  (A walk from there took up to 63 dependent loads where tensors are single
 // groups.)
-__device__ inline int find_group(const int *__restrict__ prefix, int nt, int first_g, int g)
+__device__ inline int find_group(const int *__restrict__ prefix, int nt, int first_g, int last_g, int g)
 {
     int lo = find_tensor(prefix, nt, first_g);
-    if (prefix[lo + 1] > first_g + 63) return lo;
+    if (prefix[lo + 1] > last_g) return lo;
     int hi = nt - lo > 64 ? lo + 64 : nt;              // prefix[lo] <= g < prefix[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -90,10 +89,10 @@ __device__ inline int find_group(const int *__restrict__ prefix, int nt, int fir
     }
     return lo;
 }
-__device__ inline StatRec stat_group(const Tables &tb, const StatArgs &sa, int first_g, int g)
+__device__ inline StatRec stat_group(const Tables &tb, const StatArgs &sa, int first_g, int last_g, int g)
 {
-    const int i = sa.nt > 0 ? find_group(sa.group_prefix, sa.nt, first_g, g)
-                            : find_group(tb.group_prefix, tb.nt, first_g, g);
+    const int i = sa.nt > 0 ? find_group(sa.group_prefix, sa.nt, first_g, last_g, g)
+                            : find_group(tb.group_prefix, tb.nt, first_g, last_g, g);
     return stat_rec(tb, sa, i);
 }
 
@@ -236,6 +235,18 @@ constexpr int kWideTiles = 16;
 // them cost about 4 us more in it, a launch of their own 5 to 6.
 constexpr int kWideRest = 1024;
 
+// Sum over the tiles of a wavefront's group, of which lane j holds tile j, j + 64, ...: few
+// tiles in tile order, as one thread adds them.
+__device__ inline double wide_sum(double v, int tiles)
+{
+    if (tiles >= kWideTiles) return wave_sum(v);
+    double s = 0.0;
+    for (int j = 0; j < tiles; ++j)
+        s += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), j),
+                              __builtin_amdgcn_readlane(__double2loint(v), j));
+    return s;
+}
+
 template <bool kWide>
 __global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, StatArgs sa, int begin, int end, int selector,
                                                 const float *__restrict__ tile_max,
@@ -246,25 +257,24 @@ __global__ __launch_bounds__(kSelectWG) void k_select(Tables tb, StatArgs sa, in
 {
     const int first = begin + (kWide ? blockIdx.x : blockIdx.x * kSelectWG);
     const int g = kWide ? first : (first + (int)threadIdx.x < end ? first + (int)threadIdx.x : end - 1);
-    const StatRec r = stat_group(tb, sa, first, g);
+    const StatRec r = stat_group(tb, sa, first, kWide ? first : first + kSelectWG - 1 < end ? first + kSelectWG - 1 : end - 1, g);
     const int gl = g - r.group_base;
     const long long tile0 = r.tile_base + (long long)gl * r.tpg;
     float mf = 0.0f;
     int bad = 0;
     double s2 = 0.0, s1 = 0.0;
-    const bool spread = kWide && r.tpg >= kWideTiles;      // else the lanes repeat the sums in tile order
-    for (int j = spread ? threadIdx.x : 0; j < r.tpg; j += spread ? kSelectWG : 1) {
+    for (int j = kWide ? threadIdx.x : 0; j < r.tpg; j += kWide ? kSelectWG : 1) {
         const float v = tile_max[tile0 + j];
         bad |= (v != v);
         mf = fmaxf(mf, v);
         s2 += tile_s2[tile0 + j];
         s1 += tile_s1[tile0 + j];
     }
-    if (spread) {
+    if (kWide) {
         mf = wave_max(mf);
         bad = wave_or(bad);
-        s2 = wave_sum(s2);
-        s1 = wave_sum(s1);
+        s2 = wide_sum(s2, r.tpg);
+        s1 = wide_sum(s1, r.tpg);
     }
     if (kWide) {
         if (threadIdx.x > 0) return;
@@ -332,14 +342,13 @@ __global__ __launch_bounds__(kSelectWG) void k_mse_final(Tables tb, StatArgs sa,
 {
     const int first = kWide ? blockIdx.x : blockIdx.x * kSelectWG;
     const int g = kWide ? first : (first + (int)threadIdx.x < end ? first + (int)threadIdx.x : end - 1);
-    const StatRec r = stat_group(tb, sa, first, g);
+    const StatRec r = stat_group(tb, sa, first, kWide ? first : first + kSelectWG - 1 < end ? first + kSelectWG - 1 : end - 1, g);
     const int gl = g - r.group_base;
     const long long tile0 = r.tile_base + (long long)gl * r.tpg;
     double s = 0.0;
-    const bool spread = kWide && r.tpg >= kWideTiles;
-    for (int j = spread ? threadIdx.x : 0; j < r.tpg; j += spread ? kSelectWG : 1) s += tile_sse[tile0 + j];
-    if (spread) s = wave_sum(s);
+    for (int j = kWide ? threadIdx.x : 0; j < r.tpg; j += kWide ? kSelectWG : 1) s += tile_sse[tile0 + j];
     if (kWide) {
+        s = wide_sum(s, r.tpg);
         if (threadIdx.x > 0) return;
     } else if (first + (int)threadIdx.x >= end) {
         return;
