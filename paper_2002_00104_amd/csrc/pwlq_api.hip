@@ -125,6 +125,50 @@ int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
     return look_ups_ns <= passes_ns ? shortest : always;
 }
 
+// Whether the tiles of a launch that are groups of their own look up a grid of candidates first and
+// then only those that it does not exclude (see fast_pruned): where a thread would have 11 or
+// more pairs of look-ups for all candidates, or 20 where the workgroups are fewer than the CUs, and each
+// waits out the three steps alone (us, all / pruned: 512 threads, 4096x4608, b = 4, n = 1000
+// 119/108, n = 400 88/93; 256 threads, 4096x1024, n = 700 55/46, n = 300 41/41; 128 threads,
+// 20000x128, n = 1000 191/101, n = 4000 740/170, n = 256 89/86; 1024 threads, 700x8192, n = 1000
+// 60/61, n = 4000 188/168; 64x600, n = 1000 15.5/16.1, n = 4000 31/20).  At b = 8 the grid
+// excludes a third of 1000 candidates, which often leaves a thread as many rounds
+// (64x5000, n = 1000 93/102, n = 2000 164/142).
+bool fast_prunes(int threads, int tiles, int n, int L)
+{
+    return n >= kPruneMin && (long long)n * L >= (tiles < 256 ? 20 : 11) * threads && (L < 127 || n >= 1500);
+}
+
+struct FastLaunch {
+    int begin, end, threads, longest;
+    bool prunes;
+};
+
+// The launches of k_fast.  A launch's workgroups and LDS are sized for its longest tile; shorter
+// tiles get launches of their own where both sides have enough of them.  Tensors are ordered
+// longest tile first, so the fast tiles are 0 .. fast_tiles-1.
+int plan_fast_launches(Plan &pl, int fast_tiles, int n, int L, FastLaunch (&out)[4])
+{
+    auto size_class = [](int len) { return len > kFastLong ? 0 : len > kSmallTile ? 1 : len > kFastShort ? 2 : 3; };
+    int launches = 0, begin = 0, seen = 0, longest = 0;
+    size_t first = 0;
+    for (size_t i = 0; i < pl.recs.size() && pl.recs[i].fast; ++i) {
+        longest = std::max(longest, pl.recs[i].tile_len);
+        seen += pl.recs[i].ntiles;
+        const bool last = seen == fast_tiles;
+        if (!last && (size_class(pl.recs[i + 1].tile_len) == size_class(longest) ||
+                      seen - begin < kFastLaunchTiles || fast_tiles - seen < kFastLaunchTiles))
+            continue;
+        const int threads = fast_threads(longest, seen - begin, n, L);
+        const bool prunes = fast_prunes(threads, seen - begin, n, L);
+        out[launches++] = {begin, seen, threads, longest, prunes};
+        for (; first <= i; ++first) pl.recs[first].fast = prunes && pl.recs[first].tpg == 1 ? 2 : 1;
+        begin = seen;
+        longest = 0;
+    }
+    return launches;
+}
+
 // n_cand == 0 builds a plan without search scratch (quantizer, selectors, error).
 // fast_bits > 0: the bit width of a fast search.
 int build_plan(Plan &pl, const pwlq_tensor_desc *desc, int n_tensors, int n_cand, int mode,
@@ -499,6 +543,8 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
         !launch_fits(nt_large + nt_mid, 128))
         return fail(PWLQ_EINVAL, "search grid too large");
 
+    FastLaunch fast_launches[4];
+    const int n_fast_launches = plan_fast_launches(pl, fast_tiles, n_cand, (1 << (bits - 1)) - 1, fast_launches);
     hipStream_t stream = (hipStream_t)stream_v;
     char *ws = (char *)workspace;
     Tables tb;
@@ -543,36 +589,24 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     launched.what = Launched::kSearch;
     if (pl.n_mgroups > 0) k_tile_absmax<<<NT, kWG, 0, stream>>>(tb, tile_max);
     if (fast_tiles > 0) {
-        static_assert(sizeof(unsigned long long) * kFastWords + sizeof(unsigned) * (kTileMax + kFastWalk) <= 63 * 1024,
+        static_assert(sizeof(unsigned long long) * kFastWords + sizeof(unsigned) * (kTileMax + kFastWalk) +
+                          4 * (kPruneGrid + 1) + 2 * kPruneList <= 63 * 1024,
                       "k_fast must fit the LDS a launch gets without asking for more");
-        // tensors are ordered longest tile first, so the fast tiles are 0 .. fast_tiles-1
-        auto lds_bytes = [](int len) {
-            return sizeof(unsigned long long) * ((size_t)kFastOct << fast_octave_bits(len)) +
-                   sizeof(unsigned) * (size_t)(len + kFastWalk);
+        auto lds_bytes = [&](const FastLaunch &fl) {
+            return sizeof(unsigned long long) * ((size_t)kFastOct << fast_octave_bits(fl.longest)) +
+                   sizeof(unsigned) * (size_t)(fl.longest + kFastWalk) + (size_t)(fl.prunes ? prune_bytes(n_cand) : 0);
         };
         // magnitudes in units of 1 / (2 L q) of a candidate
         const int q = (int)kFastTop / (n_cand * 2 * ((1 << (bits - 1)) - 1));
-        // A launch's workgroups and LDS are sized for its longest tile; shorter tiles get
-        // launches of their own where both sides have enough of them.
-        auto size_class = [](int len) { return len > kFastLong ? 0 : len > kSmallTile ? 1 : len > kFastShort ? 2 : 3; };
         profile_mark(4, stream);
-        int begin = 0, seen = 0, part_longest = 0;
-        for (size_t i = 0; i < pl.recs.size() && pl.recs[i].fast; ++i) {
-            const TensorRec &r = pl.recs[i];
-            part_longest = std::max(part_longest, r.tile_len);
-            seen += r.ntiles;
-            const bool last = seen == fast_tiles;
-            if (!last && (size_class(pl.recs[i + 1].tile_len) == size_class(part_longest) ||
-                          seen - begin < kFastLaunchTiles || fast_tiles - seen < kFastLaunchTiles))
-                continue;
-            const int count = seen - begin;
-            const size_t lds = lds_bytes(part_longest);
-            const int threads = fast_threads(part_longest, count, n_cand, (1 << (bits - 1)) - 1);
-            launched.fast_threads[launched.n_fast++] = threads;
+        for (int i = 0; i < n_fast_launches; ++i) {
+            const FastLaunch &fl = fast_launches[i];
+            const size_t lds = lds_bytes(fl);
+            launched.fast_threads[launched.n_fast++] = fl.threads;
             // a launch has less than 2^32 threads
-            for (int at = begin; at < seen; at += kFastGridMax) {
-                const unsigned wgs = (unsigned)std::min(seen - at, kFastGridMax);
-                switch (threads) {
+            for (int at = fl.begin; at < fl.end; at += kFastGridMax) {
+                const unsigned wgs = (unsigned)std::min(fl.end - at, kFastGridMax);
+                switch (fl.threads) {
                     case 1024:
                         k_fast<1024, kTileMax / 1024><<<wgs, 1024, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
                         break;
@@ -586,8 +620,6 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                         k_fast<256, kSmallTile / 256><<<wgs, 256, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
                 }
             }
-            begin = seen;
-            part_longest = 0;
         }
         profile_mark(5, stream);
     }

@@ -47,7 +47,7 @@ struct TensorRec {
     int tile_base, group_base, unit_base, mgroup_base;
     int emit_base;         // first chunk of this tensor in the quantize kernel's grid
     int ntiles, ngroups;
-    int fast;              // tiles evaluated by the prefix-sum kernel instead of prep + search
+    int fast;              // 1: tiles evaluated by the prefix-sum kernel instead of prep + search; 2: not all candidates
 };
 
 struct TileInfo {

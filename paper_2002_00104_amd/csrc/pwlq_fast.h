@@ -175,37 +175,216 @@ __device__ inline void fast_query2(const FastLds &L, unsigned b0, unsigned b1, u
     s1.m += __umul24(odd, w1.before);
 }
 
-// Filter value of every candidate of the tile.  `low` is the offset of the stored
-// values, A = sum (n - u)^2.
-// The parts inside a bucket, summed in 32 bits over `run` look-ups: those of its own
-// elements are below its width, those past it are zero.
-template <int kT>
-__device__ inline void fast_candidates(const FastLds &Q, int n, int Li, int q, unsigned low, double A,
-                                       int run, float *__restrict__ row)
+// What a candidate's value needs beside the tables: A = sum (n - u)^2, inv = 2 / (L 2Lq), the
+// offset `low` of the stored values, and the look-ups whose parts inside buckets fit 32
+// bits together (those of its own elements are below the bucket's width, those past it zero).
+struct FastCurve {
+    double A, inv;
+    unsigned low;
+    int n, Li, q, run;
+};
+
+// Sum over groups of 2^g lanes, in every lane of the group.
+__device__ inline double group_sum(double v, int g)
 {
-    const double inv = 1.0 / ((double)Li * (double)Li * (double)q);            // 2 / (L * 2L q)
-    for (int k = threadIdx.x + 1; k <= n; k += kT) {
-        const unsigned kk = (unsigned)(k * q), ww = (unsigned)((n - k) * q);   // half steps of the two pieces
-        const unsigned zt = 2u * (unsigned)Li * kk + low;
-        FastSums fc = {0, 0, 0, 0}, ft = {0, 0, 0, 0};
-        unsigned bc = kk + low, bt = zt + ww;
-        for (int i = 0; i < Li;) {
-            const int stop = i + run < Li ? i + run : Li;
-            fc.d = ft.d = 0;
-            for (; i < stop; ++i) {
-                fast_query2(Q, bc, bt, 2 * i + 1, fc, ft);
-                bc += 2 * kk;
-                bt += 2 * ww;
-            }
-            fc.c -= fc.d;
-            ft.c -= ft.d;
+    if (g > 0) v += dpp_f64<0xb1, 0xf>(0.0, v);         // lane ^ 1
+    if (g > 1) v += dpp_f64<0x4e, 0xf>(0.0, v);         // lane ^ 2
+    if (g > 2) v += dpp_f64<0x141, 0xf>(0.0, v);        // the other four of eight
+    if (g > 3) v += dpp_f64<0x140, 0xf>(0.0, v);        // the other eight of sixteen
+    if (g > 4) v += __shfl_xor(v, 16, 64);
+    if (g > 5) v += __shfl_xor(v, 32, 64);
+    return v;
+}
+
+// Filter value of candidate k: by one lane, or (kGroups) by a group of 2^g lanes whose
+// lane `sub` takes the half-way points sub, sub + 2^g, ... of both pieces; the loops are the
+// same in every lane.  All lanes of the wavefront come here together.
+template <bool kGroups>
+__device__ inline float fast_value(const FastLds &Q, const FastCurve &c, int k, int sub, int g)
+{
+    if (!kGroups) sub = g = 0;
+    const unsigned kk = (unsigned)(k * c.q), ww = (unsigned)((c.n - k) * c.q);   // half steps of the two pieces
+    const unsigned zt = 2u * (unsigned)c.Li * kk + c.low;
+    const unsigned odd0 = 2u * (unsigned)sub + 1u, dc = (2u * kk) << g, dt = (2u * ww) << g;
+    FastSums fc = {0, 0, 0, 0}, ft = {0, 0, 0, 0};
+    unsigned bc = odd0 * kk + c.low, bt = odd0 * ww + zt;
+    const int whole = c.Li >> g;
+    for (int i = 0; i < whole;) {
+        const int stop = i + c.run < whole ? i + c.run : whole;
+        fc.d = ft.d = 0;
+        for (; i < stop; ++i) {
+            fast_query2(Q, bc, bt, (unsigned)(2 * i << g) + odd0, fc, ft);
+            bc += dc;
+            bt += dt;
         }
-        // whole numbers below 2^52, so exact in binary64
-        const double hc = (double)kk * (double)fc.m + (double)low * (double)fc.n - (double)(long long)fc.c;
-        const double ht = (double)ww * (double)ft.m + (double)zt * (double)ft.n - (double)(long long)ft.c;
-        const double sse = A - inv * ((double)k * hc + (double)(n - k) * ht);
-        row[k - 1] = (float)(sse > 0.0 ? sse : 0.0);
+        fc.c -= fc.d;
+        ft.c -= ft.d;
     }
+    // L + 1 is a power of two: one half-way point is left to every lane but the last
+    if (kGroups && sub < (c.Li & ((1 << g) - 1))) {
+        fc.d = ft.d = 0;
+        fast_query2(Q, bc, bt, (unsigned)(2 * whole << g) + odd0, fc, ft);
+        fc.c -= fc.d;
+        ft.c -= ft.d;
+    }
+    // whole numbers below 2^52, so exact in binary64, and so are the group's sums
+    double hc = (double)kk * (double)fc.m + (double)c.low * (double)fc.n - (double)(long long)fc.c;
+    double ht = (double)ww * (double)ft.m + (double)zt * (double)ft.n - (double)(long long)ft.c;
+    if (kGroups) { hc = group_sum(hc, g); ht = group_sum(ht, g); }
+    const double sse = c.A - c.inv * ((double)k * hc + (double)(c.n - k) * ht);
+    return (float)(sse > 0.0 ? sse : 0.0);
+}
+
+// put(lead, k, value) for the candidates k_of(0 .. count-1), `lead` in one lane of each
+// one's group.  Where there are threads for it a candidate gets several lanes, four half-way points
+// of a piece each at least: what comes after the look-ups costs as much as three of them.
+template <int kT, typename KOf, typename Put>
+__device__ inline void fast_each(const FastLds &Q, const FastCurve &c, int count, KOf k_of, Put put)
+{
+    int g = 0;
+    while ((8 << g) <= c.Li + 1 && (count << (g + 1)) <= kT) ++g;
+    const int lane = threadIdx.x & 63, sub = lane & ((1 << g) - 1);
+    for (int at = uni((int)threadIdx.x & ~63); at < count << g; at += kT) {
+        const int item = (at + lane) >> g;
+        const bool live = item < count;
+        const int k = k_of(live ? item : count - 1);
+        const float v = g > 0 ? fast_value<true>(Q, c, k, sub, g) : fast_value<false>(Q, c, k, 0, 0);
+        put(live && sub == 0, k, v);
+    }
+}
+
+// Filter value of every candidate of the tile.
+template <int kT>
+__device__ inline void fast_candidates(const FastLds &Q, const FastCurve &c, float *__restrict__ row)
+{
+    fast_each<kT>(Q, c, c.n, [](int i) { return i + 1; },
+                  [&](bool lead, int k, float v) { if (lead) row[k - 1] = v; });
+}
+
+// ---------------------------------------------------------------- fewer candidates
+// A tile that is a group of its own needs the candidates within the slack of the minimum
+// only, and most candidates can be shown to be past it.  Eq.3 takes an element to the nearest
+// of the 2L+1 levels of both pieces (p is a level of both), and a level moves by at
+// most c_j candidate units when the breakpoint moves by one: c_j = j/L in the centre,
+// 1 - j/L in the tail.  With f = sqrt(SSE), the length of the vector of errors,
+//   f(k) >= f(k') - |k - k'| C(k),  C(k)^2 = sum over the elements of c_j^2, j the level under k,
+// and c_j <= min(1, u/k + 1/(2L)), so that C(k)^2 <= min(N, U2/k^2 + U1/(Lk) + N/(4L^2)) with
+// the sums U1, U2 of u and u^2.  About 128 candidates of a grid are evaluated, then those
+// between them that the bound from their two neighbours of the grid leaves below the threshold
+// of the least value: 210 to 290 of 1000 candidates in all at b = 4, 760 at b = 8.  What
+// k_exact is given is the list of candidates within the threshold of the minimum, the same
+// as from a row of all values.
+constexpr int kPruneMin = 300;                     // fewest candidates
+constexpr int kPruneGrid = 128;                    // most points of the grid
+constexpr int kPruneList = 2048;                   // most candidates between them, else all are evaluated
+constexpr int kPruneKeep = 64;                     // most of those within the threshold, else all are evaluated
+
+__host__ __device__ constexpr int prune_log(int n)
+{
+    int log = 2;
+    while (n >> log > kPruneGrid) ++log;
+    return log;
+}
+// LDS beyond the tables: the grid's values, then the list
+__host__ __device__ constexpr int prune_bytes(int n)
+{
+    return n < kPruneMin ? 0 : 4 * ((n >> prune_log(n)) + 1) + 2 * (n < kPruneList ? n : kPruneList);
+}
+
+struct FastPruneLds {
+    unsigned least;                                // binary32 pattern of the least value
+    int listed, kept;
+    float keep_v[kPruneKeep];
+    int keep_k[kPruneKeep];
+};
+
+// A row that holds a list instead of values: its first word is the count with the sign bit.
+constexpr int kRowIsList = (int)0x80000000;
+
+// U1, U2, count: bounds from above.  False, in every thread: the row has to be evaluated in full.
+template <int kT>
+__device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U1, float U2, float count,
+                                   FastPruneLds &S, float *grid, unsigned short *list, int *__restrict__ row)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int log = prune_log(c.n), step = 1 << log, points = c.n >> log;
+    const auto least = [&](bool lead, float v) {
+        const float w = -wave_max(lead ? -v : -__builtin_inff());
+        if (lane == 0) atomicMin(&S.least, __float_as_uint(w));
+        return w;
+    };
+    // keep_threshold of a value, from above
+    const float nf = (float)c.n, eps = nf * 4.7684e-7f;
+    const float flat_slack = count * (2.0001f * eps * eps + 2.0001f * (float)kFastRelErr * nf * nf);
+    const auto threshold = [&](float v) {
+        return v * 1.00007f + 4.0001f * eps * __builtin_amdgcn_sqrtf(count * v) + flat_slack;
+    };
+    fast_each<kT>(Q, c, points, [&](int i) { return (i + 1) << log; }, [&](bool lead, int k, float v) {
+        if (lead) grid[k >> log] = v;
+        least(lead, v);
+    });
+    __syncthreads();
+    // a bound above this excludes a candidate; 6e-7 n sqrt(count) covers the roundings of the
+    // roots, of at most n sqrt(count), and of the values below them
+    const float top = __builtin_amdgcn_sqrtf(threshold(__uint_as_float(S.least))) * 1.00002f + 6e-7f * nf * __builtin_amdgcn_sqrtf(count);
+    const float invL = __builtin_amdgcn_rcpf((float)c.Li), flat = 0.25f * count * invL * invL;
+    const int cap = c.n < kPruneList ? c.n : kPruneList;
+    for (int at = uni(tid & ~63); at <= points; at += kT) {
+        // the candidates between grid points i and i + 1
+        const int i = at + lane, from = i << log;
+        int lo = 1, hi = 0;
+        if (i <= points) {
+            const float r = __builtin_amdgcn_rcpf((float)(from + 1));
+            const float x = __builtin_fmaf(__builtin_fmaf(U2, r, U1 * invL), r, flat);
+            const float per = __builtin_amdgcn_rcpf(1.0001f * __builtin_amdgcn_sqrtf(x < count ? x : count));
+            hi = c.n - from < step ? c.n - from : step - 1;
+            if (i > 0) {
+                const float d = (__builtin_amdgcn_sqrtf(grid[i]) - top) * per - 0.01f;
+                if (d > 1.0f) lo = d < (float)step ? (int)__builtin_ceilf(d) : step;
+            }
+            if (i < points) {
+                const float d = (__builtin_amdgcn_sqrtf(grid[i + 1]) - top) * per - 0.01f;
+                if (d > 1.0f) hi = d < (float)step ? step - (int)__builtin_ceilf(d) : 0;
+            }
+        }
+        const int own = hi >= lo ? hi - lo + 1 : 0;
+        const int incl = wave_scan_incl(own);
+        int base = 0;
+        if (lane == 63 && incl > 0) base = atomicAdd(&S.listed, incl);
+        int pos = __builtin_amdgcn_readlane(base, 63) + incl - own;
+        for (int j = 0; j < own; ++j, ++pos)
+            if (pos < cap) list[pos] = (unsigned short)(from + lo + j);
+    }
+    __syncthreads();
+    const int listed = uni(S.listed);
+    if (listed > cap) return false;
+    fast_each<kT>(Q, c, listed, [&](int i) { return (int)list[i]; }, [&](bool lead, int k, float v) {
+        // within the threshold of the least value that the wavefront knows of
+        const float own = least(lead, v);
+        if (lead && v <= threshold(fminf(own, __uint_as_float(S.least)))) {
+            const int at = atomicAdd(&S.kept, 1);
+            if (at < kPruneKeep) { S.keep_v[at] = v; S.keep_k[at] = k; }
+        }
+    });
+    __syncthreads();
+    const int kept = uni(S.kept);
+    if (kept > kPruneKeep) return false;
+    if (tid >= 64) return true;                    // one wavefront writes the list (at most 192 entries)
+    const float thr = threshold_f32(keep_threshold((double)__uint_as_float(S.least), (double)count, c.n, true));
+    int out = 0;
+    const auto keep = [&](bool want, int k) {
+        const unsigned long long bal = __ballot(want);
+        if (want) row[1 + out + __builtin_popcountll(bal & ((1ull << lane) - 1ull))] = k;
+        out += __builtin_popcountll(bal);
+    };
+    static_assert(kPruneGrid + kPruneKeep < kPruneMin && kPruneKeep <= 64, "the list fits a row, the kept one wavefront");
+    for (int at = 0; at < points; at += 64) {
+        const int i = at + lane + 1;
+        keep(i <= points && grid[i <= points ? i : 1] <= thr, i << log);
+    }
+    keep(lane < kept && S.keep_v[lane < kept ? lane : 0] <= thr, S.keep_k[lane < kept ? lane : 0]);
+    if (lane == 0) row[0] = kRowIsList | out;
+    return true;
 }
 
 // A tile whose values crowd into a few buckets (many equal magnitudes: a bucket
@@ -256,6 +435,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     __shared__ int redbad[kW], redzero[kW], wfull[kW];      // wfull: a bucket fuller than 16, than kFastCrowd, crowded
     __shared__ unsigned long long wsum[kW];
     __shared__ double redA[kW];
+    __shared__ FastPruneLds pruned;
 
     int t;
     const int tid = threadIdx.x;
@@ -292,6 +472,10 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     sum = (float)wave_sum((double)sum);
     bad = wave_or(bad);
     if (lane == 0) { redm[wave] = m; redsum[wave] = sum; redbad[wave] = bad; }
+    if (tid == 0) {
+        pruned.least = 0x7f800000u;
+        pruned.listed = pruned.kept = 0;
+    }
     int obits = fast_octave_bits(len);
     const int T = kFastOct << obits;
     for (int i = tid; i < T; i += kT) fast_lds[i] = 0ull;
@@ -427,7 +611,20 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
             elems[i] = __float_as_uint((float)((double)(elems[i] - low) * per_unit));
         __syncthreads();
         fast_plain<kT>(elems, len - zeros, n, Li, row);
-    } else fast_candidates<kT>(Q, n, Li, q, low, A, run, row);
+        return;
+    }
+    const FastCurve c = {A, 1.0 / ((double)Li * (double)Li * (double)q), low, n, Li, q, run};
+    if (r.fast == 2 && usable && !keep_all) {
+        // the binary32 sum is within 2e-6 of the tile's
+        const double U1 = (double)sum * ((double)n / (double)m) * 1.000002;
+        const double U2 = A - (double)n * (double)n * (double)len + 2.0 * (double)n * U1;
+        float *grid = reinterpret_cast<float *>(elems + len + kFastWalk);
+        unsigned short *list = reinterpret_cast<unsigned short *>(grid + (n >> prune_log(n)) + 1);
+        if (fast_pruned<kT>(Q, c, (float)U1 * 1.0001f, (float)U2 * 1.0001f, (float)len, pruned, grid, list,
+                            reinterpret_cast<int *>(row)))
+            return;
+    }
+    fast_candidates<kT>(Q, c, row);
 }
 
 } // namespace pwlq

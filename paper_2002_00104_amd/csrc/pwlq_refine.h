@@ -21,6 +21,14 @@ __device__ inline double keep_threshold(double mn, double count, int n, bool fas
     return mn + 2.0 * (3e-5 * mn + 2.0 * eps * sqrt(count * mn) + count * eps * eps + extra);
 }
 
+// The largest binary32 value not above thr: the sums are binary32, and v <= it exactly when v <= thr.
+__device__ inline float threshold_f32(double thr)
+{
+    float f = (float)thr;
+    if ((double)f > thr) f = __int_as_float(__float_as_int(f) - 1);   // thr >= 0: the value below
+    return f;
+}
+
 // Groups spread over several tiles, step 1: add the tiles' binary32 sums in
 // binary64.  A workgroup takes 32 candidates of one group; thread (c, ph) adds
 // the tiles ph, ph+8, ph+16, ... of candidate c in that order, and the 8 partial
@@ -281,8 +289,11 @@ __device__ inline void exact_body(const TensorRec &r, const TileInfo &ti, int t,
     constexpr int kRowRegs = RowRegs<kT>::value;
     const bool in_regs = n <= kRowRegs * kT;
     const float *row = sse32 + (long long)t * n;
+    // k_fast may have left the list of kept candidates there instead
+    const int head = (r.fast == 2) ? uni(__float_as_int(row[0])) : 0;
+    const bool listed = head < 0;
     float rv[kRowRegs];
-    if (single && in_regs) {
+    if (single && in_regs && !listed) {
 #pragma unroll
         for (int x = 0; x < kRowRegs; ++x) {
             const int k0 = tid + x * kT;
@@ -311,6 +322,9 @@ __device__ inline void exact_body(const TensorRec &r, const TileInfo &ti, int t,
         if (tid == 0) llist[0] = 1;
         __syncthreads();
         exact_tile<kEpt, kT>(ti.src, ti.len, a, m, n, bits, llist, 1, true, nullptr, lds, st);
+    } else if (usable && listed) {
+        exact_tile<kEpt, kT>(ti.src, ti.len, a, m, n, bits, reinterpret_cast<const int *>(row) + 1, head & 0x7fffffff,
+                             true, nullptr, lds, st);
     } else if (usable) {
         float mnf = __builtin_inff();
         if (in_regs) {
@@ -326,9 +340,7 @@ __device__ inline void exact_body(const TensorRec &r, const TileInfo &ti, int t,
         }
         const double mn = block_min<kT / 64>((double)mnf, lds);
         const double thr = keep_threshold(mn, (double)r.gcount, n, r.fast != 0);
-        // the sums are binary32: v <= thr exactly when v <= the largest binary32 value not above thr
-        float thrf = (float)thr;
-        if ((double)thrf > thr) thrf = __int_as_float(__float_as_int(thrf) - 1);   // thr >= 0: the value below
+        const float thrf = threshold_f32(thr);
         for (int rbase = 0; rbase < n; rbase += kCap) {
             __syncthreads();
             if (tid == 0) *lcount = 0;
