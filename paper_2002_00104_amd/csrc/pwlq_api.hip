@@ -596,8 +596,7 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
             return sizeof(unsigned long long) * ((size_t)kFastOct << fast_octave_bits(fl.longest)) +
                    sizeof(unsigned) * (size_t)(fl.longest + kFastWalk) + (size_t)(fl.prunes ? prune_bytes(n_cand) : 0);
         };
-        // magnitudes in units of 1 / (2 L q) of a candidate
-        const int q = (int)kFastTop / (n_cand * 2 * ((1 << (bits - 1)) - 1));
+        const FastUnits units = fast_units(n_cand, bits);
         profile_mark(4, stream);
         for (int i = 0; i < n_fast_launches; ++i) {
             const FastLaunch &fl = fast_launches[i];
@@ -608,16 +607,16 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                 const unsigned wgs = (unsigned)std::min(fl.end - at, kFastGridMax);
                 switch (fl.threads) {
                     case 1024:
-                        k_fast<1024, kTileMax / 1024><<<wgs, 1024, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
+                        k_fast<1024, kTileMax / 1024><<<wgs, 1024, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
                         break;
                     case 512:
-                        k_fast<512, kFastLong / 512><<<wgs, 512, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
+                        k_fast<512, kFastLong / 512><<<wgs, 512, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
                         break;
                     case 128:
-                        k_fast<128, kFastShort / 128><<<wgs, 128, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
+                        k_fast<128, kFastShort / 128><<<wgs, 128, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
                         break;
                     default:
-                        k_fast<256, kSmallTile / 256><<<wgs, 256, lds, stream>>>(tb, at, n_cand, bits, q, tile_max, gm, sse32);
+                        k_fast<256, kSmallTile / 256><<<wgs, 256, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
                 }
             }
         }

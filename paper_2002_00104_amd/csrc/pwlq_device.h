@@ -92,6 +92,28 @@ __device__ inline TileInfo tile_info(const TensorRec &r, int tensor, int t)
     return ti;
 }
 
+// The magnitudes of a tile that a thread of a workgroup of kT holds: elements threadIdx.x + e kT,
+// 0 past the end.  Every load is issued whatever the length (past the end it reads the
+// last element): a load under a branch is waited for before the next is issued, kPer
+// times the latency of memory (38 400 tiles of 4096, b = 4, n = 1000, us: k_prep 356 -> 240, k_fast,
+// with its LDS adds in batches too, 665 -> 543).
+typedef __attribute__((address_space(1))) const float GlobalFloat;
+template <int kT, int kPer>
+__device__ inline void load_magnitudes(const float *src, int len, float (&a)[kPer])
+{
+    const GlobalFloat *g = (const GlobalFloat *)src;
+    const unsigned tid = threadIdx.x, last = (unsigned)len - 1u;
+    const auto load = [&](int count) {
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) a[e] = e < count ? g[tid + e * kT < last ? tid + e * kT : last] : 0.0f;
+    };
+    if (kPer > 8 && len <= kT) load(1);                        // the same in every thread
+    else if (kPer > 8 && len <= 4 * kT) load(4);
+    else load(kPer);
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) a[e] = tid + e * kT <= last ? fabsf(a[e]) : 0.0f;
+}
+
 // ---- wavefront / workgroup reductions (fixed order, so results are repeatable)
 // Built on DPP row shifts and row broadcasts: four shift-and-combine steps scan
 // each row of 16 lanes, row_bcast:15 carries a row's total into the next row
@@ -142,15 +164,50 @@ __device__ inline float wave_max(float v)
     v = fmaxf(v, dpp_f32<0x143, 0xc>(v, v));
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
+// The same where 0 changes nothing: lanes without a source take 0, no register has to be
+// set for them first, and 32-bit steps are one instruction.  Only lane 63 holds the total: rows
+// are combined without a mask.
+template <int kCtrl>
+__device__ inline unsigned dpp_or_zero(unsigned v)
+{
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)v, kCtrl, 0xf, 0xf, true);
+}
+template <int kCtrl>
+__device__ inline double dpp_or_zero(double v)
+{
+    return __hiloint2double((int)dpp_or_zero<kCtrl>((unsigned)__double2hiint(v)),
+                            (int)dpp_or_zero<kCtrl>((unsigned)__double2loint(v)));
+}
 __device__ inline double wave_sum(double v)
 {
-    v += dpp_f64<0x111, 0xf>(0.0, v);
-    v += dpp_f64<0x112, 0xf>(0.0, v);
-    v += dpp_f64<0x114, 0xf>(0.0, v);
-    v += dpp_f64<0x118, 0xf>(0.0, v);
-    v += dpp_f64<0x142, 0xa>(0.0, v);
-    v += dpp_f64<0x143, 0xc>(0.0, v);
+    v += dpp_or_zero<0x111>(v);
+    v += dpp_or_zero<0x112>(v);
+    v += dpp_or_zero<0x114>(v);
+    v += dpp_or_zero<0x118>(v);
+    v += dpp_or_zero<0x142>(v);
+    v += dpp_or_zero<0x143>(v);
     return lane63(v);
+}
+template <int kCtrl>
+__device__ inline float add_dpp(float v)
+{
+    return v + __uint_as_float(dpp_or_zero<kCtrl>(__float_as_uint(v)));
+}
+__device__ inline float wave_sum_f32(float v)
+{
+    v = add_dpp<0x143>(add_dpp<0x142>(add_dpp<0x118>(add_dpp<0x114>(add_dpp<0x112>(add_dpp<0x111>(v))))));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+template <int kCtrl>
+__device__ inline unsigned max_dpp(unsigned v)
+{
+    const unsigned o = dpp_or_zero<kCtrl>(v);
+    return o > v ? o : v;
+}
+__device__ inline unsigned wave_max_u32(unsigned v)
+{
+    v = max_dpp<0x143>(max_dpp<0x142>(max_dpp<0x118>(max_dpp<0x114>(max_dpp<0x112>(max_dpp<0x111>(v))))));
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 __device__ inline double wave_min(double v)
 {

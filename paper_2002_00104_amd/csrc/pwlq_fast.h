@@ -35,11 +35,11 @@
 // four at a time.
 // Elements that are exactly zero (pruned weights) are counted, never walked.
 //
-// Bound by vector issue and LDS together.  Per wavefront and look-up, building the tables
-// included: 51 vector instructions in tiles of 4096, 32 in tiles of 257 to 1024, 25 in
-// shorter ones, and six LDS instructions; the LDS index unit busy 68, 48 and 39 % of the
-// time.  38 400 tiles of 4096, 1000 candidates, b = 4: 1498 us with binary64 prefixes of
-// counts, sums and squares and walks of nine elements, 682 us now.
+// Bound by vector issue and LDS together: with 38 400 tiles of 4096, 1000 candidates, b = 4,
+// 275 000 vector instructions on each SIMD and the LDS index unit busy 62 % of the time, half of
+// that in bank conflicts; 190 000 and 55 % before any look-up.  In us: 1498 with binary64 prefixes of counts,
+// sums and squares and walks of nine elements, 745 with all candidates looked up and an element's
+// load and add waited for one by one, 543 now.
 #pragma once
 
 #include "pwlq_prep.h"
@@ -309,9 +309,9 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
     const int tid = threadIdx.x, lane = tid & 63;
     const int log = prune_log(c.n), step = 1 << log, points = c.n >> log;
     const auto least = [&](bool lead, float v) {
-        const float w = -wave_max(lead ? -v : -__builtin_inff());
-        if (lane == 0) atomicMin(&S.least, __float_as_uint(w));
-        return w;
+        const unsigned w = ~wave_max_u32(lead ? ~__float_as_uint(v) : ~0x7f800000u);      // v >= 0
+        if (lane == 0) atomicMin(&S.least, w);
+        return __uint_as_float(w);
     };
     // keep_threshold of a value, from above
     const float nf = (float)c.n, eps = nf * 4.7684e-7f;
@@ -420,8 +420,29 @@ __device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, i
     }
 }
 
+// What depends on n and bits alone: magnitudes are held in units of 1/unit of a candidate,
+// m as `top`; m at or below `keep_all` makes n / m overflow binary32.
+struct FastUnits {
+    double unit, per_unit, inv;            // 2 L q, its reciprocal, 2 / (L 2L q)
+    unsigned top;                          // 2 L q n: 0.97 * 2^30 or more
+    int q;
+    float keep_all;
+};
+inline FastUnits fast_units(int n, int bits)
+{
+    const int L = (1 << (bits - 1)) - 1;
+    FastUnits f;
+    f.q = (int)kFastTop / (n * 2 * L);
+    f.unit = (double)(2 * L * f.q);
+    f.per_unit = 1.0 / f.unit;
+    f.inv = 1.0 / ((double)L * (double)L * (double)f.q);
+    f.top = (unsigned)(n * 2 * L * f.q);
+    f.keep_all = (float)((double)n / (3.4028235677973366e38));      // 2^128 - 2^103
+    return f;
+}
+
 template <int kT, int kPer>
-__global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n, int bits, int q,
+__global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n, int bits, FastUnits F,
                                              const float *__restrict__ tile_max,
                                              float *__restrict__ gm,
                                              float *__restrict__ sse32)
@@ -431,8 +452,9 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     extern __shared__ unsigned long long fast_lds[];
     constexpr int kW = kT / 64;
     constexpr int kScan = ((kFastOct << fast_octave_bits(kT * kPer)) + kT - 1) / kT;   // words a thread holds at most
-    __shared__ float redm[kW], redsum[kW];
-    __shared__ int redbad[kW], redzero[kW], wfull[kW];      // wfull: a bucket fuller than 16, than kFastCrowd, crowded
+    __shared__ unsigned redm[kW];
+    __shared__ float redsum[kW];
+    __shared__ int wfull[kW];                                // a bucket fuller than 16, than kFastCrowd, crowded
     __shared__ unsigned long long wsum[kW];
     __shared__ double redA[kW];
     __shared__ FastPruneLds pruned;
@@ -448,30 +470,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     const int Li = (1 << (bits - 1)) - 1;
 
     float a[kPer];
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        const int i = tid + e * kT;
-        a[e] = (i < len) ? fabsf(ti.src[i]) : 0.0f;
-    }
-
-    // group absmax: from the registers (single-tile group) or the tile maxima; the
-    // tile's mean magnitude places the buckets
-    float m = 0.0f, sum = 0.0f;
-    int bad = 0;
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) { bad |= (a[e] != a[e]); m = fmaxf(m, a[e]); sum += a[e]; }
-    if (r.tpg > 1) {
-        const int tile0 = r.tile_base + ti.group_local * r.tpg;
-        for (int j = tid; j < r.tpg; j += kT) {
-            const float v = tile_max[tile0 + j];
-            bad |= (v != v);
-            m = fmaxf(m, v);
-        }
-    }
-    m = wave_max(m);
-    sum = (float)wave_sum((double)sum);
-    bad = wave_or(bad);
-    if (lane == 0) { redm[wave] = m; redsum[wave] = sum; redbad[wave] = bad; }
+    load_magnitudes<kT>(ti.src, len, a);
     if (tid == 0) {
         pruned.least = 0x7f800000u;
         pruned.listed = pruned.kept = 0;
@@ -479,22 +478,44 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     int obits = fast_octave_bits(len);
     const int T = kFastOct << obits;
     for (int i = tid; i < T; i += kT) fast_lds[i] = 0ull;
+
+    // group absmax: from the registers (single-tile group) or the tile maxima; the
+    // tile's mean magnitude places the buckets.  Binary32 patterns of magnitudes are in the
+    // magnitudes' order, NaN above infinity.
+    unsigned mb = 0;
+    float sum = 0.0f;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        const unsigned ab = __float_as_uint(a[e]);
+        mb = ab > mb ? ab : mb;
+        sum += a[e];
+    }
+    if (r.tpg > 1) {
+        const int tile0 = r.tile_base + ti.group_local * r.tpg;
+        for (int j = tid; j < r.tpg; j += kT) {
+            const unsigned v = __float_as_uint(fabsf(tile_max[tile0 + j]));
+            mb = v > mb ? v : mb;
+        }
+    }
+    mb = wave_max_u32(mb);
+    sum = wave_sum_f32(sum);
+    if (lane == 0) { redm[wave] = mb; redsum[wave] = sum; }
     __syncthreads();
-    m = redm[0];
+    mb = redm[0];
     sum = redsum[0];
-    bad = redbad[0];
-    for (int i = 1; i < kW; ++i) { m = fmaxf(m, redm[i]); sum += redsum[i]; bad |= redbad[i]; }
-    if (bad) m = __builtin_nanf("");
+#pragma unroll 8
+    for (int i = 1; i < kW; ++i) { mb = redm[i] > mb ? redm[i] : mb; sum += redsum[i]; }
+    mb = (unsigned)uni((int)mb);
+    sum = uni(sum);
+    const float m = mb > 0x7f800000u ? __builtin_nanf("") : __uint_as_float(mb);
     if (ti.tile_in_group == 0 && tid == 0) gm[ti.group] = m;
 
     const bool usable = (m > 0.0f) && (m < __builtin_inff());
-    const unsigned top = (unsigned)(n * 2 * Li * q);                      // the magnitude m: 0.97 * 2^30 or more
-    const double unit = (double)(2 * Li * q);                             // per candidate unit
-    const double scale = usable ? (double)top / (double)m : 0.0;
+    const double scale = uni(usable ? (double)F.top / (double)m : 0.0);
     // A group so small that n / m overflows binary32: the weights' own steps are too coarse
     // there for the filter's slack.  Every element counts as m then, which gives all
     // candidates the value 0 and keeps them.
-    const bool keep_all = usable && !((float)n / m < __builtin_inff());
+    const bool keep_all = usable && m <= F.keep_all;
     if (!usable || keep_all) {
 #pragma unroll
         for (int e = 0; e < kPer; ++e) a[e] = (usable && a[e] > 0.0f) ? m : 0.0f;
@@ -503,8 +524,8 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     // Values run from `low` to top + low, whose exponents are 30 - octaves and 29.  Seven
     // octaves, and 14 of half as many buckets where the mean lies in the lowest: near zero
     // these are 64 times as fine, elsewhere half as fine.
-    const double mean = (double)sum / (double)len * scale;
-    const bool deep = uni(mean < (double)(1u << (kFastBits - 1 - kFastOct)) ? 1 : 0) != 0;
+    const bool deep = uni((double)sum * (double)F.top <
+                          (double)len * (double)(1u << (kFastBits - 1 - kFastOct)) * (double)m ? 1 : 0) != 0;
     obits -= deep ? 1 : 0;
     const unsigned low = 1u << (kFastBits - (deep ? 2 * kFastOct : kFastOct));
     FastLds Q;
@@ -515,52 +536,59 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     // values, counts and sums per bucket; the count an add returns is the element's
     // rank inside its bucket
     unsigned v[kPer];
-    unsigned short rank[kPer];
-    int zeros = 0;
+    unsigned rank[kPer];
     double A = 0.0;
     // 2^52 + a scale, rounded once, holds the whole number in its low word: at most top, since
     // a <= m and scale is within 2^-53 of top / m
-    const double one52 = 4503599627370496.0;
+    const double one52 = 4503599627370496.0, full52 = one52 + (double)F.top;
+    // kBatch adds are in flight before the first result is looked at: one at a time, under a
+    // branch, a thread waits out the LDS for each of its elements (more at once: past 64
+    // registers).  So zero elements and threads past the end add nothing to a word of their own.
+    constexpr int kBatch = kPer % 5 == 0 ? 5 : kPer < 4 ? kPer : 4;
+    static_assert(kPer % kBatch == 0 && 64 <= kFastOct << 5, "whole batches; a word for every lane");
+    const float past = usable ? m : 0.0f;                      // counts as m: nothing in A
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        const int i = tid + e * kT;
-        unsigned u = 0;
-        if (i < len) {
-            const double whole = __builtin_fma((double)a[e], scale, one52);
-            u = (unsigned)__double2loint(whole);
-            const double d = one52 + (double)top - whole;             // exact
+    for (int e0 = 0; e0 < kPer; e0 += kBatch) {
+#pragma unroll
+        for (int e = e0; e < e0 + kBatch; ++e) { v[e] = low; rank[e] = 0; }
+        if (e0 * kT >= len) continue;                          // the same in every thread
+        unsigned long long was[kBatch];
+#pragma unroll
+        for (int x = 0; x < kBatch; ++x) {
+            const int e = e0 + x;
+            const bool within = tid + e * kT < len;
+            const double whole = __builtin_fma((double)(within ? a[e] : past), scale, one52);
+            const double d = full52 - whole;                   // exact
             A = __builtin_fma(d, d, A);
-            zeros += u == 0;
+            const unsigned u = within ? (unsigned)__double2loint(whole) : 0u;
+            v[e] = u + low;
+            const unsigned at = u > 0 ? fast_bucket(v[e], Q.shift) - bucket0 : (unsigned)lane;
+            was[x] = atomicAdd(&fast_lds[at], ((unsigned long long)(u > 0 ? 1u << (kFastSumBits - 32) : 0u) << 32) |
+                                                  (u > 0 ? v[e] : 0u));
         }
-        v[e] = u + low;
-        rank[e] = 0;
-        if (u > 0) {
-            rank[e] = (unsigned short)(atomicAdd(&fast_lds[fast_bucket(v[e], Q.shift) - bucket0],
-                                                 (1ull << kFastSumBits) | v[e]) >> kFastSumBits);
+#pragma unroll
+        for (int x = 0; x < kBatch; ++x) {
+            rank[e0 + x] = (unsigned)(was[x] >> kFastSumBits);
+            asm volatile("" : "+v"(rank[e0 + x]));             // here, not where it is used: half the registers
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
-    zeros = wave_scan_incl(zeros);
     A = wave_sum(A);
-    if (lane == 63) { redzero[wave] = zeros; redA[wave] = A; }
     __syncthreads();
-    zeros = 0;
-    A = 0.0;
-#pragma unroll 4
-    for (int i = 0; i < kW; ++i) { zeros += redzero[i]; A += redA[i]; }
-    A *= 1.0 / (unit * unit);
 
     int crowd = (len >> 4) > kFastCrowd ? len >> 4 : kFastCrowd;
     crowd = crowd < kFastCrowdMax ? crowd : kFastCrowdMax;
     // exclusive prefix of counts and sums, both fields in one word
-    const int per = (T + kT - 1) / kT;
-    const int lo = tid * per < T ? tid * per : T;
-    const int hi = lo + per < T ? lo + per : T;
+    const int per = (T + kT - 1) / kT;             // divides T
+    const int lo = tid * per;
+    const bool holds = lo < T;
+    int zeros = len;                               // less the elements counted in the buckets
     {
         unsigned long long w[kScan], tot = 0;
         unsigned fullest = 0;
 #pragma unroll
         for (int x = 0; x < kScan; ++x) {
-            w[x] = (lo + x < hi) ? fast_lds[lo + x] : 0ull;
+            w[x] = (holds && x < per) ? fast_lds[lo + x] : 0ull;
             tot += w[x];
             const unsigned c = (unsigned)(w[x] >> kFastSumBits);
             fullest = c > fullest ? c : fullest;
@@ -569,54 +597,68 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
         const int over = (__ballot(fullest > 16u) != 0ull ? 1 : 0) |
                          (__ballot(fullest > (unsigned)kFastCrowd) != 0ull ? 2 : 0) |
                          (__ballot(fullest > (unsigned)crowd) != 0ull ? 4 : 0);
-        if (lane == 63) { wsum[wave] = incl; wfull[wave] = over; }
+        if (lane == 63) { wsum[wave] = incl; wfull[wave] = over; redA[wave] = A; }
         __syncthreads();
+        unsigned long long run = incl - tot;
+#pragma unroll 8
+        for (int i = 0; i < kW; ++i) {
+            const unsigned long long s = wsum[i];
+            zeros -= (int)(s >> kFastSumBits);
+            run += i < wave ? s : 0ull;
+        }
         // the zero elements come before everything
-        unsigned long long run = incl - tot + ((unsigned long long)zeros << kFastSumBits) +
-                                 (unsigned long long)zeros * low;
-#pragma unroll 2
-        for (int i = 0; i < wave; ++i) run += wsum[i];
+        zeros = uni(zeros);
+        run += ((unsigned long long)zeros << kFastSumBits) + (unsigned long long)zeros * low;
+        if (holds) {
 #pragma unroll
-        for (int x = 0; x < kScan; ++x) {
-            if (lo + x < hi) {
-                // (a count that does not fit is a crowded tile's)
-                const unsigned long long own = w[x] >> kFastSumBits;
-                fast_lds[lo + x] = run | ((own / kFastWalkOn) << (kFastSumBits + kFastCountBits));
-                run += w[x];
+            for (int x = 0; x < kScan; ++x) {
+                if (x < per) {
+                    // (a count that does not fit is a crowded tile's)
+                    const unsigned long long own = w[x] >> kFastSumBits;
+                    fast_lds[lo + x] = run | ((own / kFastWalkOn) << (kFastSumBits + kFastCountBits));
+                    run += w[x];
+                }
             }
         }
     }
+    A = 0.0;
+    int full = 0;
+#pragma unroll 8
+    for (int i = 0; i < kW; ++i) { A += redA[i]; full |= wfull[i]; }
+    A = uni(A * (F.per_unit * F.per_unit));
+    full = uni(full);
     __syncthreads();
     unsigned *elems = reinterpret_cast<unsigned *>(fast_lds + T);
     Q.elems = (FastElemLds *)elems - zeros;
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        if (v[e] > low) {
-            elems[fast_word(Q, v[e]).before - zeros + rank[e]] = v[e];
-        }
+    for (int e0 = 0; e0 < kPer; e0 += kBatch) {
+        if (e0 * kT >= len) continue;
+        unsigned at[kBatch];
+#pragma unroll
+        for (int x = 0; x < kBatch; ++x) at[x] = fast_word(Q, v[e0 + x]).before - zeros + rank[e0 + x];
+#pragma unroll
+        for (int x = 0; x < kBatch; ++x)
+            if (v[e0 + x] > low) elems[at[x]] = v[e0 + x];
+        __builtin_amdgcn_sched_barrier(0);
     }
     // what a walk reads past the last element adds nothing
     if (tid < kFastWalk) elems[len - zeros + tid] = ~0u;
-    int full = 0;
-    for (int i = 0; i < kW; ++i) full |= wfull[i];
-    full = uni(full);
     // look-ups whose parts inside buckets fit 32 bits together: one or two at least (see
     // fast_octave_bits), eight or more as a rule
     const int run = (int)(0xffffffffu >> (kFastBits - 1 - obits)) >> (full & 2 ? kFastCrowdBits : full & 1 ? kFastCrowdLog : 4);
     __syncthreads();
     float *row = sse32 + (long long)t * n;
     if (full & 4) {
-        const double per_unit = 1.0 / unit;
         for (int i = tid; i < len - zeros; i += kT)
-            elems[i] = __float_as_uint((float)((double)(elems[i] - low) * per_unit));
+            elems[i] = __float_as_uint((float)((double)(elems[i] - low) * F.per_unit));
         __syncthreads();
         fast_plain<kT>(elems, len - zeros, n, Li, row);
         return;
     }
-    const FastCurve c = {A, 1.0 / ((double)Li * (double)Li * (double)q), low, n, Li, q, run};
+    const FastCurve c = {A, F.inv, low, n, Li, F.q, run};
     if (r.fast == 2 && usable && !keep_all) {
-        // the binary32 sum is within 2e-6 of the tile's
-        const double U1 = (double)sum * ((double)n / (double)m) * 1.000002;
+        // the binary32 sum is within 2e-6 of the tile's (at most 30 additions, 2^-24 each)
+        const double U1 = (double)sum * (scale * F.per_unit) * 1.000002;
         const double U2 = A - (double)n * (double)n * (double)len + 2.0 * (double)n * U1;
         float *grid = reinterpret_cast<float *>(elems + len + kFastWalk);
         unsigned short *list = reinterpret_cast<unsigned short *>(grid + (n >> prune_log(n)) + 1);

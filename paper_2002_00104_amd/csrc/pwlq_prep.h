@@ -106,11 +106,7 @@ __global__ __launch_bounds__(kT) void k_prep(Tables tb, int tile_begin, int n, i
     const int len = ti.len;
 
     float a[kPer];
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        const int i = tid + e * kT;
-        a[e] = (i < len) ? fabsf(ti.src[i]) : 0.0f;
-    }
+    load_magnitudes<kT>(ti.src, len, a);
 
     // group absmax: from the registers (single-tile group) or the tile maxima
     float m = 0.0f;
@@ -158,6 +154,7 @@ __global__ __launch_bounds__(kT) void k_prep(Tables tb, int tile_begin, int n, i
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
         const int i = tid + e * kT;
+        if (!kPrivate) rank[e] = 0;
         if (i < len) {
             const float u = usable ? to_units(a[e], scale, nf) : 0.0f;
             a[e] = u;
@@ -234,22 +231,30 @@ __global__ __launch_bounds__(kT) void k_prep(Tables tb, int tile_begin, int n, i
     float *stage = reinterpret_cast<float *>(hist + (kPrivate ? nb2 * kT : bins));
     for (int i = tid; i < pad; i += kT) stage[i] = 0.0f;
     __syncthreads();
+    if (kPrivate) {
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        const int i = tid + e * kT;
-        if (i < len) {
-            const float u = a[e];
-            const int b = kFine ? candidate_bin(u, n) : bucket_of(u);
-            int pos;
-            if (kPrivate) {
+        for (int e = 0; e < kPer; ++e) {
+            if (tid + e * kT < len) {
+                const int b = kFine ? candidate_bin(a[e], n) : bucket_of(a[e]);
                 const int sh = 16 * (b & 1);
                 const int old = atomicAdd(&hist[(b >> 1) * kT + tid], 1 << sh);
-                pos = wtot[b * kW + wave] + ((old >> sh) & 0xffff);
+                stage[pad + wtot[b * kW + wave] + ((old >> sh) & 0xffff)] = a[e];
             }
-            else {
-                pos = hist[b] + rank[e];          // hist now holds the first position of each bin
-            }
-            stage[pad + pos] = u;
+        }
+    } else {
+        // hist now holds the first position of each bin; the reads of four elements are
+        // issued before their first write
+        constexpr int kBatch = 4;
+        static_assert(kPer % kBatch == 0, "whole batches");
+#pragma unroll
+        for (int e0 = 0; e0 < kPer; e0 += kBatch) {
+            if (e0 * kT >= len) continue;                      // the same in every thread
+            int at[kBatch];
+#pragma unroll
+            for (int x = 0; x < kBatch; ++x) at[x] = hist[kFine ? candidate_bin(a[e0 + x], n) : bucket_of(a[e0 + x])];
+#pragma unroll
+            for (int x = 0; x < kBatch; ++x)
+                if (tid + (e0 + x) * kT < len) stage[pad + at[x] + rank[e0 + x]] = a[e0 + x];
         }
     }
     __syncthreads();

@@ -147,21 +147,16 @@ template <int kEpt, int kT>
 __device__ inline void load_tile(const float *__restrict__ src, int len,
                                  float (&a)[kEpt > 0 ? kEpt : 1])
 {
-    if (kEpt > 0) {
-#pragma unroll
-        for (int e = 0; e < kEpt; ++e) {
-            const int i = threadIdx.x + e * kT;
-            a[e] = (i < len) ? fabsf(src[i]) : 0.0f;
-        }
-    }
+    if constexpr (kEpt > 0) load_magnitudes<kT>(src, len, a);
 }
 
 template <int kEpt, int kT>
-__device__ inline void exact_tile(const float *__restrict__ src, int len,
+__device__ inline void exact_tile(const float *__restrict__ tile, int len,
                                   const float (&a)[kEpt > 0 ? kEpt : 1], float m, int n, int bits,
                                   const int *list, int count, bool single,
                                   double *__restrict__ part, double *lds, ExactState &st)
 {
+    const GlobalFloat *src = (const GlobalFloat *)tile;
     constexpr int kW = kT / 64;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -382,7 +377,7 @@ __device__ inline void exact_body(const TensorRec &r, const TileInfo &ti, int t,
 // kMaxPer (one-wavefront variant): the most elements a thread holds, 16 for tiles up to 1024
 // elements, 8 when the launch only sees tiles up to 512 (then 6 wavefronts per SIMD too).
 template <int kT, int kMaxPer = 16>
-__global__ __launch_bounds__(kT, (kT == 128 || (kT == 64 && kMaxPer == 8)) ? 6 : 1) void k_exact(Tables tb, int tile_begin, int n, int bits,
+__global__ __launch_bounds__(kT, (kT == 128 || (kT == 64 && kMaxPer == 8)) ? 6 : kT == 64 ? 4 : 1) void k_exact(Tables tb, int tile_begin, int n, int bits,
                                               const float *__restrict__ gm,
                                               const float *__restrict__ sse32,
                                               const int *__restrict__ klist,

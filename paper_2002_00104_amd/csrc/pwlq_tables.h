@@ -28,6 +28,11 @@ __device__ inline long long uni(long long v)
     int hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
     return ((long long)hi << 32) | (long long)lo;
 }
+__device__ inline float uni(float v) { return __int_as_float(uni(__float_as_int(v))); }
+__device__ inline double uni(double v)
+{
+    return __hiloint2double(uni(__double2hiint(v)), uni(__double2loint(v)));
+}
 __device__ inline TensorRec rec_of(const Tables &tb, int i)
 {
     TensorRec r = (tb.nt == 1) ? tb.one : tb.recs[i];
