@@ -63,7 +63,7 @@ __device__ inline int lin_swz(int row) { return (row >> 3) & 3; }
 // starting at element index e0 (a multiple of 16) occupy 2b bytes that start
 // 2-byte aligned (4-byte aligned for even b, 8 for b = 4, 16 for b = 8).
 // load_raw16 only issues the loads; unpack16 turns the raw bytes into 16 bytes,
-// one code per byte, in order.  Keeping the two apart lets the loads of a later
+// one code in the low bits of each byte, in order.  Keeping the two apart lets the loads of a later
 // step fly while the matrix cores work on the current one.
 template <int kBits>
 struct RawCodes {
@@ -107,8 +107,8 @@ __device__ inline void unpack16(const RawCodes<kBits> &raw, uint32_t (&out)[4])
     if (kBits == 4) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const uint32_t ev = raw.w[h] & 0x0f0f0f0fu;          // elements 0,2,4,6 of this half
-            const uint32_t od = (raw.w[h] >> 4) & 0x0f0f0f0fu;   // elements 1,3,5,7
+            const uint32_t ev = raw.w[h];                        // elements 0,2,4,6 of this half in the low nibbles
+            const uint32_t od = raw.w[h] >> 4;                   // elements 1,3,5,7
             // interleave bytes: (e0,o0,e1,o1) and (e2,o2,e3,o3)
             out[2 * h] = __builtin_amdgcn_perm(od, ev, 0x05010400u);
             out[2 * h + 1] = __builtin_amdgcn_perm(od, ev, 0x07030602u);
@@ -134,41 +134,73 @@ __device__ inline void unpack16(const RawCodes<kBits> &raw, uint32_t (&out)[4])
     }
 }
 
-// Four sign-magnitude codes (one per byte) and their four region bits (low
-// nibble of f) -> the three operand planes, four int8 each.
-__device__ inline void planes4(uint32_t codes, uint32_t f, int bits, uint32_t &w1, uint32_t &w2,
-                               uint32_t &w3)
+// Four sign-magnitude codes (one per byte; bits above the code are ignored) and their four
+// region bits (low nibble of f) -> the operand planes, four int8 each.  Byte masks and
+// values of small codes are looked up with v_perm_b32, one instruction for four: a selector
+// 0..3 takes a byte of its second source, 4..7 of its first, 8 the sign of the second's byte 1 in every bit, 13 and
+// above 0xff.  In the folded form 12 instructions for four codes at b = 4, 17 by shifts and borrows
+// (us, b = 4: 8 x 4096 x 11008 10.8 -> 10.3, 4096^3 159.9 -> 153.8;
+// b = 2: 11.8 -> 9.5, 162.7 -> 152.6).
+//
+// At five to seven bits the masks are made by borrows: a code's unpacking is the longer part
+// there and the kernels gain nothing (4096^3, b = 6, 169.5 -> 170.5), but k_linear_rows takes 20 to 40
+// registers more with look-ups, and a workgroup per CU less (31 x 1024 x 5000, b = 6, three
+// sums, 6.2 -> 7.0 us).
+template <int kBits>
+constexpr bool kLookUp = kBits <= 4 || kBits == 8;
+template <int kBits>
+struct SignedCodes {
+    uint32_t val, smask, lsig;         // signed codes; 0xff in the bytes of negative ones; L with the code's sign
+};
+template <int kBits>
+__device__ inline SignedCodes<kBits> signed_codes(uint32_t codes)
 {
-    const uint32_t magmask = ((1u << (bits - 1)) - 1u) * 0x01010101u;
-    const uint32_t mag = codes & magmask;
-    const uint32_t sgn = (codes >> (bits - 1)) & 0x01010101u;
-    // 0xff in the bytes that hold 1 (written so that it stays two full-rate
-    // instructions: x * 0xff would be a quarter-rate 32-bit multiply)
-    const uint32_t smask = (0x80808080u - sgn) ^ 0x80808080u;          // negative codes
-    const uint32_t neg = (0x80808080u - mag) ^ 0x80808080u;            // -mag per byte (mag <= 127)
-    const uint32_t val = (neg & smask) | (mag & ~smask);
-    const uint32_t f01 = __umul24(f & 0xfu, 0x00204081u) & 0x01010101u;   // region bit of each byte (24-bit multiply: full rate)
-    const uint32_t fm = (0x80808080u - f01) ^ 0x80808080u;             // tail bytes
-    w1 = val & ~fm;
-    w2 = val & fm;
-    w3 = (smask | 0x01010101u) & fm;
+    SignedCodes<kBits> r;
+    if constexpr (kBits <= 3) {        // a whole code is a selector
+        const uint32_t c = codes & ((1u << kBits) - 1u) * 0x01010101u;
+        r.val = __builtin_amdgcn_perm(0xfdfeff00u, kBits == 2 ? 0xff000100u : 0x03020100u, c);
+        r.smask = __builtin_amdgcn_perm(0xffffffffu, kBits == 2 ? 0xffff0000u : 0u, c);
+        r.lsig = __builtin_amdgcn_perm(0xfdfdfdfdu, kBits == 2 ? 0xffff0101u : 0x03030303u, c);
+    } else {
+        constexpr uint32_t L4 = ((1u << (kBits - 1)) - 1u) * 0x01010101u;      // L in every byte
+        constexpr uint32_t negL4 = (0x80808080u - L4) ^ 0x80808080u;
+        const uint32_t s = codes & ((1u << (kBits - 1)) * 0x01010101u);
+        r.smask = kLookUp<kBits> ? __builtin_amdgcn_perm(0u, kBits == 4 ? 0x00008000u : 0u, s)
+                                 : (0x80808080u - (s >> (kBits - 1))) ^ 0x80808080u;
+        const uint32_t mag = codes & L4;
+        // -mag: from a table, or by a borrow (mag <= 127)
+        const uint32_t neg = kBits == 4 ? __builtin_amdgcn_perm(0xf9fafbfcu, 0xfdfeff00u, mag)
+                                        : (0x80808080u - mag) ^ 0x80808080u;
+        r.val = (neg & r.smask) | (mag & ~r.smask);
+        r.lsig = (negL4 & r.smask) | (L4 & ~r.smask);
+    }
+    return r;
+}
+// 0xff in the tail bytes
+template <int kBits>
+__device__ inline uint32_t tail_mask(uint32_t f)
+{
+    const uint32_t f01 = __umul24(f & 0xfu, 0x00204081u) & 0x01010101u;    // region bit of each byte (24-bit multiply: full rate)
+    return kLookUp<kBits> ? __builtin_amdgcn_perm(0u, 0x0000ff00u, f01) : (0x80808080u - f01) ^ 0x80808080u;
+}
+template <int kBits>
+__device__ inline void planes4(uint32_t codes, uint32_t f, uint32_t &w1, uint32_t &w2, uint32_t &w3)
+{
+    const SignedCodes<kBits> c = signed_codes<kBits>(codes);
+    const uint32_t fm = tail_mask<kBits>(f);
+    w1 = c.val & ~fm;
+    w2 = c.val & fm;
+    w3 = (c.smask | 0x01010101u) & fm;
 }
 
 // The folded form: plane 0 holds L sigma in the tail bytes, plane 1 as above.
-__device__ inline void planes4_folded(uint32_t codes, uint32_t f, int bits, uint32_t &w1, uint32_t &w2)
+template <int kBits>
+__device__ inline void planes4_folded(uint32_t codes, uint32_t f, uint32_t &w1, uint32_t &w2)
 {
-    const uint32_t magmask = ((1u << (bits - 1)) - 1u) * 0x01010101u;      // L in every byte
-    const uint32_t mag = codes & magmask;
-    const uint32_t sgn = (codes >> (bits - 1)) & 0x01010101u;
-    const uint32_t smask = (0x80808080u - sgn) ^ 0x80808080u;
-    const uint32_t f01 = __umul24(f & 0xfu, 0x00204081u) & 0x01010101u;
-    const uint32_t fm = (0x80808080u - f01) ^ 0x80808080u;
-    const uint32_t neg = (0x80808080u - mag) ^ 0x80808080u;
-    const uint32_t val = (neg & smask) | (mag & ~smask);                   // signed code
-    const uint32_t negl = (0x80808080u - magmask) ^ 0x80808080u;           // -L in every byte
-    const uint32_t lsig = (negl & smask) | (magmask & ~smask);             // L sigma
-    w1 = (lsig & fm) | (val & ~fm);
-    w2 = val & fm;
+    const SignedCodes<kBits> c = signed_codes<kBits>(codes);
+    const uint32_t fm = tail_mask<kBits>(f);
+    w1 = (c.lsig & fm) | (c.val & ~fm);
+    w2 = c.val & fm;
 }
 
 // ---------------------------------------------------------------- constants
@@ -214,8 +246,8 @@ __global__ __launch_bounds__(kLinWG) void k_linear_wsum(const uint8_t *__restric
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             uint32_t w[3];
-            if (kPlanes == 3) planes4(c[x], f >> (4 * x), kBits, w[0], w[1], w[2]);
-            else planes4_folded(c[x], f >> (4 * x), kBits, w[0], w[1]);
+            if (kPlanes == 3) planes4<kBits>(c[x], f >> (4 * x), w[0], w[1], w[2]);
+            else planes4_folded<kBits>(c[x], f >> (4 * x), w[0], w[1]);
 #pragma unroll
             for (int pl = 0; pl < kPlanes; ++pl) sums[pl] = add_bytes(w[pl], sums[pl]);
         }
@@ -339,9 +371,9 @@ __device__ inline void lin_store(const LinStage<kBits, kAVec> &st, int8_t *__res
     for (int x = 0; x < 4; ++x) {
         uint32_t a, b, d = 0;
         if (kPlanes == 3)
-            planes4(c[x], st.flags >> (4 * x), kBits, a, b, d);
+            planes4<kBits>(c[x], st.flags >> (4 * x), a, b, d);
         else
-            planes4_folded(c[x], st.flags >> (4 * x), kBits, a, b);
+            planes4_folded<kBits>(c[x], st.flags >> (4 * x), a, b);
         w1[x] = (int)a & keep;
         w2[x] = (int)b & keep;
         w3[x] = (int)d & keep;
@@ -738,9 +770,9 @@ __device__ inline void row_planes(const RowStage<kBits> &st, int p, v4i (&b)[kPl
     for (int x = 0; x < 4; ++x) {
         uint32_t w1, w2, w3 = 0;
         if (kPlanes == 3)
-            planes4(c[x], f >> (4 * x), kBits, w1, w2, w3);
+            planes4<kBits>(c[x], f >> (4 * x), w1, w2, w3);
         else
-            planes4_folded(c[x], f >> (4 * x), kBits, w1, w2);
+            planes4_folded<kBits>(c[x], f >> (4 * x), w1, w2);
         b[0][x] = (int)w1;
         b[1][x] = (int)w2;
         if (kPlanes == 3) b[kPlanes - 1][x] = (int)w3;
