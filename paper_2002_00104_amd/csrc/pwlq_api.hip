@@ -921,6 +921,43 @@ bool linear_by_rows(int planes, int bits, long long K, int row_cap, long long ro
     return wgs <= (K <= 2048 || bits == 2 ? 900 : bits == 8 ? 512 : 740);
 }
 
+// Workgroups of k_linear_rows: `tile` channels by up to cap = tile mt - 1 rows (and one of ones).
+struct RowShape {
+    int tile, mt, cap, rows;               // rows of a workgroup, the same in all but the last
+    long long tiles, cols;                 // workgroups along the rows and along the channels
+};
+RowShape row_shape(long long M, long long N, int tile, int mt)
+{
+    RowShape rs;
+    rs.tile = tile;
+    rs.mt = mt;
+    rs.cap = tile * mt - 1;
+    rs.tiles = (M + rs.cap - 1) / rs.cap;
+    rs.cols = (N + tile - 1) / tile;
+    rs.rows = (int)((M + rs.tiles - 1) / rs.tiles);
+    return rs;
+}
+
+// Smaller workgroups than 63 rows by 32 channels, where those leave CUs idle: a workgroup takes as
+// long for its share of the reduction and its decoding whatever runs beside it, so the
+// smallest share that one workgroup per CU covers the call with is the fastest, though more of
+// them decode the same weights.  us by 32 x 63 / 16 x 31 / 32 x 31 / 16 x 63 (channels x rows):
+// 63x2048x1000, b = 4 9.3/5.2/6.5/7.6 (189 workgroups of the second shape); 63x4096x1500 14.3/
+// 11.2/9.6/11.7 (141 of the third); 250x2048x1000, b = 6, three sums, 12.2/12.2/12.7/10.1 (252 of
+// the fourth).  Past one per CU each loses (100x1024x4000 7.3/9.0/7.3/8.0; 63x4096x4096, 256 of the
+// fourth, 14.9/16.1/15.5/15.5), but for short reductions, to two per CU of the third (126x256x3000
+// 6.0/6.4/5.2/6.5).  Calls of up to 64 channels, at most a few workgroups either way, keep
+// the 32 x 63 that the tests of its edges are written for.
+RowShape smaller_row_shape(const RowShape &rs, long long M, long long K, long long N)
+{
+    if (rs.cap < 63 || N <= 64) return rs;
+    const auto wgs = [](const RowShape &r) { return r.tiles * r.cols; };
+    const RowShape a = row_shape(M, N, 16, 2), b = row_shape(M, N, 32, 1), c = row_shape(M, N, 16, 4);
+    if (wgs(a) <= 256) return a;
+    if (wgs(b) <= (K <= 512 ? 512 : 256)) return b;
+    return wgs(c) < 256 ? c : rs;
+}
+
 int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
                const uint8_t *packed_codes, const uint8_t *packed_flags, int64_t N, int bits,
                const float *p, const float *m, float *y, int32_t *acc, void *workspace,
@@ -950,11 +987,7 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     const long long wgs = 8 * tn_per_xcd * tiles_m;
     float *wconst = (float *)workspace;
     const unsigned wsum_wgs = (unsigned)((N + kLinWG / 64 - 1) / (kLinWG / 64));
-    const int row_cap = M <= 15 ? 15 : M <= 31 ? 31 : 63;          // and one row of ones
-    const int row_tile = row_cap <= 31 ? 16 : 32;
-    const long long row_tiles = (M + row_cap - 1) / row_cap, row_cols = (N + row_tile - 1) / row_tile;
-    const int rows_per_tile = (int)((M + row_tiles - 1) / row_tiles);
-    const dim3 row_grid((unsigned)row_cols, (unsigned)row_tiles);
+    RowShape rs = row_shape(M, N, M <= 31 ? 16 : 32, M <= 15 ? 1 : 2);
     // Where the rows leave it, k_linear_split up to one and a half of its workgroups per CU (each XCD counted as full as its
     // fullest: few channel tiles fill few XCDs); above that k_linear has as many
     // wavefronts without the second half's LDS traffic (K = 4096, b = 4, workgroups: us, k_linear
@@ -962,9 +995,11 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     // 512: 52.5/54.3, 704: 77.2/79.0, 1024: 83/99).
     const long long split_m = (M + kSplitBM - 1) / kSplitBM, split_wgs = 8 * tn_per_xcd * split_m;
     const bool can_split = planes == 2 && K % (2 * kLinBK) == 0 && K >= kSplitMinK && split_wgs <= kSplitMaxWgs;
-    const bool by_rows = linear_by_rows(planes, bits, K, row_cap, row_tiles, row_cols, rows_per_tile, can_split);
+    const bool by_rows = linear_by_rows(planes, bits, K, rs.cap, rs.tiles, rs.cols, rs.rows, can_split);
     const bool by_split = !by_rows && can_split;
-    if (by_rows ? !launch_fits(row_cols, 64 * kRowWaves)
+    if (by_rows) rs = smaller_row_shape(rs, M, K, N);
+    const dim3 row_grid((unsigned)rs.cols, (unsigned)rs.tiles);
+    if (by_rows ? !launch_fits(rs.cols, 64 * kRowWaves)
                 : !launch_fits(wgs, kLinWG) || !launch_fits((N + kLinWG / 64 - 1) / (kLinWG / 64), kLinWG))
         return fail(PWLQ_EINVAL, "grid too large");
     hipStream_t stream = (hipStream_t)stream_v;
@@ -972,22 +1007,26 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     g_launched.what = by_rows ? Launched::kLinearRows : by_split ? Launched::kLinearSplit : Launched::kLinear;
     g_launched.bits = bits;
     g_launched.planes = planes;
-    g_launched.row_tile = row_tile;
-    g_launched.row_mt = row_cap == 15 ? 1 : 2;
+    g_launched.row_tile = rs.tile;
+    g_launched.row_mt = rs.mt;
 #define PWLQ_LINEAR_ROWS(B, P, T, MT)                                                              \
     k_linear_rows<B, P, T, MT><<<row_grid, 64 * kRowWaves, 0, stream>>>(                           \
-        xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, y, acc, rows_per_tile)
+        xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, y, acc, rs.rows)
 #define PWLQ_LINEAR_CASE(B)                                                                       \
     case B:                                                                                        \
         if (by_rows) {                                                                             \
             profile_mark(6, stream);                                                               \
             if (planes == 3) {                                                                     \
-                if (row_cap == 15) PWLQ_LINEAR_ROWS(B, 3, 16, 1);                                  \
-                else if (row_cap == 31) PWLQ_LINEAR_ROWS(B, 3, 16, 2);                             \
+                if (rs.tile == 16 && rs.mt == 1) PWLQ_LINEAR_ROWS(B, 3, 16, 1);                    \
+                else if (rs.tile == 16 && rs.mt == 2) PWLQ_LINEAR_ROWS(B, 3, 16, 2);               \
+                else if (rs.tile == 16) PWLQ_LINEAR_ROWS(B, 3, 16, 4);                             \
+                else if (rs.mt == 1) PWLQ_LINEAR_ROWS(B, 3, 32, 1);                                \
                 else PWLQ_LINEAR_ROWS(B, 3, 32, 2);                                                \
             } else {                                                                               \
-                if (row_cap == 15) PWLQ_LINEAR_ROWS(B, 2, 16, 1);                                  \
-                else if (row_cap == 31) PWLQ_LINEAR_ROWS(B, 2, 16, 2);                             \
+                if (rs.tile == 16 && rs.mt == 1) PWLQ_LINEAR_ROWS(B, 2, 16, 1);                    \
+                else if (rs.tile == 16 && rs.mt == 2) PWLQ_LINEAR_ROWS(B, 2, 16, 2);               \
+                else if (rs.tile == 16) PWLQ_LINEAR_ROWS(B, 2, 16, 4);                             \
+                else if (rs.mt == 1) PWLQ_LINEAR_ROWS(B, 2, 32, 1);                                \
                 else PWLQ_LINEAR_ROWS(B, 2, 32, 2);                                                \
             }                                                                                      \
             profile_mark(7, stream);                                                               \
