@@ -26,6 +26,9 @@
 // n = 1000 (units of 2^-24 n: 0.061), 3.0e-5 against 5.3e-5 for 2048 of a heavy
 // tail, b = 8, n = 500 (5.1e-4).
 //
+// A tile that is a group of its own looks up a grid of candidates and those that it does not exclude
+// (fast_pruned); other tiles all of them.
+//
 // A look-up needs no full sort: elements are grouped into buckets that are
 // monotone in the magnitude (one counting pass in LDS), and a bucket's 64-bit word
 // holds the sum (43 bits) and count (14 bits) of the elements before it and its
@@ -71,7 +74,7 @@ constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launc
 
 // Error of a tile's filter value beyond the rounding of its elements: A is a sum of
 // squares added in at most 33 steps (10 per thread, 6 over the wavefront, 16 over the
-// workgroup) and scaled in three roundings, the rest is exact up to seven roundings
+// workgroup) and scaled in four roundings, the rest is exact up to seven roundings
 // of a value of at most A, and A is at most n^2 K: below 48 * 2^-53 n^2 K = 5.4e-15
 // n^2 K.  kFastRelErr * n^2 * K is added to the slack of the filter (keep_threshold).
 
@@ -275,7 +278,7 @@ __device__ inline void fast_candidates(const FastLds &Q, const FastCurve &c, flo
 // k_exact is given is the list of candidates within the threshold of the minimum, the same
 // as from a row of all values.
 constexpr int kPruneMin = 300;                     // fewest candidates
-constexpr int kPruneGrid = 128;                    // most points of the grid
+constexpr int kPruneGrid = 128;                    // most points of the grid (64: 1-7 % slower, 250: 4-12 %)
 constexpr int kPruneList = 2048;                   // most candidates between them, else all are evaluated
 constexpr int kPruneKeep = 64;                     // most of those within the threshold, else all are evaluated
 

@@ -9,7 +9,8 @@
 //                  (element, candidate) pair                    (VALU bound);
 //                  k_search_sliced where its wavefronts are few
 //   k_fast         instead of the last two, in a fast search's longer tiles: 2L
-//                  look-ups per candidate in bucketed prefix sums
+//                  look-ups per candidate in bucketed prefix sums, for a grid of
+//                  candidates and those that it does not exclude
 //   k_flag         per group: candidates whose binary32 SSE is within the
 //                  rounding slack of the minimum
 //   k_exact        flagged candidates re-evaluated with the canonical binary32
