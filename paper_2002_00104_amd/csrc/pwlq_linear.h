@@ -693,8 +693,8 @@ __global__ __launch_bounds__(2 * kLinWG, 4) void k_linear_split(const int8_t *__
 // (exact, whatever the split).  One row of the activation tile is all ones: its
 // sums are those of the weights themselves, which the offset z_x multiplies, so
 // no other pass reads the weights.  Bound by the packed weights' bytes for a few
-// rows, then by the decoding, paid again by every tile of rows (104 vector instructions per 16
-// weights of a lane in all at 8 rows, b = 4; 193 with three planes at 250 rows, b = 6).
+// rows, then by the decoding, paid again by every tile of rows (80 vector instructions per 16
+// weights of a lane in all at 8 rows, b = 4; 218 with three planes at 250 rows, b = 6).
 constexpr int kRowWaves = 8;
 constexpr int kRowLane = 64;           // weights of a lane per step
 
