@@ -1039,8 +1039,12 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
             k_linear_wsum<B, 2><<<wsum_wgs, kLinWG, 0, stream>>>(packed_codes, packed_flags, N, K, \
                                                                  p, m, wconst);                    \
         profile_mark(6, stream);                                                                   \
-        if (by_split)                                                                              \
-            k_linear_split<B><<<(unsigned)split_wgs, 2 * kLinWG, 0, stream>>>(                     \
+        if (by_split && B == 8 && K <= kSplitBorrowsMaxK)                                          \
+            k_linear_split<8, kBorrows><<<(unsigned)split_wgs, 2 * kLinWG, 0, stream>>>(           \
+                xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, wconst, y,                \
+                (int)split_m, (int)tiles_n, (int)tn_per_xcd);                                      \
+        else if (by_split)                                                                         \
+            k_linear_split<B, kLookUps><<<(unsigned)split_wgs, 2 * kLinWG, 0, stream>>>(           \
                 xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, wconst, y,                \
                 (int)split_m, (int)tiles_n, (int)tn_per_xcd);                                      \
         else if (planes == 3)                                                                      \

@@ -136,19 +136,49 @@ __device__ inline void unpack16(const RawCodes<kBits> &raw, uint32_t (&out)[4])
 }
 
 // Four sign-magnitude codes (one per byte; bits above the code are ignored) and their four
-// region bits (low nibble of f) -> the operand planes, four int8 each.  Byte masks and
-// values of small codes are looked up with v_perm_b32, one instruction for four: a selector
+// region bits (low nibble of f) -> the operand planes, four int8 each.  Two forms with the same
+// results.  By borrows: a byte mask is a subtraction and an exclusive or.  `bits` is an int or a
+// std::integral_constant: the latter lets the compiler fold the masks before it sees the kernel around
+// them, which schedules some kernels 1-4 % faster and others 1-4 % slower (see weight_planes).
+template <typename Bits>
+__device__ inline void planes4(uint32_t codes, uint32_t f, Bits bits, uint32_t &w1, uint32_t &w2, uint32_t &w3)
+{
+    const uint32_t magmask = ((1u << (bits - 1)) - 1u) * 0x01010101u;
+    const uint32_t mag = codes & magmask;
+    const uint32_t sgn = (codes >> (bits - 1)) & 0x01010101u;
+    // 0xff in the bytes that hold 1 (written so that it stays two full-rate
+    // instructions: x * 0xff would be a quarter-rate 32-bit multiply)
+    const uint32_t smask = (0x80808080u - sgn) ^ 0x80808080u;          // negative codes
+    const uint32_t neg = (0x80808080u - mag) ^ 0x80808080u;            // -mag per byte (mag <= 127)
+    const uint32_t val = (neg & smask) | (mag & ~smask);
+    const uint32_t f01 = __umul24(f & 0xfu, 0x00204081u) & 0x01010101u;   // region bit of each byte (24-bit multiply: full rate)
+    const uint32_t fm = (0x80808080u - f01) ^ 0x80808080u;             // tail bytes
+    w1 = val & ~fm;
+    w2 = val & fm;
+    w3 = (smask | 0x01010101u) & fm;
+}
+
+// The folded form: plane 0 holds L sigma in the tail bytes, plane 1 as above.
+template <typename Bits>
+__device__ inline void planes4_folded(uint32_t codes, uint32_t f, Bits bits, uint32_t &w1, uint32_t &w2)
+{
+    const uint32_t magmask = ((1u << (bits - 1)) - 1u) * 0x01010101u;      // L in every byte
+    const uint32_t mag = codes & magmask;
+    const uint32_t sgn = (codes >> (bits - 1)) & 0x01010101u;
+    const uint32_t smask = (0x80808080u - sgn) ^ 0x80808080u;
+    const uint32_t f01 = __umul24(f & 0xfu, 0x00204081u) & 0x01010101u;
+    const uint32_t fm = (0x80808080u - f01) ^ 0x80808080u;
+    const uint32_t neg = (0x80808080u - mag) ^ 0x80808080u;
+    const uint32_t val = (neg & smask) | (mag & ~smask);                   // signed code
+    const uint32_t negl = (0x80808080u - magmask) ^ 0x80808080u;           // -L in every byte
+    const uint32_t lsig = (negl & smask) | (magmask & ~smask);             // L sigma
+    w1 = (lsig & fm) | (val & ~fm);
+    w2 = val & fm;
+}
+
+// By look-ups: byte masks and values of small codes with v_perm_b32, one instruction for four: a selector
 // 0..3 takes a byte of its second source, 4..7 of its first, 8 the sign of the second's byte 1 in every bit, 13 and
-// above 0xff.  In the folded form 12 instructions for four codes at b = 4, 17 by shifts and borrows
-// (us, b = 4: 8 x 4096 x 11008 10.8 -> 10.3, 4096^3 159.9 -> 153.8;
-// b = 2: 11.8 -> 9.5, 162.7 -> 152.6).
-//
-// At five to seven bits the masks are made by borrows: a code's unpacking is the longer part
-// there and the kernels gain nothing (4096^3, b = 6, 169.5 -> 170.5), but k_linear_rows takes 20 to 40
-// registers more with look-ups, and a workgroup per CU less (31 x 1024 x 5000, b = 6, three
-// sums, 6.2 -> 7.0 us).
-template <int kBits>
-constexpr bool kLookUp = kBits <= 4 || kBits == 8;
+// above 0xff.  In the folded form 12 instructions for four codes at b = 4, 17 by borrows.
 template <int kBits>
 struct SignedCodes {
     uint32_t val, smask, lsig;         // signed codes; 0xff in the bytes of negative ones; L with the code's sign
@@ -165,9 +195,7 @@ __device__ inline SignedCodes<kBits> signed_codes(uint32_t codes)
     } else {
         constexpr uint32_t L4 = ((1u << (kBits - 1)) - 1u) * 0x01010101u;      // L in every byte
         constexpr uint32_t negL4 = (0x80808080u - L4) ^ 0x80808080u;
-        const uint32_t s = codes & ((1u << (kBits - 1)) * 0x01010101u);
-        r.smask = kLookUp<kBits> ? __builtin_amdgcn_perm(0u, kBits == 4 ? 0x00008000u : 0u, s)
-                                 : (0x80808080u - (s >> (kBits - 1))) ^ 0x80808080u;
+        r.smask = __builtin_amdgcn_perm(0u, kBits == 4 ? 0x00008000u : 0u, codes & ((1u << (kBits - 1)) * 0x01010101u));
         const uint32_t mag = codes & L4;
         // -mag: from a table, or by a borrow (mag <= 127)
         const uint32_t neg = kBits == 4 ? __builtin_amdgcn_perm(0xf9fafbfcu, 0xfdfeff00u, mag)
@@ -178,30 +206,51 @@ __device__ inline SignedCodes<kBits> signed_codes(uint32_t codes)
     return r;
 }
 // 0xff in the tail bytes
-template <int kBits>
 __device__ inline uint32_t tail_mask(uint32_t f)
 {
-    const uint32_t f01 = __umul24(f & 0xfu, 0x00204081u) & 0x01010101u;    // region bit of each byte (24-bit multiply: full rate)
-    return kLookUp<kBits> ? __builtin_amdgcn_perm(0u, 0x0000ff00u, f01) : (0x80808080u - f01) ^ 0x80808080u;
-}
-template <int kBits>
-__device__ inline void planes4(uint32_t codes, uint32_t f, uint32_t &w1, uint32_t &w2, uint32_t &w3)
-{
-    const SignedCodes<kBits> c = signed_codes<kBits>(codes);
-    const uint32_t fm = tail_mask<kBits>(f);
-    w1 = c.val & ~fm;
-    w2 = c.val & fm;
-    w3 = (c.smask | 0x01010101u) & fm;
+    return __builtin_amdgcn_perm(0u, 0x0000ff00u, __umul24(f & 0xfu, 0x00204081u) & 0x01010101u);
 }
 
-// The folded form: plane 0 holds L sigma in the tail bytes, plane 1 as above.
-template <int kBits>
-__device__ inline void planes4_folded(uint32_t codes, uint32_t f, uint32_t &w1, uint32_t &w2)
+// The form a kernel takes, the faster one in 34 calls of 1 to 4096 rows (best of four runs in turn, us).  To
+// four bits look-ups: 8x4096x11008, b = 2, 11.8/9.5, b = 4 10.8/10.3; 4096^3 162.7/152.6, 159.9/153.8.  From five
+// on a code's unpacking is the longer part:
+//  - k_linear gains with the sums apart (4096^3, b = 5 -4 %, b = 6 -2 %) and at 8 bits, and loses in
+//    the folded form at five to seven (2048x1024x2048, b = 7, 22.8/23.8; 600x1040x3000, b = 5, 21.5/22.1);
+//  - k_linear_rows gains in 15 rows by 16 channels (8x4096x11008, b = 7, 16.3/15.2, b = 8, three sums, 14.8/13.7), and
+//    at 8 bits in all workgroups of 16 channels; elsewhere look-ups take 20 to 40 registers more, and may take a
+//    workgroup per CU (31x1024x5000, b = 6, three sums, 6.2/7.0), or gain nothing (63x4096x11008, b = 8, three sums, 41.0/42.6).
+enum Decode { kBorrows, kBorrowsConst, kLookUps };        // (kBorrowsConst: `bits` an integral_constant)
+constexpr Decode linear_decode(int bits, int planes) { return bits <= 4 || bits == 8 || planes == 3 ? kLookUps : kBorrows; }
+constexpr Decode rows_decode(int bits, int planes, int tile, int mt)
 {
-    const SignedCodes<kBits> c = signed_codes<kBits>(codes);
-    const uint32_t fm = tail_mask<kBits>(f);
-    w1 = (c.lsig & fm) | (c.val & ~fm);
-    w2 = c.val & fm;
+    const bool row15 = tile == 16 && mt == 1, row31 = tile == 16 && mt == 2, row63 = tile == 32 && mt == 2;
+    if (bits <= 4) return kLookUps;
+    if (bits == 8) return row63 ? kBorrows : kLookUps;
+    if (planes == 2 && row15) return kLookUps;
+    // b = 5, 6, 7, 31x4096x11008: kBorrows 20.7/21.6/23.2, kBorrowsConst 21.3/21.1/23.0, kLookUps 20.9/20.7/22.7;
+    // 24x512x11008: 6.7/6.9/7.0, 6.7/6.9/6.8, 6.5/6.6/7.1; 31x1024x5000: 5.9/6.3/6.1, 6.1/6.4/6.0, 6.0/6.2/6.2
+    if (planes == 2 && row31) return bits == 5 ? kBorrows : bits == 6 ? kLookUps : kBorrowsConst;
+    // 63x4096x1500, b = 5, 11.5 with kBorrows, 11.1 with kBorrowsConst
+    return row15 || row31 || row63 ? kBorrows : kBorrowsConst;
+}
+
+// Four weights of each of kPlanes planes (three, or two in the folded form).
+template <int kBits, int kPlanes, Decode kDecode>
+__device__ inline void weight_planes(uint32_t codes, uint32_t f, uint32_t &w1, uint32_t &w2, uint32_t &w3)
+{
+    if constexpr (kDecode == kLookUps) {
+        const SignedCodes<kBits> c = signed_codes<kBits>(codes);
+        const uint32_t fm = tail_mask(f);
+        w1 = kPlanes == 3 ? c.val & ~fm : (c.lsig & fm) | (c.val & ~fm);
+        w2 = c.val & fm;
+        if (kPlanes == 3) w3 = (c.smask | 0x01010101u) & fm;
+    } else if constexpr (kDecode == kBorrowsConst) {
+        if constexpr (kPlanes == 3) planes4(codes, f, std::integral_constant<int, kBits>(), w1, w2, w3);
+        else planes4_folded(codes, f, std::integral_constant<int, kBits>(), w1, w2);
+    } else {
+        if constexpr (kPlanes == 3) planes4(codes, f, kBits, w1, w2, w3);
+        else planes4_folded(codes, f, kBits, w1, w2);
+    }
 }
 
 // ---------------------------------------------------------------- constants
@@ -257,8 +306,7 @@ __global__ __launch_bounds__(kLinWG) void k_linear_wsum(const uint8_t *__restric
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
                 uint32_t w[3];
-                if (kPlanes == 3) planes4<kBits>(c[x], f[i] >> (4 * x), w[0], w[1], w[2]);
-                else planes4_folded<kBits>(c[x], f[i] >> (4 * x), w[0], w[1]);
+                weight_planes<kBits, kPlanes, linear_decode(kBits, kPlanes)>(c[x], f[i] >> (4 * x), w[0], w[1], w[2]);
 #pragma unroll
                 for (int pl = 0; pl < kPlanes; ++pl) sums[pl] = add_bytes(w[pl], sums[pl]);
             }
@@ -365,7 +413,7 @@ __device__ inline void lin_load_whole(LinStage<kBits, kAVec> &st, const LinOffse
 
 // Writes one step into LDS: activations as they are, weights decoded into the
 // operand planes (three, or two in the folded form).
-template <int kBits, int kPlanes, int kAVec>
+template <int kBits, int kPlanes, Decode kDecode, int kAVec>
 __device__ inline void lin_store(const LinStage<kBits, kAVec> &st, int8_t *__restrict__ sA,
                                  int8_t *__restrict__ sB, int kvalid)
 {
@@ -385,10 +433,7 @@ __device__ inline void lin_store(const LinStage<kBits, kAVec> &st, int8_t *__res
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         uint32_t a, b, d = 0;
-        if (kPlanes == 3)
-            planes4<kBits>(c[x], st.flags >> (4 * x), a, b, d);
-        else
-            planes4_folded<kBits>(c[x], st.flags >> (4 * x), a, b);
+        weight_planes<kBits, kPlanes, kDecode>(c[x], st.flags >> (4 * x), a, b, d);
         w1[x] = (int)a & keep;
         w2[x] = (int)b & keep;
         w3[x] = (int)d & keep;
@@ -402,7 +447,7 @@ __device__ inline void lin_store(const LinStage<kBits, kAVec> &st, int8_t *__res
 // One reduction step of a wavefront: fragments of LDS buffer `buf`, the next
 // step decoded into the other buffer (kStore), 2 * kMT * kPlanes matrix
 // instructions, one barrier.
-template <int kBits, int kPlanes, bool kStore, int kMT, int kAVec>
+template <int kBits, int kPlanes, Decode kDecode, bool kStore, int kMT, int kAVec>
 __device__ inline void lin_step(v16i (&acc)[kMT][kPlanes],
                                 const LinStage<kBits, kAVec> &next, int kvalid_next,
                                 const int8_t *a_lane, const int8_t *b_lane, int swz, int half,
@@ -423,7 +468,7 @@ __device__ inline void lin_step(v16i (&acc)[kMT][kPlanes],
             af[ks][mt] = *reinterpret_cast<const v4i *>(a_base + mt * 32 * kLinStride + chunk);
     }
     if (kStore)
-        lin_store<kBits, kPlanes, kAVec>(next, sA0 + (buf ^ 1) * kABuf, sB0 + (buf ^ 1) * kBBuf, kvalid_next);
+        lin_store<kBits, kPlanes, kDecode, kAVec>(next, sA0 + (buf ^ 1) * kABuf, sB0 + (buf ^ 1) * kBBuf, kvalid_next);
 #pragma unroll
     for (int ks = 0; ks < kLinBK / 32; ++ks)
 #pragma unroll
@@ -460,6 +505,7 @@ __global__ __launch_bounds__(kLinWG, 2) void k_linear(const int8_t *__restrict__
                                                    int tiles_m, int tiles_n, int tn_per_xcd)
 {
     constexpr int kMT = lin_mt(kPlanes), kBM = lin_bm(kPlanes), kAVec = lin_avec(kPlanes);
+    constexpr Decode kDecode = linear_decode(kBits, kPlanes);
     __shared__ __attribute__((aligned(16))) int8_t sA[2][kBM * kLinStride];
     __shared__ __attribute__((aligned(16))) int8_t sB[2][kPlanes * kLinBN * kLinStride];
 
@@ -488,7 +534,7 @@ __global__ __launch_bounds__(kLinWG, 2) void k_linear(const int8_t *__restrict__
     auto valid = [&](int step) { return step == steps - 1 ? last_valid : 4; };
     LinStage<kBits, kAVec> near, far;
     lin_load<kBits, kAVec>(near, xq, M, K, pcodes, pflags, N, row0, col0, 0, valid(0));
-    lin_store<kBits, kPlanes, kAVec>(near, sA[0], sB[0], valid(0));
+    lin_store<kBits, kPlanes, kDecode, kAVec>(near, sA[0], sB[0], valid(0));
     if (steps > 1) lin_load<kBits, kAVec>(near, xq, M, K, pcodes, pflags, N, row0, col0, kLinBK, valid(1));
     __syncthreads();
     // row of this lane's fragments (every 32-row tile of a wavefront has the same
@@ -508,21 +554,21 @@ __global__ __launch_bounds__(kLinWG, 2) void k_linear(const int8_t *__restrict__
     for (; kt + 4 < steps; kt += 2) {
         const long long k2 = (long long)(kt + 2) * kLinBK, k3 = k2 + kLinBK;
         lin_load_whole<kBits, kAVec>(far, offs, a_base + k2, code_base + (k2 >> 4) * (2 * kBits), flag_base + (k2 >> 3));
-        lin_step<kBits, kPlanes, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[0], sB[0], 0);
+        lin_step<kBits, kPlanes, kDecode, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[0], sB[0], 0);
         lin_load_whole<kBits, kAVec>(near, offs, a_base + k3, code_base + (k3 >> 4) * (2 * kBits), flag_base + (k3 >> 3));
-        lin_step<kBits, kPlanes, true>(acc, far, 4, a_lane, b_lane, swz, half, sA[0], sB[0], 1);
+        lin_step<kBits, kPlanes, kDecode, true>(acc, far, 4, a_lane, b_lane, swz, half, sA[0], sB[0], 1);
     }
     for (; kt + 2 < steps; ++kt) {
         lin_load<kBits, kAVec>(far, xq, M, K, pcodes, pflags, N, row0, col0, (long long)(kt + 2) * kLinBK,
                                valid(kt + 2));
-        lin_step<kBits, kPlanes, true>(acc, near, valid(kt + 1), a_lane, b_lane, swz, half, sA[0], sB[0], kt & 1);
+        lin_step<kBits, kPlanes, kDecode, true>(acc, near, valid(kt + 1), a_lane, b_lane, swz, half, sA[0], sB[0], kt & 1);
         near = far;
     }
     if (kt + 1 < steps) {
-        lin_step<kBits, kPlanes, true>(acc, near, valid(kt + 1), a_lane, b_lane, swz, half, sA[0], sB[0], kt & 1);
+        lin_step<kBits, kPlanes, kDecode, true>(acc, near, valid(kt + 1), a_lane, b_lane, swz, half, sA[0], sB[0], kt & 1);
         ++kt;
     }
-    lin_step<kBits, kPlanes, false>(acc, near, 4, a_lane, b_lane, swz, half, sA[0], sB[0], kt & 1);
+    lin_step<kBits, kPlanes, kDecode, false>(acc, near, 4, a_lane, b_lane, swz, half, sA[0], sB[0], kt & 1);
 
     // epilogue: C2 A1 + C4 A2 + C5 A3 + (C3 + C6), per output channel
     const long long n = col0 + wn * 32 + (lane & 31);
@@ -576,8 +622,12 @@ constexpr int kSplitMT = 2, kSplitBM = kLinWM * 32 * kSplitMT;
 constexpr int kSplitAVec = kSplitBM * kLinBK / 16 / kLinWG;
 constexpr int kSplitMaxWgs = 384;      // the rule stands where it is applied
 constexpr int kSplitMinK = 512;        // K is a multiple of 128: whole steps, as many in both halves
+// At 8 bits the look-ups spill 18 registers, the borrows 8, all outside the loop over the steps, where the
+// look-ups are the faster ones (us, borrows / look-ups: 768x512x4096 14.9/15.8, 900x1024x2000 14.0/14.4,
+// 700x1536x3000 24.2/24.1, 300x3072x5000 28.2/27.8, 31x4096x11008 35.9/34.3).
+constexpr int kSplitBorrowsMaxK = 1024;
 
-template <int kBits>
+template <int kBits, Decode kDecode>
 __global__ __launch_bounds__(2 * kLinWG, 4) void k_linear_split(const int8_t *__restrict__ xq, long long M, long long K,
                                                          float s_x, float z_x, const uint8_t *__restrict__ pcodes,
                                                          const uint8_t *__restrict__ pflags, long long N,
@@ -620,7 +670,7 @@ __global__ __launch_bounds__(2 * kLinWG, 4) void k_linear_split(const int8_t *__
         lin_load_whole<kBits, kAVec>(st, offs, a_base + k0, code_base + (k0 >> 4) * (2 * kBits), flag_base + (k0 >> 3));
     };
     load(near, 0);
-    lin_store<kBits, 2, kAVec>(near, sA[group], sB[group], 4);
+    lin_store<kBits, 2, kDecode, kAVec>(near, sA[group], sB[group], 4);
     load(near, 1);
     __syncthreads();
     const int8_t *a_lane = sA[group] + (wm * 32 * kMT + (lane & 31)) * kLinStride;
@@ -629,18 +679,18 @@ __global__ __launch_bounds__(2 * kLinWG, 4) void k_linear_split(const int8_t *__
     int kt = 0;
     for (; kt + 3 < steps; kt += 2) {
         load(far, kt + 2);
-        lin_step<kBits, 2, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 0);
+        lin_step<kBits, 2, kDecode, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 0);
         load(near, kt + 3);
-        lin_step<kBits, 2, true>(acc, far, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 1);
+        lin_step<kBits, 2, kDecode, true>(acc, far, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 1);
     }
     if (kt + 2 < steps) {
         load(far, kt + 2);
-        lin_step<kBits, 2, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 0);
+        lin_step<kBits, 2, kDecode, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], 0);
         near = far;
         ++kt;
     }
-    lin_step<kBits, 2, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], kt & 1);
-    lin_step<kBits, 2, false>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], (kt + 1) & 1);
+    lin_step<kBits, 2, kDecode, true>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], kt & 1);
+    lin_step<kBits, 2, kDecode, false>(acc, near, 4, a_lane, b_lane, swz, half, sA[group], sB[group], (kt + 1) & 1);
 
     // the last step's barrier has ended every fragment read, so the buffers are free:
     // group g finishes the rows of its g-th 32-row tile: the other's sums of them come through LDS
@@ -764,7 +814,7 @@ __device__ inline void row_load_part(RowStage<kBits> &st, const uint8_t *__restr
 }
 
 // The operand planes of run p (0..3, 16 weights) of a stage.
-template <int kBits, int kPlanes>
+template <int kBits, int kPlanes, Decode kDecode>
 __device__ inline void row_planes(const RowStage<kBits> &st, int p, v4i (&b)[kPlanes])
 {
     RawCodes<kBits> raw;
@@ -784,10 +834,9 @@ __device__ inline void row_planes(const RowStage<kBits> &st, int p, v4i (&b)[kPl
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         uint32_t w1, w2, w3 = 0;
-        if (kPlanes == 3)
-            planes4<kBits>(c[x], f >> (4 * x), w1, w2, w3);
-        else
-            planes4_folded<kBits>(c[x], f >> (4 * x), w1, w2);
+        // (kBorrows here, not a call further in: the constant has to come after the inlining)
+        if constexpr (kDecode == kBorrows && kPlanes == 3) planes4(c[x], f >> (4 * x), kBits, w1, w2, w3);
+        else weight_planes<kBits, kPlanes, kDecode>(c[x], f >> (4 * x), w1, w2, w3);
         b[0][x] = (int)w1;
         b[1][x] = (int)w2;
         if (kPlanes == 3) b[kPlanes - 1][x] = (int)w3;
@@ -796,8 +845,10 @@ __device__ inline void row_planes(const RowStage<kBits> &st, int p, v4i (&b)[kPl
 
 // A workgroup's rows: [row0, row0 + rows), rows < kTile kMT; row `rows` of its tile is
 // the row of ones.
+// (b = 4, three planes, 31 rows: 80 registers, so that a CU holds three workgroups; by itself the compiler takes 87 and two:
+// 24x512x11008 5.7 us by borrows, 6.5 by look-ups, 5.4 with the bound.)
 template <int kBits, int kPlanes, int kTile, int kMT>
-__global__ __launch_bounds__(64 * kRowWaves) void k_linear_rows(
+__global__ __launch_bounds__(64 * kRowWaves, kBits == 4 && kPlanes == 3 && kTile == 16 && kMT == 2 ? 6 : 1) void k_linear_rows(
     const int8_t *__restrict__ xq, long long M, long long K, float s_x, float z_x,
     const uint8_t *__restrict__ pcodes, const uint8_t *__restrict__ pflags, long long N,
     const float *__restrict__ p, const float *__restrict__ m, float *__restrict__ y,
@@ -839,7 +890,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_linear_rows(
     v4i a[kMT][4];
     auto products = [&](const RowStage<kBits> &st, int s) {
         v4i b[kPlanes];
-        row_planes<kBits, kPlanes>(st, s, b);
+        row_planes<kBits, kPlanes, rows_decode(kBits, kPlanes, kTile, kMT)>(st, s, b);
 #pragma unroll
         for (int mt = 0; mt < kMT; ++mt) {
             v4i x = a[mt][s];

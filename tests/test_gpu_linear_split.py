@@ -17,3 +17,10 @@ pytestmark = pytest.mark.gpu
 def test_tile_edges(P, M, K, N, bits):  # noqa: F811
     rows = np.unique(np.r_[0:M:61, 31, 32, 63, 64, 127, 128, M - 2, M - 1])
     case(P, M, K, N, bits, seed=M * 7 + K + N + bits, dist="normal" if bits & 1 else "laplace", check_rows=rows)
+
+
+@pytest.mark.parametrize("M,K,N", [(64, 1024, 8321), (64, 1152, 11008), (250, 1152, 8321), (250, 2176, 2113)])
+def test_eight_bits_either_side_of_the_longest_reduction_by_borrows(P, M, K, N):  # noqa: F811
+    """Weights are decoded by borrows up to K = 1024 and by look-ups beyond."""
+    case(P, M, K, N, 8, seed=M + K + N, check_rows=np.unique(np.r_[0:M:31, M - 1]))
+    assert P.last_kernels() in ("k_linear_split<8>", "k_linear_rows<8, 2, 32, 2>")
