@@ -405,7 +405,10 @@ __device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, i
         const float rc = Lf / kf;
         const float rt = (k < n) ? Lf / nk : 0.0f;
         const float ct = -kf * rt;
-        const float stepc = kf / Lf, stept = nk / Lf;
+        float stepc = kf / Lf, stept = nk / Lf;
+        // else the compiler divides once per element, after the choice of the piece: 21 vector instructions
+        // instead of 10 (4096x512 of log-uniform weights, b = 4, n = 2000, us: 2106, 817 now)
+        asm("" : "+v"(stepc), "+v"(stept));
         float outer = 0.0f;
         for (int cb = 0; cb < len; cb += kChunk) {
             const int ce = (cb + kChunk < len) ? cb + kChunk : len;
