@@ -1,7 +1,11 @@
 """The fast search's grid of candidates at its edges, against the oracle: as few candidates as
 the grid takes and one less, a last interval of one candidate and of a full step, more
 candidates between the grid points than its list holds, more within the threshold than it
-keeps (equal errors everywhere), and tiles that are not a group of their own."""
+keeps (equal errors everywhere), and tiles that are not a group of their own.
+
+Whether a tile took the grid is seen in the workspace: it leaves a list of candidates there, whose
+first word is their number (192 at most) with the sign bit, in place of a row of values, which
+are not negative."""
 import numpy as np
 import pytest
 
@@ -27,11 +31,23 @@ def rows(K, rng):
     return w.astype(np.float32)
 
 
-@pytest.mark.parametrize("bits,n,K", [(6, 299, 600), (6, 300, 600), (4, 512, 130), (5, 513, 1030), (4, 515, 257),
-                                      (2, 1500, 64), (4, 1000, 5121), (3, 1024, 700), (7, 1025, 2816), (7, 300, 6000), (8, 1500, 4200),
-                                      (5, 2049, 1155), (8, 4100, 4200), (4, 20000, 600), (6, 1000, 8193), (2, 65535, 600)])
-def test_fast_search_of_many_candidates(P, bits, n, K):
+def search(P, tensors, bits, n):
+    """The outputs of a fast search, and how many tiles left a list in the workspace."""
     import torch
+    tl = P.TensorList([torch.from_numpy(w).cuda() for w in tensors], P.PER_CHANNEL)
+    ws = torch.zeros((P.search_list_workspace_bytes(tl, bits, n) + 3) // 4, dtype=torch.int32, device="cuda")
+    got = P.search_list(tl, bits, n, ws.view(torch.uint8), P.alloc_search_outputs(tl.n_groups, "cuda"), True)
+    assert "k_fast" in P.last_kernels()
+    count = ws.bitwise_xor(-2 ** 31)                          # 1 .. 192 in a list's first word
+    return {k: v.cpu().numpy() for k, v in got.items()}, int(((count >= 1) & (count <= 192)).sum())
+
+
+@pytest.mark.parametrize("bits,n,K,pruned", [
+    (6, 299, 600, False), (6, 300, 600, True), (4, 512, 130, True), (5, 513, 1030, True), (4, 515, 257, True),
+    (2, 1500, 64, True), (4, 1000, 5121, False), (4, 1700, 5121, True), (3, 1024, 700, True), (7, 1025, 2816, True),
+    (7, 300, 6000, True), (8, 1500, 4200, True), (5, 2049, 1155, True), (8, 4100, 4200, None), (4, 20000, 600, None),
+    (6, 1000, 8193, False), (2, 65535, 600, None)])
+def test_fast_search_of_many_candidates(P, bits, n, K, pruned):
     w = rows(K, np.random.default_rng(bits * 1000 + n))
     w = np.concatenate([w, w[:1] * 1e-37, np.zeros_like(w[:1]), np.full_like(w[:1], np.inf), w[:1] * np.nan])
     print(f"[case] bits={bits} n={n} K={K}", flush=True)
@@ -39,8 +55,39 @@ def test_fast_search_of_many_candidates(P, bits, n, K):
     try:
         # 2048 more groups: the look-ups, not the passes of few tiles
         many = np.concatenate([w, np.repeat(w[:1], 2048, 0)])
-        got = {k: v[:len(w)].cpu().numpy() for k, v in P.search(torch.from_numpy(many).cuda(), bits, n, fast=True).items()}
-        assert "k_fast" in P.last_kernels()
+        got, lists = search(P, [many], bits, n)
+        got = {k: v[:len(w)] for k, v in got.items()}
+        # Gaussian rows have a list; of many candidates within the threshold, some rows and others not
+        assert pruned is None or (lists >= 2048 if pruned else lists == 0)
         assert_search_matches(got, R.search(w, bits, n, want_curve=True), f"bits={bits} n={n} K={K}")
+    finally:
+        P.set_small_call_tiles(before)
+
+
+@pytest.mark.parametrize("shape,bits,n", [
+    # threads of a workgroup: 512, 1024, 256, 128; 11 pairs of look-ups a thread, or 20 below 256 workgroups
+    ((256, 1500), 4, 805), ((255, 1500), 4, 1463), ((256, 6000), 4, 1610), ((513, 600), 6, 300), ((1025, 200), 2, 1408),
+    # at 8 bits from 1500 candidates on
+    ((256, 4200), 8, 1500)])
+def test_either_side_of_where_the_grid_is_taken(P, shape, bits, n):
+    before = P.set_small_call_tiles(0)
+    try:
+        w = np.random.default_rng(n).standard_normal(shape).astype(np.float32)
+        assert search(P, [w], bits, n)[1] > shape[0] * 3 // 4
+        assert search(P, [w], bits, n - 1)[1] == 0
+    finally:
+        P.set_small_call_tiles(before)
+
+
+def test_a_launch_of_tiles_that_are_groups_and_of_parts_of_groups(P):
+    rng = np.random.default_rng(8)
+    tensors = [rng.standard_normal((1100, 1500)).astype(np.float32), rng.laplace(0, 1, (40, 9000)).astype(np.float32)]
+    before = P.set_small_call_tiles(0)
+    try:
+        got, lists = search(P, tensors, 4, 1700)
+        assert P.last_kernels() == "k_fast<1024>" and 1000 <= lists <= 1100
+        for w, at in ((tensors[0][:30], 0), (tensors[1], 1100)):
+            part = {k: v[at:at + len(w)] for k, v in got.items()}
+            assert_search_matches(part, R.search(w, 4, 1700, want_curve=True), f"groups {at}..")
     finally:
         P.set_small_call_tiles(before)
