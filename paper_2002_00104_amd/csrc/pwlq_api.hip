@@ -131,12 +131,27 @@ int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
 // waits out the three steps alone (us, all / pruned: 512 threads, 4096x4608, b = 4, n = 1000
 // 119/108, n = 400 88/93; 256 threads, 4096x1024, n = 700 55/46, n = 300 41/41; 128 threads,
 // 20000x128, n = 1000 191/101, n = 4000 740/170, n = 256 89/86; 1024 threads, 700x8192, n = 1000
-// 60/61, n = 4000 188/168; 64x600, n = 1000 15.5/16.1, n = 4000 31/20).  At b = 8 the grid
-// excludes a third of 1000 candidates, which often leaves a thread as many rounds
-// (64x5000, n = 1000 93/102, n = 2000 164/142).
+// 60/61, n = 4000 188/168; 64x600, n = 1000 15.5/16.1, n = 4000 31/20).
+//
+// Not where most tiles would have more candidates within the threshold than are kept, and be evaluated in
+// full after all.  The threshold is 6e-5 + 2.4e-5 L above the least value, since the rounding in its slack
+// is in proportion to n / m as the error is, and the values are a parabola in k / n around the least
+// one: about n sqrt(6e-5 + 2.4e-5 L) candidates, in proportion.  At 112 of that measure no weights but uniform ones lose
+// (64x5000, all / pruned: b = 4, n = 7000 137/108, n = 12000 166/173; b = 6, n = 3000 87/63, n = 6000 155/161; b = 8,
+// n = 2000 179/159, n = 5000 408/424); from n = 8000 on at two and three bits some do (200x700, b = 3, n = 10000 78/84).
+//
+// At 7 and 8 bits the grid leaves about 60 and 76 of 100 candidates.  Fewer workgroups than CUs take as long
+// as a thread's candidates, so these have to get fewer (250x2000, b = 7: n = 1000 47/51, n = 1300 61/52; 64x5000, b = 8: n = 1500
+// 143/149, n = 1700 169/155); more of them gain from n = 600 and 1500 on, or always (1024x1155, b = 7: n = 500 51/54,
+// n = 700 66/59; 2500x4608 n = 500 182/158; 300x7000, b = 8, n = 1500 213/196; 64x5000, n = 1000 93/102).
 bool fast_prunes(int threads, int tiles, int n, int L)
 {
-    return n >= kPruneMin && (long long)n * L >= (tiles < 256 ? 20 : 11) * threads && (L < 127 || n >= 1500);
+    if (n < kPruneMin || n > 8000 || (long long)n * n * (60 + 24 * L) > 112LL * 112 * 1000000) return false;
+    if ((long long)n * L < (tiles < 256 ? 20 : 11) * threads) return false;
+    if (L < 63) return true;
+    const auto rounds = [&](int count) { return (count + threads - 1) / threads; };
+    if (tiles < 256) return rounds(n * (L == 63 ? 60 : 76) / 100) < rounds(n);
+    return L == 63 ? n >= 600 || tiles >= 2048 : n >= 1500;
 }
 
 struct FastLaunch {
