@@ -189,16 +189,6 @@ __device__ inline double wave_sum(double v)
     return lane63(v);
 }
 template <int kCtrl>
-__device__ inline float add_dpp(float v)
-{
-    return v + __uint_as_float(dpp_or_zero<kCtrl>(__float_as_uint(v)));
-}
-__device__ inline float wave_sum_f32(float v)
-{
-    v = add_dpp<0x143>(add_dpp<0x142>(add_dpp<0x118>(add_dpp<0x114>(add_dpp<0x112>(add_dpp<0x111>(v))))));
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-template <int kCtrl>
 __device__ inline unsigned max_dpp(unsigned v)
 {
     const unsigned o = dpp_or_zero<kCtrl>(v);

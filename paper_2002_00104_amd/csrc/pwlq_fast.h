@@ -74,7 +74,7 @@ constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launc
 
 // Error of a tile's filter value beyond the rounding of its elements: A is a sum of
 // squares added in at most 33 steps (10 per thread, 6 over the wavefront, 16 over the
-// workgroup) and scaled in four roundings, the rest is exact up to seven roundings
+// workgroup) and scaled in three roundings, the rest is exact up to seven roundings
 // of a value of at most A, and A is at most n^2 K: below 48 * 2^-53 n^2 K = 5.4e-15
 // n^2 K.  kFastRelErr * n^2 * K is added to the slack of the filter (keep_threshold).
 
@@ -429,7 +429,7 @@ __device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, i
 // What depends on n and bits alone: magnitudes are held in units of 1/unit of a candidate,
 // m as `top`; m at or below `keep_all` makes n / m overflow binary32.
 struct FastUnits {
-    double unit, per_unit, inv;            // 2 L q, its reciprocal, 2 / (L 2L q)
+    double per_unit, per_unit2, inv;       // 1 / (2 L q), 1 / (2 L q)^2, 2 / (L 2L q)
     unsigned top;                          // 2 L q n: 0.97 * 2^30 or more
     int q;
     float keep_all;
@@ -439,8 +439,9 @@ inline FastUnits fast_units(int n, int bits)
     const int L = (1 << (bits - 1)) - 1;
     FastUnits f;
     f.q = (int)kFastTop / (n * 2 * L);
-    f.unit = (double)(2 * L * f.q);
-    f.per_unit = 1.0 / f.unit;
+    const double unit = (double)(2 * L * f.q);
+    f.per_unit = 1.0 / unit;
+    f.per_unit2 = 1.0 / (unit * unit);
     f.inv = 1.0 / ((double)L * (double)L * (double)f.q);
     f.top = (unsigned)(n * 2 * L * f.q);
     f.keep_all = (float)((double)n / (3.4028235677973366e38));      // 2^128 - 2^103
@@ -504,7 +505,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
         }
     }
     mb = wave_max_u32(mb);
-    sum = wave_sum_f32(sum);
+    sum = (float)wave_sum((double)sum);
     if (lane == 0) { redm[wave] = mb; redsum[wave] = sum; }
     __syncthreads();
     mb = redm[0];
@@ -631,7 +632,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     int full = 0;
 #pragma unroll 8
     for (int i = 0; i < kW; ++i) { A += redA[i]; full |= wfull[i]; }
-    A = uni(A * (F.per_unit * F.per_unit));
+    A = uni(A * F.per_unit2);
     full = uni(full);
     __syncthreads();
     unsigned *elems = reinterpret_cast<unsigned *>(fast_lds + T);
@@ -663,7 +664,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     }
     const FastCurve c = {A, F.inv, low, n, Li, F.q, run};
     if (r.fast == 2 && usable && !keep_all) {
-        // the binary32 sum is within 2e-6 of the tile's (at most 30 additions, 2^-24 each)
+        // the sum is within 2e-6 of the tile's (at most 27 binary32 additions, 2^-24 each)
         const double U1 = (double)sum * (scale * F.per_unit) * 1.000002;
         const double U2 = A - (double)n * (double)n * (double)len + 2.0 * (double)n * U1;
         float *grid = reinterpret_cast<float *>(elems + len + kFastWalk);
