@@ -959,18 +959,22 @@ RowShape row_shape(long long M, long long N, int tile, int mt)
 // them decode the same weights.  us by 32 x 63 / 16 x 31 / 32 x 31 / 16 x 63 (channels x rows):
 // 63x2048x1000, b = 4 9.3/5.2/6.5/7.6 (189 workgroups of the second shape); 63x4096x1500 14.3/
 // 11.2/9.6/11.7 (141 of the third); 250x2048x1000, b = 6, three sums, 12.2/12.2/12.7/10.1 (252 of
-// the fourth).  Past one per CU each loses (100x1024x4000 7.3/9.0/7.3/8.0; 63x4096x4096, 256 of the
+// the fourth).  Past one per CU they lose in the folded form (100x1024x4000 7.3/9.0/7.3/8.0; 63x4096x4096, 256 of the
 // fourth, 14.9/16.1/15.5/15.5), but for short reductions, to two per CU of the third (126x256x3000
-// 6.0/6.4/5.2/6.5).  Calls of up to 64 channels, at most a few workgroups either way, keep
+// 6.0/6.4/5.2/6.5); with the sums apart some calls past it would gain (700x512x1000, b = 6, 14.9/11.3 by the third).
+// The fourth has twice the columns of workgroups, and each column reads all activations: only where
+// these fit an XCD's 4 MiB of L2, or at 8 bits in the folded form, where it gains more than the
+// reads cost (32 x 63 / 16 x 63: 2000x1024x100, b = 4, 7.2/6.4; 3000x4096x80 17.3/23.1; b = 8, 3000x8192x80 35.3/30.5).
+// Calls of up to 64 channels, at most a few workgroups either way, keep
 // the 32 x 63 that the tests of its edges are written for.
-RowShape smaller_row_shape(const RowShape &rs, long long M, long long K, long long N)
+RowShape smaller_row_shape(const RowShape &rs, long long M, long long K, long long N, int bits, int planes)
 {
     if (rs.cap < 63 || N <= 64) return rs;
     const auto wgs = [](const RowShape &r) { return r.tiles * r.cols; };
     const RowShape a = row_shape(M, N, 16, 2), b = row_shape(M, N, 32, 1), c = row_shape(M, N, 16, 4);
     if (wgs(a) <= 256) return a;
     if (wgs(b) <= (K <= 512 ? 512 : 256)) return b;
-    return wgs(c) < 256 ? c : rs;
+    return wgs(c) < 256 && (M * K <= 4 << 20 || (bits == 8 && planes == 2)) ? c : rs;
 }
 
 int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
@@ -1012,7 +1016,7 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     const bool can_split = planes == 2 && K % (2 * kLinBK) == 0 && K >= kSplitMinK && split_wgs <= kSplitMaxWgs;
     const bool by_rows = linear_by_rows(planes, bits, K, rs.cap, rs.tiles, rs.cols, rs.rows, can_split);
     const bool by_split = !by_rows && can_split;
-    if (by_rows) rs = smaller_row_shape(rs, M, K, N);
+    if (by_rows) rs = smaller_row_shape(rs, M, K, N, bits, planes);
     const dim3 row_grid((unsigned)rs.cols, (unsigned)rs.tiles);
     if (by_rows ? !launch_fits(rs.cols, 64 * kRowWaves)
                 : !launch_fits(wgs, kLinWG) || !launch_fits((N + kLinWG / 64 - 1) / (kLinWG / 64), kLinWG))

@@ -28,3 +28,17 @@ def test_either_side_of_each_limit(P, M, K, N, want):  # noqa: F811
     p = torch.ones(N, device="cuda")
     P.linear_i8(x, 1.0, 0.0, z, z, N, 4, p, p)
     assert P.last_kernels() == f"k_linear_rows<4, 2, {want}>"
+
+
+@pytest.mark.parametrize("M,K,N,bits,acc,want", [
+    # 16 channels by 63 rows while the activations are at most 4 MiB, at 8 bits in the folded form always
+    (1024, 4096, 230, 4, False, "4, 2, 16, 4"), (1025, 4096, 230, 4, False, "4, 2, 32, 2"), (1024, 4112, 230, 4, False, "4, 2, 32, 2"),
+    (3000, 1392, 80, 4, True, "4, 3, 16, 4"), (3000, 4096, 80, 4, True, "4, 3, 32, 2"), (3000, 4096, 80, 2, False, "2, 2, 32, 2"),
+    (3000, 4096, 80, 8, False, "8, 2, 16, 4"), (3000, 4096, 80, 8, True, "8, 3, 32, 2")])
+def test_activations_that_fit_the_l2(P, M, K, N, bits, acc, want):  # noqa: F811
+    import torch
+    x = torch.zeros((M, K), dtype=torch.int8, device="cuda")
+    z = torch.zeros(N * K, dtype=torch.uint8, device="cuda")
+    p = torch.ones(N, device="cuda")
+    P.linear_i8(x, 1.0, 0.0, z, z, N, bits, p, p, want_acc=acc)
+    assert P.last_kernels() == f"k_linear_rows<{want}>"
