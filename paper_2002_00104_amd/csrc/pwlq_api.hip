@@ -965,11 +965,10 @@ RowShape row_shape(long long M, long long N, int tile, int mt)
 // The fourth has twice the columns of workgroups, and each column reads all activations: only where
 // these fit an XCD's 4 MiB of L2, or at 8 bits in the folded form, where it gains more than the
 // reads cost (32 x 63 / 16 x 63: 2000x1024x100, b = 4, 7.2/6.4; 3000x4096x80 17.3/23.1; b = 8, 3000x8192x80 35.3/30.5).
-// Calls of up to 64 channels, at most a few workgroups either way, keep
-// the 32 x 63 that the tests of its edges are written for.
+// Few channels, where 32 x 63 are a handful of workgroups, gain most (16 x 31: 63x2304x64, b = 4, 9.9/5.4; 1900x4096x64 14.2/8.6).
 RowShape smaller_row_shape(const RowShape &rs, long long M, long long K, long long N, int bits, int planes)
 {
-    if (rs.cap < 63 || N <= 64) return rs;
+    if (rs.cap < 63) return rs;
     const auto wgs = [](const RowShape &r) { return r.tiles * r.cols; };
     const RowShape a = row_shape(M, N, 16, 2), b = row_shape(M, N, 32, 1), c = row_shape(M, N, 16, 4);
     if (wgs(a) <= 256) return a;

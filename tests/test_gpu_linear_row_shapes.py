@@ -20,7 +20,8 @@ def test_shapes(P, M, K, N, tile, mt, bits):  # noqa: F811
 
 @pytest.mark.parametrize("M,K,N,want", [
     (62, 1024, 2048, "16, 2"), (62, 1024, 2049, "32, 1"), (62, 1024, 4096, "32, 1"), (63, 1024, 4080, "16, 4"),
-    (63, 1024, 4096, "32, 2"), (62, 512, 8192, "32, 1"), (62, 512, 8193, "32, 2"), (63, 512, 64, "32, 2"), (63, 512, 65, "16, 2")])
+    (63, 1024, 4096, "32, 2"), (62, 512, 8192, "32, 1"), (62, 512, 8193, "32, 2"), (63, 512, 64, "16, 2"), (63, 512, 65, "16, 2"),
+    (63, 2304, 64, "16, 2"), (1900, 1024, 64, "16, 2"), (2048, 1024, 64, "32, 1")])
 def test_either_side_of_each_limit(P, M, K, N, want):  # noqa: F811
     import torch
     x = torch.zeros((M, K), dtype=torch.int8, device="cuda")

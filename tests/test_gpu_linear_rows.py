@@ -17,6 +17,16 @@ def test_tile_edges(P, M, K, N, bits):  # noqa: F811
     case(P, M, K, N, bits, seed=M * 7 + K + N + bits, dist="normal" if bits & 1 else "laplace")
 
 
+@pytest.mark.parametrize("bits", [2, 3, 4, 5, 8])
+@pytest.mark.parametrize("M,K,N", [(63, 16, 5473), (32, 528, 4129), (63, 656, 4097), (64, 592, 2753), (126, 560, 2049),
+                                   (127, 544, 1665), (63, 2000, 4111)])
+def test_tile_edges_of_63_rows_by_32_channels(P, M, K, N, bits):  # noqa: F811
+    """The same for the largest workgroups, which calls of few channels do not get."""
+    rows = np.unique(np.r_[0, 1, 31, 32, M // 2 - 1:M // 2 + 2, M - 2, M - 1])
+    case(P, M, K, N, bits, seed=M + K + N + bits, dist="normal" if bits & 1 else "laplace", check_rows=rows[rows < M])
+    assert P.last_kernels() == f"k_linear_rows<{bits}, 2, 32, 2>"
+
+
 @pytest.mark.parametrize("extra", range(16, 257, 48))
 def test_what_is_left_of_a_step(P, extra):  # noqa: F811
     for M in (9, 20, 40):

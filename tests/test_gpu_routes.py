@@ -64,7 +64,7 @@ def test_fast_search_of_few_tiles(P, shape, bits, n, want):
 
 @pytest.mark.parametrize("M,K,N,bits,acc,want", [
     (15, 256, 16, 4, False, "k_linear_rows<4, 2, 16, 1>"), (16, 272, 17, 4, True, "k_linear_rows<4, 3, 16, 2>"),
-    (32, 512, 33, 4, False, "k_linear_rows<4, 2, 32, 2>"), (63, 2304, 64, 4, True, "k_linear_rows<4, 3, 32, 2>"),
+    (32, 512, 33, 4, False, "k_linear_rows<4, 2, 16, 2>"), (63, 2304, 64, 4, True, "k_linear_rows<4, 3, 16, 2>"),
     (64, 64, 14400, 4, False, "k_linear_rows<4, 2, 32, 2>"), (64, 64, 14432, 4, False, "k_linear<4, 2>"),
     (1025, 512, 1729, 4, False, "k_linear_split<4>"), (1025, 528, 1729, 4, False, "k_linear<4, 2>"),
     (1025, 448, 1729, 4, False, "k_linear<4, 2>"), (1025, 512, 1729, 4, True, "k_linear<4, 3>"),
