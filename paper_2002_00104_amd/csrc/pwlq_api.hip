@@ -92,18 +92,22 @@ int fast_threads(int longest, long long tiles, int n, int L)
 // Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
 // candidate grows with the number of half-way points (2L look-ups) and hardly depends on
 // the tile length, the plain evaluation costs one pass over the tile.  16384 tiles, 1000
-// candidates, b = 4, us, look-ups / pass: 160 elements 168 / 249, 96 elements 162 / 178,
+// candidates, b = 4, us, look-ups of all candidates / pass: 160 elements 168 / 249, 96 elements 162 / 178,
 // 64 elements 157 / 144; but a line at 6 * 2L cost MobileNetV2 shapes 216 -> 238, one more
 // launch beside the passes over the shorter tiles, which stay.  At b = 8 and many
-// candidates the line is a little longer (2048 and 1024 tiles of 2048, n = 1000: 299/289,
-// 170/160; n = 300: 149/195, 81/120).
+// candidates the line is a little longer (2048 and 1024 tiles of 2048, n = 1000: 297/286,
+// 169/160; n = 300: 149/194, 78/120).
 //
 // Below 2048 tiles the look-ups of a tile, L pairs for every candidate of a thread one after
 // the other at about 0.3 us, take as long for one tile as for all, and the passes are spread over
 // the chip: tiles not far above that length are handed over only where the look-ups'
 // time is less than the passes' at 1.6e13 evaluations a second on a full chip and 6 us for
-// their launch (16x121, n = 20000, us, look-ups / pass 273/55; 64x2048, b = 8, n = 2000 146/59; 512x121,
-// n = 1000 15.8/20.4).
+// their launch (16x121, n = 20000, us, look-ups / pass 99/54; 64x2048, b = 8, n = 2000 116/46; 512x121,
+// n = 1000 15.5/20.3).
+//
+// Both price the look-ups of all candidates.  Where the tiles look up a grid of them first (fast_prunes) the
+// line errs to the side of the passes: 16384 tiles, n = 1000, with the grid / pass: 160 elements 91 / 262, 96
+// elements 82 / 175, 64 elements 76 / 138.
 int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
 {
     const int L = (1 << (bits - 1)) - 1;
@@ -130,7 +134,7 @@ int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
 // more pairs of look-ups for all candidates, or 20 where the workgroups are fewer than the CUs, and each
 // waits out the three steps alone (us, all / pruned: 512 threads, 4096x4608, b = 4, n = 1000
 // 119/108, n = 400 88/93; 256 threads, 4096x1024, n = 700 55/46, n = 300 41/41; 128 threads,
-// 20000x128, n = 1000 191/101, n = 4000 740/170, n = 256 89/86; 1024 threads, 700x8192, n = 1000
+// 20000x128, n = 1000 191/101, n = 4000 740/155, n = 256 89/86; 1024 threads, 700x8192, n = 1000
 // 60/61, n = 4000 188/168; 64x600, n = 1000 15.5/16.1, n = 4000 31/20).
 //
 // Not where most tiles would have more candidates within the threshold than are kept, and be evaluated in

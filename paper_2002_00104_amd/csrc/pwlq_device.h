@@ -93,10 +93,11 @@ __device__ inline TileInfo tile_info(const TensorRec &r, int tensor, int t)
 }
 
 // The magnitudes of a tile that a thread of a workgroup of kT holds: elements threadIdx.x + e kT,
-// 0 past the end.  Every load is issued whatever the length (past the end it reads the
+// 0 past the end.  No load depends on the length (past the end it reads the
 // last element): a load under a branch is waited for before the next is issued, kPer
 // times the latency of memory (38 400 tiles of 4096, b = 4, n = 1000, us: k_prep 356 -> 240, k_fast,
-// with its LDS adds in batches too, 665 -> 543).
+// with its LDS adds in batches too, 665 -> 543).  A thread of more than 8 elements issues one load, four or
+// all kPer, by the length: tiles of a few elements to a wavefront pay for 16 (k_prep<64, 16> 2-9 %).
 typedef __attribute__((address_space(1))) const float GlobalFloat;
 template <int kT, int kPer>
 __device__ inline void load_magnitudes(const float *src, int len, float (&a)[kPer])

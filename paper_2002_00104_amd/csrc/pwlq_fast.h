@@ -27,7 +27,7 @@
 // tail, b = 8, n = 500 (5.1e-4).
 //
 // A tile that is a group of its own looks up a grid of candidates and those that it does not exclude
-// (fast_pruned); other tiles all of them.
+// (fast_pruned), in launches where that is less work (fast_prunes); other tiles all of them.
 //
 // A look-up needs no full sort: elements are grouped into buckets that are
 // monotone in the magnitude (one counting pass in LDS), and a bucket's 64-bit word
@@ -39,10 +39,10 @@
 // Elements that are exactly zero (pruned weights) are counted, never walked.
 //
 // Bound by vector issue and LDS together: with 38 400 tiles of 4096, 1000 candidates, b = 4,
-// 275 000 vector instructions on each SIMD and the LDS index unit busy 62 % of the time, half of
-// that in bank conflicts; 190 000 and 55 % before any look-up.  In us: 1498 with binary64 prefixes of counts,
-// sums and squares and walks of nine elements, 745 with all candidates looked up and an element's
-// load and add waited for one by one, 543 now.
+// 290 000 vector instructions on each SIMD, two thirds of them before any look-up, and the LDS index unit active for
+// 297 us at 2.4 GHz, half of that in bank conflicts.  In us: 1498 with binary64
+// prefixes of counts, sums and squares and walks of nine elements, 745 with all candidates looked up and an
+// element's load and add waited for one by one, 550 now.
 #pragma once
 
 #include "pwlq_prep.h"

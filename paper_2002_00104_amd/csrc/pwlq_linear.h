@@ -288,7 +288,8 @@ __global__ __launch_bounds__(kLinWG) void k_linear_wsum(const uint8_t *__restric
     int sums[kPlanes] = {};
     constexpr int kStep = 16 * 64, kAhead = 4;
     // kCount runs of 16 codes, all loads in flight first: a channel's wavefront waits for memory
-    // and little else (b = 4, us: K = 4096, 4096 channels 6.1 -> 4.8; K = 11008 11.6 -> 9.6)
+    // and little else (b = 4, us: K = 4096, 4096 channels 6.1 -> 4.8; K = 11008 11.6 -> 9.6).  A lane's last
+    // runs, up to three, are waited for one by one: up to K = 3072 that is all of them.
     const auto runs = [&](long long k0, auto count) {
         constexpr int kCount = decltype(count)::value;
         RawCodes<kBits> raw[kCount];
