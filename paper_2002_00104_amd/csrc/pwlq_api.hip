@@ -1031,8 +1031,8 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     g_launched.planes = planes;
     g_launched.row_tile = rs.tile;
     g_launched.row_mt = rs.mt;
-#define PWLQ_LINEAR_ROWS(B, P, T, MT)                                                              \
-    k_linear_rows<B, P, T, MT><<<row_grid, 64 * kRowWaves, 0, stream>>>(                           \
+#define PWLQ_LINEAR_ROWS(B, P, T, ...)                                                             \
+    k_linear_rows<B, P, T, __VA_ARGS__><<<row_grid, 64 * kRowWaves, 0, stream>>>(                  \
         xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, y, acc, rs.rows)
 #define PWLQ_LINEAR_CASE(B)                                                                       \
     case B:                                                                                        \
@@ -1040,6 +1040,8 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
             profile_mark(6, stream);                                                               \
             if (planes == 3) {                                                                     \
                 if (rs.tile == 16 && rs.mt == 1) PWLQ_LINEAR_ROWS(B, 3, 16, 1);                    \
+                else if (B == 4 && rs.tile == 16 && rs.mt == 2 && rs.tiles * rs.cols > kRows31WavesWgs) \
+                    PWLQ_LINEAR_ROWS(4, 3, 16, 2, kLookUps, kRows31Waves);                         \
                 else if (rs.tile == 16 && rs.mt == 2) PWLQ_LINEAR_ROWS(B, 3, 16, 2);               \
                 else if (rs.tile == 16) PWLQ_LINEAR_ROWS(B, 3, 16, 4);                             \
                 else if (rs.mt == 1) PWLQ_LINEAR_ROWS(B, 3, 32, 1);                                \
@@ -1049,6 +1051,8 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
                 else if (rs.tile == 16 && rs.mt == 2) PWLQ_LINEAR_ROWS(B, 2, 16, 2);               \
                 else if (rs.tile == 16) PWLQ_LINEAR_ROWS(B, 2, 16, 4);                             \
                 else if (rs.mt == 1) PWLQ_LINEAR_ROWS(B, 2, 32, 1);                                \
+                else if (B == 8 && K > kRows63BorrowsK && rs.tiles * rs.cols > 256)                \
+                    PWLQ_LINEAR_ROWS(8, 2, 32, 2, kBorrows);                                       \
                 else PWLQ_LINEAR_ROWS(B, 2, 32, 2);                                                \
             }                                                                                      \
             profile_mark(7, stream);                                                               \

@@ -217,15 +217,15 @@ __device__ inline uint32_t tail_mask(uint32_t f)
 //  - k_linear gains with the sums apart (4096^3, b = 5 -4 %, b = 6 -2 %) and at 8 bits, and loses in
 //    the folded form at five to seven (2048x1024x2048, b = 7, 22.8/23.8; 600x1040x3000, b = 5, 21.5/22.1);
 //  - k_linear_rows gains in 15 rows by 16 channels (8x4096x11008, b = 7, 16.3/15.2, b = 8, three sums, 14.8/13.7), and
-//    at 8 bits in all workgroups of 16 channels; elsewhere look-ups take 20 to 40 registers more, and may take a
-//    workgroup per CU (31x1024x5000, b = 6, three sums, 6.2/7.0), or gain nothing (63x4096x11008, b = 8, three sums, 41.0/42.6).
+//    at 8 bits but for 63 rows with the sums apart (63x4096x11008 41.0/42.6); elsewhere look-ups take 20 to 40 registers more,
+//    and may take a workgroup per CU (31x1024x5000, b = 6, three sums, 6.2/7.0).
 enum Decode { kBorrows, kBorrowsConst, kLookUps };        // (kBorrowsConst: `bits` an integral_constant)
 constexpr Decode linear_decode(int bits, int planes) { return bits <= 4 || bits == 8 || planes == 3 ? kLookUps : kBorrows; }
 constexpr Decode rows_decode(int bits, int planes, int tile, int mt)
 {
     const bool row15 = tile == 16 && mt == 1, row31 = tile == 16 && mt == 2, row63 = tile == 32 && mt == 2;
     if (bits <= 4) return kLookUps;
-    if (bits == 8) return row63 ? kBorrows : kLookUps;
+    if (bits == 8) return row63 && planes == 3 ? kBorrows : kLookUps;      // (planes == 2: see kRows63BorrowsK)
     if (planes == 2 && row15) return kLookUps;
     // b = 5, 6, 7, 31x4096x11008: kBorrows 20.7/21.6/23.2, kBorrowsConst 21.3/21.1/23.0, kLookUps 20.9/20.7/22.7;
     // 24x512x11008: 6.7/6.9/7.0, 6.7/6.9/6.8, 6.5/6.6/7.1; 31x1024x5000: 5.9/6.3/6.1, 6.1/6.4/6.0, 6.0/6.2/6.2
@@ -814,6 +814,14 @@ __device__ inline void row_load_part(RowStage<kBits> &st, const uint8_t *__restr
     }
 }
 
+// 63 rows by 32 channels at 8 bits, y alone: past one workgroup per CU and this K, where the memory they share is what
+// they wait for, borrows (us, borrows / look-ups: 1245x4160x448, 280 workgroups, 34.5/35.6; 63x4160x11008, 344, 34.9/37.3;
+// but 41x2080x5106, 160, 10.2/9.8; 1245x4160x256, 160, 22.6/21.5; 126x1536x5106, 320, 14.0/14.1).
+constexpr int kRows63BorrowsK = 2048;
+// 31 rows by 16 channels at 4 bits, three planes: by itself the compiler takes 87 registers, two workgroups per CU.  Past
+// those, 80 and three (us, 87 / 80: 24x512x11008, 688 workgroups, 6.5/5.4; 16x2080x8566, 536, 9.6/8.3; but 16x8192x2500, 157, 10.4/11.2).
+constexpr int kRows31Waves = 6, kRows31WavesWgs = 512;
+
 // The operand planes of run p (0..3, 16 weights) of a stage.
 template <int kBits, int kPlanes, Decode kDecode>
 __device__ inline void row_planes(const RowStage<kBits> &st, int p, v4i (&b)[kPlanes])
@@ -846,10 +854,9 @@ __device__ inline void row_planes(const RowStage<kBits> &st, int p, v4i (&b)[kPl
 
 // A workgroup's rows: [row0, row0 + rows), rows < kTile kMT; row `rows` of its tile is
 // the row of ones.
-// (b = 4, three planes, 31 rows: 80 registers, so that a CU holds three workgroups; by itself the compiler takes 87 and two:
-// 24x512x11008 5.7 us by borrows, 6.5 by look-ups, 5.4 with the bound.)
-template <int kBits, int kPlanes, int kTile, int kMT>
-__global__ __launch_bounds__(64 * kRowWaves, kBits == 4 && kPlanes == 3 && kTile == 16 && kMT == 2 ? 6 : 1) void k_linear_rows(
+// kWaves: wavefronts per SIMD that the registers have to leave room for.
+template <int kBits, int kPlanes, int kTile, int kMT, Decode kDecode = rows_decode(kBits, kPlanes, kTile, kMT), int kWaves = 1>
+__global__ __launch_bounds__(64 * kRowWaves, kWaves) void k_linear_rows(
     const int8_t *__restrict__ xq, long long M, long long K, float s_x, float z_x,
     const uint8_t *__restrict__ pcodes, const uint8_t *__restrict__ pflags, long long N,
     const float *__restrict__ p, const float *__restrict__ m, float *__restrict__ y,
@@ -891,7 +898,7 @@ __global__ __launch_bounds__(64 * kRowWaves, kBits == 4 && kPlanes == 3 && kTile
     v4i a[kMT][4];
     auto products = [&](const RowStage<kBits> &st, int s) {
         v4i b[kPlanes];
-        row_planes<kBits, kPlanes, rows_decode(kBits, kPlanes, kTile, kMT)>(st, s, b);
+        row_planes<kBits, kPlanes, kDecode>(st, s, b);
 #pragma unroll
         for (int mt = 0; mt < kMT; ++mt) {
             v4i x = a[mt][s];

@@ -27,6 +27,19 @@ def test_tile_edges_of_63_rows_by_32_channels(P, M, K, N, bits):  # noqa: F811
     assert P.last_kernels() == f"k_linear_rows<{bits}, 2, 32, 2>"
 
 
+@pytest.mark.parametrize("M,N", [(16, 8192), (31, 8193), (31, 11007)])
+def test_either_side_of_three_workgroups_per_cu(P, M, N):  # noqa: F811
+    """At 4 bits, 31 rows by 16 channels and the sums apart: other registers past 512 workgroups."""
+    case(P, M, 528, N, 4, seed=M + N, check_rows=np.array([0, M // 2, M - 1]))
+
+
+@pytest.mark.parametrize("M,K,N", [(63, 2064, 8193), (63, 2064, 8177), (63, 2048, 8193)])
+def test_eight_bits_by_borrows_and_by_look_ups(P, M, K, N):  # noqa: F811
+    """Past 256 workgroups and K = 2048 codes are decoded by borrows."""
+    case(P, M, K, N, 8, seed=K + N, check_rows=np.array([0, 31, 32, 62]))
+    assert P.last_kernels() == "k_linear_rows<8, 2, 32, 2>"
+
+
 @pytest.mark.parametrize("extra", range(16, 257, 48))
 def test_what_is_left_of_a_step(P, extra):  # noqa: F811
     for M in (9, 20, 40):
