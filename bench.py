@@ -448,6 +448,7 @@ def main() -> int:
                 pwlq.profile_enable(0)
                 lm = float(np.mean(lin_ms))
                 return {
+                    "kernel": pwlq.last_kernels(),
                     "planes": planes,
                     "kernel_ms": lm,
                     "achieved": planes * ops / (lm * 1e-3) / 1e12,
@@ -460,7 +461,6 @@ def main() -> int:
             y_folded = y_lin.clone()
             apart = time_linear((y_lin, sums_lin), 3)
             result["linear_i8"] = {
-                "kernel": pwlq.kernel_name(3),
                 "shape": f"xq [{Ml},{Kl}] int8 x packed PWLQ weight [{Nl},{Kl}], b={bl}",
                 "bound": "mfma",
                 "peak": 5000.0,

@@ -42,7 +42,7 @@ const char *pwlq_last_search_kernel(void);
  * to evaluate candidates or to multiply, in order, with a space between: "k_small";
  * "k_fast<T>" per launch of T threads to a tile, and "k_search" or "k_search_sliced(S)",
  * a tile in S slices; "k_linear_rows<bits, planes, tile, row tiles>",
- * "k_linear_split<bits>" or "k_linear<bits, planes>".  The text is the thread's own and
+ * "k_linear_split<bits>", "k_linear_wide<bits>" or "k_linear<bits, planes>".  The text is the thread's own and
  * valid until its next such call. */
 const char *pwlq_last_kernels(void);
 
@@ -56,7 +56,7 @@ int pwlq_set_small_call_tiles(int tiles);
 
 /* What the names of the library's kernels begin with in a kernel trace, by role:
  * 0 search (dominant; also k_search_sliced), 1 quantize, 2 prefix-sum evaluation,
- * 3 integer inner product (also k_linear_rows and k_linear_split).  Returns NULL for
+ * 3 integer inner product (also k_linear_rows, k_linear_split and k_linear_wide).  Returns NULL for
  * other roles. */
 const char *pwlq_kernel_name(int role);
 

@@ -30,7 +30,7 @@ thread_local long long g_last_tiles = 0, g_last_groups = 0, g_last_units = 0;
 thread_local const char *g_last_search_kernel = "k_search";
 // What the thread's last search or inner product launched, for pwlq_last_kernels.
 struct Launched {
-    enum { kNone, kSmall, kSearch, kLinearRows, kLinearSplit, kLinear } what = kNone;
+    enum { kNone, kSmall, kSearch, kLinearRows, kLinearSplit, kLinearWide, kLinear } what = kNone;
     int fast_threads[4] = {};      // workgroup sizes of the k_fast launches, in order
     int n_fast = 0;
     int slices = 0;                // of k_search_sliced; 1: k_search; 0: neither
@@ -980,6 +980,26 @@ RowShape smaller_row_shape(const RowShape &rs, long long M, long long K, long lo
     return wgs(c) < 256 && (M * K <= 4 << 20 || (bits == 8 && planes == 2)) ? c : rs;
 }
 
+// Whether a call of y alone goes to k_linear_wide: its estimated time (us) against k_linear's, from 455 calls of 65 to
+// 4096 rows and 100 to 1500 tiles of 256 x 128.  Both pay per pass over the chip, of 256 workgroups (k_linear: half a pass;
+// `xcd_wgs` of its workgroups are on the fullest XCD), for its start, its end and the reduction; and per tile for y, k_linear_wide
+// more of it where rows of y are no whole vectors.  Taken so, the calls' mean is 0.871 of the time by k_linear and k_linear_split (0.866 if
+// the faster one were known each time; the worst 1.19 times the faster one's): 1024x2064x8000 60.6/40.8, 4096x4096x5500 212/166,
+// 100x4096x30000 91/58, but 1300x1024x3100, where 130 tiles of 256 rows are half a pass, 27/26, 4096x272x11008 64/70, 4096x64x3001
+// 18.7/23.9.  Below 100 tiles most of its CUs are idle (2048x4096x1600, 104 tiles, 49/54; 768x4096x2048, 48, 33/52), and
+// k_linear_split, which has at most 384 workgroups, is beaten from 129 tiles on (128x4096x17000 60.1/55.5; 2600x4096x1000, 88
+// tiles, 50/54).  A quarter of a tile's rows, or less, is left to k_linear, and so are the
+// shortest reductions past one pass, which are their output (2048x64x11008 26.7/27.9).
+bool linear_wide(long long M, long long K, long long N, long long tiles, long long xcd_wgs, bool can_split)
+{
+    if (M <= kLinWideBM / 4 || tiles < (can_split ? 129 : 100) || (tiles > 256 && K < 128)) return false;
+    const auto passes = [](long long wgs, int per) { return (double)((wgs + per - 1) / per); };
+    const double k = (double)K / 1000.0;
+    const double wide = 3.5 + passes((tiles + 7) / 8, 32) * (3.9 + 12.2 * k) + (N % 4 ? 6.8 : 3.9) * (double)tiles / 256.0;
+    const double tall = 9.9 + 2.7 * passes(xcd_wgs, 64) + 8.35 * passes(xcd_wgs, 32) * k + 2.3 * (double)xcd_wgs / 64.0;
+    return wide < tall;
+}
+
 int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
                const uint8_t *packed_codes, const uint8_t *packed_flags, int64_t N, int bits,
                const float *p, const float *m, float *y, int32_t *acc, void *workspace,
@@ -1018,15 +1038,23 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     const long long split_m = (M + kSplitBM - 1) / kSplitBM, split_wgs = 8 * tn_per_xcd * split_m;
     const bool can_split = planes == 2 && K % (2 * kLinBK) == 0 && K >= kSplitMinK && split_wgs <= kSplitMaxWgs;
     const bool by_rows = linear_by_rows(planes, bits, K, rs.cap, rs.tiles, rs.cols, rs.rows, can_split);
-    const bool by_split = !by_rows && can_split;
+    LinWideTiles wide;
+    wide.rows = (int)((M + kLinWideBM - 1) / kLinWideBM);
+    wide.chans = (int)((N + kLinWideBN - 1) / kLinWideBN);
+    wide.cols = (wide.chans + 7) / 8;
+    const long long wide_tiles = (long long)wide.rows * wide.chans;
+    const bool by_wide = planes == 2 && !by_rows && wide_tiles <= kLinWideMaxTiles &&
+                         linear_wide(M, K, N, wide_tiles, tn_per_xcd * tiles_m, can_split);
+    const bool by_split = !by_rows && !by_wide && can_split;
     if (by_rows) rs = smaller_row_shape(rs, M, K, N, bits, planes);
     const dim3 row_grid((unsigned)rs.cols, (unsigned)rs.tiles);
     if (by_rows ? !launch_fits(rs.cols, 64 * kRowWaves)
+        : by_wide ? !launch_fits(wide_tiles + 7, kLinWideWG)
                 : !launch_fits(wgs, kLinWG) || !launch_fits((N + kLinWG / 64 - 1) / (kLinWG / 64), kLinWG))
         return fail(PWLQ_EINVAL, "grid too large");
     hipStream_t stream = (hipStream_t)stream_v;
     g_launched = Launched();
-    g_launched.what = by_rows ? Launched::kLinearRows : by_split ? Launched::kLinearSplit : Launched::kLinear;
+    g_launched.what = by_rows ? Launched::kLinearRows : by_wide ? Launched::kLinearWide : by_split ? Launched::kLinearSplit : Launched::kLinear;
     g_launched.bits = bits;
     g_launched.planes = planes;
     g_launched.row_tile = rs.tile;
@@ -1055,6 +1083,13 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
                     PWLQ_LINEAR_ROWS(8, 2, 32, 2, kBorrows);                                       \
                 else PWLQ_LINEAR_ROWS(B, 2, 32, 2);                                                \
             }                                                                                      \
+            profile_mark(7, stream);                                                               \
+            break;                                                                                 \
+        }                                                                                          \
+        if (by_wide) {                                                                             \
+            profile_mark(6, stream);                                                               \
+            k_linear_wide<B><<<(unsigned)((wide_tiles + 7) / 8 * 8), kLinWideWG, 0, stream>>>(        \
+                xq, M, K, s_x, z_x, packed_codes, packed_flags, N, p, m, y, wide);                 \
             profile_mark(7, stream);                                                               \
             break;                                                                                 \
         }                                                                                          \
@@ -1389,6 +1424,7 @@ const char *pwlq_last_kernels(void)
             snprintf(text, room, "k_linear_rows<%d, %d, %d, %d>", l.bits, l.planes, l.row_tile, l.row_mt);
             break;
         case Launched::kLinearSplit: snprintf(text, room, "k_linear_split<%d>", l.bits); break;
+        case Launched::kLinearWide: snprintf(text, room, "k_linear_wide<%d>", l.bits); break;
         case Launched::kLinear: snprintf(text, room, "k_linear<%d, %d>", l.bits, l.planes); break;
     }
     return text;

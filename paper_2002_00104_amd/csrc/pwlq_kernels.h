@@ -28,8 +28,8 @@
 // magnitudes) and k_select (one thread per group solves for p); the error at a
 // given (m, p) runs k_mse_tile and, for groups of several tiles, k_mse_final.
 //
-// The inner product runs k_linear_wsum and k_linear (k_linear_split
-// for tiles that do not fill the chip), or k_linear_rows for few rows.
+// The inner product runs k_linear_wide for many tiles of y alone, k_linear_rows for few rows, else
+// k_linear_wsum and k_linear (k_linear_split for tiles that do not fill the chip).
 #pragma once
 
 #include "pwlq_prep.h"
@@ -39,4 +39,5 @@
 #include "pwlq_select.h"
 #include "pwlq_fast.h"
 #include "pwlq_linear.h"
+#include "pwlq_linear_wide.h"
 #include "pwlq_small.h"
