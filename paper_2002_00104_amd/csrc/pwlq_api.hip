@@ -56,6 +56,7 @@ struct Plan {
     std::vector<int> tile_prefix, group_prefix, unit_prefix, mgroup_prefix, emit_prefix;
     int nt = 0;
     long long n_tiles = 0, n_groups = 0, n_units = 0, n_mgroups = 0, n_chunks = 0;
+    long long n_all_units = 0;     // n_units if k_fast took no tiles
     int n = 0, nblk = 0;
     // workspace offsets in bytes
     size_t off_recs = 0, off_prefix = 0, off_tile_max = 0, off_gm = 0, off_offsets = 0,
@@ -231,7 +232,6 @@ int build_plan(Plan &pl, const pwlq_tensor_desc *desc, int n_tensors, int n_cand
         r.ngroups = (int)groups;
         r.ntiles = (int)(groups * tpg);
         r.stride = (r.tile_len + kVec - 1) / kVec * kVec + kVec;   // one spare vector: loads may run one ahead
-        r.tpu = std::max(1, kUnitElems / r.tile_len);
         tmp[i] = r;
         order[i] = {i, r.tile_len};
     }
@@ -240,19 +240,28 @@ int build_plan(Plan &pl, const pwlq_tensor_desc *desc, int n_tensors, int n_cand
         for (TensorRec &r : tmp) r.fast = r.tile_len >= min_len ? 1 : 0;
     }
     // a search workgroup walks tpu tiles one after the other; keep enough
-    // workgroups to fill the chip when the call is small
-    {
-        long long total_tiles = 0;
-        for (const TensorRec &r : tmp) total_tiles += r.ntiles;
+    // workgroups to fill the chip when the call is small.  Tiles that k_fast evaluates are in no unit.
+    const auto size_units = [&](bool all) {
+        long long total_tiles = 0, tiny_tiles = 0, units = 0;
+        const auto tiny = [](const TensorRec &r) { return r.tile_len <= kTinyTile && r.tpg == 1; };
+        for (const TensorRec &r : tmp)
+            if (all || !r.fast) {
+                total_tiles += r.ntiles;
+                if (tiny(r)) tiny_tiles += r.ntiles;
+            }
         const int cap = (int)std::max(1LL, total_tiles / kMinUnits);
         // tiles of at most kTinyTile elements cost a unit little each (no offsets, loads one
         // tile ahead): up to kTinyUnit per unit while they still make about a thousand units
-        long long tiny_tiles = 0;
-        for (const TensorRec &r : tmp) if (r.tile_len <= kTinyTile && r.tpg == 1) tiny_tiles += r.ntiles;
         const int tiny_cap = (int)std::min((long long)kTinyUnit, std::max((long long)cap, tiny_tiles / 1024));
         for (TensorRec &r : tmp)
-            r.tpu = std::min(r.tpu, (r.tile_len <= kTinyTile && r.tpg == 1) ? tiny_cap : cap);
-    }
+            if (all || !r.fast) {
+                r.tpu = std::min(std::max(1, kUnitElems / r.tile_len), tiny(r) ? tiny_cap : cap);
+                units += (r.ntiles + r.tpu - 1) / r.tpu;
+            }
+        return units;
+    };
+    pl.n_all_units = size_units(true);
+    if (fast_bits > 0) size_units(false);
     // longest tiles first: the search kernel's workgroups are dispatched in
     // index order, so the big items start early and the small ones fill gaps
     // (selectors and error: of these, the groups of most tiles in front)
@@ -284,7 +293,7 @@ int build_plan(Plan &pl, const pwlq_tensor_desc *desc, int n_tensors, int n_cand
         chunks += ((long long)r.ngroups * r.gcount + kEmitChunk - 1) / kEmitChunk;
         tiles += r.ntiles;
         groups += r.ngroups;
-        units += (r.ntiles + r.tpu - 1) / r.tpu;
+        if (!r.fast) units += (r.ntiles + r.tpu - 1) / r.tpu;
         if (r.tpg > 1) { mgroups += r.ngroups; parts += r.ntiles; }
         if (!r.fast) sorted += (long long)r.ntiles * r.stride;
         if (tiles > 0x3fffffffLL || units > 0x3fffffffLL || chunks > 0x3fffffffLL)
@@ -508,13 +517,18 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     if (rc) return rc;
     // every limit is checked before the first launch: a failing call enqueues nothing
     const int ny = (pl.nblk + kSearchWaves - 1) / kSearchWaves;
-    int bpw_log2 = 0;                      // candidate blocks per unit in a workgroup, as a power of two
-    while ((1 << bpw_log2) < std::min(pl.nblk, kSearchWaves)) ++bpw_log2;
-    // ... but a small call keeps one unit per workgroup rather than a handful of workgroups
-    while (bpw_log2 < 4 && pl.n_units / (kSearchWaves >> bpw_log2) < 2048) ++bpw_log2;
-    const int upw = kSearchWaves >> bpw_log2;       // units per workgroup
-    const long long unit_groups = (pl.n_units + upw - 1) / upw;
-    const long long wgs = (unit_groups + 7) / 8 * 8 * ny;
+    int bpw_log2 = 0, upw = 1;             // candidate blocks per unit in a workgroup, as a power of two; units per workgroup
+    const auto search_wgs = [&](long long units) {
+        bpw_log2 = 0;
+        while ((1 << bpw_log2) < std::min(pl.nblk, kSearchWaves)) ++bpw_log2;
+        // ... but a small call keeps one unit per workgroup rather than a handful of workgroups
+        while (bpw_log2 < 4 && units / (kSearchWaves >> bpw_log2) < 2048) ++bpw_log2;
+        upw = kSearchWaves >> bpw_log2;
+        const long long unit_groups = (units + upw - 1) / upw;
+        return (unit_groups + 7) / 8 * 8 * ny;
+    };
+    // (a fast search is refused where the exhaustive one of the same tensors would be)
+    const long long all_wgs = search_wgs(pl.n_all_units), wgs = search_wgs(pl.n_units);
     // Too few wavefronts to keep the SIMDs busy: the tiles' elements are cut into slices.  With
     // 16 candidate blocks or more k_search's workgroups are full without slices, and those
     // past 2048 wavefronts gain only on long tiles (n = 4000, 4032 wavefronts, us, one / two
@@ -557,7 +571,7 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     if (pl.n_mgroups == 0 && nt_large > 0 && nt_small > 0)
         for (const TensorRec &r : pl.recs)
             if (r.tile_len <= kSmallTile && r.tile_len > 512) nt_mid += r.ntiles;
-    if ((fast_tiles < NT && slices == 1 && !launch_fits(wgs, kSearchWaves * 64)) || !launch_fits(nt_small, 64) ||
+    if ((fast_tiles < NT && slices == 1 && !launch_fits(std::max(wgs, all_wgs), kSearchWaves * 64)) || !launch_fits(nt_small, 64) ||
         (longest > kSmallTile && !launch_fits(nt_large, pl.fine && longest > 256 * 16 ? 512 : kWG)) ||
         !launch_fits(nt_large + nt_mid, 128))
         return fail(PWLQ_EINVAL, "search grid too large");
@@ -644,37 +658,39 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     if (fast_tiles < NT) {
         auto stage_bytes = [](int len) { return sizeof(float) * (size_t)((len + kVec - 1) / kVec * kVec); };
         const int nb2 = (pl.nblk + 1) / 2;
-        const bool large = nt_large > 0 && (longest > kSmallTile || nt_small == 0);
-        const bool small = nt_small > 0 && longest_small > 0;
+        // tiles that are not k_fast's, which come first
+        const int large0 = std::min(fast_tiles, nt_large), small0 = std::max(fast_tiles, nt_large);
+        const int n_large = nt_large - large0, n_small = NT - small0;
+        const bool large = n_large > 0, small = n_small > 0;
         // long tiles are ordered by candidate (one bin per candidate and the switch
         // positions written out: worth it only where buckets can be long), short
         // ones by block of 64 candidates
         if (pl.fine) {
             if (large) {    // 512 threads x 16 elements: 256 x 32 measured 7-27 % slower, 1024 x 8 slower still
                 if (longest <= 256 * 16)    // tiles of at most 4096 elements: smaller workgroups, twice as many in flight
-                    k_prep<false, true, 256, 16><<<nt_large, 256, sizeof(int) * n_cand + stage_bytes(longest), stream>>>(
-                        tb, 0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
+                    k_prep<false, true, 256, 16><<<n_large, 256, sizeof(int) * n_cand + stage_bytes(longest), stream>>>(
+                        tb, large0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
                 else
-                    k_prep<false, true, 512, 16><<<nt_large, 512, sizeof(int) * n_cand + stage_bytes(longest), stream>>>(
-                        tb, 0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
+                    k_prep<false, true, 512, 16><<<n_large, 512, sizeof(int) * n_cand + stage_bytes(longest), stream>>>(
+                        tb, large0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
             }
             if (small)
-                k_prep<true, false, 64, kSmallPer><<<nt_small, 64, sizeof(int) * nb2 * 64 + stage_bytes(longest_small), stream>>>(
-                    tb, nt_large, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
+                k_prep<true, false, 64, kSmallPer><<<n_small, 64, sizeof(int) * nb2 * 64 + stage_bytes(longest_small), stream>>>(
+                    tb, small0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
         } else if (pl.nblk <= 32) {
             if (large)
-                k_prep<true, false, kWG, kPerThread><<<nt_large, kWG, sizeof(int) * nb2 * kWG + stage_bytes(longest), stream>>>(
-                    tb, 0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
+                k_prep<true, false, kWG, kPerThread><<<n_large, kWG, sizeof(int) * nb2 * kWG + stage_bytes(longest), stream>>>(
+                    tb, large0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
             if (small)
-                k_prep<true, false, 64, kSmallPer><<<nt_small, 64, sizeof(int) * nb2 * 64 + stage_bytes(longest_small), stream>>>(
-                    tb, nt_large, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
+                k_prep<true, false, 64, kSmallPer><<<n_small, 64, sizeof(int) * nb2 * 64 + stage_bytes(longest_small), stream>>>(
+                    tb, small0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
         } else {
             if (large)
-                k_prep<false, false, kWG, kPerThread><<<nt_large, kWG, sizeof(int) * pl.nblk + stage_bytes(longest), stream>>>(
-                    tb, 0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
+                k_prep<false, false, kWG, kPerThread><<<n_large, kWG, sizeof(int) * pl.nblk + stage_bytes(longest), stream>>>(
+                    tb, large0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
             if (small)
-                k_prep<false, false, 64, kSmallPer><<<nt_small, 64, sizeof(int) * pl.nblk + stage_bytes(longest_small), stream>>>(
-                    tb, nt_large, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
+                k_prep<false, false, 64, kSmallPer><<<n_small, 64, sizeof(int) * pl.nblk + stage_bytes(longest_small), stream>>>(
+                    tb, small0, n_cand, pl.nblk, tile_max, gm, offsets, fine, sorted);
         }
         profile_mark(0, stream);
         launched.slices = slices;

@@ -102,7 +102,6 @@ __global__ __launch_bounds__(kT) void k_prep(Tables tb, int tile_begin, int n, i
     const int wave = tid >> 6;
     TensorRec r;
     TileInfo ti = tile_of(tb, tile_begin + blockIdx.x, r, t);
-    if (r.fast) return;               // evaluated by k_fast
     const int len = ti.len;
 
     float a[kPer];

@@ -188,7 +188,6 @@ __global__ __launch_bounds__(kSearchWaves * 64) void k_search(Tables tb, int n, 
 
     const int tensor = find_tensor(tb.unit_prefix, tb.nt, unit);
     const TensorRec r = rec_of(tb, tensor);
-    if (r.fast) return;               // evaluated by k_fast
     int first = r.tile_base + (unit - r.unit_base) * r.tpu;
     int last = first + r.tpu;
     if (last > r.tile_base + r.ntiles) last = r.tile_base + r.ntiles;
@@ -286,7 +285,6 @@ __global__ __launch_bounds__(kSearchWaves * 64) void k_search_sliced(Tables tb, 
     const int j = (blockIdx.x - unit * ny) * bw + jb;
     const int tensor = find_tensor(tb.unit_prefix, tb.nt, unit);
     const TensorRec r = rec_of(tb, tensor);
-    if (r.fast) return;               // evaluated by k_fast
     const int t = slot_to_tile(r, r.tile_base + unit - r.unit_base);      // one tile per unit
     int k = j * kBlk + lane + 1;
     const bool live = k <= n;
