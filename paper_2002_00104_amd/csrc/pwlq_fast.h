@@ -45,6 +45,8 @@
 // element's load and add waited for one by one, 550 now.
 #pragma once
 
+#include <type_traits>
+
 #include "pwlq_prep.h"
 #include "pwlq_refine.h"
 #include "pwlq_tables.h"
@@ -448,6 +450,22 @@ inline FastUnits fast_units(int n, int bits)
     return f;
 }
 
+// The elements of a thread in batches, e0 .. e0 + count - 1: batch(first, count), both compile-time.  What a wavefront does with
+// a batch depends on whether the tile ends in it: batches are as many as the tiles of a launch's range end in
+// usefully, and no longer than the LDS adds that a thread can hold in flight within 64 registers.
+template <int kPer, typename F>
+__device__ inline void fast_batches(F batch)
+{
+    static_assert(kPer == 2 || kPer == 4 || kPer == 8 || kPer == 10, "no batches for this many");
+    const auto call = [&](auto e0, auto count) { batch(e0, count); };
+#define PWLQ_BATCH(E, C) call(std::integral_constant<int, E>(), std::integral_constant<int, C>())
+    if constexpr (kPer == 2) { PWLQ_BATCH(0, 1); PWLQ_BATCH(1, 1); }
+    if constexpr (kPer == 4) { PWLQ_BATCH(0, 2); PWLQ_BATCH(2, 2); }
+    if constexpr (kPer == 8) { PWLQ_BATCH(0, 4); PWLQ_BATCH(4, 4); }
+    if constexpr (kPer == 10) { PWLQ_BATCH(0, 5); PWLQ_BATCH(5, 3); PWLQ_BATCH(8, 2); }
+#undef PWLQ_BATCH
+}
+
 template <int kT, int kPer>
 __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n, int bits, FastUnits F,
                                              const float *__restrict__ tile_max,
@@ -456,7 +474,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
 {
     // dynamic LDS: the buckets' words (first the counts and sums of the buckets
     // themselves, then of everything before them), then the grouped elements
-    extern __shared__ unsigned long long fast_lds[];
+    extern __shared__ __attribute__((aligned(16))) unsigned long long fast_lds[];
     constexpr int kW = kT / 64;
     constexpr int kScan = ((kFastOct << fast_octave_bits(kT * kPer)) + kT - 1) / kT;   // words a thread holds at most
     __shared__ unsigned redm[kW];
@@ -476,27 +494,60 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     const int len = ti.len;
     const int Li = (1 << (bits - 1)) - 1;
 
+    // Whether the wavefront has elements in a batch, and whether all of its lanes have all of them: no
+    // lane of a whole batch looks at the length (half of the instructions of a thread's 8 elements did).
+    const int wave_end = len - wave * 64;                  // elements from the wavefront's first on
+    const auto none = [&](int e0) { return e0 * kT >= wave_end; };
+    const auto all = [&](int e0, int count) { return (e0 + count - 1) * kT + 64 <= wave_end; };
+
+    // No load depends on the length: past the end it reads the tile's last element.
     float a[kPer];
-    load_magnitudes<kT>(ti.src, len, a);
+    {
+        const GlobalFloat *src = (const GlobalFloat *)ti.src;
+        const unsigned last = (unsigned)len - 1u;
+        fast_batches<kPer>([&](auto first, auto count) {
+            constexpr int e0 = decltype(first)::value, e1 = e0 + decltype(count)::value;
+            if (none(e0)) {
+#pragma unroll
+                for (int e = e0; e < e1; ++e) a[e] = 0.0f;
+            } else if (all(e0, e1 - e0)) {
+#pragma unroll
+                for (int e = e0; e < e1; ++e) a[e] = (src + e * kT)[(unsigned)tid];
+            } else {
+#pragma unroll
+                for (int e = e0; e < e1; ++e) a[e] = src[tid + e * kT < last ? tid + e * kT : last];
+            }
+        });
+    }
     if (tid == 0) {
         pruned.least = 0x7f800000u;
         pruned.listed = pruned.kept = 0;
     }
     int obits = fast_octave_bits(len);
     const int T = kFastOct << obits;
-    for (int i = tid; i < T; i += kT) fast_lds[i] = 0ull;
+    for (int i = tid; i < T / 2; i += kT) reinterpret_cast<ulonglong2 *>(fast_lds)[i] = make_ulonglong2(0ull, 0ull);
 
     // group absmax: from the registers (single-tile group) or the tile maxima; the
     // tile's mean magnitude places the buckets.  Binary32 patterns of magnitudes are in the
     // magnitudes' order, NaN above infinity.
     unsigned mb = 0;
     float sum = 0.0f;
+    fast_batches<kPer>([&](auto first, auto count) {
+        constexpr int e0 = decltype(first)::value, e1 = e0 + decltype(count)::value;
+        if (none(e0)) return;
+        if (!all(e0, e1 - e0)) {
+            asm volatile("");                                  // a branch: not a choice for every element of every batch
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        const unsigned ab = __float_as_uint(a[e]);
-        mb = ab > mb ? ab : mb;
-        sum += a[e];
-    }
+            for (int e = e0; e < e1; ++e) a[e] = tid + e * kT < len ? a[e] : 0.0f;
+        }
+#pragma unroll
+        for (int e = e0; e < e1; ++e) {
+            a[e] = fabsf(a[e]);
+            const unsigned ab = __float_as_uint(a[e]);
+            mb = ab > mb ? ab : mb;
+            sum += a[e];
+        }
+    });
     if (r.tpg > 1) {
         const int tile0 = r.tile_base + ti.group_local * r.tpg;
         for (int j = tid; j < r.tpg; j += kT) {
@@ -548,38 +599,58 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     // 2^52 + a scale, rounded once, holds the whole number in its low word: at most top, since
     // a <= m and scale is within 2^-53 of top / m
     const double one52 = 4503599627370496.0, full52 = one52 + (double)F.top;
-    // kBatch adds are in flight before the first result is looked at: one at a time, under a
+    // A batch's adds are in flight before the first result is looked at: one at a time, under a
     // branch, a thread waits out the LDS for each of its elements (more at once: past 64
-    // registers).  So zero elements and threads past the end add nothing to a word of their own.
-    constexpr int kBatch = kPer % 5 == 0 ? 5 : kPer < 4 ? kPer : 4;
-    static_assert(kPer % kBatch == 0 && 64 <= kFastOct << 5, "whole batches; a word for every lane");
+    // registers).  So zero elements and threads past the end add nothing to a word of their own; where a
+    // wavefront has neither in a batch, it does without the choice.
+    static_assert(64 <= kFastOct << 5, "a word for every lane");
     const float past = usable ? m : 0.0f;                      // counts as m: nothing in A
+    unsigned some_zero = 0;                                    // batches, by their first element, in which the wavefront has zeros
+    typedef __attribute__((address_space(3))) unsigned long long WordLds;
+    fast_batches<kPer>([&](auto first, auto count) {
+        constexpr int e0 = decltype(first)::value, kCount = decltype(count)::value;
+        if (none(e0)) return;
+        const bool whole = all(e0, kCount);
+        if (!whole) {
+            asm volatile("");                                  // a branch: not a choice for every element of every batch
 #pragma unroll
-    for (int e0 = 0; e0 < kPer; e0 += kBatch) {
+            for (int e = e0; e < e0 + kCount; ++e) a[e] = tid + e * kT < len ? a[e] : past;
+        }
+        unsigned least = ~0u;
 #pragma unroll
-        for (int e = e0; e < e0 + kBatch; ++e) { v[e] = low; rank[e] = 0; }
-        if (e0 * kT >= len) continue;                          // the same in every thread
-        unsigned long long was[kBatch];
-#pragma unroll
-        for (int x = 0; x < kBatch; ++x) {
-            const int e = e0 + x;
-            const bool within = tid + e * kT < len;
-            const double whole = __builtin_fma((double)(within ? a[e] : past), scale, one52);
-            const double d = full52 - whole;                   // exact
+        for (int e = e0; e < e0 + kCount; ++e) {
+            const double w = __builtin_fma((double)a[e], scale, one52);
+            const double d = full52 - w;                       // exact
             A = __builtin_fma(d, d, A);
-            const unsigned u = within ? (unsigned)__double2loint(whole) : 0u;
+            const unsigned u = (unsigned)__double2loint(w);
             v[e] = u + low;
-            const unsigned at = u > 0 ? fast_bucket(v[e], Q.shift) - bucket0 : (unsigned)lane;
-            was[x] = atomicAdd(&fast_lds[at], ((unsigned long long)(u > 0 ? 1u << (kFastSumBits - 32) : 0u) << 32) |
-                                                  (u > 0 ? v[e] : 0u));
+            least = u < least ? u : least;
+        }
+        const bool zeros = __ballot(least == 0u) != 0ull;
+        unsigned long long was[kCount];
+        if (whole && !zeros) {
+#pragma unroll
+            for (int x = 0; x < kCount; ++x)
+                was[x] = __hip_atomic_fetch_add((WordLds *)(uintptr_t)((fast_bucket(v[e0 + x], Q.shift) << 3) + Q.words),
+                                                (1ull << kFastSumBits) | v[e0 + x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else {
+            some_zero |= 1u << e0;
+#pragma unroll
+            for (int x = 0; x < kCount; ++x) {
+                const int e = e0 + x;
+                const bool counts = tid + e * kT < len && v[e] > low;
+                v[e] = counts ? v[e] : low;
+                const unsigned at = counts ? fast_bucket(v[e], Q.shift) - bucket0 : (unsigned)lane;
+                was[x] = atomicAdd(&fast_lds[at], counts ? (1ull << kFastSumBits) | v[e] : 0ull);
+            }
         }
 #pragma unroll
-        for (int x = 0; x < kBatch; ++x) {
+        for (int x = 0; x < kCount; ++x) {
             rank[e0 + x] = (unsigned)(was[x] >> kFastSumBits);
             asm volatile("" : "+v"(rank[e0 + x]));             // here, not where it is used: half the registers
         }
         __builtin_amdgcn_sched_barrier(0);
-    }
+    });
     A = wave_sum(A);
     __syncthreads();
 
@@ -606,16 +677,17 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
                          (__ballot(fullest > (unsigned)crowd) != 0ull ? 4 : 0);
         if (lane == 63) { wsum[wave] = incl; wfull[wave] = over; redA[wave] = A; }
         __syncthreads();
-        unsigned long long run = incl - tot;
-#pragma unroll 8
+        // (sums that are the same in every lane, in scalar registers)
+        unsigned long long before = 0;
+#pragma unroll
         for (int i = 0; i < kW; ++i) {
-            const unsigned long long s = wsum[i];
+            const unsigned long long s = (unsigned long long)uni((long long)wsum[i]);
             zeros -= (int)(s >> kFastSumBits);
-            run += i < wave ? s : 0ull;
+            before += i < wave ? s : 0ull;
         }
         // the zero elements come before everything
-        zeros = uni(zeros);
-        run += ((unsigned long long)zeros << kFastSumBits) + (unsigned long long)zeros * low;
+        before += ((unsigned long long)zeros << kFastSumBits) + (unsigned long long)zeros * low;
+        unsigned long long run = incl - tot + before;
         if (holds) {
 #pragma unroll
             for (int x = 0; x < kScan; ++x) {
@@ -637,17 +709,18 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     __syncthreads();
     unsigned *elems = reinterpret_cast<unsigned *>(fast_lds + T);
     Q.elems = (FastElemLds *)elems - zeros;
+    fast_batches<kPer>([&](auto first, auto count) {
+        constexpr int e0 = decltype(first)::value, kCount = decltype(count)::value;
+        if (none(e0)) return;
+        unsigned at[kCount];
 #pragma unroll
-    for (int e0 = 0; e0 < kPer; e0 += kBatch) {
-        if (e0 * kT >= len) continue;
-        unsigned at[kBatch];
+        for (int x = 0; x < kCount; ++x) at[x] = fast_word(Q, v[e0 + x]).before - zeros + rank[e0 + x];
+        const bool choose = (some_zero >> e0 & 1u) != 0;       // the same in every lane
 #pragma unroll
-        for (int x = 0; x < kBatch; ++x) at[x] = fast_word(Q, v[e0 + x]).before - zeros + rank[e0 + x];
-#pragma unroll
-        for (int x = 0; x < kBatch; ++x)
-            if (v[e0 + x] > low) elems[at[x]] = v[e0 + x];
+        for (int x = 0; x < kCount; ++x)
+            if (!choose || v[e0 + x] > low) elems[at[x]] = v[e0 + x];
         __builtin_amdgcn_sched_barrier(0);
-    }
+    });
     // what a walk reads past the last element adds nothing
     if (tid < kFastWalk) elems[len - zeros + tid] = ~0u;
     // look-ups whose parts inside buckets fit 32 bits together: one or two at least (see
