@@ -623,11 +623,11 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     if (pl.n_mgroups > 0) k_tile_absmax<<<NT, kWG, 0, stream>>>(tb, tile_max);
     if (fast_tiles > 0) {
         static_assert(sizeof(unsigned long long) * kFastWords + sizeof(unsigned) * (kTileMax + kFastWalk) +
-                          4 * (kPruneGrid + 1) + 2 * kPruneList <= 63 * 1024,
+                          8 * (kPruneGrid + 2) + 2 * kPruneList <= 63 * 1024,
                       "k_fast must fit the LDS a launch gets without asking for more");
         auto lds_bytes = [&](const FastLaunch &fl) {
             return sizeof(unsigned long long) * ((size_t)kFastOct << fast_octave_bits(fl.longest)) +
-                   sizeof(unsigned) * (size_t)(fl.longest + kFastWalk) + (size_t)(fl.prunes ? prune_bytes(n_cand) : 0);
+                   sizeof(unsigned) * (size_t)(fl.longest + kFastWalk) + (size_t)(fl.prunes ? prune_bytes(n_cand, (1 << (bits - 1)) - 1) : 0);
         };
         const FastUnits units = fast_units(n_cand, bits);
         profile_mark(4, stream);

@@ -201,11 +201,17 @@ __device__ inline double group_sum(double v, int g)
     return v;
 }
 
+// What the bound between two candidates needs: (2 / L) (sum H in the tail - sum H in the centre), and the latter
+// part, in squared candidate units per candidate.
+struct FastSlope {
+    float d, centre;
+};
+
 // Filter value of candidate k: by one lane, or (kGroups) by a group of 2^g lanes whose
 // lane `sub` takes the half-way points sub, sub + 2^g, ... of both pieces; the loops are the
 // same in every lane.  All lanes of the wavefront come here together.
-template <bool kGroups>
-__device__ inline float fast_value(const FastLds &Q, const FastCurve &c, int k, int sub, int g)
+template <bool kGroups, bool kSlope>
+__device__ inline float fast_value(const FastLds &Q, const FastCurve &c, int k, int sub, int g, FastSlope &slope)
 {
     if (!kGroups) sub = g = 0;
     const unsigned kk = (unsigned)(k * c.q), ww = (unsigned)((c.n - k) * c.q);   // half steps of the two pieces
@@ -236,14 +242,18 @@ __device__ inline float fast_value(const FastLds &Q, const FastCurve &c, int k, 
     double hc = (double)kk * (double)fc.m + (double)c.low * (double)fc.n - (double)(long long)fc.c;
     double ht = (double)ww * (double)ft.m + (double)zt * (double)ft.n - (double)(long long)ft.c;
     if (kGroups) { hc = group_sum(hc, g); ht = group_sum(ht, g); }
+    if (kSlope) {
+        slope.d = (float)(c.inv * (ht - hc));
+        slope.centre = (float)(c.inv * hc);
+    }
     const double sse = c.A - c.inv * ((double)k * hc + (double)(c.n - k) * ht);
     return (float)(sse > 0.0 ? sse : 0.0);
 }
 
-// put(lead, k, value) for the candidates k_of(0 .. count-1), `lead` in one lane of each
+// put(lead, k, value, slope) for the candidates k_of(0 .. count-1), `lead` in one lane of each
 // one's group.  Where there are threads for it a candidate gets several lanes, four half-way points
 // of a piece each at least: what comes after the look-ups costs as much as three of them.
-template <int kT, typename KOf, typename Put>
+template <int kT, bool kSlope = false, typename KOf, typename Put>
 __device__ inline void fast_each(const FastLds &Q, const FastCurve &c, int count, KOf k_of, Put put)
 {
     int g = 0;
@@ -253,8 +263,9 @@ __device__ inline void fast_each(const FastLds &Q, const FastCurve &c, int count
         const int item = (at + lane) >> g;
         const bool live = item < count;
         const int k = k_of(live ? item : count - 1);
-        const float v = g > 0 ? fast_value<true>(Q, c, k, sub, g) : fast_value<false>(Q, c, k, 0, 0);
-        put(live && sub == 0, k, v);
+        FastSlope slope = {0.0f, 0.0f};
+        const float v = g > 0 ? fast_value<true, kSlope>(Q, c, k, sub, g, slope) : fast_value<false, kSlope>(Q, c, k, 0, 0, slope);
+        put(live && sub == 0, k, v, slope);
     }
 }
 
@@ -263,37 +274,51 @@ template <int kT>
 __device__ inline void fast_candidates(const FastLds &Q, const FastCurve &c, float *__restrict__ row)
 {
     fast_each<kT>(Q, c, c.n, [](int i) { return i + 1; },
-                  [&](bool lead, int k, float v) { if (lead) row[k - 1] = v; });
+                  [&](bool lead, int k, float v, const FastSlope &) { if (lead) row[k - 1] = v; });
 }
 
 // ---------------------------------------------------------------- fewer candidates
 // A tile that is a group of its own needs the candidates within the slack of the minimum
-// only, and most candidates can be shown to be past it.  Eq.3 takes an element to the nearest
-// of the 2L+1 levels of both pieces (p is a level of both), and a level moves by at
+// only, and most candidates can be shown to be past it, from a grid of candidates that are evaluated.
+//
+// H is convex, and so are its sums over the half-way points of a piece, h(k) in the centre and t(k) in the tail, whose
+// half-way points move evenly with k.  Between neighbours k0, k1 of the grid both lie below their chords, and as
+// SSE(k) = A - (2/L) (k h(k) + (n-k) t(k)),
+//   SSE(k) >= chord of SSE - (k - k0) (k1 - k) (D1 - D0) / (k1 - k0),  D = (2/L) (t - h):
+// a parabola per interval, 3 % below SSE in the middle of steps of 8 of 1000 for long-tailed weights at b = 4.  Candidate 0
+// is the ends' partner of n: its half-way points are those of n, all in the tail.
+//
+// Eq.3 takes an element to the nearest of the 2L+1 levels of both pieces (p is a level of both), and a level moves by at
 // most c_j candidate units when the breakpoint moves by one: c_j = j/L in the centre,
 // 1 - j/L in the tail.  With f = sqrt(SSE), the length of the vector of errors,
 //   f(k) >= f(k') - |k - k'| C(k),  C(k)^2 = sum over the elements of c_j^2, j the level under k,
 // and c_j <= min(1, u/k + 1/(2L)), so that C(k)^2 <= min(N, U2/k^2 + U1/(Lk) + N/(4L^2)) with
-// the sums U1, U2 of u and u^2.  About 128 candidates of a grid are evaluated, then those
-// between them that the bound from their two neighbours of the grid leaves below the threshold
-// of the least value: 210 to 290 of 1000 candidates in all at b = 4, 760 at b = 8.  What
-// k_exact is given is the list of candidates within the threshold of the minimum, the same
-// as from a row of all values.
+// the sums U1, U2 of u and u^2.  That excludes more where the steps are long for the curve: 2-5 % of the candidates at 8 bits.
+//
+// The candidates that neither bound excludes are evaluated, and what k_exact is given is the list of candidates within
+// the threshold of the minimum, the same as from a row of all values.  Of 1000 candidates this
+// evaluates (grid and others) 60 at b = 2 and 3, 100 to 140 at b = 4, 150 to 200 at b = 5, 220 to 300 at b = 6, 430 to 770 at b = 8;
+// by the second bound alone, from a grid of 128, 180 to 280 at b = 4.
 constexpr int kPruneMin = 300;                     // fewest candidates
-constexpr int kPruneGrid = 128;                    // most points of the grid (64: 1-7 % slower, 250: 4-12 %)
+constexpr int kPruneGrid = 128;                    // most points of the grid
 constexpr int kPruneList = 2048;                   // most candidates between them, else all are evaluated
 constexpr int kPruneKeep = 64;                     // most of those within the threshold, else all are evaluated
 
-__host__ __device__ constexpr int prune_log(int n)
+// log2 of the grid's step.  The gap below the chord goes with the square of the step and, against the error,
+// of L: a quarter of the points where a step of the levels is long.
+__host__ __device__ constexpr int prune_log(int n, int L)
 {
+    const int grid = L <= 3 ? kPruneGrid / 4 : L <= 7 ? kPruneGrid / 2 : kPruneGrid;
     int log = 2;
-    while (n >> log > kPruneGrid) ++log;
+    while (n >> log > grid) ++log;
     return log;
 }
-// LDS beyond the tables: the grid's values, then the list
-__host__ __device__ constexpr int prune_bytes(int n)
+// number of the last point, which is candidate n
+__host__ __device__ constexpr int prune_points(int n, int L) { return (n + (1 << prune_log(n, L)) - 1) >> prune_log(n, L); }
+// LDS beyond the tables: the grid's values and slopes, then the list
+__host__ __device__ constexpr int prune_bytes(int n, int L)
 {
-    return n < kPruneMin ? 0 : 4 * ((n >> prune_log(n)) + 1) + 2 * (n < kPruneList ? n : kPruneList);
+    return n < kPruneMin ? 0 : 8 * (prune_points(n, L) + 1) + 2 * (n < kPruneList ? n : kPruneList);
 }
 
 struct FastPruneLds {
@@ -309,10 +334,12 @@ constexpr int kRowIsList = (int)0x80000000;
 // U1, U2, count: bounds from above.  False, in every thread: the row has to be evaluated in full.
 template <int kT>
 __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U1, float U2, float count,
-                                   FastPruneLds &S, float *grid, unsigned short *list, int *__restrict__ row)
+                                   FastPruneLds &S, float *value, unsigned short *list, int *__restrict__ row)
 {
     const int tid = threadIdx.x, lane = tid & 63;
-    const int log = prune_log(c.n), step = 1 << log, points = c.n >> log;
+    const int log = prune_log(c.n, c.Li), step = 1 << log, points = prune_points(c.n, c.Li);
+    float *slope = value + points + 1;
+    const auto point = [&](int i) { return i << log < c.n ? i << log : c.n; };
     const auto least = [&](bool lead, float v) {
         const unsigned w = ~wave_max_u32(lead ? ~__float_as_uint(v) : ~0x7f800000u);      // v >= 0
         if (lane == 0) atomicMin(&S.least, w);
@@ -324,33 +351,61 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
     const auto threshold = [&](float v) {
         return v * 1.00007f + 4.0001f * eps * __builtin_amdgcn_sqrtf(count * v) + flat_slack;
     };
-    fast_each<kT>(Q, c, points, [&](int i) { return (i + 1) << log; }, [&](bool lead, int k, float v) {
-        if (lead) grid[k >> log] = v;
+    fast_each<kT, true>(Q, c, points, [&](int i) { return point(i + 1); }, [&](bool lead, int k, float v, const FastSlope &s) {
+        if (lead) {
+            const int i = (k + step - 1) >> log;
+            value[i] = v;
+            slope[i] = s.d;
+            if (k == c.n) { value[0] = v; slope[0] = s.centre; }
+        }
         least(lead, v);
     });
     __syncthreads();
-    // a bound above this excludes a candidate; 6e-7 n sqrt(count) covers the roundings of the
-    // roots, of at most n sqrt(count), and of the values below them
-    const float top = __builtin_amdgcn_sqrtf(threshold(__uint_as_float(S.least))) * 1.00002f + 6e-7f * nf * __builtin_amdgcn_sqrtf(count);
+    // A bound above these excludes a candidate.  A parabola's ends are within 1e-14 n^2 count and a rounding to binary32 of their
+    // values, and so is the value that it bounds; 6e-7 n sqrt(count) covers the roundings of the
+    // roots, of at most n sqrt(count), and of the values below them.
+    const float near = threshold(__uint_as_float(S.least));
+    const float top = near * 1.00002f + 4.0f * (float)kFastRelErr * nf * nf * count;
+    const float top_root = __builtin_amdgcn_sqrtf(near) * 1.00002f + 6e-7f * nf * __builtin_amdgcn_sqrtf(count);
     const float invL = __builtin_amdgcn_rcpf((float)c.Li), flat = 0.25f * count * invL * invL;
     const int cap = c.n < kPruneList ? c.n : kPruneList;
-    for (int at = uni(tid & ~63); at <= points; at += kT) {
-        // the candidates between grid points i and i + 1
-        const int i = at + lane, from = i << log;
-        int lo = 1, hi = 0;
-        if (i <= points) {
+    for (int at = uni(tid & ~63); at < points; at += kT) {
+        // the candidates between grid points i and i + 1: x = lo .. hi past the first
+        const int i = at + lane;
+        int lo = 1, hi = 0, from = 0;
+        if (i < points) {
+            from = point(i);
+            const int s = point(i + 1) - from;
+            const float sf = (float)s, rs = __builtin_amdgcn_rcpf(sf) * 1.000001f;
+            const float v0 = value[i], v1 = value[i + 1], d0 = slope[i], d1 = slope[i + 1];
+            // the parabola less the threshold is g x^2 + b x + v: g from above, positive
+            const float up = d1 - d0 + 2e-7f * (__builtin_fabsf(d0) + __builtin_fabsf(d1));
+            const float g = (up > 0.0f ? up * 1.0001f : 0.0f) * rs + 1e-6f * (v0 + v1 + top) * rs * rs;
+            const float b = (v1 - v0) * rs - g * sf, v = v0 - top;
+            const float disc = b * b - 4.0f * g * v + 4e-6f * (b * b + 4.0f * g * __builtin_fabsf(v));
+            hi = s - 1;
+            if (disc < 0.0f) hi = 0;
+            else {
+                const float root = __builtin_amdgcn_sqrtf(disc);
+                const float q = -0.5f * (b + (b < 0.0f ? -root : root));
+                // the roots q / g and v / q, in either order; 0.01 for the roundings of a quotient of at most s
+                const float x0 = q / g, x1 = v / q;
+                const float first = fminf(x0, x1) - 0.01f, last = fmaxf(x0, x1) + 0.01f;
+                if (first > 1.0f) lo = first < sf ? (int)__builtin_ceilf(first) : s;
+                if (last < sf) hi = last > 0.0f ? (int)last : 0;
+                hi = hi < s ? hi : s - 1;
+            }
             const float r = __builtin_amdgcn_rcpf((float)(from + 1));
-            const float x = __builtin_fmaf(__builtin_fmaf(U2, r, U1 * invL), r, flat);
-            const float per = __builtin_amdgcn_rcpf(1.0001f * __builtin_amdgcn_sqrtf(x < count ? x : count));
-            hi = c.n - from < step ? c.n - from : step - 1;
+            const float y = __builtin_fmaf(__builtin_fmaf(U2, r, U1 * invL), r, flat);
+            const float per = __builtin_amdgcn_rcpf(1.0001f * __builtin_amdgcn_sqrtf(y < count ? y : count));
             if (i > 0) {
-                const float d = (__builtin_amdgcn_sqrtf(grid[i]) - top) * per - 0.01f;
-                if (d > 1.0f) lo = d < (float)step ? (int)__builtin_ceilf(d) : step;
+                const float d = (__builtin_amdgcn_sqrtf(v0) - top_root) * per - 0.01f;
+                const int l = d < sf ? (int)__builtin_ceilf(d) : s;
+                if (d > 1.0f && l > lo) lo = l;
             }
-            if (i < points) {
-                const float d = (__builtin_amdgcn_sqrtf(grid[i + 1]) - top) * per - 0.01f;
-                if (d > 1.0f) hi = d < (float)step ? step - (int)__builtin_ceilf(d) : 0;
-            }
+            const float d = (__builtin_amdgcn_sqrtf(v1) - top_root) * per - 0.01f;
+            const int h = d < sf ? s - (int)__builtin_ceilf(d) : 0;
+            if (d > 1.0f && h < hi) hi = h;
         }
         const int own = hi >= lo ? hi - lo + 1 : 0;
         const int incl = wave_scan_incl(own);
@@ -363,7 +418,7 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
     __syncthreads();
     const int listed = uni(S.listed);
     if (listed > cap) return false;
-    fast_each<kT>(Q, c, listed, [&](int i) { return (int)list[i]; }, [&](bool lead, int k, float v) {
+    fast_each<kT>(Q, c, listed, [&](int i) { return (int)list[i]; }, [&](bool lead, int k, float v, const FastSlope &) {
         // within the threshold of the least value that the wavefront knows of
         const float own = least(lead, v);
         if (lead && v <= threshold(fminf(own, __uint_as_float(S.least)))) {
@@ -382,10 +437,10 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
         if (want) row[1 + out + __builtin_popcountll(bal & ((1ull << lane) - 1ull))] = k;
         out += __builtin_popcountll(bal);
     };
-    static_assert(kPruneGrid + kPruneKeep < kPruneMin && kPruneKeep <= 64, "the list fits a row, the kept one wavefront");
+    static_assert(kPruneGrid + 1 + kPruneKeep < kPruneMin && kPruneKeep <= 64, "the list fits a row, the kept one wavefront");
     for (int at = 0; at < points; at += 64) {
         const int i = at + lane + 1;
-        keep(i <= points && grid[i <= points ? i : 1] <= thr, i << log);
+        keep(i <= points && value[i <= points ? i : 1] <= thr, point(i));
     }
     keep(lane < kept && S.keep_v[lane < kept ? lane : 0] <= thr, S.keep_k[lane < kept ? lane : 0]);
     if (lane == 0) row[0] = kRowIsList | out;
@@ -741,7 +796,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
         const double U1 = (double)sum * (scale * F.per_unit) * 1.000002;
         const double U2 = A - (double)n * (double)n * (double)len + 2.0 * (double)n * U1;
         float *grid = reinterpret_cast<float *>(elems + len + kFastWalk);
-        unsigned short *list = reinterpret_cast<unsigned short *>(grid + (n >> prune_log(n)) + 1);
+        unsigned short *list = reinterpret_cast<unsigned short *>(grid + 2 * (prune_points(n, Li) + 1));
         if (fast_pruned<kT>(Q, c, (float)U1 * 1.0001f, (float)U2 * 1.0001f, (float)len, pruned, grid, list,
                             reinterpret_cast<int *>(row)))
             return;
