@@ -81,10 +81,15 @@ int check_common(int bits, int mode)
 // walks many candidates one after the other: where the tiles are too few to hide that
 // (b = 4, n = 4000, us, 128 or 256 / 512 threads: 512x121 72/37, 512x300 46/39; n = 1000,
 // 1024x121 24.7/22.6, 2048x121 31.8/36.1; n = 300, 1024x121 14.9/17.2) they get 512.
+//
+// Longer tiles likewise: 256 threads where a launch has many and their look-ups are few, 512 where not (us, 512 / 256:
+// 38 400 tiles of 4096, n = 1000, b = 4, k_fast alone 508/386; but 2500x4608, 512 threads with fewer candidates left out than
+// now: n = 290, without the grid of candidates, b = 5, 68/75, b = 6 85/101; b = 7, n = 700 146/196).
 int fast_threads(int longest, long long tiles, int n, int L)
 {
     if (longest > kFastLong) return 1024;
-    if (longest > kSmallTile) return 512;
+    if (longest > kSmallTile)
+        return tiles > kFastManyTiles && L <= 15 && (n >= kPruneMin || n * L <= 2500) ? 256 : 512;
     const bool short_tiles = longest <= kFastShort;
     if (tiles <= (short_tiles ? 1024 : 512) && (long long)n * L >= 3500) return 512;
     return short_tiles ? 128 : 256;
@@ -626,8 +631,8 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                           8 * (kPruneGrid + 2) + 2 * kPruneList <= 63 * 1024,
                       "k_fast must fit the LDS a launch gets without asking for more");
         auto lds_bytes = [&](const FastLaunch &fl) {
-            return sizeof(unsigned long long) * ((size_t)kFastOct << fast_octave_bits(fl.longest)) +
-                   sizeof(unsigned) * (size_t)(fl.longest + kFastWalk) + (size_t)(fl.prunes ? prune_bytes(n_cand, (1 << (bits - 1)) - 1) : 0);
+            return sizeof(unsigned long long) * ((size_t)kFastOct << fast_octave_bits(fl.longest, fl.threads)) +
+                   sizeof(unsigned) * (size_t)(fl.longest + kFastWalk) + (size_t)(fl.prunes ? prune_bytes(n_cand, (1 << (bits - 1)) - 1, fl.threads) : 0);
         };
         const FastUnits units = fast_units(n_cand, bits);
         profile_mark(4, stream);
@@ -649,7 +654,10 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                         k_fast<128, kFastShort / 128><<<wgs, 128, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
                         break;
                     default:
-                        k_fast<256, kSmallTile / 256><<<wgs, 256, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
+                        if (fl.longest > kSmallTile)
+                            k_fast<256, kFastLong / 256><<<wgs, 256, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
+                        else
+                            k_fast<256, kSmallTile / 256><<<wgs, 256, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
                 }
             }
         }

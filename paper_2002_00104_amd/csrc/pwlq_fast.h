@@ -38,11 +38,11 @@
 // four at a time.
 // Elements that are exactly zero (pruned weights) are counted, never walked.
 //
-// Bound by vector issue and LDS together: with 38 400 tiles of 4096, 1000 candidates, b = 4,
-// 290 000 vector instructions on each SIMD, two thirds of them before any look-up, and the LDS index unit active for
-// 297 us at 2.4 GHz, half of that in bank conflicts.  In us: 1498 with binary64
+// Bound by vector issue and LDS together, and by what a workgroup waits for alone between its eight barriers: with 38 400
+// tiles of 4096, 1000 candidates, b = 4, us: 1498 with binary64
 // prefixes of counts, sums and squares and walks of nine elements, 745 with all candidates looked up and an
-// element's load and add waited for one by one, 550 now.
+// element's load and add waited for one by one, 544 with one bound on the candidates, 508 with chords and without the choices for
+// elements that do not exist, 386 in workgroups of 256 threads and 26 KB (see k_fast).
 #pragma once
 
 #include <type_traits>
@@ -53,8 +53,9 @@
 
 namespace pwlq {
 
-// Most buckets per octave, 2^8.  2^9 halves the walks and costs the fourth workgroup per
+// Most buckets per octave, 2^8.  2^9 halves the walks and costs the fourth workgroup of 512 threads per
 // CU its LDS (38 400 tiles of 4096, search + quantize, with 24-bit units: 1228 us with 2^9, 1145 with 2^8).
+// Workgroups of 256 threads have 2^7: six of them, not four, then fit a CU (k_fast alone, us: 485 with 2^8, 386).
 constexpr int kFastOctBits = 8;
 constexpr int kFastOct = 7;                        // octaves, or twice as many of half as many buckets each
 constexpr int kFastWords = kFastOct << kFastOctBits;   // most buckets per tile
@@ -71,6 +72,7 @@ constexpr int kFastWalk = 3;                       // elements read unasked (4: 
 constexpr int kFastWalkOn = 4;                     // ... and then per step
 constexpr int kFastShort = 256;                    // longest tile of a launch of 128 threads
 constexpr int kFastLong = 5120;                    // longest tile of a launch of 512 threads: four workgroups' LDS per CU
+constexpr int kFastManyTiles = 2048;               // more tiles of 1025 to kFastLong elements get 256 threads instead of 512
 constexpr int kFastGridMax = 1 << 21;              // workgroups of a launch
 constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones
 
@@ -84,11 +86,13 @@ constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launc
 // parts of H inside one bucket then fit 32 bits.  With 2^m buckets in an octave
 // (2^(m-1) where there are 14 octaves) the widest, in the last octave, has 2^(30-m) units,
 // and a tile is crowded when a bucket has more than max(kFastCrowd, len / 16) elements:
-// 64 * 2^25 for m = 5 (up to 255 elements), 511 * 2^22 at most for m = 8 (from 1024 on).
-__host__ __device__ constexpr int fast_octave_bits(int len)
+// 64 * 2^25 for m = 5 (up to 255 elements), 511 * 2^22 at most for m = 8 (from 1024 on), and with twice the elements,
+// 511 * 2^23 at most for m = 7 in workgroups of 256 threads.
+__host__ __device__ constexpr int fast_octave_bits(int len, int threads)
 {
+    const int most = threads == 256 ? kFastOctBits - 1 : kFastOctBits;
     int bits = 5;
-    while (bits < kFastOctBits && (8 << bits) <= len) ++bits;
+    while (bits < most && (8 << bits) <= len) ++bits;
     return bits;
 }
 
@@ -304,21 +308,24 @@ constexpr int kPruneGrid = 128;                    // most points of the grid
 constexpr int kPruneList = 2048;                   // most candidates between them, else all are evaluated
 constexpr int kPruneKeep = 64;                     // most of those within the threshold, else all are evaluated
 
-// log2 of the grid's step.  The gap below the chord goes with the square of the step and, against the error,
-// of L: a quarter of the points where a step of the levels is long.
-__host__ __device__ constexpr int prune_log(int n, int L)
+// log2 of the grid's step.  The gap below the chord goes with the square of the step and, against the error, of L: up to
+// four bits half of the points leave fewer candidates in all, which larger workgroups evaluate as fast as few.
+__host__ __device__ constexpr int prune_log(int n, int L, int threads)
 {
-    const int grid = L <= 3 ? kPruneGrid / 4 : L <= 7 ? kPruneGrid / 2 : kPruneGrid;
+    const int grid = threads <= 256 && L <= 7 ? kPruneGrid / 2 : kPruneGrid;
     int log = 2;
     while (n >> log > grid) ++log;
     return log;
 }
 // number of the last point, which is candidate n
-__host__ __device__ constexpr int prune_points(int n, int L) { return (n + (1 << prune_log(n, L)) - 1) >> prune_log(n, L); }
-// LDS beyond the tables: the grid's values and slopes, then the list
-__host__ __device__ constexpr int prune_bytes(int n, int L)
+__host__ __device__ constexpr int prune_points(int n, int L, int threads)
 {
-    return n < kPruneMin ? 0 : 8 * (prune_points(n, L) + 1) + 2 * (n < kPruneList ? n : kPruneList);
+    return (n + (1 << prune_log(n, L, threads)) - 1) >> prune_log(n, L, threads);
+}
+// LDS beyond the tables: the grid's values and slopes, then the list
+__host__ __device__ constexpr int prune_bytes(int n, int L, int threads)
+{
+    return n < kPruneMin ? 0 : 8 * (prune_points(n, L, threads) + 1) + 2 * (n < kPruneList ? n : kPruneList);
 }
 
 struct FastPruneLds {
@@ -337,7 +344,7 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
                                    FastPruneLds &S, float *value, unsigned short *list, int *__restrict__ row)
 {
     const int tid = threadIdx.x, lane = tid & 63;
-    const int log = prune_log(c.n, c.Li), step = 1 << log, points = prune_points(c.n, c.Li);
+    const int log = prune_log(c.n, c.Li, kT), step = 1 << log, points = prune_points(c.n, c.Li, kT);
     float *slope = value + points + 1;
     const auto point = [&](int i) { return i << log < c.n ? i << log : c.n; };
     const auto least = [&](bool lead, float v) {
@@ -451,12 +458,51 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
 // holding more than 1/16 of the tile) would make every look-up walk a long bucket; it is evaluated element by element
 // instead, from binary32 magnitudes in candidate units, with the chunked sums of the
 // plain search kernel (all lanes read the same LDS word, which is a broadcast).
-template <int kT>
+//
+// kPairs: two candidates of a thread at a time, half of the reads and two chains of additions, for workgroups of few threads
+// (up to 5120 elements in 256 threads: 4100x5000 of log-uniform weights, b = 4, n = 600, us: 3364 one by one, 2697 so; in
+// 512 threads, most of which have one candidate there, 145 and 168 for 512x1155).
+template <int kT, bool kPairs>
 __device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, int n, int Li,
                                   float *__restrict__ row)
 {
     const float Lf = (float)Li;
-    for (int k = threadIdx.x + 1; k <= n; k += kT) {
+    int k = threadIdx.x + 1;
+    if constexpr (kPairs) {
+        for (; k + kT <= n; k += 2 * kT) {
+            float kf[2], rc[2], rt[2], ct[2], stepc[2], stept[2], outer[2] = {0.0f, 0.0f};
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const int kx = k + x * kT;
+                kf[x] = (float)kx;
+                rc[x] = Lf / kf[x];
+                rt[x] = (kx < n) ? Lf / (float)(n - kx) : 0.0f;
+                ct[x] = -kf[x] * rt[x];
+                stepc[x] = kf[x] / Lf;
+                stept[x] = (float)(n - kx) / Lf;
+                asm("" : "+v"(stepc[x]), "+v"(stept[x]));
+            }
+            for (int cb = 0; cb < len; cb += kChunk) {
+                const int ce = (cb + kChunk < len) ? cb + kChunk : len;
+                float acc[2] = {0.0f, 0.0f};
+                for (int i = cb; i < ce; ++i) {
+                    const float u = __uint_as_float(elems[i]);
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        const bool tail = u > kf[x];
+                        const float t = tail ? __builtin_fmaf(u, rt[x], ct[x]) : u * rc[x];
+                        const float err = (t - __builtin_rintf(t)) * (tail ? stept[x] : stepc[x]);
+                        acc[x] = __builtin_fmaf(err, err, acc[x]);
+                    }
+                }
+                outer[0] += acc[0];
+                outer[1] += acc[1];
+            }
+            row[k - 1] = outer[0];
+            row[k + kT - 1] = outer[1];
+        }
+    }
+    for (; k <= n; k += kT) {
         const float kf = (float)k;
         const float nk = (float)(n - k);
         const float rc = Lf / kf;
@@ -511,18 +557,22 @@ inline FastUnits fast_units(int n, int bits)
 template <int kPer, typename F>
 __device__ inline void fast_batches(F batch)
 {
-    static_assert(kPer == 2 || kPer == 4 || kPer == 8 || kPer == 10, "no batches for this many");
+    static_assert(kPer == 2 || kPer == 4 || kPer == 8 || kPer == 10 || kPer == 20, "no batches for this many");
     const auto call = [&](auto e0, auto count) { batch(e0, count); };
 #define PWLQ_BATCH(E, C) call(std::integral_constant<int, E>(), std::integral_constant<int, C>())
-    if constexpr (kPer == 2) { PWLQ_BATCH(0, 1); PWLQ_BATCH(1, 1); }
-    if constexpr (kPer == 4) { PWLQ_BATCH(0, 2); PWLQ_BATCH(2, 2); }
+    if constexpr (kPer == 2) PWLQ_BATCH(0, 2);
+    if constexpr (kPer == 4) PWLQ_BATCH(0, 4);
+    if constexpr (kPer == 20) { PWLQ_BATCH(0, 4); PWLQ_BATCH(4, 4); PWLQ_BATCH(8, 4); PWLQ_BATCH(12, 4); PWLQ_BATCH(16, 4); }
     if constexpr (kPer == 8) { PWLQ_BATCH(0, 4); PWLQ_BATCH(4, 4); }
-    if constexpr (kPer == 10) { PWLQ_BATCH(0, 5); PWLQ_BATCH(5, 3); PWLQ_BATCH(8, 2); }
+    if constexpr (kPer == 10) { PWLQ_BATCH(0, 5); PWLQ_BATCH(5, 5); }
 #undef PWLQ_BATCH
 }
 
+// Long tiles in 256 threads (kPer 20) where a launch has many: what every wavefront of a tile does once (reductions, prefixes,
+// candidates' ends) is done by four instead of eight, all of them have candidates to look up, and six workgroups fit a CU's
+// LDS where 512 threads are four at most (transformer_fast 925 -> 801 us, 5608 tiles of 1152 to 4608 82 -> 69).
 template <int kT, int kPer>
-__global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n, int bits, FastUnits F,
+__global__ __launch_bounds__(kT, kPer == 20 ? 6 : 8) void k_fast(Tables tb, int tile_begin, int n, int bits, FastUnits F,
                                              const float *__restrict__ tile_max,
                                              float *__restrict__ gm,
                                              float *__restrict__ sse32)
@@ -531,7 +581,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     // themselves, then of everything before them), then the grouped elements
     extern __shared__ __attribute__((aligned(16))) unsigned long long fast_lds[];
     constexpr int kW = kT / 64;
-    constexpr int kScan = ((kFastOct << fast_octave_bits(kT * kPer)) + kT - 1) / kT;   // words a thread holds at most
+    constexpr int kScan = ((kFastOct << fast_octave_bits(kT * kPer, kT)) + kT - 1) / kT;   // words a thread holds at most
     __shared__ unsigned redm[kW];
     __shared__ float redsum[kW];
     __shared__ int wfull[kW];                                // a bucket fuller than 16, than kFastCrowd, crowded
@@ -578,14 +628,14 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
         pruned.least = 0x7f800000u;
         pruned.listed = pruned.kept = 0;
     }
-    int obits = fast_octave_bits(len);
+    int obits = fast_octave_bits(len, kT);
     const int T = kFastOct << obits;
     for (int i = tid; i < T / 2; i += kT) reinterpret_cast<ulonglong2 *>(fast_lds)[i] = make_ulonglong2(0ull, 0ull);
 
     // group absmax: from the registers (single-tile group) or the tile maxima; the
     // tile's mean magnitude places the buckets.  Binary32 patterns of magnitudes are in the
     // magnitudes' order, NaN above infinity.
-    unsigned mb = 0;
+    unsigned mb = 0, lowest = ~0u;
     float sum = 0.0f;
     fast_batches<kPer>([&](auto first, auto count) {
         constexpr int e0 = decltype(first)::value, e1 = e0 + decltype(count)::value;
@@ -593,11 +643,18 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
         if (!all(e0, e1 - e0)) {
             asm volatile("");                                  // a branch: not a choice for every element of every batch
 #pragma unroll
-            for (int e = e0; e < e1; ++e) a[e] = tid + e * kT < len ? a[e] : 0.0f;
+            for (int e = e0; e < e1; ++e) {
+                const bool within = tid + e * kT < len;
+                const unsigned ab = __float_as_uint(fabsf(a[e]));
+                lowest = within && ab < lowest ? ab : lowest;
+                a[e] = within ? a[e] : 0.0f;
+            }
         }
+        const bool whole = all(e0, e1 - e0);
 #pragma unroll
         for (int e = e0; e < e1; ++e) {
             a[e] = fabsf(a[e]);
+            if (whole) lowest = __float_as_uint(a[e]) < lowest ? __float_as_uint(a[e]) : lowest;
             const unsigned ab = __float_as_uint(a[e]);
             mb = ab > mb ? ab : mb;
             sum += a[e];
@@ -660,7 +717,8 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     // wavefront has neither in a batch, it does without the choice.
     static_assert(64 <= kFastOct << 5, "a word for every lane");
     const float past = usable ? m : 0.0f;                      // counts as m: nothing in A
-    unsigned some_zero = 0;                                    // batches, by their first element, in which the wavefront has zeros
+    // whether the wavefront has magnitudes that may round to zero
+    const bool zeros_here = __ballot((double)__uint_as_float(lowest) * scale < 1.0) != 0ull;
     typedef __attribute__((address_space(3))) unsigned long long WordLds;
     fast_batches<kPer>([&](auto first, auto count) {
         constexpr int e0 = decltype(first)::value, kCount = decltype(count)::value;
@@ -671,25 +729,20 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
 #pragma unroll
             for (int e = e0; e < e0 + kCount; ++e) a[e] = tid + e * kT < len ? a[e] : past;
         }
-        unsigned least = ~0u;
 #pragma unroll
         for (int e = e0; e < e0 + kCount; ++e) {
             const double w = __builtin_fma((double)a[e], scale, one52);
             const double d = full52 - w;                       // exact
             A = __builtin_fma(d, d, A);
-            const unsigned u = (unsigned)__double2loint(w);
-            v[e] = u + low;
-            least = u < least ? u : least;
+            v[e] = (unsigned)__double2loint(w) + low;
         }
-        const bool zeros = __ballot(least == 0u) != 0ull;
         unsigned long long was[kCount];
-        if (whole && !zeros) {
+        if (whole && !zeros_here) {
 #pragma unroll
             for (int x = 0; x < kCount; ++x)
                 was[x] = __hip_atomic_fetch_add((WordLds *)(uintptr_t)((fast_bucket(v[e0 + x], Q.shift) << 3) + Q.words),
                                                 (1ull << kFastSumBits) | v[e0 + x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         } else {
-            some_zero |= 1u << e0;
 #pragma unroll
             for (int x = 0; x < kCount; ++x) {
                 const int e = e0 + x;
@@ -709,8 +762,10 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     A = wave_sum(A);
     __syncthreads();
 
+    // (twice as many in buckets that may be twice as wide)
+    constexpr int kWide = kT == 256 ? 1 : 0;
     int crowd = (len >> 4) > kFastCrowd ? len >> 4 : kFastCrowd;
-    crowd = crowd < kFastCrowdMax ? crowd : kFastCrowdMax;
+    crowd = crowd << kWide < kFastCrowdMax ? crowd << kWide : kFastCrowdMax;
     // exclusive prefix of counts and sums, both fields in one word
     const int per = (T + kT - 1) / kT;             // divides T
     const int lo = tid * per;
@@ -770,7 +825,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
         unsigned at[kCount];
 #pragma unroll
         for (int x = 0; x < kCount; ++x) at[x] = fast_word(Q, v[e0 + x]).before - zeros + rank[e0 + x];
-        const bool choose = (some_zero >> e0 & 1u) != 0;       // the same in every lane
+        const bool choose = zeros_here || !all(e0, kCount);    // the same in every lane
 #pragma unroll
         for (int x = 0; x < kCount; ++x)
             if (!choose || v[e0 + x] > low) elems[at[x]] = v[e0 + x];
@@ -780,14 +835,15 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
     if (tid < kFastWalk) elems[len - zeros + tid] = ~0u;
     // look-ups whose parts inside buckets fit 32 bits together: one or two at least (see
     // fast_octave_bits), eight or more as a rule
-    const int run = (int)(0xffffffffu >> (kFastBits - 1 - obits)) >> (full & 2 ? kFastCrowdBits : full & 1 ? kFastCrowdLog : 4);
+    int run = (int)(0xffffffffu >> (kFastBits - 1 - obits)) >> (full & 2 ? kFastCrowdBits : full & 1 ? kFastCrowdLog : 4);
+    run = run > 0 ? run : 1;                       // (one of a bucket of kFastCrowdMax: 511 * 2^23 at most)
     __syncthreads();
     float *row = sse32 + (long long)t * n;
     if (full & 4) {
         for (int i = tid; i < len - zeros; i += kT)
             elems[i] = __float_as_uint((float)((double)(elems[i] - low) * F.per_unit));
         __syncthreads();
-        fast_plain<kT>(elems, len - zeros, n, Li, row);
+        fast_plain<kT, kPer == 20>(elems, len - zeros, n, Li, row);
         return;
     }
     const FastCurve c = {A, F.inv, low, n, Li, F.q, run};
@@ -796,7 +852,7 @@ __global__ __launch_bounds__(kT, 8) void k_fast(Tables tb, int tile_begin, int n
         const double U1 = (double)sum * (scale * F.per_unit) * 1.000002;
         const double U2 = A - (double)n * (double)n * (double)len + 2.0 * (double)n * U1;
         float *grid = reinterpret_cast<float *>(elems + len + kFastWalk);
-        unsigned short *list = reinterpret_cast<unsigned short *>(grid + 2 * (prune_points(n, Li) + 1));
+        unsigned short *list = reinterpret_cast<unsigned short *>(grid + 2 * (prune_points(n, Li, kT) + 1));
         if (fast_pruned<kT>(Q, c, (float)U1 * 1.0001f, (float)U2 * 1.0001f, (float)len, pruned, grid, list,
                             reinterpret_cast<int *>(row)))
             return;
