@@ -323,9 +323,9 @@ __global__ __launch_bounds__(kWG) void k_mse_tile(Tables tb, StatArgs sa, int n_
 #pragma unroll
         for (int u = 0; u < kStatUnroll; ++u) a[u] = fabsf(ti.src[i + 64 * u]);
 #pragma unroll
-        for (int u = 0; u < kStatUnroll; ++u) acc[u] += exact_error_sq(q, a[u]);
+        for (int u = 0; u < kStatUnroll; ++u) acc[u] = exact_add(q, a[u], acc[u]);
     }
-    for (; i < ti.len; i += 64) acc[0] += exact_error_sq(q, fabsf(ti.src[i]));
+    for (; i < ti.len; i += 64) acc[0] = exact_add(q, fabsf(ti.src[i]), acc[0]);
     const double s = wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
     if (lane == 0) {
         if (ti.whole) mse[ti.og] = s / (double)ti.len;      // the group's only tile
