@@ -1,14 +1,17 @@
-"""Builds libpwlq.so (HIP, gfx950) in-tree with hipcc."""
+"""Builds libpwlq.so (HIP, gfx950) in-tree with hipcc, and the module that calls it from Python with gcc."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpwlq.so")
+CALL_SOURCE = os.path.join(CSRC, "pwlq_call.c")
+CALL = os.path.join(HERE, "_pwlq_call" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = [os.path.join(CSRC, "pwlq_api.hip")]
 HEADERS = [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith(".h")] + [
            os.path.join(os.path.dirname(HERE), "include", "pwlq.h"),
@@ -41,17 +44,20 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def stale() -> bool:
-    if not os.path.exists(LIB):
+def stale(built: str = LIB, sources=None) -> bool:
+    if not os.path.exists(built):
         return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS)
+    t = os.path.getmtime(built)
+    return any(os.path.getmtime(p) > t for p in sources or SOURCES + HEADERS)
 
 
 def build(force: bool = True, extra=()) -> str:
     if force or stale():
         cmd = [hipcc(), *HIPCC_FLAGS, *extra, *SOURCES, "-o", LIB]
         subprocess.run(cmd, check=True)
+    if force or stale(CALL, [CALL_SOURCE]):
+        subprocess.run(["gcc", "-O2", "-std=c11", "-Wall", "-Wextra", "-fPIC", "-shared",
+                        "-I" + sysconfig.get_paths()["include"], CALL_SOURCE, "-o", CALL], check=True)
     return LIB
 
 
