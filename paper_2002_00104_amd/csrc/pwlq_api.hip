@@ -95,6 +95,18 @@ int fast_threads(int longest, long long tiles, int n, int L)
     return short_tiles ? 128 : 256;
 }
 
+// Whether n candidates are enough for a grid of them, and not so many that most tiles would have more within the
+// threshold than are kept, and be evaluated in full after all.  The threshold is 6e-5 + 2.4e-5 L above the least
+// value, since the rounding in its slack is in proportion to n / m as the error is, and the values are a parabola in
+// k / n around the least one: about n sqrt(6e-5 + 2.4e-5 L) candidates, in proportion.  At 112 of that measure no
+// weights but uniform ones lose (64x5000, all / pruned: b = 4, n = 7000 137/108, n = 12000 166/173; b = 6, n = 3000
+// 87/63, n = 6000 155/161; b = 8, n = 2000 179/159, n = 5000 408/424); from n = 8000 on at two and three bits some do
+// (200x700, b = 3, n = 10000 78/84).
+bool grid_pays(int n, int L)
+{
+    return n >= kPruneMin && n <= 8000 && (long long)n * n * (60 + 24 * L) <= 112LL * 112 * 1000000;
+}
+
 // Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
 // candidate grows with the number of half-way points (2L look-ups) and hardly depends on
 // the tile length, the plain evaluation costs one pass over the tile.  16384 tiles, 1000
@@ -111,14 +123,26 @@ int fast_threads(int longest, long long tiles, int n, int L)
 // their launch (16x121, n = 20000, us, look-ups / pass 99/54; 64x2048, b = 8, n = 2000 116/46; 512x121,
 // n = 1000 15.5/20.3).
 //
-// Both price the look-ups of all candidates.  Where the tiles look up a grid of them first (fast_prunes) the
-// line errs to the side of the passes: 16384 tiles, n = 1000, with the grid / pass: 160 elements 91 / 262, 96
-// elements 82 / 175, 64 elements 76 / 138.
+// Both price the look-ups of all candidates.  Where 2048 tiles and more look up a grid of them first (see grid_pays) a
+// tile costs the same whatever its length, and less than its pass, down to the 3x3 kernels of a depthwise layer
+// (kFastShortest): at up to four bits at every length (us, passes / look-ups: 7136x9, b = 4, n = 1000 44/34, n = 3000
+// 108/41, b = 3, n = 300 32/32; the searches of MobileNetV2's shapes, b = 4, n = 1000 164/118, for which the shortest
+// tiles need no launches of their own; 16384 tiles of 18 to 119, n = 1000, 0.60 to 0.33 of the time), at five bits at
+// every length from 1000 candidates on and else from 64 (n = 300, 16384x48 1.00, x64 0.93 of the time), at six from
+// 150 and 1000 (16384x150 0.81, x64 1.07; n = 300 1.25).  What loses on this side of the line are tiles of nine alone:
+// 7136x9, b = 4, n = 300 31/32, and cubes of normal numbers at b = 5, n = 3000 133/141.
 int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
 {
     const int L = (1 << (bits - 1)) - 1;
     const int shortest = (bits == 8 && n >= 800 ? 9 : 8) * (2 * L) + 8, always = 16 * (2 * L + 1) + 64;
     long long tiles = 0, elements = 0;
+    if (grid_pays(n, L) && (L <= 15 || (L == 31 && n >= 1000))) {
+        const int low = L == 31 ? 150 : L == 15 && n < 1000 ? 64 : kFastShortest;
+        for (const TensorRec &r : recs)
+            if (r.tile_len >= low && r.tile_len < always) tiles += r.ntiles;
+        if (tiles >= 2048) return low;
+        tiles = 0;
+    }
     int longest = 0;
     for (const TensorRec &r : recs) {
         if (r.tile_len < shortest || r.tile_len >= always) continue;
@@ -143,20 +167,13 @@ int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
 // 20000x128, n = 1000 191/101, n = 4000 740/155, n = 256 89/86; 1024 threads, 700x8192, n = 1000
 // 60/61, n = 4000 188/168; 64x600, n = 1000 15.5/16.1, n = 4000 31/20).
 //
-// Not where most tiles would have more candidates within the threshold than are kept, and be evaluated in
-// full after all.  The threshold is 6e-5 + 2.4e-5 L above the least value, since the rounding in its slack
-// is in proportion to n / m as the error is, and the values are a parabola in k / n around the least
-// one: about n sqrt(6e-5 + 2.4e-5 L) candidates, in proportion.  At 112 of that measure no weights but uniform ones lose
-// (64x5000, all / pruned: b = 4, n = 7000 137/108, n = 12000 166/173; b = 6, n = 3000 87/63, n = 6000 155/161; b = 8,
-// n = 2000 179/159, n = 5000 408/424); from n = 8000 on at two and three bits some do (200x700, b = 3, n = 10000 78/84).
-//
 // At 7 and 8 bits the grid leaves about 60 and 76 of 100 candidates.  Fewer workgroups than CUs take as long
 // as a thread's candidates, so these have to get fewer (250x2000, b = 7: n = 1000 47/51, n = 1300 61/52; 64x5000, b = 8: n = 1500
 // 143/149, n = 1700 169/155); more of them gain from n = 600 and 1500 on, or always (1024x1155, b = 7: n = 500 51/54,
 // n = 700 66/59; 2500x4608 n = 500 182/158; 300x7000, b = 8, n = 1500 213/196; 64x5000, n = 1000 93/102).
 bool fast_prunes(int threads, int tiles, int n, int L)
 {
-    if (n < kPruneMin || n > 8000 || (long long)n * n * (60 + 24 * L) > 112LL * 112 * 1000000) return false;
+    if (!grid_pays(n, L)) return false;
     if ((long long)n * L < (tiles < 256 ? 20 : 11) * threads) return false;
     if (L < 63) return true;
     const auto rounds = [&](int count) { return (count + threads - 1) / threads; };
