@@ -76,25 +76,6 @@ int check_common(int bits, int mode)
     return PWLQ_OK;
 }
 
-// Threads that k_fast gives a tile, by the longest of a launch's tiles.  A short tile is
-// served fastest by few threads where there are many tiles (see k_fast), but a thread then
-// walks many candidates one after the other: where the tiles are too few to hide that
-// (b = 4, n = 4000, us, 128 or 256 / 512 threads: 512x121 72/37, 512x300 46/39; n = 1000,
-// 1024x121 24.7/22.6, 2048x121 31.8/36.1; n = 300, 1024x121 14.9/17.2) they get 512.
-//
-// Longer tiles likewise: 256 threads where a launch has many and their look-ups are few, 512 where not (us, 512 / 256:
-// 38 400 tiles of 4096, n = 1000, b = 4, k_fast alone 508/386; but 2500x4608, 512 threads with fewer candidates left out than
-// now: n = 290, without the grid of candidates, b = 5, 68/75, b = 6 85/101; b = 7, n = 700 146/196).
-int fast_threads(int longest, long long tiles, int n, int L)
-{
-    if (longest > kFastLong) return 1024;
-    if (longest > kSmallTile)
-        return tiles > kFastManyTiles && L <= 15 && (n >= kPruneMin || n * L <= 2500) ? 256 : 512;
-    const bool short_tiles = longest <= kFastShort;
-    if (tiles <= (short_tiles ? 1024 : 512) && (long long)n * L >= 3500) return 512;
-    return short_tiles ? 128 : 256;
-}
-
 // Whether n candidates are enough for a grid of them, and not so many that most tiles would have more within the
 // threshold than are kept, and be evaluated in full after all.  The threshold is 6e-5 + 2.4e-5 L above the least
 // value, since the rounding in its slack is in proportion to n / m as the error is, and the values are a parabola in
@@ -105,6 +86,32 @@ int fast_threads(int longest, long long tiles, int n, int L)
 bool grid_pays(int n, int L)
 {
     return n >= kPruneMin && n <= 8000 && (long long)n * n * (60 + 24 * L) <= 112LL * 112 * 1000000;
+}
+
+// Threads that k_fast gives a tile, by the longest of a launch's tiles.  A short tile is
+// served fastest by few threads where there are many tiles (see k_fast), but a thread then
+// walks many candidates one after the other: where the tiles are too few to hide that
+// (b = 4, n = 4000, us, 128 or 256 / 512 threads: 512x121 72/37, 512x300 46/39; n = 1000,
+// 1024x121 24.7/22.6, 2048x121 31.8/36.1; n = 300, 1024x121 14.9/17.2) they get 512.
+//
+// Longer tiles likewise: 256 threads where a launch has many and their look-ups are few, 512 where not (us, 512 / 256:
+// 38 400 tiles of 4096, n = 1000, b = 4, k_fast alone 508/386; but 2500x4608, 512 threads with fewer candidates left out than
+// now: n = 290, without the grid of candidates, b = 5, 68/75, b = 6 85/101; b = 7, n = 700 146/196).
+//
+// One wavefront to a short tile where a launch has many and a grid leaves it few candidates, 60 to 140 of 1000: both
+// wavefronts of 128 threads repeat the reductions and prefixes, and one waits for the other (9000 tiles of 9 to 256, us, 128 /
+// 64: b = 2, n = 1000 51-58 / 29-39, b = 3, n = 300 0.74 to 0.81 of the time, b = 4, n = 1000 0.81 to 0.98).  Not at five bits
+// (1.01 to 1.13) nor past 1000 candidates (b = 4, n = 3000 up to 1.11), nor for few tiles (2100, b = 4, n = 1000
+// up to 1.05).
+int fast_threads(int longest, long long tiles, int n, int L)
+{
+    if (longest > kFastLong) return 1024;
+    if (longest > kSmallTile)
+        return tiles > kFastManyTiles && L <= 15 && (n >= kPruneMin || n * L <= 2500) ? 256 : 512;
+    const bool short_tiles = longest <= kFastShort;
+    if (short_tiles && tiles >= kFastWaveTiles && L <= 7 && n <= kFastWaveCand && grid_pays(n, L)) return 64;
+    if (tiles <= (short_tiles ? 1024 : 512) && (long long)n * L >= 3500) return 512;
+    return short_tiles ? 128 : 256;
 }
 
 // Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
@@ -666,6 +673,9 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
                         break;
                     case 512:
                         k_fast<512, kFastLong / 512><<<wgs, 512, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
+                        break;
+                    case 64:
+                        k_fast<64, kFastShort / 64><<<wgs, 64, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
                         break;
                     case 128:
                         k_fast<128, kFastShort / 128><<<wgs, 128, lds, stream>>>(tb, at, n_cand, bits, units, tile_max, gm, sse32);
