@@ -3,8 +3,9 @@
  * A call of one small tensor is bound by the host: of 5.0 us for an inner product of 8 x 256 x 64, the launch
  * included, 0.9 us were ctypes converting sixteen arguments and 1.4 us the binding around it.
  * A function takes the address of the library's function (ctypes knows it), then that function's arguments;
- * where it has a pointer, a tensor (its data_ptr() is asked for here), an address, or None.  The
- * interpreter's lock is released during the call.  Returns the library's status. */
+ * where it has a pointer, a tensor (its data_ptr() is asked for here), or None where the library takes NULL.
+ * An integer is taken for the function and for the stream only: in the place of a tensor it would reach a
+ * kernel as a device address.  The interpreter's lock is released during the call.  Returns the library's status. */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
@@ -13,7 +14,7 @@ static PyObject *data_ptr_name;
 
 static int64_t whole(PyObject *o, int *bad)
 {
-    const long long v = PyLong_AsLongLong(o);
+    const long long v = *bad ? 0 : PyLong_AsLongLong(o);
     if (v == -1 && PyErr_Occurred()) *bad = 1;
     return v;
 }
@@ -30,22 +31,41 @@ static int small(PyObject *o, int *bad)
 
 static float real(PyObject *o, int *bad)
 {
-    const double v = PyFloat_AsDouble(o);
+    const double v = *bad ? 0.0 : PyFloat_AsDouble(o);
     if (v == -1.0 && PyErr_Occurred()) *bad = 1;
     return (float)v;
 }
 
-static void *pointer(PyObject *o, int *bad)
+/* The function or the stream. */
+static void *handle(PyObject *o, int *bad)
 {
     void *p;
-    if (*bad || o == Py_None) return NULL;
-    if (PyLong_Check(o)) p = PyLong_AsVoidPtr(o);
-    else {
-        PyObject *v = PyObject_CallMethodNoArgs(o, data_ptr_name);
-        if (!v) {
-            *bad = 1;
-            return NULL;
-        }
+    if (*bad) return NULL;
+    if (!PyLong_Check(o)) {
+        PyErr_SetString(PyExc_TypeError, "the function and the stream are integers");
+        *bad = 1;
+        return NULL;
+    }
+    p = PyLong_AsVoidPtr(o);
+    if (!p && PyErr_Occurred()) *bad = 1;
+    return p;
+}
+
+static void *function(PyObject *o, int *bad)
+{
+    void *p = handle(o, bad);
+    if (!p && !*bad) {
+        PyErr_SetString(PyExc_TypeError, "the function is NULL");
+        *bad = 1;
+    }
+    return p;
+}
+
+static void *tensor(PyObject *o, int *bad)
+{
+    PyObject *v = *bad ? NULL : PyObject_CallMethodNoArgs(o, data_ptr_name);
+    void *p = NULL;
+    if (v) {
         p = PyLong_AsVoidPtr(v);
         Py_DECREF(v);
     }
@@ -60,7 +80,10 @@ static int count(const char *name, Py_ssize_t got, Py_ssize_t want)
     return 0;
 }
 
-#define PTR(i) pointer(a[i], &bad)
+#define FN(i) function(a[i], &bad)
+#define TENSOR(i) tensor(a[i], &bad)
+#define TENSOR_OR_NONE(i) (a[i] == Py_None ? NULL : tensor(a[i], &bad))
+#define STREAM(i) handle(a[i], &bad)
 #define INT(i) small(a[i], &bad)
 #define I64(i) whole(a[i], &bad)
 #define F32(i) real(a[i], &bad)
@@ -74,8 +97,8 @@ static PyObject *call_search(PyObject *self, PyObject *const *a, Py_ssize_t n)
     int bad = 0, rc;
     (void)self;
     if (!count("search", n, 14)) return NULL;
-    SearchFn fn = (SearchFn)PTR(0);
-    void *w = PTR(1), *p = PTR(7), *m = PTR(8), *k = PTR(9), *mse = PTR(10), *ws = PTR(11), *stream = PTR(13);
+    SearchFn fn = (SearchFn)FN(0);
+    void *w = TENSOR(1), *p = TENSOR(7), *m = TENSOR(8), *k = TENSOR(9), *mse = TENSOR(10), *ws = TENSOR(11), *stream = STREAM(13);
     const int64_t C = I64(2), K = I64(3), bytes = I64(12);
     const int bits = INT(4), cand = INT(5), mode = INT(6);
     if (bad) return NULL;
@@ -94,8 +117,9 @@ static PyObject *call_quantize(PyObject *self, PyObject *const *a, Py_ssize_t n)
     int bad = 0, rc;
     (void)self;
     if (!count("quantize", n, 12)) return NULL;
-    QuantizeFn fn = (QuantizeFn)PTR(0);
-    void *w = PTR(1), *p = PTR(6), *m = PTR(7), *codes = PTR(8), *flags = PTR(9), *hat = PTR(10), *stream = PTR(11);
+    QuantizeFn fn = (QuantizeFn)FN(0);
+    void *w = TENSOR(1), *p = TENSOR(6), *m = TENSOR(7), *codes = TENSOR(8), *flags = TENSOR(9), *hat = TENSOR_OR_NONE(10),
+         *stream = STREAM(11);
     const int64_t C = I64(2), K = I64(3);
     const int bits = INT(4), mode = INT(5);
     if (bad) return NULL;
@@ -114,9 +138,9 @@ static PyObject *call_linear(PyObject *self, PyObject *const *a, Py_ssize_t n)
     int bad = 0, rc;
     (void)self;
     if (!count("linear_i8", n, 17)) return NULL;
-    LinearFn fn = (LinearFn)PTR(0);
-    void *xq = PTR(1), *codes = PTR(6), *flags = PTR(7), *p = PTR(10), *m = PTR(11), *y = PTR(12), *acc = PTR(13),
-         *ws = PTR(14), *stream = PTR(16);
+    LinearFn fn = (LinearFn)FN(0);
+    void *xq = TENSOR(1), *codes = TENSOR(6), *flags = TENSOR(7), *p = TENSOR(10), *m = TENSOR(11), *y = TENSOR(12), *acc = TENSOR_OR_NONE(13),
+         *ws = TENSOR(14), *stream = STREAM(16);
     const int64_t M = I64(2), K = I64(3), N = I64(8), bytes = I64(15);
     const float s_x = F32(4), z_x = F32(5);
     const int bits = INT(9);

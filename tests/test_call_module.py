@@ -30,6 +30,11 @@ def test_the_signatures_are_the_library_s():
             assert getattr(pwlq.lib, f).argtypes == SIGNATURES[name], f
 
 
+# pointers that the library takes as NULL or that are handles: everything else has to be a tensor
+OPTIONAL = {"search": [], "quantize": [9], "linear_i8": [12]}
+STREAM = {"search": 12, "quantize": 10, "linear_i8": 15}
+
+
 @pytest.mark.parametrize("name", list(SIGNATURES))
 @pytest.mark.parametrize("seed", [1, 2, 3])
 def test_every_argument_arrives_in_its_place(name, seed):
@@ -37,13 +42,12 @@ def test_every_argument_arrives_in_its_place(name, seed):
     keep, args, want = [], [], []
     for i, t in enumerate(types):
         if t is VP:
-            kind = (i + seed) % 4
-            if kind == 0:
+            if i in OPTIONAL[name] and seed % 2:
                 args.append(None)
                 want.append(None)
-            elif kind == 1:
-                args.append(int(rng.integers(1, 1 << 47)))
-                want.append(args[-1])
+            elif i == STREAM[name]:
+                args.append(int(rng.integers(1, 1 << 47)) if seed < 3 else 0)
+                want.append(args[-1] or None)
             else:
                 keep.append(torch.empty(int(rng.integers(1, 50))))
                 args.append(keep[-1])
@@ -60,15 +64,41 @@ def test_every_argument_arrives_in_its_place(name, seed):
     assert got == want
 
 
+@pytest.mark.parametrize("name", list(SIGNATURES))
+def test_an_address_is_taken_for_the_stream_alone(name):
+    """An integer in the place of a tensor (a width for a parameter) would reach a kernel as a device address."""
+    types, got = SIGNATURES[name], []
+    fn = ctypes.cast(recorder(types, got, 0), VP).value
+    t = torch.empty(4)
+    good = [t if x is VP else 1 for x in types]
+    good[STREAM[name]] = 0
+    for i, x in enumerate(types):
+        if x is not VP or i == STREAM[name]:
+            continue
+        for value in [16, 0, True, 1 << 40, np.int64(16)] + [None] * (i not in OPTIONAL[name]):
+            with pytest.raises(AttributeError):
+                getattr(_pwlq_call, name)(fn, *good[:i], value, *good[i + 1:])
+    for value in (None, t, 1.5):
+        with pytest.raises(TypeError):
+            getattr(_pwlq_call, name)(fn, *good[:-1], value)
+        with pytest.raises(TypeError):
+            getattr(_pwlq_call, name)(value, *good)
+    with pytest.raises(TypeError):
+        getattr(_pwlq_call, name)(0, *good)
+    assert got == []
+    assert getattr(_pwlq_call, name)(fn, *good) == 0 and got[0] == t.data_ptr()
+
+
 def test_what_is_no_argument_is_refused_before_the_call():
     got = []
     fn = recorder(SIGNATURES["quantize"], got, 0)
-    good = [ctypes.cast(fn, VP).value, 16, 1, 1, 4, 0, None, None, None, None, None, 0]
+    t = torch.empty(4)
+    good = [ctypes.cast(fn, VP).value, t, 1, 1, 4, 0, t, t, t, t, None, 0]
     for at, value, error in ((1, 1.5, AttributeError), (2, 1.5, TypeError), (2, 1 << 70, OverflowError), (4, 1 << 40, OverflowError),
-                             (4, None, TypeError), (8, "x", AttributeError)):
+                             (4, None, TypeError), (8, "x", AttributeError), (11, 1 << 70, OverflowError)):
         with pytest.raises(error):
             _pwlq_call.quantize(*good[:at], value, *good[at + 1:])
     with pytest.raises(TypeError):
         _pwlq_call.quantize(*good[:-1])
     assert got == []
-    assert _pwlq_call.quantize(*good) == 0 and got[0] == 16
+    assert _pwlq_call.quantize(*good) == 0 and got[0] == t.data_ptr()
