@@ -461,74 +461,77 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
 // instead, from binary32 magnitudes in candidate units, with the chunked sums of the
 // plain search kernel (all lanes read the same LDS word, which is a broadcast).
 //
+// Four elements to a read: element by element a wavefront waits out the LDS for every ten vector instructions (tiles crowded all
+// of them, us, one by one / four to a read: 512x1155 of log-uniform weights, b = 4, n = 600, in 512 threads, 109/72;
+// 1141x2738 of cubes of normal numbers, b = 7, n = 463, 389/291; 2361x5110 of these, b = 4, n = 2464, in 256 threads, 6580/5150).
+//
 // kPairs: two candidates of a thread at a time, half of the reads and two chains of additions, for workgroups of few threads
-// (up to 5120 elements in 256 threads: 4100x5000 of log-uniform weights, b = 4, n = 600, us: 3364 one by one, 2697 so; in
-// 512 threads, most of which have one candidate there, 145 and 168 for 512x1155).
+// (up to 5120 elements in 256 threads: 4100x5000 of log-uniform weights, b = 4, n = 600, us: 1638 one by one, 1573 so).
+// A wavefront takes a pair where any of its lanes has two candidates left, so that no wavefront walks the
+// tile for a part of its pairs and once more for the rest.
+//
+// fast_plain_row: candidates k0 and k0 + apart, those up to n.
+template <int kC>
+__device__ inline void fast_plain_row(const unsigned *__restrict__ elems, int len, int n, float Lf, int k0, int apart,
+                                      float *__restrict__ row)
+{
+    float kf[kC], rc[kC], rt[kC], ct[kC], stepc[kC], stept[kC], outer[kC], acc[kC];
+#pragma unroll
+    for (int x = 0; x < kC; ++x) {
+        const int k = k0 + x * apart < n ? k0 + x * apart : n;
+        kf[x] = (float)k;
+        rc[x] = Lf / kf[x];
+        rt[x] = (k < n) ? Lf / (float)(n - k) : 0.0f;
+        ct[x] = -kf[x] * rt[x];
+        stepc[x] = kf[x] / Lf;
+        stept[x] = (float)(n - k) / Lf;
+        // else the compiler divides once per element, after the choice of the piece: 21 vector instructions
+        // instead of 10 (4096x512 of log-uniform weights, b = 4, n = 2000, us: 2106, 817 now)
+        asm("" : "+v"(stepc[x]), "+v"(stept[x]));
+        outer[x] = 0.0f;
+    }
+    const auto add = [&](unsigned e) {
+        const float u = __uint_as_float(e);
+#pragma unroll
+        for (int x = 0; x < kC; ++x) {
+            const bool tail = u > kf[x];
+            const float t = tail ? __builtin_fmaf(u, rt[x], ct[x]) : u * rc[x];
+            const float err = (t - __builtin_rintf(t)) * (tail ? stept[x] : stepc[x]);
+            acc[x] = __builtin_fmaf(err, err, acc[x]);
+        }
+    };
+    static_assert(kChunk % 4 == 0, "chunks of whole 16-byte words");
+    for (int cb = 0; cb < len; cb += kChunk) {
+        const int ce = (cb + kChunk < len) ? cb + kChunk : len;
+#pragma unroll
+        for (int x = 0; x < kC; ++x) acc[x] = 0.0f;
+        int i = cb;
+        for (; i + 4 <= ce; i += 4) {
+            const uint4 e = *reinterpret_cast<const uint4 *>(elems + i);
+            add(e.x);
+            add(e.y);
+            add(e.z);
+            add(e.w);
+        }
+        for (; i < ce; ++i) add(elems[i]);
+#pragma unroll
+        for (int x = 0; x < kC; ++x) outer[x] += acc[x];
+    }
+#pragma unroll
+    for (int x = 0; x < kC; ++x)
+        if (k0 + x * apart <= n) row[k0 + x * apart - 1] = outer[x];
+}
+
 template <int kT, bool kPairs>
 __device__ inline void fast_plain(const unsigned *__restrict__ elems, int len, int n, int Li,
                                   float *__restrict__ row)
 {
-    const float Lf = (float)Li;
-    int k = threadIdx.x + 1;
-    if constexpr (kPairs) {
-        for (; k + kT <= n; k += 2 * kT) {
-            float kf[2], rc[2], rt[2], ct[2], stepc[2], stept[2], outer[2] = {0.0f, 0.0f};
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const int kx = k + x * kT;
-                kf[x] = (float)kx;
-                rc[x] = Lf / kf[x];
-                rt[x] = (kx < n) ? Lf / (float)(n - kx) : 0.0f;
-                ct[x] = -kf[x] * rt[x];
-                stepc[x] = kf[x] / Lf;
-                stept[x] = (float)(n - kx) / Lf;
-                asm("" : "+v"(stepc[x]), "+v"(stept[x]));
-            }
-            for (int cb = 0; cb < len; cb += kChunk) {
-                const int ce = (cb + kChunk < len) ? cb + kChunk : len;
-                float acc[2] = {0.0f, 0.0f};
-                for (int i = cb; i < ce; ++i) {
-                    const float u = __uint_as_float(elems[i]);
-#pragma unroll
-                    for (int x = 0; x < 2; ++x) {
-                        const bool tail = u > kf[x];
-                        const float t = tail ? __builtin_fmaf(u, rt[x], ct[x]) : u * rc[x];
-                        const float err = (t - __builtin_rintf(t)) * (tail ? stept[x] : stepc[x]);
-                        acc[x] = __builtin_fmaf(err, err, acc[x]);
-                    }
-                }
-                outer[0] += acc[0];
-                outer[1] += acc[1];
-            }
-            row[k - 1] = outer[0];
-            row[k + kT - 1] = outer[1];
-        }
-    }
-    for (; k <= n; k += kT) {
-        const float kf = (float)k;
-        const float nk = (float)(n - k);
-        const float rc = Lf / kf;
-        const float rt = (k < n) ? Lf / nk : 0.0f;
-        const float ct = -kf * rt;
-        float stepc = kf / Lf, stept = nk / Lf;
-        // else the compiler divides once per element, after the choice of the piece: 21 vector instructions
-        // instead of 10 (4096x512 of log-uniform weights, b = 4, n = 2000, us: 2106, 817 now)
-        asm("" : "+v"(stepc), "+v"(stept));
-        float outer = 0.0f;
-        for (int cb = 0; cb < len; cb += kChunk) {
-            const int ce = (cb + kChunk < len) ? cb + kChunk : len;
-            float acc = 0.0f;
-            for (int i = cb; i < ce; ++i) {
-                const float u = __uint_as_float(elems[i]);
-                const bool tail = u > kf;
-                const float t = tail ? __builtin_fmaf(u, rt, ct) : u * rc;
-                const float err = (t - __builtin_rintf(t)) * (tail ? stept : stepc);
-                acc = __builtin_fmaf(err, err, acc);
-            }
-            outer += acc;
-        }
-        row[k - 1] = outer;
-    }
+    const int tid = threadIdx.x;
+    int at = 0;                                    // candidates at + 1 .. at + kT, one per thread
+    const int wave = uni(tid & ~63);
+    if constexpr (kPairs)
+        for (; at + kT + wave < n; at += 2 * kT) fast_plain_row<2>(elems, len, n, (float)Li, at + tid + 1, kT, row);
+    for (; at + wave < n; at += kT) fast_plain_row<1>(elems, len, n, (float)Li, at + tid + 1, kT, row);
 }
 
 // What depends on n and bits alone: magnitudes are held in units of 1/unit of a candidate,
