@@ -176,7 +176,7 @@ __device__ inline void exact_tile(const float *__restrict__ tile, int len,
         const Pieces q1 = k1 < 0 ? q0 : make_pieces(m, grid_point(m, k1, n), bits);
         // two places at a time: short chains side by side, and whole wavefronts skip what no lane has
         constexpr int kSome = kEpt >= 2 ? 2 : 1;
-        const bool plain = exact_zero_adds_nothing(q0) && exact_zero_adds_nothing(q1);
+        const bool plain = kEpt > 1 && exact_zero_adds_nothing(q0) && exact_zero_adds_nothing(q1);
         if (k1 < 0) {
             if (kEpt > 0) {
                 if (plain) {
