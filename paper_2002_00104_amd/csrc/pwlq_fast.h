@@ -558,7 +558,8 @@ inline FastUnits fast_units(int n, int bits)
 
 // The elements of a thread in batches, e0 .. e0 + count - 1: batch(first, count), both compile-time.  What a wavefront does with
 // a batch depends on whether the tile ends in it: batches are as many as the tiles of a launch's range end in
-// usefully, and no longer than the LDS adds that a thread can hold in flight within 64 registers.
+// usefully, and no longer than the LDS adds that a thread can hold in flight within 64 registers.  Two in workgroups of
+// 1024 threads, where a tile may end in any (four: 0.996 to 1.04 of the time; 59x7021 and 1533x1051 in one launch, b = 4, n = 97, us, 46.7/45.1).
 template <int kPer, typename F>
 __device__ inline void fast_batches(F batch)
 {
@@ -568,7 +569,7 @@ __device__ inline void fast_batches(F batch)
     if constexpr (kPer == 2) PWLQ_BATCH(0, 2);
     if constexpr (kPer == 4) PWLQ_BATCH(0, 4);
     if constexpr (kPer == 20) { PWLQ_BATCH(0, 4); PWLQ_BATCH(4, 4); PWLQ_BATCH(8, 4); PWLQ_BATCH(12, 4); PWLQ_BATCH(16, 4); }
-    if constexpr (kPer == 8) { PWLQ_BATCH(0, 4); PWLQ_BATCH(4, 4); }
+    if constexpr (kPer == 8) { PWLQ_BATCH(0, 2); PWLQ_BATCH(2, 2); PWLQ_BATCH(4, 2); PWLQ_BATCH(6, 2); }
     if constexpr (kPer == 10) { PWLQ_BATCH(0, 5); PWLQ_BATCH(5, 5); }
 #undef PWLQ_BATCH
 }
