@@ -50,6 +50,8 @@ int fail(int status, const char *fmt, ...)
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+constexpr long long kBeside = 1;                   // tiles of k_fast that count for the units' size, per tile that is not
+
 // Everything a call needs to know about its tensors, built on the host.
 struct Plan {
     std::vector<TensorRec> recs;
@@ -269,15 +271,20 @@ int build_plan(Plan &pl, const pwlq_tensor_desc *desc, int n_tensors, int n_cand
         for (TensorRec &r : tmp) r.fast = r.tile_len >= min_len ? 1 : 0;
     }
     // a search workgroup walks tpu tiles one after the other; keep enough
-    // workgroups to fill the chip when the call is small.  Tiles that k_fast evaluates are in no unit.
+    // workgroups to fill the chip when the call is small.  Tiles that k_fast evaluates are in no unit, but
+    // as many of them as others count here: fewer and larger units and workgroups beside them are faster (us, sized for the others
+    // alone / so: 470x6256 and 8056x104, b = 7, n = 985, 180/171; 553x5959 and 3924x338, b = 6, n = 77, 103/97; 1735x632 and 7957x118,
+    // b = 4, n = 209, 81/78), but not where few are left (all counted: up to 1.03 times the time, on the average the same).
     const auto size_units = [&](bool all) {
-        long long total_tiles = 0, tiny_tiles = 0, units = 0;
+        long long total_tiles = 0, tiny_tiles = 0, fast_tiles = 0, fast_tiny = 0, units = 0;
         const auto tiny = [](const TensorRec &r) { return r.tile_len <= kTinyTile && r.tpg == 1; };
-        for (const TensorRec &r : tmp)
-            if (all || !r.fast) {
-                total_tiles += r.ntiles;
-                if (tiny(r)) tiny_tiles += r.ntiles;
-            }
+        for (const TensorRec &r : tmp) {
+            const bool in = all || !r.fast;
+            (in ? total_tiles : fast_tiles) += r.ntiles;
+            if (tiny(r)) (in ? tiny_tiles : fast_tiny) += r.ntiles;
+        }
+        total_tiles += std::min(fast_tiles, kBeside * total_tiles);
+        tiny_tiles += std::min(fast_tiny, kBeside * tiny_tiles);
         const int cap = (int)std::max(1LL, total_tiles / kMinUnits);
         // tiles of at most kTinyTile elements cost a unit little each (no offsets, loads one
         // tile ahead): up to kTinyUnit per unit while they still make about a thousand units
@@ -548,10 +555,11 @@ int run_search(const pwlq_tensor_desc *desc, int n_tensors, int bits, int n_cand
     const int ny = (pl.nblk + kSearchWaves - 1) / kSearchWaves;
     int bpw_log2 = 0, upw = 1;             // candidate blocks per unit in a workgroup, as a power of two; units per workgroup
     const auto search_wgs = [&](long long units) {
+        const long long sized = std::min(pl.n_all_units, (1 + kBeside) * units);
         bpw_log2 = 0;
         while ((1 << bpw_log2) < std::min(pl.nblk, kSearchWaves)) ++bpw_log2;
         // ... but a small call keeps one unit per workgroup rather than a handful of workgroups
-        while (bpw_log2 < 4 && units / (kSearchWaves >> bpw_log2) < 2048) ++bpw_log2;
+        while (bpw_log2 < 4 && sized / (kSearchWaves >> bpw_log2) < 2048) ++bpw_log2;
         upw = kSearchWaves >> bpw_log2;
         const long long unit_groups = (units + upw - 1) / upw;
         return (unit_groups + 7) / 8 * 8 * ny;
