@@ -116,58 +116,6 @@ int fast_threads(int longest, long long tiles, int n, int L)
     return short_tiles ? 128 : 256;
 }
 
-// Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
-// candidate grows with the number of half-way points (2L look-ups) and hardly depends on
-// the tile length, the plain evaluation costs one pass over the tile.  16384 tiles, 1000
-// candidates, b = 4, us, look-ups of all candidates / pass: 160 elements 168 / 249, 96 elements 162 / 178,
-// 64 elements 157 / 144; but a line at 6 * 2L cost MobileNetV2 shapes 216 -> 238, one more
-// launch beside the passes over the shorter tiles, which stay.  At b = 8 and many
-// candidates the line is a little longer (2048 and 1024 tiles of 2048, n = 1000: 297/286,
-// 169/160; n = 300: 149/194, 78/120).
-//
-// Below 2048 tiles the look-ups of a tile, L pairs for every candidate of a thread one after
-// the other at about 0.3 us, take as long for one tile as for all, and the passes are spread over
-// the chip: tiles not far above that length are handed over only where the look-ups'
-// time is less than the passes' at 1.6e13 evaluations a second on a full chip and 6 us for
-// their launch (16x121, n = 20000, us, look-ups / pass 99/54; 64x2048, b = 8, n = 2000 116/46; 512x121,
-// n = 1000 15.5/20.3).
-//
-// Both price the look-ups of all candidates.  Where 2048 tiles and more look up a grid of them first (see grid_pays) a
-// tile costs the same whatever its length, and less than its pass, down to the 3x3 kernels of a depthwise layer
-// (kFastShortest): at up to four bits at every length (us, passes / look-ups: 7136x9, b = 4, n = 1000 44/34, n = 3000
-// 108/41, b = 3, n = 300 32/32; the searches of MobileNetV2's shapes, b = 4, n = 1000 164/118, for which the shortest
-// tiles need no launches of their own; 16384 tiles of 18 to 119, n = 1000, 0.60 to 0.33 of the time), at five bits at
-// every length from 1000 candidates on and else from 64 (n = 300, 16384x48 1.00, x64 0.93 of the time), at six from
-// 150 and 1000 (16384x150 0.81, x64 1.07; n = 300 1.25).  What loses on this side of the line are tiles of nine alone:
-// 7136x9, b = 4, n = 300 31/32, and cubes of normal numbers at b = 5, n = 3000 133/141.
-int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
-{
-    const int L = (1 << (bits - 1)) - 1;
-    const int shortest = (bits == 8 && n >= 800 ? 9 : 8) * (2 * L) + 8, always = 16 * (2 * L + 1) + 64;
-    long long tiles = 0, elements = 0;
-    if (grid_pays(n, L) && (L <= 15 || (L == 31 && n >= 1000))) {
-        const int low = L == 31 ? 150 : L == 15 && n < 1000 ? 64 : kFastShortest;
-        for (const TensorRec &r : recs)
-            if (r.tile_len >= low && r.tile_len < always) tiles += r.ntiles;
-        if (tiles >= 2048) return low;
-        tiles = 0;
-    }
-    int longest = 0;
-    for (const TensorRec &r : recs) {
-        if (r.tile_len < shortest || r.tile_len >= always) continue;
-        tiles += r.ntiles;
-        elements += (long long)r.ntiles * r.tile_len;
-        longest = std::max(longest, r.tile_len);
-    }
-    if (tiles >= 2048) return shortest;
-    const int threads = fast_threads(longest, tiles, n, L);
-    const long long look_ups_ns = (long long)((n + threads - 1) / threads) * L * 300;
-    const long long wavefronts = tiles * ((n + kBlk - 1) / kBlk);
-    const long long per_ns = 16000 * std::min(wavefronts + 1024, 8192LL) / 8192;
-    const long long passes_ns = 6000 + elements * n / per_ns;
-    return look_ups_ns <= passes_ns ? shortest : always;
-}
-
 // Whether the tiles of a launch that are groups of their own look up a grid of candidates first and
 // then only those that it does not exclude (see fast_pruned): where a thread would have 11 or
 // more pairs of look-ups for all candidates, or 20 where the workgroups are fewer than the CUs, and each
@@ -190,6 +138,101 @@ bool fast_prunes(int threads, int tiles, int n, int L)
     return L == 63 ? n >= 600 || tiles >= 2048 : n >= 1500;
 }
 
+// Tiles by length, longest first: those of a class need workgroups and LDS of one size.
+int size_class(int len) { return len > kFastLong ? 0 : len > kSmallTile ? 1 : len > kFastShort ? 2 : 3; }
+
+// Whether the `shorter` tiles of at most `next` elements behind the `longer` ones of at most `longest` of a launch get a
+// launch of their own: where both sides have enough of them, or the shorter ones alone.  Workgroups of 512 and 1024 threads
+// are much too large for them (us, together / apart: 500x8000 and 5000x9, b = 4, n = 1000 158/65, 77x5816 and 3776x377,
+// n = 1128 130/70; 1281 tiles of 838 behind 39 of 5652 38/41).  Of 256 threads, which tiles of more than kFastShort elements
+// would have in either case, only those that get fewer, and only where they are many (12x607 and 4308x59, b = 2, n = 1223 47/58,
+// 70x4518 and 5564x77, b = 3, n = 1628 72/64, 41x3171 and 8351x19, n = 369 64/44).
+bool own_launch(int longest, long long longer, int next, long long shorter, int n, int L)
+{
+    if (shorter < kFastLaunchTiles) return false;
+    if (longer >= kFastLaunchTiles) return true;
+    if (fast_threads(longest, longer + shorter, n, L) >= 512) return shorter >= kFastOwnTiles;
+    return next <= kFastShort && (shorter >= kFastWaveTiles || (shorter >= kFastOwnShort &&
+                                                                fast_prunes(fast_threads(next, shorter, n, L), (int)shorter, n, L)));
+}
+
+// Whether tiles from `low` elements on are handed to the prefix-sum evaluator, shorter ones than its look-ups of all
+// candidates pay for: where 2048 tiles and more look up a grid of them first (see grid_pays) a
+// tile costs the same whatever its length, and less than its pass, down to the 3x3 kernels of a depthwise layer
+// (kFastShortest): at up to four bits at every length (us, passes / look-ups: 7136x9, b = 4, n = 1000 44/34, n = 3000
+// 108/41, b = 3, n = 300 32/32; the searches of MobileNetV2's shapes, b = 4, n = 1000 164/118, for which the shortest
+// tiles need no launches of their own; 16384 tiles of 18 to 119, n = 1000, 0.60 to 0.33 of the time), at five bits at
+// every length from 1000 candidates on and else from 64 (n = 300, 16384x48 1.00, x64 0.93 of the time), at six from
+// 150 and 1000 (16384x150 0.81, x64 1.07; n = 300 1.25).
+//
+// Where launches of the short tiles alone look up all candidates after all (b = 2 below 1408 candidates, or 704 in one
+// wavefront; b = 3 below 470) these are few enough for any length but nine, whose pass is two vectors: tiles of nine alone
+// lose from some number on (b = 3, n = 400, 4000 tiles 0.96, 7136 1.06 of the time; b = 2, n = 700, 20000 tiles 0.96, 60000
+// 1.06; with the grid b = 5, n = 1000, 12000 tiles 1.00, 20000 1.05, 60000 1.21, but n = 1100, one more block of candidates
+// in the pass, 0.79).
+//
+// Not where they would share workgroups of 512 or 1024 threads with a few longer tiles (see own_launch).
+bool many_short(const std::vector<TensorRec> &recs, int low, int always, int n, int L)
+{
+    long long counts[4] = {}, tiles = 0, nine = 0;             // by size_class
+    for (const TensorRec &r : recs) {
+        if (r.tile_len < low) continue;
+        counts[size_class(r.tile_len)] += r.ntiles;
+        if (r.tile_len < always && r.tile_len <= kSmallTile) tiles += r.ntiles;
+        if (r.tile_len == kFastShortest) nine += r.ntiles;
+    }
+    if (tiles < 2048) return false;
+    const long long small = counts[2] + counts[3];
+    const int next = counts[2] > 0 ? kSmallTile : kFastShort;
+    const bool cut = counts[0] > 0 && counts[1] > 0 && own_launch(kTileMax, counts[0], kFastLong, counts[1] + small, n, L);
+    const long long longer = counts[1] + (cut ? 0 : counts[0]);
+    const int longest = longer > counts[1] ? kTileMax : kFastLong;
+    if (longer > 0 && !own_launch(longest, longer, next, small, n, L) && fast_threads(longest, longer + small, n, L) > 256) return false;
+    if (4 * nine <= 3 * small) return true;
+    if (L == 15) return n > 1024 || small <= 12288;
+    return small * L <= 16384 || fast_prunes(fast_threads(kFastShort, small, n, L), (int)small, n, L);
+}
+
+// Shortest tile handed to the prefix-sum evaluator by the fast search: its cost per
+// candidate grows with the number of half-way points (2L look-ups) and hardly depends on
+// the tile length, the plain evaluation costs one pass over the tile.  16384 tiles, 1000
+// candidates, b = 4, us, look-ups of all candidates / pass: 160 elements 168 / 249, 96 elements 162 / 178,
+// 64 elements 157 / 144; but a line at 6 * 2L cost MobileNetV2 shapes 216 -> 238, one more
+// launch beside the passes over the shorter tiles, which stay.  At b = 8 and many
+// candidates the line is a little longer (2048 and 1024 tiles of 2048, n = 1000: 297/286,
+// 169/160; n = 300: 149/194, 78/120).
+//
+// Below 2048 tiles the look-ups of a tile, L pairs for every candidate of a thread one after
+// the other at about 0.3 us, take as long for one tile as for all, and the passes are spread over
+// the chip: tiles not far above that length are handed over only where the look-ups'
+// time is less than the passes' at 1.6e13 evaluations a second on a full chip and 6 us for
+// their launch (16x121, n = 20000, us, look-ups / pass 99/54; 64x2048, b = 8, n = 2000 116/46; 512x121,
+// n = 1000 15.5/20.3).
+int fast_min_len(const std::vector<TensorRec> &recs, int bits, int n)
+{
+    const int L = (1 << (bits - 1)) - 1;
+    const int shortest = (bits == 8 && n >= 800 ? 9 : 8) * (2 * L) + 8, always = 16 * (2 * L + 1) + 64;
+    long long tiles = 0, elements = 0;
+    if (grid_pays(n, L) && (L <= 15 || (L == 31 && n >= 1000))) {
+        const int low = L == 31 ? 150 : L == 15 && n < 1000 ? 64 : kFastShortest;
+        if (many_short(recs, low, always, n, L)) return low;
+    }
+    int longest = 0;
+    for (const TensorRec &r : recs) {
+        if (r.tile_len < shortest || r.tile_len >= always) continue;
+        tiles += r.ntiles;
+        elements += (long long)r.ntiles * r.tile_len;
+        longest = std::max(longest, r.tile_len);
+    }
+    if (tiles >= 2048) return shortest;
+    const int threads = fast_threads(longest, tiles, n, L);
+    const long long look_ups_ns = (long long)((n + threads - 1) / threads) * L * 300;
+    const long long wavefronts = tiles * ((n + kBlk - 1) / kBlk);
+    const long long per_ns = 16000 * std::min(wavefronts + 1024, 8192LL) / 8192;
+    const long long passes_ns = 6000 + elements * n / per_ns;
+    return look_ups_ns <= passes_ns ? shortest : always;
+}
+
 struct FastLaunch {
     int begin, end, threads, longest;
     bool prunes;
@@ -200,7 +243,6 @@ struct FastLaunch {
 // longest tile first, so the fast tiles are 0 .. fast_tiles-1.
 int plan_fast_launches(Plan &pl, int fast_tiles, int n, int L, FastLaunch (&out)[4])
 {
-    auto size_class = [](int len) { return len > kFastLong ? 0 : len > kSmallTile ? 1 : len > kFastShort ? 2 : 3; };
     int launches = 0, begin = 0, seen = 0, longest = 0;
     size_t first = 0;
     for (size_t i = 0; i < pl.recs.size() && pl.recs[i].fast; ++i) {
@@ -208,7 +250,7 @@ int plan_fast_launches(Plan &pl, int fast_tiles, int n, int L, FastLaunch (&out)
         seen += pl.recs[i].ntiles;
         const bool last = seen == fast_tiles;
         if (!last && (size_class(pl.recs[i + 1].tile_len) == size_class(longest) ||
-                      seen - begin < kFastLaunchTiles || fast_tiles - seen < kFastLaunchTiles))
+                      !own_launch(longest, seen - begin, pl.recs[i + 1].tile_len, fast_tiles - seen, n, L)))
             continue;
         const int threads = fast_threads(longest, seen - begin, n, L);
         const bool prunes = fast_prunes(threads, seen - begin, n, L);

@@ -76,7 +76,8 @@ constexpr int kFastShortest = 9;                   // shortest tile that many sh
 constexpr int kFastWaveTiles = 8192, kFastWaveCand = 1000;   // a wavefront for a short tile: fewest tiles, most candidates (fast_threads)
 constexpr int kFastManyTiles = 2048;               // more tiles of 1025 to kFastLong elements get 256 threads instead of 512
 constexpr int kFastGridMax = 1 << 21;              // workgroups of a launch
-constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones
+constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones,
+constexpr int kFastOwnTiles = 2048, kFastOwnShort = 6144;   // ... or than these where it has fewer longer ones (own_launch)
 
 // Error of a tile's filter value beyond the rounding of its elements: A is a sum of
 // squares added in at most 33 steps (10 per thread, 6 over the wavefront, 16 over the
