@@ -143,7 +143,7 @@ int size_class(int len) { return len > kFastLong ? 0 : len > kSmallTile ? 1 : le
 
 // Whether the `shorter` tiles of at most `next` elements behind the `longer` ones of at most `longest` of a launch get a
 // launch of their own: where both sides have enough of them, or the shorter ones alone.  Workgroups of 512 and 1024 threads
-// are much too large for them (us, together / apart: 500x8000 and 5000x9, b = 4, n = 1000 158/65, 77x5816 and 3776x377,
+// are much too large for them (us, together / apart: 500x8000 and 5000x9, b = 4, n = 1000 159/76, 77x5816 and 3776x377,
 // n = 1128 130/70; 1281 tiles of 838 behind 39 of 5652 38/41).  Of 256 threads, which tiles of more than kFastShort elements
 // would have in either case, only those that get fewer, and only where they are many (12x607 and 4308x59, b = 2, n = 1223 47/58,
 // 70x4518 and 5564x77, b = 3, n = 1628 72/64, 41x3171 and 8351x19, n = 369 64/44).
