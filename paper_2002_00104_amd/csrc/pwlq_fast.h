@@ -313,18 +313,23 @@ constexpr int kPruneKeep = 64;                     // most of those within the t
 
 // log2 of the grid's step.  The gap below the chord goes with the square of the step and, against the error, of L: up to
 // four bits half of the points leave fewer candidates in all, which larger workgroups evaluate as fast as few.
+__host__ __device__ constexpr int prune_grid(int L, int threads) { return threads <= 256 && L <= 7 ? kPruneGrid / 2 : kPruneGrid; }
 __host__ __device__ constexpr int prune_log(int n, int L, int threads)
 {
-    const int grid = threads <= 256 && L <= 7 ? kPruneGrid / 2 : kPruneGrid;
     int log = 2;
-    while (n >> log > grid) ++log;
+    while (n >> log > prune_grid(L, threads)) ++log;
     return log;
 }
-// number of the last point, which is candidate n
+// number of the last point, which is candidate n.  Of a full grid its neighbour may be up to two steps away: a point more than 64
+// or 128 would halve the lanes that each gets (7048x65, b = 3, n = 517, us, 65 points 30.4, 64 28.5).
 __host__ __device__ constexpr int prune_points(int n, int L, int threads)
 {
-    return (n + (1 << prune_log(n, L, threads)) - 1) >> prune_log(n, L, threads);
+    const int log = prune_log(n, L, threads), points = (n + (1 << log) - 1) >> log, grid = prune_grid(L, threads);
+    return points < grid ? points : grid;
 }
+static_assert(prune_points(512, 7, 128) == 64 && prune_points(519, 3, 256) == 64 && prune_points(520, 3, 64) == 33 &&
+                  prune_points(528, 7, 128) == 33 && prune_points(1031, 15, 512) == 128 && prune_points(300, 1, 64) == 38,
+              "no more points than the grid has");
 // LDS beyond the tables: the grid's values and slopes, then the list
 __host__ __device__ constexpr int prune_bytes(int n, int L, int threads)
 {
@@ -347,9 +352,9 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
                                    FastPruneLds &S, float *value, unsigned short *list, int *__restrict__ row)
 {
     const int tid = threadIdx.x, lane = tid & 63;
-    const int log = prune_log(c.n, c.Li, kT), step = 1 << log, points = prune_points(c.n, c.Li, kT);
+    const int log = prune_log(c.n, c.Li, kT), points = prune_points(c.n, c.Li, kT);
     float *slope = value + points + 1;
-    const auto point = [&](int i) { return i << log < c.n ? i << log : c.n; };
+    const auto point = [&](int i) { return i < points ? i << log : c.n; };
     const auto least = [&](bool lead, float v) {
         const unsigned w = ~wave_max_u32(lead ? ~__float_as_uint(v) : ~0x7f800000u);      // v >= 0
         if (lane == 0) atomicMin(&S.least, w);
@@ -363,7 +368,7 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
     };
     fast_each<kT, true>(Q, c, points, [&](int i) { return point(i + 1); }, [&](bool lead, int k, float v, const FastSlope &s) {
         if (lead) {
-            const int i = (k + step - 1) >> log;
+            const int i = k < c.n ? k >> log : points;
             value[i] = v;
             slope[i] = s.d;
             if (k == c.n) { value[0] = v; slope[0] = s.centre; }

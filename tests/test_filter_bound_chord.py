@@ -43,7 +43,8 @@ def grid_of(n, bits):
     log = 2
     while n >> log > most:
         log += 1
-    return np.minimum(np.arange((n + (1 << log) - 1 >> log) + 1) << log, n)
+    points = min(n + (1 << log) - 1 >> log, most)               # of a full grid the last step may be up to two
+    return np.append(np.arange(points) << log, n)
 
 
 @pytest.mark.parametrize("bits,n,K", [(2, 300, 300), (3, 515, 64), (4, 1000, 2000), (5, 777, 1155), (8, 300, 700)])
@@ -90,7 +91,7 @@ def pruned_list(values, D, count, n, grid):
 
 
 @pytest.mark.parametrize("bits,n,K", [(2, 300, 300), (2, 1000, 64), (3, 2000, 200), (4, 301, 4096), (4, 1000, 576),
-                                      (4, 1000, 2000), (5, 303, 1155), (6, 515, 700), (8, 1000, 2100), (4, 5000, 130)])
+                                      (4, 1000, 2000), (5, 303, 1155), (3, 262, 500), (4, 519, 300), (6, 515, 700), (8, 1000, 2100), (4, 5000, 130)])
 def test_the_list_is_that_of_the_full_row(bits, n, K):
     evaluated = []
     for w in rows(K, bits * 7919 + n):

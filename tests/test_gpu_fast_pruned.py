@@ -1,5 +1,5 @@
 """The fast search's grid of candidates at its edges, against the oracle: as few candidates as
-the grid takes and one less, a last interval of one candidate and of a full step, more
+the grid takes and one less, a last interval of one candidate, of a full step and of almost two, more
 candidates between the grid points than its list holds, more within the threshold than it
 keeps (equal errors everywhere), and tiles that are not a group of their own.
 
@@ -46,7 +46,7 @@ def search(P, tensors, bits, n):
     (6, 299, 600, False), (6, 300, 600, True), (4, 512, 130, True), (5, 513, 1030, True), (4, 515, 257, True),
     (2, 1500, 64, True), (4, 1000, 5121, False), (4, 1700, 5121, True), (3, 1024, 700, True), (7, 1025, 2816, True),
     (7, 300, 6000, True), (8, 1500, 4200, True), (5, 2049, 1155, True), (8, 4100, 4200, False), (4, 20000, 600, False),
-    (6, 1000, 8193, False), (2, 65535, 600, False)])
+    (6, 1000, 8193, False), (2, 65535, 600, False), (4, 519, 700, True), (3, 1039, 130, True), (2, 4159, 1100, True)])
 def test_fast_search_of_many_candidates(P, bits, n, K, pruned):
     w = rows(K, np.random.default_rng(bits * 1000 + n))
     w = np.concatenate([w, w[:1] * 1e-37, np.zeros_like(w[:1]), np.full_like(w[:1], np.inf), w[:1] * np.nan])
