@@ -1081,24 +1081,28 @@ RowShape smaller_row_shape(const RowShape &rs, long long M, long long K, long lo
     return wgs(c) < 256 && (M * K <= 4 << 20 || (bits == 8 && planes == 2)) ? c : rs;
 }
 
-// Whether a call of y alone goes to k_linear_wide: its estimated time (us) against k_linear's, from 455 calls of 65 to
-// 4096 rows and 100 to 1500 tiles of 256 x 128.  Both pay per pass over the chip, of 256 workgroups (k_linear: half a pass;
-// `xcd_wgs` of its workgroups are on the fullest XCD), for its start, its end and the reduction; and per tile for y, k_linear_wide
-// more of it where rows of y are no whole vectors.  Taken so, the calls' mean is 0.871 of the time by k_linear and k_linear_split (0.866 if
-// the faster one were known each time; the worst 1.19 times the faster one's): 1024x2064x8000 60.6/40.8, 4096x4096x5500 212/166,
-// 100x4096x30000 91/58, but 1300x1024x3100, where 130 tiles of 256 rows are half a pass, 27/26, 4096x272x11008 64/70, 4096x64x3001
-// 18.7/23.9.  Below 100 tiles most of its CUs are idle (2048x4096x1600, 104 tiles, 49/54; 768x4096x2048, 48, 33/52), and
+// Whether a call of y alone goes to k_linear_wide: its estimated time (us) against 0.97 of that of k_linear with k_linear_wsum,
+// from 898 calls of 65 to 4096 rows and 90 to 1600 tiles of 256 x 128, most of them near the line (each within 7 % on
+// the average).  Both pay per pass over the chip, of 256 workgroups (k_linear: half a pass; `xcd_wgs` of its workgroups are on the
+// fullest XCD), for its start, its end and the reduction; and for y, k_linear_wide more where rows of y are no whole
+// vectors, and then no less than a pass of full tiles does.  k_linear_wsum goes with N and N K.  Taken so, the calls' mean is
+// 0.900 of the time by k_linear and k_linear_split (0.898 if the faster one were known each time), 7 of them lose more than
+// 5 % and the worst 10: 1024x2064x8000 60.6/40.8, 4096x4096x5500 212/166, 100x4096x30000 91/58, 1721x7968x6440 242/211, but
+// 4096x272x11008 64/70, 1072x16x3782 10.8/12.8, 1183x592x2977 16.5/19.1, 4096x64x3001 18.7/23.9.
+// Below 100 tiles most of its CUs are idle (2048x4096x1600, 104 tiles, 49/54; 768x4096x2048, 48, 33/52), and
 // k_linear_split, which has at most 384 workgroups, is beaten from 129 tiles on (128x4096x17000 60.1/55.5; 2600x4096x1000, 88
 // tiles, 50/54).  A quarter of a tile's rows, or less, is left to k_linear, and so are the
 // shortest reductions past one pass, which are their output (2048x64x11008 26.7/27.9).
-bool linear_wide(long long M, long long K, long long N, long long tiles, long long xcd_wgs, bool can_split)
+bool linear_wide(long long M, long long K, long long N, const LinWideTiles &tiles, long long xcd_wgs, bool can_split)
 {
-    if (M <= kLinWideBM / 4 || tiles < (can_split ? 129 : 100) || (tiles > 256 && K < 128)) return false;
+    const long long count = (long long)tiles.rows * tiles.chans;
+    if (M <= kLinWideBM / 4 || count < (can_split ? 129 : 100) || (count > 256 && K < 128)) return false;
     const auto passes = [](long long wgs, int per) { return (double)((wgs + per - 1) / per); };
-    const double k = (double)K / 1000.0;
-    const double wide = 3.5 + passes((tiles + 7) / 8, 32) * (3.9 + 12.2 * k) + (N % 4 ? 6.8 : 3.9) * (double)tiles / 256.0;
-    const double tall = 9.9 + 2.7 * passes(xcd_wgs, 64) + 8.35 * passes(xcd_wgs, 32) * k + 2.3 * (double)xcd_wgs / 64.0;
-    return wide < tall;
+    const double k = (double)K / 1000.0, full = (double)M / (double)(kLinWideBM * (long long)tiles.rows), part = (double)count / 256.0;
+    const double wide = 1.5 + passes((count + 7) / 8, 32) * (5.4 + 13.1 * k) + full * (N % 4 ? 7.1 * std::max(part, 1.0) : 2.5 * part);
+    const double tall = 7.1 + 2.8 * passes(xcd_wgs, 64) + 9.1 * passes(xcd_wgs, 32) * k + 2.2 * (double)xcd_wgs / 64.0 +
+                        2.2e-4 * (double)N + 8.7e-5 * (double)N * k;
+    return wide < 0.97 * tall;
 }
 
 int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
@@ -1145,7 +1149,7 @@ int run_linear(const int8_t *xq, int64_t M, int64_t K, float s_x, float z_x,
     wide.cols = (wide.chans + 7) / 8;
     const long long wide_tiles = (long long)wide.rows * wide.chans;
     const bool by_wide = planes == 2 && !by_rows && wide_tiles <= kLinWideMaxTiles &&
-                         linear_wide(M, K, N, wide_tiles, tn_per_xcd * tiles_m, can_split);
+                         linear_wide(M, K, N, wide, tn_per_xcd * tiles_m, can_split);
     const bool by_split = !by_rows && !by_wide && can_split;
     if (by_rows) rs = smaller_row_shape(rs, M, K, N, bits, planes);
     const dim3 row_grid((unsigned)rs.cols, (unsigned)rs.tiles);

@@ -49,7 +49,11 @@ def test_y_between_vectors(P):  # noqa: F811
     (128, 1024, 16384, "k_linear_split<4>"), (128, 1024, 16385, "k_linear_wide<4>"),      # 128 and 129
     # by the estimate: y in short reductions, few tiles in a second pass
     (4096, 4096, 4096, "k_linear_wide<4>"), (4096, 64, 4096, "k_linear<4, 2>"), (4096, 256, 11008, "k_linear<4, 2>"),
-    (2048, 4096, 1600, "k_linear<4, 2>"), (4096, 8192, 1000, "k_linear<4, 2>")])
+    (2048, 4096, 1600, "k_linear<4, 2>"), (4096, 8192, 1000, "k_linear<4, 2>"),
+    (1721, 7968, 6440, "k_linear_wide<4>"),
+    # rows of y that are no whole vectors, in one pass
+    (1072, 16, 3782, "k_linear<4, 2>"), (1072, 16, 3784, "k_linear_wide<4>"), (1183, 592, 2977, "k_linear<4, 2>"),
+    (2791, 32, 1719, "k_linear<4, 2>"), (2791, 32, 1720, "k_linear_wide<4>")])
 def test_rule(P, M, K, N, want):  # noqa: F811
     import torch
     x = torch.zeros((M, K), dtype=torch.int8, device="cuda")
