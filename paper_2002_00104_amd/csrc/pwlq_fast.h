@@ -64,8 +64,8 @@ constexpr int kFastBits = 30;
 // binary32 below 2^30, so that no bucket number passes the last octave's.
 constexpr unsigned kFastTop = (1u << kFastBits) - 64u - (1u << (kFastBits - kFastOct));
 static_assert(kFastTop / (65535u * 254u) >= 63u, "every grid fits, with 63 units or more to half its finest step");
-constexpr int kFastCrowd = 64;                     // fullest bucket the look-ups may walk: this or 1/16 of the tile,
-constexpr int kFastCrowdMax = 511;                 // ... and never more
+constexpr int kFastCrowd = 64;                     // fullest bucket the look-ups may walk: this or 1/16 of the tile, twice
+constexpr int kFastCrowdMax = 511;                 // as much in workgroups of 256 threads (fast_crowd), and never more than this
 constexpr int kFastCrowdLog = 6, kFastCrowdBits = 9;
 static_assert(kFastCrowd <= 1 << kFastCrowdLog && kFastCrowdMax < 1 << kFastCrowdBits, "as powers of two");
 constexpr int kFastWalk = 3;                       // elements read unasked (4: 0.5-2 % slower, 6: 3-7 %)
@@ -80,17 +80,15 @@ constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launc
 constexpr int kFastOwnTiles = 2048, kFastOwnShort = 6144;   // ... or than these where it has fewer longer ones (own_launch)
 
 // Error of a tile's filter value beyond the rounding of its elements: A is a sum of
-// squares added in at most 33 steps (10 per thread, 6 over the wavefront, 16 over the
-// workgroup) and scaled in three roundings, the rest is exact up to seven roundings
+// squares added in at most 33 steps (20 per thread, 6 over the wavefront and 4 over a workgroup of
+// 256; 10, 6 and 8; 8, 6 and 16) and scaled in three roundings, the rest is exact up to seven roundings
 // of a value of at most A, and A is at most n^2 K: below 48 * 2^-53 n^2 K = 5.4e-15
 // n^2 K.  kFastRelErr * n^2 * K is added to the slack of the filter (keep_threshold).
 
-// log2 of a tile's buckets per octave, about two buckets per element, 32 at least: the
-// parts of H inside one bucket then fit 32 bits.  With 2^m buckets in an octave
-// (2^(m-1) where there are 14 octaves) the widest, in the last octave, has 2^(30-m) units,
-// and a tile is crowded when a bucket has more than max(kFastCrowd, len / 16) elements:
-// 64 * 2^25 for m = 5 (up to 255 elements), 511 * 2^22 at most for m = 8 (from 1024 on), and with twice the elements,
-// 511 * 2^23 at most for m = 7 in workgroups of 256 threads.
+// log2 of a tile's buckets per octave, about two buckets per element, 32 at least, and in workgroups of 256 threads 128 at
+// most: the parts of H inside one bucket then fit 32 bits.  With 2^m buckets in an octave
+// (2^(m-1) where there are 14 octaves) the widest, in the last octave, has 2^(30-m) units, so that its elements
+// are at most 2^(30-m) - 1 below a half-way point in it.
 __host__ __device__ constexpr int fast_octave_bits(int len, int threads)
 {
     const int most = threads == 256 ? kFastOctBits - 1 : kFastOctBits;
@@ -98,6 +96,22 @@ __host__ __device__ constexpr int fast_octave_bits(int len, int threads)
     while (bits < most && (8 << bits) <= len) ++bits;
     return bits;
 }
+// Most elements of a bucket: a tile with more in one is evaluated element by element.  Twice as many in workgroups of 256 threads,
+// of long tiles since their buckets are twice as wide, of others since walks are the cheaper by far (4229x573 of
+// cubes of normal numbers, b = 4, n = 2962, us, 64 / 128: 549/51).
+__host__ __device__ constexpr int fast_crowd(int len, int threads)
+{
+    int most = (len >> 4) > kFastCrowd ? len >> 4 : kFastCrowd;
+    if (threads == 256) most *= 2;
+    return most < kFastCrowdMax ? most : kFastCrowdMax;
+}
+constexpr bool fast_parts_fit(int longest, int threads)
+{
+    for (int len = 1; len <= longest; ++len)
+        if (fast_crowd(len, threads) * ((1ull << (kFastBits - fast_octave_bits(len, threads))) - 1) >> 32) return false;
+    return true;
+}
+static_assert(fast_parts_fit(kFastLong, 256) && fast_parts_fit(kTileMax, 1024), "the parts inside any bucket fit 32 bits");
 
 // inclusive prefix sum of 64-bit words over the wavefront
 template <int kCtrl, int kRows>
@@ -463,7 +477,7 @@ __device__ inline bool fast_pruned(const FastLds &Q, const FastCurve &c, float U
 }
 
 // A tile whose values crowd into a few buckets (many equal magnitudes: a bucket
-// holding more than 1/16 of the tile) would make every look-up walk a long bucket; it is evaluated element by element
+// holding more than fast_crowd) would make every look-up walk a long bucket; it is evaluated element by element
 // instead, from binary32 magnitudes in candidate units, with the chunked sums of the
 // plain search kernel (all lanes read the same LDS word, which is a broadcast).
 //
@@ -774,10 +788,7 @@ __global__ __launch_bounds__(kT, kPer == 20 ? 6 : 8) void k_fast(Tables tb, int 
     A = wave_sum(A);
     __syncthreads();
 
-    // (twice as many in buckets that may be twice as wide)
-    constexpr int kWide = kT == 256 ? 1 : 0;
-    int crowd = (len >> 4) > kFastCrowd ? len >> 4 : kFastCrowd;
-    crowd = crowd << kWide < kFastCrowdMax ? crowd << kWide : kFastCrowdMax;
+    const int crowd = fast_crowd(len, kT);
     // exclusive prefix of counts and sums, both fields in one word
     const int per = (T + kT - 1) / kT;             // divides T
     const int lo = tid * per;
@@ -848,7 +859,7 @@ __global__ __launch_bounds__(kT, kPer == 20 ? 6 : 8) void k_fast(Tables tb, int 
     // look-ups whose parts inside buckets fit 32 bits together: one or two at least (see
     // fast_octave_bits), eight or more as a rule
     int run = (int)(0xffffffffu >> (kFastBits - 1 - obits)) >> (full & 2 ? kFastCrowdBits : full & 1 ? kFastCrowdLog : 4);
-    run = run > 0 ? run : 1;                       // (one of a bucket of kFastCrowdMax: 511 * 2^23 at most)
+    run = run > 0 ? run : 1;                       // (a bucket's own parts fit: fast_parts_fit)
     __syncthreads();
     float *row = sse32 + (long long)t * n;
     if (full & 4) {

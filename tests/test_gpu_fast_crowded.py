@@ -39,3 +39,31 @@ def test_crowded(P, bits, n, K, tiles, want):  # noqa: F811
         assert_search_matches(got, R.search(w, bits, n, want_curve=True), f"bits={bits} n={n} K={K}")
     finally:
         P.set_small_call_tiles(before)
+
+
+def full(K, runs, rng):
+    """Runs of weights within one bucket, low, high and last, among others."""
+    out = []
+    for run in runs:
+        w = rng.standard_normal(K) * 0.3
+        w[0] = top = 2.0
+        for at in (0.31, 0.77, 0.99999):
+            v = w.copy()
+            v[rng.choice(K, run, replace=False)] = top * at * (1 - rng.random(run) * 2.0 ** -14)
+            out.append(v)
+    return np.stack(out).astype(np.float32)
+
+
+@pytest.mark.parametrize("bits,n,K,beside", [(4, 300, 200, 600), (3, 1000, 255, 1000), (4, 1000, 300, 0), (2, 700, 1023, 0), (4, 301, 1100, 0),
+                                             (4, 1000, 2064, 0), (5, 400, 4096, 0)])
+def test_buckets_as_full_as_256_threads_walk(P, bits, n, K, beside):  # noqa: F811
+    import torch
+    most = max(64, K // 16) * 2
+    w = full(K, (65, most - 1, most, min(most + 1, K)), np.random.default_rng(K))
+    many = torch.from_numpy(np.concatenate([w, np.repeat(w[:1], 2049, 0)])).cuda()
+    more = [torch.randn((20, beside), generator=torch.Generator().manual_seed(1)).cuda()] if beside else []
+    print(f"[case] bits={bits} n={n} K={K}", flush=True)
+    got = P.search_list(P.TensorList([many] + more, P.PER_CHANNEL), bits, n, fast=True)
+    assert P.last_kernels() == "k_fast<256>"
+    assert_search_matches({k: v.cpu().numpy()[:len(w)] for k, v in got.items()}, R.search(w, bits, n, want_curve=True),
+                          f"bits={bits} n={n} K={K}")
