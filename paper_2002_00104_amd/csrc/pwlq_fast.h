@@ -578,10 +578,12 @@ inline FastUnits fast_units(int n, int bits)
 
 // The elements of a thread in batches, e0 .. e0 + count - 1: batch(first, count), both compile-time.  What a wavefront does with
 // a batch depends on whether the tile ends in it: batches are as many as the tiles of a launch's range end in
-// usefully, and no longer than the LDS adds that a thread can hold in flight within 64 registers.  Two in workgroups of
-// 1024 threads, where a tile may end in any (four: 0.996 to 1.04 of the time; 59x7021 and 1533x1051 in one launch, b = 4, n = 97, us, 46.7/45.1).
+// usefully, and no longer than the LDS adds that a thread can hold in flight within 64 registers.  In workgroups of
+// 1024 threads, where a tile may end in any, four where the wavefront has `all` of its elements and else two (always four / always two / so,
+// against no batches: 60 calls of groups of many tiles, whole but for the last, 0.986 / 1.001 / 0.986 of the time, 60 of tiles of 5121 to 8192
+// 0.979 / 0.975 / 0.970, 40 with shorter tiles in the launch 0.973 / 0.961 / 0.964; 59x7021 and 1533x1051, b = 4, n = 97, us, 46.7/45.1).
 template <int kPer, typename F>
-__device__ inline void fast_batches(F batch)
+__device__ inline void fast_batches([[maybe_unused]] bool all, F batch)
 {
     static_assert(kPer == 2 || kPer == 4 || kPer == 8 || kPer == 10 || kPer == 20, "no batches for this many");
     const auto call = [&](auto e0, auto count) { batch(e0, count); };
@@ -589,7 +591,10 @@ __device__ inline void fast_batches(F batch)
     if constexpr (kPer == 2) PWLQ_BATCH(0, 2);
     if constexpr (kPer == 4) PWLQ_BATCH(0, 4);
     if constexpr (kPer == 20) { PWLQ_BATCH(0, 4); PWLQ_BATCH(4, 4); PWLQ_BATCH(8, 4); PWLQ_BATCH(12, 4); PWLQ_BATCH(16, 4); }
-    if constexpr (kPer == 8) { PWLQ_BATCH(0, 2); PWLQ_BATCH(2, 2); PWLQ_BATCH(4, 2); PWLQ_BATCH(6, 2); }
+    if constexpr (kPer == 8) {
+        if (all) { PWLQ_BATCH(0, 4); PWLQ_BATCH(4, 4); }
+        else { PWLQ_BATCH(0, 2); PWLQ_BATCH(2, 2); PWLQ_BATCH(4, 2); PWLQ_BATCH(6, 2); }
+    }
     if constexpr (kPer == 10) { PWLQ_BATCH(0, 5); PWLQ_BATCH(5, 5); }
 #undef PWLQ_BATCH
 }
@@ -636,7 +641,7 @@ __global__ __launch_bounds__(kT, kPer == 20 ? 6 : 8) void k_fast(Tables tb, int 
     {
         const GlobalFloat *src = (const GlobalFloat *)ti.src;
         const unsigned last = (unsigned)len - 1u;
-        fast_batches<kPer>([&](auto first, auto count) {
+        fast_batches<kPer>(all(0, kPer), [&](auto first, auto count) {
             constexpr int e0 = decltype(first)::value, e1 = e0 + decltype(count)::value;
             if (none(e0)) {
 #pragma unroll
@@ -663,7 +668,7 @@ __global__ __launch_bounds__(kT, kPer == 20 ? 6 : 8) void k_fast(Tables tb, int 
     // magnitudes' order, NaN above infinity.
     unsigned mb = 0, lowest = ~0u;
     float sum = 0.0f;
-    fast_batches<kPer>([&](auto first, auto count) {
+    fast_batches<kPer>(all(0, kPer), [&](auto first, auto count) {
         constexpr int e0 = decltype(first)::value, e1 = e0 + decltype(count)::value;
         if (none(e0)) return;
         if (!all(e0, e1 - e0)) {
@@ -746,7 +751,7 @@ __global__ __launch_bounds__(kT, kPer == 20 ? 6 : 8) void k_fast(Tables tb, int 
     // whether the wavefront has magnitudes that may round to zero
     const bool zeros_here = __ballot((double)__uint_as_float(lowest) * scale < 1.0) != 0ull;
     typedef __attribute__((address_space(3))) unsigned long long WordLds;
-    fast_batches<kPer>([&](auto first, auto count) {
+    fast_batches<kPer>(all(0, kPer), [&](auto first, auto count) {
         constexpr int e0 = decltype(first)::value, kCount = decltype(count)::value;
         if (none(e0)) return;
         const bool whole = all(e0, kCount);
@@ -842,7 +847,7 @@ __global__ __launch_bounds__(kT, kPer == 20 ? 6 : 8) void k_fast(Tables tb, int 
     __syncthreads();
     unsigned *elems = reinterpret_cast<unsigned *>(fast_lds + T);
     Q.elems = (FastElemLds *)elems - zeros;
-    fast_batches<kPer>([&](auto first, auto count) {
+    fast_batches<kPer>(all(0, kPer), [&](auto first, auto count) {
         constexpr int e0 = decltype(first)::value, kCount = decltype(count)::value;
         if (none(e0)) return;
         unsigned at[kCount];

@@ -69,3 +69,28 @@ def test_full_buckets_and_tiny_scales(P, bits, n, K):
         assert_search_matches(got, R.search(w, bits, n, want_curve=True), f"bits={bits} n={n} K={K}")
     finally:
         P.set_small_call_tiles(before)
+
+
+@pytest.mark.parametrize("bits,n", [(4, 100), (5, 700)])
+def test_where_the_wavefronts_of_1024_threads_have_all_of_their_elements(P, bits, n):
+    """Eight elements to a thread: from 7232 on the first wavefront has all of them, from 8192 on the last; short tiles beside
+    them; a wavefront with zeros and one without."""
+    import torch
+    rng = np.random.default_rng(n)
+    ws = []
+    for K in (7231, 7232, 7233, 7295, 7296, 8128, 8191, 8192, 600, 2049):
+        w = rows(K, rng)
+        w[2, 64:128] = 0.0
+        ws.append(w)
+    print(f"[case] bits={bits} n={n}", flush=True)
+    before = P.set_small_call_tiles(0)
+    try:
+        got = P.search_list(P.TensorList([torch.from_numpy(w).cuda() for w in ws], P.PER_CHANNEL), bits, n, fast=True)
+        assert P.last_kernels() == "k_fast<1024>"
+    finally:
+        P.set_small_call_tiles(before)
+    got, at = {k: v.cpu().numpy() for k, v in got.items()}, 0
+    for w in ws:
+        part = {k: v[at:at + len(w)] for k, v in got.items()}
+        assert_search_matches(part, R.search(w, bits, n, want_curve=True), f"bits={bits} n={n} K={w.shape[1]}")
+        at += len(w)
