@@ -100,11 +100,12 @@ bool grid_pays(int n, int L)
 // 38 400 tiles of 4096, n = 1000, b = 4, k_fast alone 508/386; but 2500x4608, 512 threads with fewer candidates left out than
 // now: n = 290, without the grid of candidates, b = 5, 68/75, b = 6 85/101; b = 7, n = 700 146/196).
 //
-// One wavefront to a short tile where a launch has many and a grid leaves it few candidates, 60 to 140 of 1000: both
-// wavefronts of 128 threads repeat the reductions and prefixes, and one waits for the other (9000 tiles of 9 to 256, us, 128 /
-// 64: b = 2, n = 1000 51-58 / 29-39, b = 3, n = 300 0.74 to 0.81 of the time, b = 4, n = 1000 0.81 to 0.98).  Not at five bits
-// (1.01 to 1.13) nor past 1000 candidates (b = 4, n = 3000 up to 1.11), nor for few tiles (2100, b = 4, n = 1000
-// up to 1.05).
+// One wavefront to a short tile where a launch has many and its look-ups are few (at b = 3 and 4 a grid leaves 60 to 140 of 1000
+// candidates; at b = 2 all below 704 are looked up, two each): both wavefronts of 128 threads repeat the reductions and prefixes, and
+// one waits for the other.  8192 and 25 000 tiles of 9 to 256, time with 64 threads / 128: b = 2, n = 300 to 703 0.89 to 1.03, 704 to 1200,
+// which 128 threads look up without a grid, 0.45 to 0.73, 1500 and 2000 0.84 to 0.98; b = 3, n = 300 to 1000 0.63 to 0.90, to
+// 2000 0.84 to 1.00; b = 4, n = 300 to 1000 0.76 to 0.93, to 1500 0.80 to 1.00, 2000 0.87 to 1.02, 3000 0.90 to 1.08; b = 2, n = 5000
+// up to 1.34.  Not at five bits (1.01 to 1.13), nor for few tiles (2100, b = 4, n = 1000 up to 1.05).
 int fast_threads(int longest, long long tiles, int n, int L)
 {
     if (longest > kFastLong) return 1024;

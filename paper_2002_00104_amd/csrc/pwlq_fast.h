@@ -73,7 +73,7 @@ constexpr int kFastWalkOn = 4;                     // ... and then per step
 constexpr int kFastShort = 256;                    // longest tile of a launch of 128 or 64 threads
 constexpr int kFastLong = 5120;                    // longest tile of a launch of 512 threads: four workgroups' LDS per CU
 constexpr int kFastShortest = 9;                   // shortest tile that many short ones have looked up (see fast_min_len)
-constexpr int kFastWaveTiles = 8192, kFastWaveCand = 1000;   // a wavefront for a short tile: fewest tiles, most candidates (fast_threads)
+constexpr int kFastWaveTiles = 8192, kFastWaveCand = 2000;   // a wavefront for a short tile: fewest tiles, most candidates (fast_threads)
 constexpr int kFastManyTiles = 2048;               // more tiles of 1025 to kFastLong elements get 256 threads instead of 512
 constexpr int kFastGridMax = 1 << 21;              // workgroups of a launch
 constexpr int kFastLaunchTiles = 1024;             // fewer tiles join the launch of the next longer ones,

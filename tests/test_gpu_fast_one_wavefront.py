@@ -10,7 +10,7 @@ from test_gpu_routes import searched
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("bits,n", [(2, 1000), (3, 470), (4, 300), (4, 1000)])
+@pytest.mark.parametrize("bits,n", [(2, 1000), (3, 470), (4, 300), (4, 1000), (2, 500), (3, 2000), (4, 2000)])
 def test_one_wavefront(P, bits, n):  # noqa: F811
     import torch
     rng = np.random.default_rng(10 * bits + n)
@@ -36,7 +36,7 @@ def test_one_wavefront(P, bits, n):  # noqa: F811
 
 @pytest.mark.parametrize("shapes,bits,n,want", [
     ([(8192, 256)], 4, 300, "k_fast<64>"), ([(8191, 256)], 4, 300, "k_fast<128>"), ([(8192, 257)], 4, 300, "k_fast<256>"),
-    ([(8192, 256)], 4, 299, "k_fast<128>"), ([(8192, 256)], 4, 1000, "k_fast<64>"), ([(8192, 256)], 4, 1001, "k_fast<128>"),
+    ([(8192, 256)], 4, 299, "k_fast<128>"), ([(8192, 256)], 4, 2000, "k_fast<64>"), ([(8192, 256)], 4, 2001, "k_fast<128>"),
     ([(8192, 256)], 5, 1000, "k_fast<128>"), ([(4096, 9), (4096, 100)], 2, 500, "k_fast<64>")])
 def test_either_side_of_the_limits(P, shapes, bits, n, want):  # noqa: F811
     assert searched(P, shapes, bits, n, fast=True) == want
