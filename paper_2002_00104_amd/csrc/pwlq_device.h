@@ -268,14 +268,4 @@ __device__ inline Pieces make_pieces(float m, float p, int bits)
     return q;
 }
 
-// Eq.3 on a magnitude: region (closed centre) and saturated, half-to-even code.
-__device__ inline float piece_code(const Pieces &q, float a, bool &tail)
-{
-    tail = a > q.p;
-    float x = a - q.p;
-    float t = tail ? x * q.i2 : a * q.i1;
-    float code = rintf(t);
-    return (code > q.L) ? q.L : code;
-}
-
 } // namespace pwlq

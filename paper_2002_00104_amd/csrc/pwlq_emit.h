@@ -6,8 +6,8 @@
 namespace pwlq {
 
 // Eq.3 with given (m, p): code, region flag and dequantized value per weight.
-// Same arithmetic as piece_code (t = a*i1 in the centre, (a-p)*i2 in the tail,
-// half-to-even, saturated) with the piece's parameters selected once per
+// Region (closed centre) and t = a*i1 in the centre, (a-p)*i2 in the tail, half-to-even,
+// saturated, with the piece's parameters selected once per
 // element instead of two evaluations selected afterwards; the centre value
 // code*s1 is written fma(code, s1, +0), which rounds the same product.
 // kHat = false: the dequantized value is not wanted.  The sign bit of a code is set for a
