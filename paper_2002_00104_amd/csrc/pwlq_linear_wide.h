@@ -1,15 +1,17 @@
 // k_linear_wide: the folded form (y alone) of the inner product for calls of many tiles.
 //
-// What bounds a large call is power: a loop of nothing but int8 matrix instructions runs at 2.4 GHz on zeros
-// (4.8 POP/s) and gives up clock for operands that toggle, and a kernel that leaves its units less idle
-// runs at a lower clock.  So the tile is large (256 rows by 128 channels, eight wavefronts of 64 x
-// 64 outputs, one workgroup per CU), which halves what is read from L2 and decoded per product against
+// What bounds a large call is cycles in which the matrix cores wait, for LDS, decoding, loads and the barrier: they are busy in
+// 47 % of them ([4096]^3, b = 4), one workgroup of eight wavefronts to a CU.  The clock is the smaller part: with operands that are
+// all zero, which toggle nothing, the same 0.27 million cycles pass at 2.48 instead of 2.23 GHz (110 us instead of 124, counted by
+// GRBM_GUI_ACTIVE).  So the tile is large (256 rows by 128 channels, eight wavefronts of 64 x
+// 64 outputs), which halves what is read from L2 and decoded per product against
 // k_linear's 256 x 64, and the instruction is the 16 x 16 x 64 one, whose 32-bit accumulators are read and
 // written half as often per product (random operands, in registers only: 4.1 POP/s against 3.4-3.6 of 32 x 32 x 32).
-// [4096]^3, b = 4: k_linear with k_linear_wsum before it 148 us, this kernel with 32 x 32 x 32 130, so 122, with the weights'
-// sums off the matrix cores 117 = 2.35 POP/s; 8192 x 4096 x 11008 769 -> 629; b = 2 148 -> 121, b = 6 169 -> 137, b = 8
-// 155 -> 122.  (A library product of the same int8 work, 4096 x 4096 x 8192, takes 121-137 here.)  Measured and no
-// faster: tiles taken by resident workgroups with the next one's loads in flight across the epilogue, wave
+// Calls back to back, until the chip has its sustained clock, k_linear with k_linear_wsum before it / this kernel, us: [4096]^3, b = 4,
+// 153/122 (2.25 POP/s; first calls and calls with others between them 131 to 136), b = 2 151/120, b = 6 172/142, b = 8 159/127;
+// 8192 x 4096 x 11008 811/662.  When it was written: with 32 x 32 x 32 130, with the
+// weights' sums on the matrix cores 122 where it took 117.  (A library product of the same int8 work, 4096 x 4096 x 8192, takes 121-137 here.)
+// Measured and no faster: tiles taken by resident workgroups with the next one's loads in flight across the epilogue, wave
 // priorities, other places for the decoding in a step.  With the sums apart (192 rows, 96 KB of
 // planes) it gained 9 % at [4096]^3 and lost 2-15 % at two passes over the chip: k_linear keeps those calls.
 #pragma once
@@ -29,7 +31,8 @@ constexpr int kLinWideMaxTiles = 1 << 22;         // of a launch: indices of til
 
 // LDS rows hold 128 reduction bytes as eight 16-byte chunks; chunk c of row r is stored at position
 // c ^ lin_wide_swz(r): the sixteen lanes that a cycle of a 16-byte read serves (see lin_swz) then lie in
-// different banks, whether they hold one chunk of sixteen rows or two of eight.
+// different banks, whether they hold one chunk of sixteen rows or two of eight.  The writes of weights do not: eight lanes
+// write four chunks of each of two rows with one swizzle, two to a bank (SQ_LDS_BANK_CONFLICT 2^22 at [4096]^3, 16 % of the LDS cycles).
 __device__ inline int lin_wide_swz(int row) { return (row >> 1) & 7; }
 
 // What a thread loads for one step: activation rows (t >> 3) + 64 v, chunk t & 7; of channel

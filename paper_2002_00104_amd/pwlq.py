@@ -1,4 +1,4 @@
-"""ctypes binding over libpwlq.so: argument marshalling only.
+"""Binding over libpwlq.so, by ctypes and, for calls of one tensor, by a module of C: argument marshalling only.
 
 Every step of the search and of the quantizer runs in the library's HIP
 kernels; PyTorch is used for device memory and for the current stream.  There

@@ -1,5 +1,5 @@
-"""k_linear itself against the oracle, at sizes that neither k_linear_rows nor k_linear_split
-takes: every bit width, reductions of one to six steps of 64 whose last step holds one to four
+"""k_linear itself against the oracle, at sizes that k_linear_rows, k_linear_split and k_linear_wide leave
+to it: every bit width, reductions of one to six steps of 64 whose last step holds one to four
 pieces of 16, and remainders of the row tile (256, or 192 with the sums apart) and of the
 channel tile (64)."""
 import numpy as np
